@@ -33,7 +33,9 @@
 // to 16 workers and up to 64 entries per worker in the tile, every entry
 // stays in a register of one lane from the load to the store: the weight at
 // its index is fetched while the LDS sums are formed, and the first entry to
-// swap the finished sum out of LDS writes the new weight.
+// swap the finished sum out of LDS writes the new weight. Long vectors with
+// sparse messages take one kernel instead (k_weights), whose workgroups form
+// the sums in a hash table, whatever stretch of coordinates the entries span.
 #include "rtopk_common.h"
 #include "../../include/rtopk.h"
 
@@ -47,6 +49,18 @@ constexpr int kAggTile = 2048;
 constexpr int kAggAhead = 8;              // workers whose next pairs are fetched together
 constexpr int kAggMore = 8;               // further slices of one crowded message fetched together
 constexpr unsigned kAggMaxWaves = 4096;
+// The sparse weight step takes k_weights (one kernel) where the vector is long and the
+// messages are sparse: from kWeightsTiles tiles on, up to kWeightsWorkers workers and
+// kWeightsPerTile entries per tile; k_tile_starts + k_update elsewhere. Measured (us,
+// k_weights / the pair): four workers of 66 M coordinates, 8 entries per tile,
+// 19.5 / 38.7; eight of 2^28, 2 per tile, 21 / 131; two of 2^28, 8 per tile, 62 / 116;
+// eight of 25.6 M, 16 per tile, 19.6 / 19.7; five of 11.2 M, 10 per tile, 14.5 / 10.0;
+// five of 11.2 M, 102 per tile, 27.8 / 22.3; sixteen of 25.6 M (a table twice as
+// large, half the workgroups) 51 / 36.
+constexpr u64 kWeightsTiles = 1u << 14;
+constexpr u32 kWeightsWorkers = 8;
+constexpr u32 kWeightsPerTile = 12;
+constexpr u32 kWeightsBlocks = 1024;      // four workgroups per compute unit
 constexpr unsigned kMomentumLdsClaim = 30u * 1024u;   // with the 32 KB of tiles: two workgroups per unit
 
 __device__ __forceinline__ u32 popc_mask(u64 m) { return (u32)__popcll((unsigned long long)m); }
@@ -63,9 +77,10 @@ __device__ __forceinline__ u64 read_lane_u64(u64 v, int lane)
 // first position in the worker's ascending index list whose entry is >= x.
 // Every step the P lanes of a group probe P evenly spaced positions of the
 // remaining range, which shrinks (P + 1)-fold. Returns the result of worker
-// `lane` in lane `lane` (lanes >= nw: unspecified).
+// `lane` in lane `lane` (lanes >= nw: unspecified). The lanes of a group bring
+// the range [lo, hi] of positions that is known to hold their worker's result.
 __device__ __forceinline__ u64 wave_lower_bounds(const u32 *__restrict__ idx, u32 w0, u32 nw, u64 k,
-                                                 u64 x)
+                                                 u64 x, u64 lo, u64 hi)
 {
     const u32 lane = lane_id();
     u32 P = 1;
@@ -73,7 +88,7 @@ __device__ __forceinline__ u64 wave_lower_bounds(const u32 *__restrict__ idx, u3
     const u32 w = lane / P, p = lane % P;
     const bool live = w < nw;
     const u32 *wi = idx + (u64)(w0 + (live ? w : 0)) * k;
-    u64 lo = 0, hi = live ? k : 0;                  // the answer lies in [lo, hi]
+    if (!live) lo = hi;
     const float inv = 1.0f / (float)(P + 1);
     while (__any(hi > lo)) {
         // probe positions lo <= pos_0 <= pos_1 <= ... < hi, roughly evenly spaced (any
@@ -138,7 +153,7 @@ k_aggregate(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u
     // lane w: where the current tile starts in the message of worker w (first group only;
     // with more than 64 workers the position is searched again for every tile)
     u64 pos0 = 0;
-    if (groups == 1) pos0 = wave_lower_bounds(idx, 0, n, k, first_tile * kAggTile);
+    if (groups == 1) pos0 = wave_lower_bounds(idx, 0, n, k, first_tile * kAggTile, 0, k);
 
     for (u64 t = first_tile; t < last_tile; ++t) {
         const u64 tile_base = t * kAggTile;
@@ -148,7 +163,7 @@ k_aggregate(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u
 
         for (u32 w0 = 0; w0 < n; w0 += kWave) {
             const u32 nw = n - w0 < (u32)kWave ? n - w0 : (u32)kWave;
-            u64 lo = groups == 1 ? pos0 : wave_lower_bounds(idx, w0, nw, k, tile_base);
+            u64 lo = groups == 1 ? pos0 : wave_lower_bounds(idx, w0, nw, k, tile_base, 0, k);
             // ---- worker after worker: the next 64 pairs of its message in one
             //      coalesced load, those below the tile's end added into the tile;
             //      the loads of kAggAhead workers are in flight together --------
@@ -271,6 +286,255 @@ k_aggregate(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u
                 }
             }
         }
+    }
+}
+
+// lane l gets lane l - 1's value, lane 0 gets `first`
+__device__ __forceinline__ u32 lane_left(u32 v, u32 first)
+{
+    return (u32)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+}
+
+// Bits that the wavefronts of a workgroup collect for each other: every thread
+// gets the union of what the wavefronts put in (one barrier). Three words in
+// turn: the one used after next is cleared once everybody has read it.
+struct BitExchange {
+    u32 *word;          // 3 words of LDS, zero before the first exchange
+    u32 turn;
+    __device__ __forceinline__ u32 operator()(u32 mine /* uniform over the wavefront */)
+    {
+        if (lane_id() == 0 && mine != 0u) atomicOr(&word[turn], mine);
+        lds_barrier();
+        const u32 all = (u32)__builtin_amdgcn_readfirstlane((int)word[turn]);
+        const u32 next = turn == 2u ? 0u : turn + 1u;
+        if (threadIdx.x == 0) word[next == 2u ? 0u : next + 1u] = 0u;
+        turn = next;
+        return all;
+    }
+};
+
+// The coordinates [x0, x1) of one of the kWeightsBlocks workgroups, and where
+// x0 starts in every worker's list (pos, LDS). Messages cluster (the top
+// coordinates sit in a few layers), and no two workers' need cluster alike: so
+// evenly spaced entries of EVERY worker, at most 255 in all, cut the coordinates
+// into pieces, and each piece is cut into equal quarters. A piece lies between two
+// neighbouring samples of any worker: it holds at most an S-th of a
+// message of which S entries were sampled. Where the samples lie in the message
+// also narrows the search for x0 down. lds: 2 * kAggThreads words.
+__device__ __forceinline__ bool weights_range(const u32 *__restrict__ idx, u32 n, u64 k, u64 d, u32 *lds,
+                                              u64 *x0, u64 *x1, u64 *pos)
+{
+    static_assert(kWeightsBlocks == 4 * kAggThreads, "a cut per thread, four workgroups between two cuts");
+    const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    const u32 per = (kAggThreads - 1) / n, cuts = per * n;      // samples of one worker, of all
+    // position of worker v's sample s (staggered, or the samples of like messages would coincide)
+    auto at = [&](u32 v, u32 s) { return (u64)(s * n + v + 1u) * k / (cuts + 1u); };
+    const u32 w = tid / per, s = tid - w * per;
+    u32 mine = 0xFFFFFFFFu;
+    if (tid < cuts) mine = idx[w * k + at(w, s)];
+    u32 *cut = lds, *sorted = lds + kAggThreads;
+    cut[tid] = mine;
+    lds_barrier();
+    // samples of worker v that are below x (kLess) or at most x
+    auto below = [&](u32 v, u64 x) {
+        u32 lo = 0, hi = per;
+        while (lo < hi) {
+            const u32 mid = (lo + hi) / 2u;
+            if ((u64)cut[v * per + mid] < x) lo = mid + 1u; else hi = mid;
+        }
+        return lo;
+    };
+    if (tid < cuts) {
+        // place among all samples: ties in worker order
+        u32 rank = s;
+        for (u32 v = 0; v < n; ++v)
+            if (v != w) rank += below(v, (u64)mine + (v < w ? 1u : 0u));
+        sorted[rank] = mine;
+    }
+    lds_barrier();
+    const u32 piece = blockIdx.x / 4u, quarter = blockIdx.x % 4u;
+    u64 lo = piece == 0u || piece > cuts ? 0ull : (u64)sorted[piece - 1u], hi = piece >= cuts ? d : (u64)sorted[piece];
+    if (lo > d) lo = d;
+    if (hi > d) hi = d;
+    *x0 = lo + (hi - lo) * quarter / 4u;
+    *x1 = lo + (hi - lo) * (quarter + 1u) / 4u;
+    if (piece > cuts || lo >= hi || *x0 >= *x1) return false;
+    const u32 of_wave = (n + kAggWaves - 1) / kAggWaves, first = wave * of_wave;
+    if (first < n) {
+        const u32 here = n - first < of_wave ? n - first : of_wave;
+        u32 lanes = 1;
+        while (2 * lanes * here <= (u32)kWave) lanes *= 2;
+        const u32 v = first + (lane / lanes < here ? lane / lanes : 0u);
+        const u32 c = below(v, *x0);
+        const u64 start = wave_lower_bounds(idx, first, here, k, *x0, c == 0u ? 0ull : at(v, c - 1u) + 1u,
+                                            c == per ? k : at(v, c));
+        if (lane < here) pos[first + lane] = start;
+    }
+    lds_barrier();                                             // the words are the caller's again
+    return true;
+}
+
+// ---------------------------------------------------------------------------
+// weights: the sparse weight step for up to kWeightsWorkers workers:
+// omega[i] = fma(neg_step, average[i], omega[i]) wherever the average of what
+// the workers sent for i is not zero.
+//
+// A few MB are moved: what bounds it is the chain of dependent trips to
+// memory (the search, the entries, the weights) and how many such chains one
+// workgroup walks one after the other. So a workgroup takes ALL entries of its
+// range at once, 256 per worker and round, whatever the coordinates between
+// them: the sums are formed in a hash table in LDS (keyed by coordinate, at
+// most half full) and not in a tile of coordinates. Every entry takes its slot;
+// the one that finds the slot empty (the leader) has the weight fetched
+// meanwhile and writes it. If no coordinate was sent twice, a leader's sum is its own value;
+// otherwise the workers are added in order with a barrier in between.
+// Four workers of 66 M coordinates (66,034 entries each): 19.3 us; the
+// pair of kernels with a wavefront per tile of 2048 coordinates takes 4.8 + 33.8,
+// as its 32,244 tiles walk the same chain in six rounds.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(kAggThreads, 4)
+k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64 k, u64 d,
+          float neg_step, float *__restrict__ omega)
+{
+    constexpr u32 kWindows = kWeightsWorkers;
+    constexpr u32 kSlots = 2 * kWindows * kAggThreads;     // a power of two
+    constexpr u32 kEmpty = 0xFFFFFFFFu;                    // never a coordinate
+    __shared__ u32 key[kSlots];
+    __shared__ float sum[kSlots];
+    __shared__ u64 pos[kWindows];
+    __shared__ u32 word[3];
+    __shared__ u32 bound_s;
+    const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    u64 x0, x1;
+    if (!weights_range(idx, n, k, d, key, &x0, &x1, pos)) return;
+    const float fn = (float)n;
+    const bool n_pow2 = (n & (n - 1u)) == 0u;
+    const float rn = 1.0f / fn;
+    auto average = [&](float s) { return n_pow2 ? s * rn : s / fn; };
+    for (u32 i = tid; i < kSlots; i += kAggThreads) { key[i] = kEmpty; sum[i] = 0.0f; }
+    if (tid < 3u) word[tid] = 0u;
+    BitExchange exchange{word, 0u};
+    lds_barrier();
+
+    for (;;) {
+        // ---- the next 256 entries of every worker --------------------------------
+        u32 e_i[kWindows], left[kWindows];
+        float e_v[kWindows];
+        u32 bound = (u32)(x1 - 1);             // last coordinate of this round, at most
+        bool cut = false;
+#pragma unroll
+        for (u32 q = 0; q < kWindows; ++q) {
+            e_i[q] = left[q] = kEmpty;
+            e_v[q] = 0.0f;
+            if (q < n) {
+                const u64 from = pos[q], j = from + tid;
+                if (j < k) {
+                    e_i[q] = idx[q * k + j];
+                    e_v[q] = val[q * k + j];
+                    if (lane == 0 && tid != 0u) left[q] = idx[q * k + j - 1];
+                }
+            }
+        }
+        // A round ends before the last entry of any window that has entries behind it (an
+        // index may occur several times: what follows the window may belong to the same
+        // coordinate), so that it holds every entry of its coordinates.
+        if (tid == kAggThreads - 1) {
+            u32 b = kEmpty;
+#pragma unroll
+            for (u32 q = 0; q < kWindows; ++q)
+                if (q < n && pos[q] + kAggThreads < k && e_i[q] < b) b = e_i[q];
+            bound_s = b;
+        }
+        lds_barrier();
+        {
+            const u32 b = bound_s;
+            cut = b <= bound;
+            if (cut) bound = b;
+        }
+        const u32 base = (u32)x0;
+        // coordinates [x0, bound) of a round that was cut short, [x0, bound] otherwise
+        const u32 span = bound - base + (cut ? 0u : 1u);
+        auto inside = [&](u32 i) { return i - base < span && i != kEmpty; };
+        float w[kWindows];
+        u32 slot[kWindows];
+        u32 leader = 0, mine = 0;
+#pragma unroll
+        for (u32 q = 0; q < kWindows; ++q) w[q] = inside(e_i[q]) ? omega[e_i[q]] : 0.0f;
+        // bits: 1 some slot was taken by another entry already; 2 << q: worker q holds entries;
+        // 2^17 a message repeats an index
+#pragma unroll
+        for (u32 q = 0; q < kWindows; ++q) {
+            slot[q] = (e_i[q] * 0x9E3779B1u) >> (32 - __builtin_ctz(kSlots));
+            const bool in = inside(e_i[q]);
+            const u64 m = __ballot(in);
+            if (m == 0ull) continue;
+            mine |= 2u << q;
+            if (__ballot(in && lane_left(e_i[q], left[q]) == e_i[q]) != 0ull) mine |= 1u << 17;
+            if (lane == 0) atomicAdd(reinterpret_cast<unsigned long long *>(&pos[q]), (unsigned long long)popc_mask(m));
+            if (in) {
+                u32 was = atomicCAS(&key[slot[q]], kEmpty, e_i[q]);
+                while (was != kEmpty && was != e_i[q]) {
+                    slot[q] = (slot[q] + 1u) & (kSlots - 1u);
+                    was = atomicCAS(&key[slot[q]], kEmpty, e_i[q]);
+                }
+                if (was == kEmpty) leader |= 1u << q;
+            }
+            if (__ballot(in && ((leader >> q) & 1u) == 0u) != 0ull) mine |= 1u;
+        }
+        const u32 seen = exchange(mine);
+        if ((seen & 1u) != 0u) {
+            // ---- coordinates sent by several workers: sums in worker order -------------
+#pragma unroll
+            for (u32 q = 0; q < kWindows; ++q) {
+                if (((seen >> (q + 1u)) & 1u) == 0u) continue;
+                const bool in = inside(e_i[q]);
+                if (__builtin_expect((seen >> 17) == 0u, 1)) {
+                    if (in) sum[slot[q]] += e_v[q];
+                    lds_barrier();
+                } else {
+                    // repeated indices inside one message: in position order
+                    for (u32 wv = 0; wv < (u32)kAggWaves; ++wv) {
+                        if (wave == wv)
+                            for (u64 rest = __ballot(in); rest; rest &= rest - 1) {
+                                const int src = __ffsll((unsigned long long)rest) - 1;
+                                if ((int)lane == src) sum[slot[q]] += e_v[q];
+                            }
+                        lds_barrier();
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (u32 q = 0; q < kWindows; ++q) {
+            if (((leader >> q) & 1u) != 0u) {
+                const float total = (seen & 1u) != 0u ? sum[slot[q]] : 0.0f + e_v[q];
+                sum[slot[q]] = 0.0f;
+                key[slot[q]] = kEmpty;
+                const float avg = average(total);
+                if (avg != 0.0f) omega[e_i[q]] = fmaf(neg_step, avg, w[q]);
+            }
+        }
+        if (!cut) break;
+        if (__builtin_expect(seen == 0u, 0)) {
+            // Nothing lies below the bound: a window holds one coordinate only (an index
+            // that occurs more than 255 times in one message). One thread takes it.
+            if (tid == 0) {
+                float s = 0.0f;
+                u32 moved = 0;
+                for (u32 q = 0; q < n; ++q)
+                    for (u64 p = pos[q]; p < k && idx[q * k + p] == bound; ++p) {
+                        s += val[q * k + p];
+                        pos[q] = p + 1;
+                        moved = 1;
+                    }
+                const float avg = average(s);
+                if (avg != 0.0f && bound >= base) omega[bound] = fmaf(neg_step, avg, omega[bound]);
+                // (a list that is not sorted, a broken precondition: the loop ends all the same)
+                if (!moved)
+                    for (u32 q = 0; q < n; ++q) pos[q] += kAggThreads;
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -636,16 +900,21 @@ extern "C" int rtopk_aggregate_update_workspace_bytes(uint64_t d, uint32_t n, ui
     return RTOPK_OK;
 }
 
-// the two kernels of the fused update; `start` holds (tiles + 1) * n words
+// the kernels of the fused update; `start` holds (tiles + 1) * n words
 static int launch_update(const uint32_t *idx, const float *val, uint32_t n, uint64_t k, uint64_t d,
                          float eta, float scale, float *omega, u32 *start, hipStream_t stream)
 {
     if (const int rc = debug_check_messages(idx, n, k, d, stream)) return rc;
+    volatile float step = eta * scale;                  // one binary32 rounding, then negated
+    if (n <= kWeightsWorkers && d / kAggTile >= kWeightsTiles && (u64)n * k <= d / kAggTile * kWeightsPerTile) {
+        k_weights<<<kWeightsBlocks, kAggThreads, 0, stream>>>(idx, val, n, k, d, -step, omega);
+        if (hipGetLastError() != hipSuccess) return RTOPK_EHIP;
+        return RTOPK_OK;
+    }
     const u64 tiles = (d + kAggTile - 1) / kAggTile;
     const dim3 sgrid((unsigned)((k + 1 + kStartThreads - 1) / kStartThreads), n);
     k_tile_starts<<<sgrid, kStartThreads, 0, stream>>>(idx, n, k, tiles, start);
     if (hipGetLastError() != hipSuccess) return RTOPK_EHIP;
-    volatile float step = eta * scale;                  // one binary32 rounding, then negated
     const unsigned grid = (unsigned)((tiles + kAggWaves - 1) / kAggWaves);
     k_update<<<grid, kAggThreads, 0, stream>>>(idx, val, n, k, d, tiles, start, -step, omega);
     if (hipGetLastError() != hipSuccess) return RTOPK_EHIP;

@@ -119,6 +119,16 @@ __device__ __forceinline__ u32 wave_max(u32 v)
     return v;
 }
 
+// Workgroup barrier that orders LDS accesses only: global loads, stores and
+// atomics a thread has in flight stay in flight (__syncthreads would wait for
+// all of them to complete first).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 __host__ __device__ constexpr u64 align_up(u64 x, u64 a) { return (x + a - 1) / a * a; }
 
 }  // namespace rtopk

@@ -325,16 +325,6 @@ static EncodeLayout make_layout(const Geom &g)
 __device__ __forceinline__ u32 mag_of(u32 bits) { return bits & 0x7FFFFFFFu; }
 __device__ __forceinline__ u32 popc64(u64 m) { return (u32)__popcll((unsigned long long)m); }
 
-// Workgroup barrier that orders LDS accesses only: global loads, stores and
-// atomics a thread has in flight stay in flight (__syncthreads would wait for
-// all of them to complete first).
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Orders one wavefront's own LDS accesses: what its lanes wrote before is what
 // its lanes read after (the hardware keeps a wavefront's LDS operations in
 // order; this keeps the compiler from moving them).
