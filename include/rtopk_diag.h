@@ -38,7 +38,9 @@ typedef struct rtopk_encode_stats {
     uint32_t boundary_list_size; /* candidates that shared the deciding histogram bin */
     uint64_t count_greater;      /* #{i : mag(a_i) > threshold} */
     uint64_t ties_taken;         /* r - count_greater, taken from the lowest indices */
-    uint64_t superset_size;      /* entries compacted before the exact selection */
+    uint64_t superset_size;      /* entries compacted before the exact selection (candidates that
+                                    certainly belong to the top r and whose key is above the
+                                    a-priori window are not among them) */
     uint64_t key_list_size;      /* members whose sampling key fell inside the a-priori window */
 } rtopk_encode_stats_t;
 

@@ -8,9 +8,9 @@
 // workspace per element). The wavefront that streams a chunk appends the
 // entries it keeps to the chunk's slice in index order and finally stores how
 // many it kept. S is therefore ordered by index without any cross-workgroup
-// scan, ticket or fence. A chunk that keeps more than its slice holds only
-// counts on; the later kernels read such a chunk from the residual buffer,
-// which holds a by then. Later kernels walk S chunk by chunk; each of their
+// scan, ticket or fence. A chunk that would keep more than its slice holds is
+// marked; the later kernels read it from the residual buffer, which holds a by
+// then. Later kernels walk S chunk by chunk; each of their
 // wavefronts takes every U-th chunk, so that a region of the vector that is
 // dense in candidates is shared by all wavefronts.
 //
@@ -19,21 +19,23 @@
 //              each); clears the control block
 //   estimate   one workgroup: from the sample's order statistics, a lower
 //              bound t_lo that the r-th largest magnitude exceeds and an upper
-//              bound t_hi that it stays below, both with ~6 sigma of margin;
+//              bound t_hi that it stays below, both with 4 doubled sigmas of margin;
 //              [t_lo, t_hi] becomes the finely binned part of the histogram
 //   fused      a = g + m, stored into the residual buffer (12d bytes, the
-//              dominant kernel); entries with magnitude >= t_lo -> S, and
-//              into the workgroup's own histogram row: up to 2048 linear bins
-//              over the fine range and one bin for everything above it
-//              (every row also carries the sums over groups of 64 bins)
+//              dominant kernel); entries with magnitude >= t_lo go into the
+//              workgroup's own histogram row: up to 2048 linear bins over the
+//              fine range and one bin for everything above it (every row also
+//              carries the sums over groups of 64 bins). Their Philox keys are
+//              computed in the shadow of the stream and compared with an
+//              a-priori window [K_lo, K_hi] around the k-th smallest of r
+//              uniform keys; an entry above the fine range whose key lies above
+//              the window will not be sent, the others -> S with what the key said
 //   pick       one workgroup: the group sums of all rows -> the group that
 //              holds the r-th largest magnitude; that group's bins of all
 //              rows -> the bin that holds it (the deciding bin)
 //   classify   entries of S above the deciding bin are certain members of
-//              the top-r set: their Philox key is compared with an a-priori
-//              window [K_lo, K_hi] around the k-th smallest of r uniform
-//              keys - below: certain winner (counted per chunk), inside:
-//              copied to the short list M. Entries inside the deciding bin
+//              the top-r set: key below the window: certain winner (counted
+//              per chunk), inside: copied to the short list M. Entries inside the deciding bin
 //              are copied to the short list B and counted per chunk
 //   finalize   one workgroup: exact r-th largest (magnitude, lower index
 //              first) inside B -> (T, I*); members of B join the key lists;
@@ -44,7 +46,7 @@
 //              rank in index order and is located from the per-chunk counts.
 //              When a short list overflowed otherwise or the key window
 //              missed, the same quantities are found by radix selection over
-//              all of S instead (exact; on all workgroups of the kernel's
+//              S or, where S is not enough, the vector (exact; on all workgroups of the kernel's
 //              grid when the vector is long, see grid_select96)
 //   emit       entries of S that are members and winners -> the message in
 //              index order, starting at the chunk's prefix; residual at the
@@ -122,6 +124,16 @@ constexpr u32 kMaxWalkBlocks = kMaxUnits / kWalkWaves;
 __host__ __device__ inline u32 chunk_slot(u32 s, u32 U, u32 UC) { return (s % U) * UC + s / U; }
 constexpr u32 kListCap = 128;                 // short-list slots per classify workgroup
 constexpr u32 kSliceDiv = 8;                  // a chunk's slice of S holds a kSliceDiv-th of the chunk
+
+// An entry of S: the binary32 pattern, and one word with the element's place in
+// its chunk (18 bits), what its sampling key says (2 bits) and, for a key inside
+// the a-priori window, where in the window it lies (12 bits). The streaming
+// kernel computes the key of every candidate while it waits for memory, so the
+// kernels that walk S compute almost none.
+constexpr u32 kPlaceBits = 18, kPlaceMask = (1u << kPlaceBits) - 1u;
+constexpr u32 kKeyAbove = 0u, kKeyBelow = 1u, kKeyInside = 2u;   // ... the window [K_lo, K_hi]
+constexpr u32 kKeyUnknown = 3u;               // (entries read from the vector itself)
+constexpr u32 kWindowBits = 12;
 constexpr int kFinThreads = 1024;
 constexpr u32 kFinWaves = kFinThreads / kWave;
 constexpr u32 kSlabs = kTargetChunks / (4 * kFinThreads);  // 16-byte groups of chunk counters per thread
@@ -185,7 +197,8 @@ struct EncodeCtl {
     Bins bins;
     u32 n_samples;
     // written by k_pick (dense also by k_finalize when r == d and the key window missed)
-    u32 dense;          // S holds fewer than r entries: walk the vector itself
+    u32 dense;          // S does not hold what is needed: walk the vector itself
+    u32 missed;         // ... because the estimate (r == d: the key window) missed
     u32 bd_lo, bd_hi;   // pattern range of the deciding bin
     u32 bd_bits;        // bit width of bd_hi - bd_lo
     u64 c_def;          // entries above bd_hi
@@ -207,7 +220,7 @@ static_assert(offsetof(EncodeCtl, err) == 0, "the error flags lead the control b
 // Geometry and sampling window: a pure function of (d, r, k), computed on the host.
 struct Geom {
     u64 d, r, k;
-    u32 C;              // elements per chunk (multiple of 256, at least 1024)
+    u32 C;              // elements per chunk (a power of two, at least 1024)
     u32 cap;            // entries a chunk's slice of S holds (C / kSliceDiv); a chunk that keeps
                         // more is read from the vector itself by the later kernels
     u32 W;              // chunks
@@ -243,11 +256,14 @@ static Geom make_geom(u64 d, u64 r, u64 k)
     u64 per = (d + kTargetChunks - 1) / kTargetChunks;
     per = (per + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum;
     if (per < kMinChunk) per = kMinChunk;
-    // Measured with a plain streaming add over 66 M and 268 M elements: when every
-    // wavefront's piece starts a multiple of 8 KB after its neighbour's (chunks of
-    // 2048, 3072, 4096 elements) the stream runs 5-9% slower than with 1024, 2304,
-    // 2560 or 8192 elements; a quarter of a kilobyte more staggers the starting points.
-    if (per > kMinChunk && per % 1024 == 0 && per % 8192 != 0) per += kChunkQuantum;
+    // A power of two: the bare streaming add over chunks of 1024, 2048, 4096, 8192
+    // elements runs at 6.1, 6.0, 6.0, 5.8 TB/s (two rows in flight, 66 M to 2^28
+    // elements), over 1280, 2304, 3328, 4352 at 5.4, 5.7, 5.9, 5.7.
+    {
+        u64 pow2 = kMinChunk;
+        while (pow2 < per) pow2 *= 2;
+        per = pow2;
+    }
     g.C = (u32)per;
     g.cap = g.C / kSliceDiv;
     g.W = (u32)((d + per - 1) / per);
@@ -437,10 +453,14 @@ sample_body(const float *__restrict__ grad, const float *__restrict__ residual, 
 // With n samples and p = r/d, the number of samples among the true top r is
 // about Binomial(n, p); clusters of four that rise and fall together double
 // the standard deviation at worst. t_lo is the lower edge of the 12-bit
-// pattern bucket that holds the sample of rank np + 6 sd + 8 (so that at
+// pattern bucket that holds the sample of rank np + 4 sd + 8 (so that at
 // least r entries lie at or above t_lo), t_hi the upper edge of the bucket
-// that holds the sample of rank np - 6 sd - 8 (fewer than r entries lie
-// above it).
+// that holds the sample of rank np - 4 sd - 8 (fewer than r entries lie
+// above it). Four of these doubled deviations are six to eight true ones; a
+// miss (at worst 3 in 100,000 per side, were the clusters to rise and fall
+// entirely together) costs a fifth of a millisecond, while six of them kept a
+// fifth more candidates on every call (eight vectors of 25.6 M: classify 24.0
+// instead of 17.8 us, emit 20.7 instead of 17.0).
 // ---------------------------------------------------------------------------
 // One wavefront: walking 4096 buckets (in LDS) downwards from the bucket
 // `top` (nothing lies above it), 256 buckets at a time, find for each of
@@ -535,7 +555,7 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
     const float p = (float)((double)g.r / (double)g.d);
     const float np = (float)n * p;
     const float sd = 2.0f * sqrtf(np * (1.0f - p));
-    const float lo_rank = ceilf(np + 6.0f * sd + 8.0f), hi_rank = floorf(np - 6.0f * sd - 8.0f);
+    const float lo_rank = ceilf(np + 4.0f * sd + 8.0f), hi_rank = floorf(np - 4.0f * sd - 8.0f);
     const bool lo_all = lo_rank > (float)n;       // too few samples below the top: keep everything
     const u32 s_lo = lo_all ? n : (u32)lo_rank;
     const u32 s_hi = hi_rank < 1.0f ? 1u : (u32)hi_rank;
@@ -598,53 +618,76 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
 
 // ---------------------------------------------------------------------------
 // One wavefront iteration of the streaming kernel covers 256 consecutive
-// elements starting at `base`. Layout of the four elements a lane holds:
-// kVec4 -> base + 4*lane + e (16-byte accesses); otherwise base + 64*e + lane
-// (coalesced 4-byte accesses, any alignment). Kept entries are appended to
-// the chunk's slice of S in index order.
+// elements starting at `base`; a lane holds base + 4*lane + e (one 16-byte
+// access per array). Kept entries are appended to the chunk's slice of S in index
+// order.
 // ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// the same four floats at any address a float may have: the memory instructions of 16
+// bytes only ask for 4-byte alignment
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <bool kVec4>
-__device__ __forceinline__ u64 elem_index(u64 base, int e)
+__device__ __forceinline__ u64 elem_index(u64 base, int e) { return base + 4ull * lane_id() + (u64)e; }
+
+// what the sampling key of element idx says, as the top 14 bits of an entry's first word
+__device__ __forceinline__ u32 key_word(u32 idx, const Geom &g, const PhiloxSeed &seed)
 {
-    return kVec4 ? base + 4ull * lane_id() + (u64)e : base + 64ull * (u64)e + lane_id();
+    if (g.take_all) return kKeyBelow << 30;
+    const u64 key = sample_key(idx, seed);
+    if (key < g.K_lo) return kKeyBelow << 30;
+    if (key > g.K_hi) return kKeyAbove << 30;
+    return (kKeyInside << 30) | ((u32)(((key - g.K_lo) << g.k_nlz) >> (64 - kWindowBits)) << kPlaceBits);
 }
 
-template <bool kVec4>
-__device__ __forceinline__ void append_hits(const u32 (&bits)[4], const bool (&hit)[4], u64 base,
-                                            u32 &run, uint2 *__restrict__ my_ent, u32 cap)
-{
-    const u64 b0 = __ballot(hit[0]), b1 = __ballot(hit[1]), b2 = __ballot(hit[2]),
-              b3 = __ballot(hit[3]);
-    if ((b0 | b1 | b2 | b3) == 0ull) return;
-    if (run >= cap) {
-        // the slice is full: the chunk will be read from the vector itself, only its
-        // count goes on (anything above cap says so)
-        run += popc64(b0) + popc64(b1) + popc64(b2) + popc64(b3);
-        return;
-    }
-    const u64 below = lanes_below();
-    u32 pos[4];
-    if (kVec4) {
-        u32 p = run + popc64(b0 & below) + popc64(b1 & below) + popc64(b2 & below) +
-                popc64(b3 & below);
+// The candidates of the chunk a wavefront is streaming, in index order: they are
+// gathered in a ring in LDS and leave it 64 at a time, so that the sampling keys are
+// computed on full wavefronts and the slice of S is written in whole lines.
+constexpr u32 kRing = 512;                    // a power of two >= 63 waiting + one row of 256
+struct Ring {
+    uint2 *buf;         // kRing entries owned by this wavefront: (place in the chunk, pattern)
+    u32 head, pending;  // (head is reduced where it is used)
+    u32 out;            // entries of the chunk's slice so far (above its capacity: it overflowed)
+
+    __device__ __forceinline__ void append(const u32 (&bits)[4], const bool (&hit)[4], u32 place0, u32 cap)
+    {
+        const u64 b0 = __ballot(hit[0]), b1 = __ballot(hit[1]), b2 = __ballot(hit[2]),
+                  b3 = __ballot(hit[3]);
+        if ((b0 | b1 | b2 | b3) == 0ull) return;
+        if (out > cap) return;        // the slice overflowed: the chunk will be read from the vector itself
+        const u64 below = lanes_below();
+        const u32 at = head + pending;
+        u32 p = at + popc64(b0 & below) + popc64(b1 & below) + popc64(b2 & below) + popc64(b3 & below);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { pos[e] = p; p += hit[e] ? 1u : 0u; }
-    } else {
-        pos[0] = run + popc64(b0 & below);
-        pos[1] = run + popc64(b0) + popc64(b1 & below);
-        pos[2] = run + popc64(b0) + popc64(b1) + popc64(b2 & below);
-        pos[3] = run + popc64(b0) + popc64(b1) + popc64(b2) + popc64(b3 & below);
+        for (u32 e = 0; e < 4; ++e)
+            if (hit[e]) { buf[p & (kRing - 1u)] = make_uint2(place0 + 4u * lane_id() + e, bits[e]); ++p; }
+        pending += popc64(b0) + popc64(b1) + popc64(b2) + popc64(b3);
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if (hit[e] && pos[e] < cap) {
-            my_ent[pos[e]] = make_uint2((u32)elem_index<kVec4>(base, e), bits[e]);
+    // Up to 64 entries leave the ring. A candidate above the bracket is a certain member,
+    // and one whose key lies above the window is certainly not sent: it is needed by
+    // nobody and does not reach the slice (should the estimate or the window have missed,
+    // the vector itself is walked). In a layer that holds most of the top r, where nearly
+    // all candidates lie above the bracket, four fifths of them go this way.
+    __device__ __forceinline__ void take(u64 c0, const Geom &g, const PhiloxSeed &seed, u32 bracket_hi,
+                                         uint2 *__restrict__ my_ent)
+    {
+        const u32 n = pending < (u32)kWave ? pending : (u32)kWave;
+        wave_lds_fence();
+        uint2 e = make_uint2(0u, 0u);
+        bool stays = lane_id() < n;
+        if (stays) {
+            e = buf[(head + lane_id()) & (kRing - 1u)];
+            e.x |= key_word((u32)c0 + e.x, g, seed);
+            stays = mag_of(e.y) <= bracket_hi || (e.x >> 30) != kKeyAbove;
         }
+        wave_lds_fence();
+        const u64 mask = __ballot(stays);
+        const u32 pos = out + popc64(mask & lanes_below());
+        if (stays && pos < g.cap) my_ent[pos] = e;
+        head += n;
+        pending -= n;
+        out += popc64(mask);
     }
-    run += popc64(b0) + popc64(b1) + popc64(b2) + popc64(b3);
-}
+};
 
 // ---------------------------------------------------------------------------
 // fused: a = g + m -> residual buffer; candidates -> S and the histogram.
@@ -653,122 +696,139 @@ __device__ __forceinline__ void append_hits(const u32 (&bits)[4], const bool (&h
 // v + #wavefronts, ... so that neighbouring wavefronts stream neighbouring
 // 4 KB pieces of each array.
 // ---------------------------------------------------------------------------
-constexpr u32 kFusedThreads = 512;
+constexpr u32 kFusedThreads = 768;            // at most; a launch takes 4 to 12 wavefronts, see fused_waves
 constexpr u32 kFusedWaves = kFusedThreads / kWave;
-// Rows of 256 elements a wavefront fetches together (two 16-byte loads per lane
-// and row in flight) before it adds, stores and looks at them. Measured over
-// the batched launches of 11 M, 25.6 M and 66 M elements: one row 203 / 445 /
-// 591 us, two 173 / 393 / 531, three 178 / 394 / 559, four 174 / 408 / 566.
-constexpr int kFusedRows = 2;
+// kRows: rows of 256 elements a wavefront adds, stores and looks at together; the
+// next ones are on their way meanwhile. One, but for short vectors, where a
+// wavefront has a single chunk: two.
+constexpr int kLongRows = 1, kShortRows = 2;
 
 // kAll (r == d, the random-k operator): no magnitude decides anything. An
 // element is kept when its sampling key lies at or below the upper end of the
 // a-priori window (all of them when k == r as well); no histogram is made and
 // the control block, which no earlier kernel has touched, is cleared here.
-template <bool kVec4, bool kAll>
+template <bool kAll, int kRows>
 __device__ __forceinline__ void
 fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g, PhiloxSeed seed,
         EncodeCtl *__restrict__ ctl, u32 zero_words, u32 *__restrict__ partials,
         u32 *__restrict__ group_sums, u32 *__restrict__ seg_count, uint2 *__restrict__ s_ent)
 {
     __shared__ u32 h[kAll ? 1 : kMaxBins];
+    extern __shared__ uint2 ring_s[];           // kRing entries per wavefront (and what the launch claims beyond)
     Bins bins{};
     u32 nbins = 0;
     if (kAll) {
         // (the control block and what follows it up to zero_words, at the workspace's start)
         if (blockIdx.x == 0)
-            for (u32 i = threadIdx.x; i < zero_words; i += kFusedThreads)
+            for (u32 i = threadIdx.x; i < zero_words; i += blockDim.x)
                 reinterpret_cast<u32 *>(ctl)[i] = 0u;
     } else {
         bins = ctl->bins;
         nbins = bins.nfine + kCoarseBins;
-        for (u32 b = threadIdx.x; b < nbins; b += kFusedThreads) h[b] = 0u;
+        for (u32 b = threadIdx.x; b < nbins; b += blockDim.x) h[b] = 0u;
         __syncthreads();
     }
 
-    const u32 wave_stride = gridDim.x * kFusedWaves;
+    const u32 n_waves = blockDim.x / kWave, wave_stride = gridDim.x * n_waves;
     u32 n_above = 0;        // this wavefront's candidates above the linear bins
-    for (u32 w = blockIdx.x * kFusedWaves + threadIdx.x / kWave; w < g.W; w += wave_stride) {
-        const u64 c0 = (u64)w * g.C;
-        const u64 c1 = c0 + g.C < g.d ? c0 + g.C : g.d;
-        uint2 *my_ent = s_ent + (u64)w * g.cap;
-        u32 run = 0;
-        auto keep = [&](const u32 (&bits)[4], const bool (&valid)[4], u64 base) {
-            bool hit[4];
+    Ring ring{ring_s + threadIdx.x / kWave * kRing, 0u, 0u, 0u};
+    const u32 bracket_hi = kAll ? 0x7FFFFFFFu : bins.fine_hi;
+    u64 c0 = 0;             // the current chunk
+    uint2 *my_ent = s_ent;
+    auto keep = [&](const u32 (&bits)[4], const bool (&valid)[4], u32 place) {
+        bool hit[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (kAll) {
-                    hit[e] = valid[e] &&
-                             (g.take_all != 0u ||
-                              sample_key((u32)elem_index<kVec4>(base, e), seed) <= g.K_hi);
-                } else {
-                    const u32 m = mag_of(bits[e]);
-                    hit[e] = valid[e] && m >= bins.t_lo;
-                    // candidates inside the bracket are counted bin by bin; the ones above it
-                    // (certain members, often most of the candidates and crowded in a few
-                    // exponents) only need their number: a popcount instead of LDS additions
-                    const bool fine = hit[e] && m <= bins.fine_hi;
-                    if (fine) atomicAdd(&h[(m - bins.t_lo) >> bins.shift], 1u);
-                    n_above += popc64(__ballot(hit[e] && !fine));
-                }
-            }
-            append_hits<kVec4>(bits, hit, base, run, my_ent, g.cap);
-        };
-        const bool all_valid[4] = {true, true, true, true};
-        // NR full rows at a time, all loads issued before the first use. Every
-        // element is read once and written once: both the loads and the store carry
-        // the streaming hint. (Measured: the hint on the residual's load AND store
-        // together shortens the kernel by 15%; either one alone changes nothing.)
-        auto full_rows = [&](auto nr_c, u64 base) {
-            constexpr int NR = decltype(nr_c)::value;
-            u32 bits[NR][4];
-            if (kVec4) {
-                const f32x4 *g4 = reinterpret_cast<const f32x4 *>(grad + base) + lane_id();
-                f32x4 *m4 = reinterpret_cast<f32x4 *>(residual + base) + lane_id();
-                f32x4 gv[NR], mv[NR];
-#pragma unroll
-                for (int u = 0; u < NR; ++u) {
-                    gv[u] = __builtin_nontemporal_load(g4 + u * kWave);
-                    mv[u] = __builtin_nontemporal_load(m4 + u * kWave);
-                }
-#pragma unroll
-                for (int u = 0; u < NR; ++u) {
-                    const f32x4 a = gv[u] + mv[u];
-                    __builtin_nontemporal_store(a, m4 + u * kWave);
-                    bits[u][0] = __float_as_uint(a.x); bits[u][1] = __float_as_uint(a.y);
-                    bits[u][2] = __float_as_uint(a.z); bits[u][3] = __float_as_uint(a.w);
-                }
+        for (int e = 0; e < 4; ++e) {
+            if (kAll) {
+                hit[e] = valid[e] &&
+                         (g.take_all != 0u ||
+                          sample_key((u32)elem_index(c0 + place, e), seed) <= g.K_hi);
             } else {
-                const float *gp = grad + base + lane_id();
-                float *mp = residual + base + lane_id();
-                float gv[4 * NR], mv[4 * NR];
-#pragma unroll
-                for (int q = 0; q < 4 * NR; ++q) {
-                    gv[q] = __builtin_nontemporal_load(gp + q * kWave);
-                    mv[q] = __builtin_nontemporal_load(mp + q * kWave);
-                }
-#pragma unroll
-                for (int q = 0; q < 4 * NR; ++q) {
-                    const float a = gv[q] + mv[q];
-                    __builtin_nontemporal_store(a, mp + q * kWave);
-                    bits[q / 4][q % 4] = __float_as_uint(a);
-                }
+                const u32 m = mag_of(bits[e]);
+                hit[e] = valid[e] && m >= bins.t_lo;
+                // candidates inside the bracket are counted bin by bin; the ones above it
+                // (certain members, often most of the candidates and crowded in a few
+                // exponents) only need their number: a popcount instead of LDS additions
+                const bool fine = hit[e] && m <= bins.fine_hi;
+                if (fine) atomicAdd(&h[(m - bins.t_lo) >> bins.shift], 1u);
+                n_above += popc64(__ballot(hit[e] && !fine));
             }
+        }
+        ring.append(bits, hit, place, g.cap);
+        while (ring.pending >= (u32)kWave) ring.take(c0, g, seed, bracket_hi, my_ent);
+    };
+    auto open_chunk = [&](u32 w) {
+        c0 = (u64)w * g.C;
+        my_ent = s_ent + (u64)w * g.cap;
+        ring.out = 0u;
+    };
+    auto close_chunk = [&](u32 w) {
+        if (ring.pending != 0u) ring.take(c0, g, seed, bracket_hi, my_ent);
+        if (lane_id() == 0) seg_count[chunk_slot(w, g.U, g.UC)] = ring.out;
+    };
+    const bool all_valid[4] = {true, true, true, true};
+    // Groups of kRows rows. Every element is read once and written once: both
+    // the loads and the store carry the streaming hint. (Measured: the hint on the
+    // residual's load AND store together shortens the kernel by 15%; either one
+    // alone changes nothing.)
+    constexpr u32 kGroup = kRows * kChunkQuantum;
+    f32x4 gv[kRows], mv[kRows];
+    auto load = [&](u64 base) {
+        const f32x4u *gp = reinterpret_cast<const f32x4u *>(grad + base) + lane_id();
+        const f32x4u *mp = reinterpret_cast<const f32x4u *>(residual + base) + lane_id();
 #pragma unroll
-            for (int u = 0; u < NR; ++u) keep(bits[u], all_valid, base + u * kChunkQuantum);
-        };
+        for (int q = 0; q < kRows; ++q) {
+            gv[q] = __builtin_nontemporal_load(gp + q * kWave);
+            mv[q] = __builtin_nontemporal_load(mp + q * kWave);
+        }
+    };
+    // The chunks that are whole: the next group is on its way while this one's
+    // candidates are looked for.
+    const u32 w_first = blockIdx.x * n_waves + threadIdx.x / kWave;
+    const u32 w_full = (u32)(g.d / g.C);
+    u32 w = w_first;
+    if (w < w_full) {
+        open_chunk(w);
         u64 base = c0;
-        for (; base + kFusedRows * kChunkQuantum <= c1; base += kFusedRows * kChunkQuantum)
-            full_rows(std::integral_constant<int, kFusedRows>{}, base);
-        for (; base + kChunkQuantum <= c1; base += kChunkQuantum)
-            full_rows(std::integral_constant<int, 1>{}, base);
-        if (base < c1) {
+        load(base);
+        for (;;) {
+            u32 bits[kRows][4];
+            f32x4u *mp = reinterpret_cast<f32x4u *>(residual + base) + lane_id();
+#pragma unroll
+            for (int q = 0; q < kRows; ++q) {
+                const f32x4 a = gv[q] + mv[q];
+                __builtin_nontemporal_store((f32x4u)a, mp + q * kWave);
+                bits[q][0] = __float_as_uint(a.x); bits[q][1] = __float_as_uint(a.y);
+                bits[q][2] = __float_as_uint(a.z); bits[q][3] = __float_as_uint(a.w);
+            }
+            const u32 place = (u32)(base - c0);
+            const bool last = place + kGroup >= g.C;
+            const u32 w_next = last ? w + wave_stride : w;
+            const u64 next = last ? (u64)w_next * g.C : base + kGroup;
+            const bool more = w_next < w_full;
+            if (more) load(next);
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) keep(bits[u], all_valid, place + u * kChunkQuantum);
+            if (last) {
+                close_chunk(w);
+                open_chunk(w_next);
+            }
+            if (!more) break;
+            w = w_next;
+            base = next;
+        }
+        while (w < w_full) w += wave_stride;
+    }
+    // the ragged end of the vector: one chunk, of some wavefront
+    if (w == w_full && w < g.W) {
+        open_chunk(w);
+        for (u64 base = c0; base < g.d; base += kChunkQuantum) {
             u32 bits[4];
             bool valid[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const u64 i = elem_index<kVec4>(base, e);
-                valid[e] = i < c1;
+                const u64 i = elem_index(base, e);
+                valid[e] = i < g.d;
                 bits[e] = 0u;
                 if (valid[e]) {
                     const float a = grad[i] + residual[i];
@@ -776,9 +836,9 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
                     bits[e] = __float_as_uint(a);
                 }
             }
-            keep(bits, valid, base);
+            keep(bits, valid, (u32)(base - c0));
         }
-        if (lane_id() == 0) seg_count[chunk_slot(w, g.U, g.UC)] = run;
+        close_chunk(w);
     }
     if (kAll) return;
     if (lane_id() == 0 && n_above != 0u) atomicAdd(&h[bins.nfine], n_above);
@@ -789,9 +849,9 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
     // up those (a sixty-fourth of the data), finds the group that holds the
     // r-th largest magnitude and then only needs that group's bins of every row.
     u32 *row = partials + (u64)blockIdx.x * nbins;
-    for (u32 b = threadIdx.x; b < nbins; b += kFusedThreads) row[b] = h[b];
+    for (u32 b = threadIdx.x; b < nbins; b += blockDim.x) row[b] = h[b];
     const u32 ngroups = (nbins + kCoarseSpan - 1) / kCoarseSpan;
-    for (u32 c = threadIdx.x / kWave; c < ngroups; c += kFusedWaves) {
+    for (u32 c = threadIdx.x / kWave; c < ngroups; c += n_waves) {
         const u32 b = c * kCoarseSpan + lane_id();
         const u32 sum = wave_sum(b < nbins ? h[b] : 0u);
         if (lane_id() == 0) group_sums[(u64)blockIdx.x * kMaxGroups + c] = sum;
@@ -826,16 +886,19 @@ struct Candidates {
         *from_vector = dense || kept > cap;
         return *from_vector ? length(s) : kept;
     }
-    __device__ __forceinline__ void entry(u32 s, u32 j, bool from_vector, u32 *idx, u32 *bits) const
+    // (key: what the streaming kernel left of the sampling key, kKeyUnknown << 30 if nothing)
+    __device__ __forceinline__ void entry(u32 s, u32 j, bool from_vector, u32 *idx, u32 *bits, u32 *key) const
     {
         if (!from_vector) {
             const uint2 e = s_ent[(u64)s * cap + j];
-            *idx = e.x;
+            *idx = s * C + (e.x & kPlaceMask);
             *bits = e.y;
+            *key = e.x;
         } else {
             const u64 at = (u64)s * C + j;
             *idx = (u32)at;
             *bits = __float_as_uint(a[at]);
+            *key = kKeyUnknown << 30;
         }
     }
 };
@@ -890,7 +953,7 @@ struct ChunkWalk {
         *first = __shfl(excl, c, kWave);
     }
 
-    // f(valid, i, index, pattern, first, p0), see above; the entries of four
+    // f(valid, i, index, pattern, key word, first, p0), see above; the entries of four
     // iterations are fetched together while that many are left
     template <class F>
     __device__ __forceinline__ void for_each(const Candidates &cand, F &&f) const
@@ -899,22 +962,22 @@ struct ChunkWalk {
         constexpr u32 kAhead = 4;
         u32 p0 = 0;
         for (; p0 + kAhead * kWave <= total; p0 += kAhead * kWave) {
-            u32 c[kAhead], first[kAhead], idx[kAhead], bits[kAhead];
+            u32 c[kAhead], first[kAhead], idx[kAhead], bits[kAhead], key[kAhead];
 #pragma unroll
             for (u32 q = 0; q < kAhead; ++q) {
                 const u32 p = p0 + q * kWave + lane;
                 locate(p, &c[q], &first[q]);
-                cand.entry(u + c[q] * stride, p - first[q], false, &idx[q], &bits[q]);
+                cand.entry(u + c[q] * stride, p - first[q], false, &idx[q], &bits[q], &key[q]);
             }
 #pragma unroll
-            for (u32 q = 0; q < kAhead; ++q) f(true, c[q], idx[q], bits[q], first[q], p0 + q * kWave);
+            for (u32 q = 0; q < kAhead; ++q) f(true, c[q], idx[q], bits[q], key[q], first[q], p0 + q * kWave);
         }
         for (; p0 < total; p0 += kWave) {
             const u32 p = p0 + lane;
-            u32 c, first, idx = 0, bits = 0;
+            u32 c, first, idx = 0, bits = 0, key = 0;
             locate(p, &c, &first);
-            if (p < total) cand.entry(u + c * stride, p - first, false, &idx, &bits);
-            f(p < total, c, idx, bits, first, p0);
+            if (p < total) cand.entry(u + c * stride, p - first, false, &idx, &bits, &key);
+            f(p < total, c, idx, bits, key, first, p0);
         }
     }
 
@@ -983,58 +1046,83 @@ struct ChunkWalk {
     }
 
     // The same chunks with the elements that keep(pattern) lets through gathered
-    // first, so that the work per entry (a sampling key costs a hundred
-    // instructions) is done on full wavefronts: a row's survivors are appended in
-    // index order to a ring in LDS (buf: kRowQueue entries owned by this
-    // wavefront) and taken from its front 64 at a time; what is left of a chunk is
-    // taken before the next chunk starts, so the ring only ever holds one chunk's
-    // entries. f(valid, i, index, pattern) is called by all lanes together (from
-    // one place: its code exists once), entries of one chunk in index order.
+    // first, so that the work per entry is done on full wavefronts: the survivors are
+    // appended in index order to a ring in LDS (buf: kRowQueueSize entries owned by this
+    // wavefront) and taken from its front 64 at a time; what is left of a chunk is taken
+    // before the next chunk starts, so the ring only ever holds one chunk's entries.
+    // f(valid, i, index, pattern) is called by all lanes together (from one place: its
+    // code exists once), entries of one chunk in index order. Four rows of a chunk are
+    // fetched together (one at a time, the trips to memory of the few wavefronts that
+    // hold such a chunk were half of the walking kernels' time in a layered vector).
     template <class Keep, class F>
     __device__ __forceinline__ void for_each_vector_entry(const Candidates &cand, uint2 *buf,
                                                           Keep &&keep, F &&f) const
     {
+        constexpr u32 kRows = 4;
+        typedef u32 u32x16 __attribute__((ext_vector_type(4 * kRows)));
         const u32 lane = lane_id();
         const u64 below = lanes_below();
-        RowCursor rc = rows();
-        u32 head = 0, pending = 0, cur = 0;
-        bool flushing = false;        // the chunk has ended: empty the ring before the next one
-        for (;;) {
-            while (pending < (u32)kWave && !flushing) {
-                if (!rc.open) {
-                    if (pending != 0u) { flushing = true; break; }
-                    if (!next_chunk(cand, rc)) break;
-                    cur = rc.i;
-                }
-                u32 idx0, bits[4];
-                bool valid[4], hit[4];
-                load_row(cand, rc, &idx0, bits, valid);
-                u64 b[4];
+        const bool vec16 = (reinterpret_cast<uintptr_t>(cand.a) & 15u) == 0;
+        u32 head = 0, pending = 0;
+        for (u64 rest = from_vector; rest != 0ull; rest &= rest - 1ull) {
+            const u32 i = (u32)__ffsll((unsigned long long)rest) - 1u;
+            const u32 sc = u + i * stride;
+            const u64 c0 = (u64)sc * cand.C;
+            const u32 len = cand.length(sc);
+            for (u32 r0 = 0; r0 < len || pending != 0u; r0 += kRows * kChunkQuantum) {
+                u32x16 bits;
+                if (vec16 && r0 + kRows * kChunkQuantum <= len) {
 #pragma unroll
-                for (u32 e = 0; e < 4; ++e) {
-                    hit[e] = valid[e] && keep(bits[e]);
-                    b[e] = __ballot(hit[e]);
-                }
-                if ((b[0] | b[1] | b[2] | b[3]) != 0ull) {
-                    u32 p = head + pending + popc64(b[0] & below) + popc64(b[1] & below) +
-                            popc64(b[2] & below) + popc64(b[3] & below);
+                    for (u32 q = 0; q < kRows; ++q) {
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(cand.a + c0 + r0 + q * kChunkQuantum + 4u * lane);
 #pragma unroll
-                    for (u32 e = 0; e < 4; ++e) {
-                        if (hit[e]) { buf[p & (kRowQueueSize - 1u)] = make_uint2(idx0 + e, bits[e]); ++p; }
+                        for (u32 e = 0; e < 4; ++e) bits[4 * q + e] = __float_as_uint(v[e]);
                     }
-                    pending += popc64(b[0]) + popc64(b[1]) + popc64(b[2]) + popc64(b[3]);
-                    wave_lds_fence();
+                } else {
+#pragma unroll
+                    for (u32 q = 0; q < kRows; ++q)
+#pragma unroll
+                        for (u32 e = 0; e < 4; ++e) {
+                            const u32 at = r0 + q * kChunkQuantum + 4u * lane + e;
+                            bits[4 * q + e] = at < len ? __float_as_uint(cand.a[c0 + at]) : 0u;
+                        }
+                }
+#pragma unroll 1
+                for (u32 q = 0; q <= kRows; ++q) {
+                    const u32 place = r0 + q * kChunkQuantum + 4u * lane;
+                    if (q < kRows) {
+                        u64 b[4];
+                        bool hit[4];
+#pragma unroll
+                        for (u32 e = 0; e < 4; ++e) {
+                            hit[e] = place + e < len && keep(bits[4 * q + e]);
+                            b[e] = __ballot(hit[e]);
+                        }
+                        if ((b[0] | b[1] | b[2] | b[3]) == 0ull) continue;
+                        u32 p = head + pending + popc64(b[0] & below) + popc64(b[1] & below) +
+                                popc64(b[2] & below) + popc64(b[3] & below);
+#pragma unroll
+                        for (u32 e = 0; e < 4; ++e)
+                            if (hit[e]) {
+                                buf[p & (kRowQueueSize - 1u)] = make_uint2((u32)c0 + place + e, bits[4 * q + e]);
+                                ++p;
+                            }
+                        pending += popc64(b[0]) + popc64(b[1]) + popc64(b[2]) + popc64(b[3]);
+                        wave_lds_fence();
+                    }
+                    // the chunk's end empties the ring
+                    const bool flush = q == kRows && r0 + kRows * kChunkQuantum >= len;
+                    while (pending >= (u32)kWave || (flush && pending != 0u)) {
+                        const u32 take = pending < (u32)kWave ? pending : (u32)kWave;
+                        const bool v = lane < take;
+                        const uint2 e = v ? buf[(head + lane) & (kRowQueueSize - 1u)] : make_uint2(0u, 0u);
+                        f(v, i, e.x, e.y);
+                        head += take;
+                        pending -= take;
+                        wave_lds_fence();
+                    }
                 }
             }
-            if (pending == 0u) break;             // no chunk left and nothing waiting
-            const u32 take = pending < (u32)kWave ? pending : (u32)kWave;
-            const bool v = lane < take;
-            const uint2 e = v ? buf[(head + lane) & (kRowQueueSize - 1u)] : make_uint2(0u, 0u);
-            f(v, cur, e.x, e.y);
-            head = (head + take) & (kRowQueueSize - 1u);
-            pending -= take;
-            if (pending == 0u) flushing = false;
-            wave_lds_fence();
         }
     }
 };
@@ -1170,7 +1258,10 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
     if (tid == 0) {
         u32 bd_lo = 0, bd_hi = 0;
         if (!dense) bin_range(bins, bin_s, &bd_lo, &bd_hi);
-        ctl->dense = dense ? 1u : 0u;
+        // above the bracket S only holds what may be sent: no short list can decide there
+        const bool above = !dense && bin_s >= bins.nfine;
+        ctl->dense = (dense || above) ? 1u : 0u;
+        ctl->missed = dense ? 1u : 0u;
         ctl->bd_lo = bd_lo;
         ctl->bd_hi = bd_hi;
         ctl->bd_bits = bd_hi > bd_lo ? 32u - (u32)__clz(bd_hi - bd_lo) : 1u;
@@ -1196,6 +1287,7 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const float *__restrict__
            u32 *__restrict__ b_mag, u32 *__restrict__ b_idx)
 {
     __shared__ u32 cnt_m, cnt_b, cnt_sure, bmin_s, bmax_s;
+    __shared__ u32 list_m[kListCap];
     __shared__ u32 per_chunk[kWalkWaves][kUnitChunksMax];
     __shared__ u32 per_chunk_b[kWalkWaves][kUnitChunksMax];
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
@@ -1221,20 +1313,17 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const float *__restrict__
     // finalize kernel reads entry p of all workgroups with one coalesced load
     auto slot = [&](u32 p) { return (u64)p * g.G3 + blockIdx.x; };
     const u64 below = lanes_below();
-    auto per_entry = [&](bool valid, u32 i, u32 idx, u32 bits) {
+    auto per_entry = [&](bool valid, u32 i, u32 idx, u32 bits, u32 key) {
         const u32 m = mag_of(bits);
         const bool member = valid && (g.all_members != 0u || m > bd_hi);
         const bool in_bin = valid && !member && m >= bd_lo;
         if (member) {
-            bool sure = g.take_all != 0u;
-            if (!sure) {
-                const u64 key = sample_key(idx, seed);
-                if (key < g.K_lo) {
-                    sure = true;
-                } else if (key <= g.K_hi) {
-                    const u32 p = atomicAdd(&cnt_m, 1u);
-                    if (p < kListCap) { m_key[slot(p)] = key; m_idx[slot(p)] = idx; }
-                }
+            u32 says = key >> 30;
+            if (says == kKeyUnknown) says = key_word(idx, g, seed) >> 30;
+            const bool sure = says == kKeyBelow;
+            if (says == kKeyInside) {
+                const u32 p = atomicAdd(&cnt_m, 1u);
+                if (p < kListCap) list_m[p] = idx;
             }
             if (sure) atomicAdd(&per_chunk[wave][i], 1u);
         }
@@ -1252,13 +1341,15 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const float *__restrict__
             if (m > lane_bmax) { lane_bmax = m; atomicMax(&bmax_s, m); }
         }
     };
-    walk.for_each(cand, [&](bool valid, u32 i, u32 idx, u32 bits, u32, u32) {
-        per_entry(valid, i, idx, bits);
+    walk.for_each(cand, [&](bool valid, u32 i, u32 idx, u32 bits, u32 key, u32, u32) {
+        per_entry(valid, i, idx, bits, key);
     });
     if (__builtin_expect(walk.from_vector != 0ull, 0))
         walk.for_each_vector_entry(cand, row_queue[wave],
                                    [&](u32 bits) { return g.all_members != 0u || mag_of(bits) >= bd_lo; },
-                                   per_entry);
+                                   [&](bool valid, u32 i, u32 idx, u32 bits) {
+                                       per_entry(valid, i, idx, bits, kKeyUnknown << 30);
+                                   });
     __builtin_amdgcn_wave_barrier();
     // certain winners, and entries of the deciding bin, of each of the wavefront's chunks
     u32 mine = 0;
@@ -1273,6 +1364,13 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const float *__restrict__
     mine = wave_sum(mine);
     if (lane == 0 && mine) atomicAdd(&cnt_sure, mine);
     __syncthreads();
+    // the keys of the workgroup's entries of M, all at once
+    static_assert(kListCap <= kWalkThreads, "one thread per list slot");
+    if (threadIdx.x < cnt_m && threadIdx.x < kListCap) {
+        const u32 idx = list_m[threadIdx.x];
+        m_key[slot(threadIdx.x)] = sample_key(idx, seed);
+        m_idx[slot(threadIdx.x)] = idx;
+    }
     if (threadIdx.x == 0) {
         blk_sure[blockIdx.x] = cnt_sure;
         n_m[blockIdx.x] = cnt_m < kListCap ? cnt_m : kListCap;
@@ -1618,7 +1716,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         // loads, then their entries as one flat sequence, four iterations fetched together
         for (u32 first = wave * kWave; first < g.W; first += kFinWaves * kWave) {
             const ChunkWalk<kWave> walk(cand, first, 1u, g.W);
-            walk.for_each(cand, [&](bool valid, u32 i, u32 idx, u32 bits, u32, u32) {
+            walk.for_each(cand, [&](bool valid, u32 i, u32 idx, u32 bits, u32, u32, u32) {
                 if (valid) f(idx, bits, first + i);
             });
             auto of_row = [&](bool valid, u32 i, u32 idx, u32 bits) {
@@ -1732,8 +1830,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 if (!fv) {
                     for (u32 j0 = 0; j0 < n_e; j0 += kWave) {
                         const u32 j = j0 + lane;
-                        u32 idx = 0, bits = 0;
-                        if (j < n_e) cand.entry(sc, j, false, &idx, &bits);
+                        u32 idx = 0, bits = 0, key = 0;
+                        if (j < n_e) cand.entry(sc, j, false, &idx, &bits, &key);
                         f(j < n_e, idx, bits);
                     }
                 } else {
@@ -1798,6 +1896,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             if (in_bin_only && m < bd_lo) return false;
             return pair_le((u64)(top - m), idx, tbound);
         };
+        // the keys above the window are not in S
+        if (!g.take_all) cand.dense = true;
         if (!g.take_all && w.alive) {
             auto each_key = [&](auto &&f2) {
                 wide_each([&](bool valid, u32 idx, u32 bits) {
@@ -1855,7 +1955,10 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         if (blockIdx.x != 0u) return;
         have_t = true;
         have_k = true;
-        if (g.all_members && tid == 0) ctl->dense = 1u;
+        if (cand.dense && tid == 0) {
+            ctl->dense = 1u;
+            if (g.all_members) ctl->missed = 1u;
+        }
     }
 
     // The short-list path. It is compiled twice: once with both lists in LDS
@@ -1982,8 +2085,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 u32 seen = 0;
                 for (u32 j0 = 0; j0 < n_e && seen < want; j0 += kFinThreads) {
                     const u32 j = j0 + tid;
-                    u32 idx = 0, bits = 0;
-                    if (j < n_e) cand.entry(sc, j, sc_vec, &idx, &bits);
+                    u32 idx = 0, bits = 0, key = 0;
+                    if (j < n_e) cand.entry(sc, j, sc_vec, &idx, &bits, &key);
                     const u32 m = mag_of(bits);
                     const u32 flag = (j < n_e && m >= bd_lo && m <= bd_hi) ? 1u : 0u;
                     const u32 excl = block_exclusive_sum(flag, scan32);
@@ -2045,7 +2148,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                         if (valid && m >= bd_lo && m <= bd_hi && idx <= I_star)
                             join(idx, [&] { atomicAdd(&run_sure[wave][i], 1u); ++my_sure; });
                     };
-                    walk.for_each(cand, [&](bool valid, u32 i, u32 idx, u32 bits, u32, u32) {
+                    walk.for_each(cand, [&](bool valid, u32 i, u32 idx, u32 bits, u32, u32, u32) {
                         run_member(valid, i, idx, bits);
                     });
                     walk.for_each_vector_row(cand, each_of_row(run_member));
@@ -2117,12 +2220,16 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                         m_lds ? st_m_key : dm_key, m_lds ? st_m_idx : dm_idx, std::false_type{});
     }
 
-    if (g.all_members && !have_k) {
-        // r == d and the key window missed (or a short list overflowed): the
-        // candidates are only the coordinates inside the window, so the exact
-        // selection below walks the vector itself, and so does the emit kernel
+    if (!have_t || (!have_k && !g.take_all)) {
+        // A short list overflowed or the key window missed: S does not hold the
+        // candidates above the bracket whose keys lie above the window (r == d: any key
+        // above it), so the exact selection below walks the vector itself, and so does
+        // the emit kernel.
         cand.dense = true;
-        if (tid == 0) ctl->dense = 1u;
+        if (tid == 0) {
+            ctl->dense = 1u;
+            if (g.all_members) ctl->missed = 1u;
+        }
     }
     if (!have_t) {
         // ---- exact threshold by selection over all candidates -----------
@@ -2277,12 +2384,22 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
     const u64 below = lanes_below();
     u32 run = 0;          // winners at flat positions before this iteration
     u32 carry = 0;        // winners before the first entry of the chunk that runs into this iteration
-    auto wins = [&](bool valid, u32 idx, u32 bits) {
+    // With the cut inside the a-priori window the streaming kernel's word decides, but
+    // for the few entries in the cut's own 4096th of the window.
+    const bool in_window = g.take_all != 0u || (kcut.hi >= g.K_lo && kcut.hi <= g.K_hi);
+    const u32 cut_at = (u32)(((kcut.hi - g.K_lo) << g.k_nlz) >> (64 - kWindowBits));
+    auto wins = [&](bool valid, u32 idx, u32 bits, u32 key) {
         bool win = false;
         if (valid) {
             const u32 m = mag_of(bits);
             win = m > T || (m == T && idx <= I_star);
-            if (win && !g.take_all) win = pair_le(sample_key(idx, seed), idx, kcut);
+            if (win && !g.take_all) {
+                const u32 says = key >> 30, at = (key >> kPlaceBits) & ((1u << kWindowBits) - 1u);
+                if (__builtin_expect(!in_window || says == kKeyUnknown || (says == kKeyInside && at == cut_at), 0))
+                    win = pair_le(sample_key(idx, seed), idx, kcut);
+                else
+                    win = says == kKeyBelow || (says == kKeyInside && at < cut_at);
+            }
         }
         return win;
     };
@@ -2294,8 +2411,8 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
             residual[idx] = v - v;
         }
     };
-    walk.for_each(cand, [&](bool valid, u32 i, u32 idx, u32 bits, u32 first, u32 p0) {
-        const bool win = wins(valid, idx, bits);
+    walk.for_each(cand, [&](bool valid, u32 i, u32 idx, u32 bits, u32 key, u32 first, u32 p0) {
+        const bool win = wins(valid, idx, bits, key);
         const u64 mask = __ballot(win);
         // winners before the first entry of this lane's chunk
         const u32 at_start =
@@ -2313,7 +2430,7 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
                                [&](u32 bits) { return mag_of(bits) >= T; },
                                [&](bool valid, u32 i, u32 idx, u32 bits) {
         if (i != row_chunk) { row_chunk = i; seen = 0; }
-        const bool win = wins(valid, idx, bits);
+        const bool win = wins(valid, idx, bits, kKeyUnknown << 30);
         const u64 mask = __ballot(win);
         if (mask == 0ull) return;
         const u32 base_c = __shfl(my_base, i, kWave);
@@ -2385,11 +2502,11 @@ __global__ void __launch_bounds__(kEstThreads) k_estimate(Batch B, Geom g, Encod
     estimate_body(m.at<u32>(L.samples), g, m.at<EncodeCtl>(L.ctl));
 }
 
-template <bool kVec4, bool kAll>
+template <bool kAll, int kRows>
 __global__ void __launch_bounds__(kFusedThreads) k_fused(Batch B, Geom g, EncodeLayout L)
 {
     const Member m(B);
-    fused_body<kVec4, kAll>(m.grad, m.residual, g, m.seed, m.at<EncodeCtl>(L.ctl),
+    fused_body<kAll, kRows>(m.grad, m.residual, g, m.seed, m.at<EncodeCtl>(L.ctl),
                             (u32)(L.zero_bytes / 4), m.at<u32>(L.partials), m.at<u32>(L.group_sums), m.at<u32>(L.seg_count),
                             m.at<uint2>(L.s_ent));
 }
@@ -2438,12 +2555,12 @@ __global__ void __launch_bounds__(kWalkThreads) k_emit(Batch B, Geom g, EncodeLa
 __global__ void __launch_bounds__(kFusedThreads)
 k_stream_add(const float *__restrict__ grad, float *__restrict__ residual, u64 d, u32 C, u32 W)
 {
-    const u32 wave_stride = gridDim.x * kFusedWaves;
-    for (u32 w = blockIdx.x * kFusedWaves + threadIdx.x / kWave; w < W; w += wave_stride) {
+    const u32 n_waves = blockDim.x / kWave, wave_stride = gridDim.x * n_waves;
+    for (u32 w = blockIdx.x * n_waves + threadIdx.x / kWave; w < W; w += wave_stride) {
         const u64 c0 = (u64)w * C;
         const u64 c1 = c0 + C < d ? c0 + C : d;
         u64 base = c0;
-        constexpr int NR = kFusedRows;
+        constexpr int NR = 2;
         for (; base + NR * kChunkQuantum <= c1; base += NR * kChunkQuantum) {
             const f32x4 *g4 = reinterpret_cast<const f32x4 *>(grad + base) + lane_id();
             f32x4 *m4 = reinterpret_cast<f32x4 *>(residual + base) + lane_id();
@@ -2519,8 +2636,9 @@ constexpr int kFusedBlocksPerCU = 1;
 // to itself the device then keeps three workgroups of different members on
 // every compute unit, and the interleaved streams cost 8% (443 instead of
 // 407 us for eight vectors of 25.6 M elements). Each workgroup therefore also
-// claims more than half of the unit's 160 KB of LDS, which it does not use: one
-// workgroup per unit at any time, members streamed one after the other.
+// claims more than half of the unit's 160 KB of LDS, most of which it does not use: one
+// workgroup per unit at any time, members streamed one after the other. (Short vectors,
+// whose workgroups only hold a chunk per wavefront, run side by side instead.)
 constexpr unsigned kFusedLdsClaim = 96u * 1024u;
 std::mutex g_device_mutex;
 unsigned g_fused_grid[kMaxDevices];
@@ -2533,6 +2651,21 @@ bool allow_lds_claim(K kernel)
                                (int)kFusedLdsClaim) == hipSuccess;
 }
 
+// Wavefronts per workgroup of the streaming kernel, and its grid. Measured (us, a
+// launch with 8, 10, 12 wavefronts): five vectors of 11.2 M elements 131, 123, 116;
+// eight of 25.6 M 419, 391, 399; four of 66 M 534, 524, 550; four of 134 M 1067, 1117,
+// 1112; four of 2^28 2372, 2510, 2554. Short vectors are a few rounds of chunks (more
+// wavefronts, fewer rounds), long ones stream best with least in flight.
+struct FusedShape { unsigned threads, grid, lds; bool is_short; };
+FusedShape fused_shape(u32 W, u64 d, unsigned grid_limit)
+{
+    unsigned waves = W <= 1024u ? 4u : W <= 2048u ? 8u : d < (1ull << 24) ? 12u : d <= (1ull << 26) ? 10u : 8u;
+    unsigned grid = (W + waves - 1) / waves;
+    const bool is_short = W <= 2048u;
+    return FusedShape{waves * (unsigned)kWave, grid > grid_limit ? grid_limit : grid,
+                      is_short ? waves * kRing * (unsigned)sizeof(uint2) : kFusedLdsClaim, is_short};
+}
+
 int fused_grid_limit(unsigned *out)
 {
     int dev = 0;
@@ -2540,14 +2673,14 @@ int fused_grid_limit(unsigned *out)
     std::lock_guard<std::mutex> lock(g_device_mutex);
     if (g_fused_grid[dev] == 0) {
         int cus = 0, fit_t = 0, fit_f = 0;
-        if (!allow_lds_claim(k_fused<true, false>) || !allow_lds_claim(k_fused<false, false>) ||
-            !allow_lds_claim(k_fused<true, true>) || !allow_lds_claim(k_fused<false, true>))
+        if (!allow_lds_claim(k_fused<false, kLongRows>) || !allow_lds_claim(k_fused<false, kShortRows>) ||
+            !allow_lds_claim(k_fused<true, kLongRows>) || !allow_lds_claim(k_fused<true, kShortRows>))
             return RTOPK_EHIP;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_t, k_fused<true, false>,
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_t, k_fused<false, kShortRows>,
                                                          (int)kFusedThreads,
                                                          kFusedLdsClaim) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_f, k_fused<false, true>,
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_f, k_fused<true, kShortRows>,
                                                          (int)kFusedThreads,
                                                          kFusedLdsClaim) != hipSuccess)
             return RTOPK_EHIP;
@@ -2595,12 +2728,10 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
     if (n < 1 || !grad || !residual || !seed || !out_idx || !out_val) return RTOPK_EINVAL;
     const int rc = check_sizes(d, r, k);
     if (rc) return rc;
-    bool vec4 = true;
     for (uint32_t i = 0; i < n; ++i) {
         if (!grad[i] || !residual[i] || !out_idx[i] || !out_val[i]) return RTOPK_EINVAL;
         const uintptr_t g0 = (uintptr_t)grad[i], m0 = (uintptr_t)residual[i];
         if (g0 < m0 + d * 4 && m0 < g0 + d * 4) return RTOPK_EINVAL;
-        vec4 = vec4 && ((g0 | m0) & 15u) == 0;
     }
     Geom g = make_geom(d, r, k);
     const EncodeLayout L = make_layout(g);
@@ -2623,8 +2754,8 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
     unsigned grid_limit = 0;
     const int rc2 = fused_grid_limit(&grid_limit);
     if (rc2) return rc2;
-    unsigned fgrid = (g.W + kFusedWaves - 1) / kFusedWaves;
-    if (fgrid > grid_limit) fgrid = grid_limit;
+    const FusedShape fs = fused_shape(g.W, g.d, grid_limit);
+    const unsigned fgrid = fs.grid;
 
     const TraceRequest trace = g_trace;
     g_trace = TraceRequest{};
@@ -2652,10 +2783,10 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         if (g.all_members) {
             // r == d (random-k): no estimate, no histogram, no threshold
             StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
-            if (vec4)
-                k_fused<true, true><<<fg, kFusedThreads, kFusedLdsClaim, stream>>>(B, gg, L);
+            if (fs.is_short)
+                k_fused<true, kShortRows><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
             else
-                k_fused<false, true><<<fg, kFusedThreads, kFusedLdsClaim, stream>>>(B, gg, L);
+                k_fused<true, kLongRows><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
             RTOPK_LAUNCH_CHECK();
         } else {
             {
@@ -2668,10 +2799,10 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
             }
             {
                 StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
-                if (vec4)
-                    k_fused<true, false><<<fg, kFusedThreads, kFusedLdsClaim, stream>>>(B, gg, L);
+                if (fs.is_short)
+                    k_fused<false, kShortRows><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
                 else
-                    k_fused<false, false><<<fg, kFusedThreads, kFusedLdsClaim, stream>>>(B, gg, L);
+                    k_fused<false, kLongRows><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
                 RTOPK_LAUNCH_CHECK();
             }
         }
@@ -2747,9 +2878,9 @@ extern "C" int rtopk_diag_stream_add(const float *grad, float *residual, uint64_
     unsigned grid_limit = 0;
     const int rc = fused_grid_limit(&grid_limit);
     if (rc) return rc;
-    unsigned fgrid = (g.W + kFusedWaves - 1) / kFusedWaves;
-    if (fgrid > grid_limit) fgrid = grid_limit;
-    k_stream_add<<<fgrid, kFusedThreads, 0, (hipStream_t)stream_v>>>(grad, residual, d, g.C, g.W);
+    const FusedShape fs = fused_shape(g.W, g.d, grid_limit);
+    const unsigned fgrid = fs.grid;
+    k_stream_add<<<fgrid, fs.threads, 0, (hipStream_t)stream_v>>>(grad, residual, d, g.C, g.W);
     RTOPK_LAUNCH_CHECK();
     return RTOPK_OK;
 }
@@ -2775,7 +2906,7 @@ extern "C" int rtopk_encode_stats(const void *workspace, void *stream_v,
         for (u32 s2 = 0; s2 < c.W; ++s2) superset += counts[chunk_slot(s2, c.U, c.UC)];
     }
     host_out->error_flags = c.err;
-    host_out->path = c.path | (c.dense ? 2u : 0u);
+    host_out->path = c.path | (c.missed ? 2u : 0u);
     host_out->threshold_bits = c.T;
     host_out->boundary_list_size = c.n_b;
     host_out->count_greater = c.count_greater;

@@ -1,0 +1,46 @@
+"""The streaming kernel's launch shapes and the candidates it leaves out: chunk
+counts on both sides of each change of shape, gradient and residual at
+different 4-byte offsets, layers so hot that most candidates lie above the
+bracket (and are dropped unless they may be sent), against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,off_g,off_m", [
+    (1024, 0, 0), (1023, 1, 2), (1025, 3, 0),
+    (1024 * 1024, 0, 1), (1024 * 1024 + 1, 0, 0),            # one more chunk than 4 wavefronts x 256
+    (2048 * 1024, 2, 0), (2048 * 1024 + 257, 0, 3),          # the last length with two rows at a time
+    ((1 << 24) - 1, 0, 0), ((1 << 24) + 5, 1, 1),            # 12 and 10 wavefronts per workgroup
+])
+@pytest.mark.parametrize("layout", ["even", "hot"])
+def test_stream_shapes(d, off_g, off_m, layout):
+    import torch
+
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    rng = np.random.default_rng(d + off_g)
+    g = rng.standard_normal(d).astype(np.float32)
+    if layout == "hot":
+        g *= np.float32(1e-3)
+        g[d // 3: d // 3 + max(1, d // 50)] *= np.float32(1e4)
+    m = (rng.standard_normal(d) * 1e-4).astype(np.float32)
+    for r, k in ((max(1, d // 60), max(1, d // 600)), (max(1, d // 100), max(1, d // 100)), (d, max(1, d // 100))):
+        tg = torch.zeros(d + off_g, device=u.DEV)[off_g:]
+        tm = torch.zeros(d + off_m, device=u.DEV)[off_m:]
+        tg.copy_(torch.from_numpy(g))
+        tm.copy_(torch.from_numpy(m))
+        idx = torch.empty(k, dtype=torch.int32, device=u.DEV)
+        val = torch.empty(k, device=u.DEV)
+        ws = torch.empty(rt.encode_workspace_bytes(d, r, k), dtype=torch.uint8, device=u.DEV)
+        ws.fill_(0xA5)
+        rt.encode(tg, tm, r, k, 3, 4, idx, val, ws)
+        st = rt.encode_stats(ws)
+        # (a layer of few chunks puts more keys of the window than its 128 places into one
+        # classify workgroup's list: the exact selection then decides, as it does by design)
+        assert st["error_flags"] == 0 and (layout == "hot" or st["path"] == 0), st
+        got = (idx.cpu().numpy().view(np.uint32), val.cpu().numpy(), tm.cpu().numpy())
+        u.assert_encode_equal(got, oracle.encode(g, m, r, k, 3, 4), f"d={d} r={r} k={k}")
