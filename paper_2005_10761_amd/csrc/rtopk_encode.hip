@@ -99,6 +99,7 @@ constexpr u32 kSampleLoc = 16384;             // sampled locations, 4 consecutiv
 constexpr u32 kSampleThreads = 256;
 constexpr u32 kEstThreads = 1024;
 constexpr u32 kNoSample = 0xFFFFFFFFu;
+constexpr u64 kShortVector = 1u << 22;
 
 constexpr u32 kChunkQuantum = 256;            // one wavefront iteration: 64 lanes x 4 elements
 constexpr u32 kMinChunk = 4 * kChunkQuantum;  // short vectors: chunks of four iterations
@@ -228,6 +229,7 @@ struct Geom {
     u32 UC;             // ... at most this many of them (W <= U * UC)
     u32 G3;             // classify / emit workgroups
     u32 L;              // sampled locations
+    u32 est_vecs;       // sampled locations per thread of the estimate kernel, a power of two (empty ones included)
     u32 nfine;          // linear histogram bins
     u32 force_dense;    // diagnostics: make the estimate keep nothing, as if the sample had misled it
     u32 force_abort;    // diagnostics: the workgroups of the wide selection decide "abort" at check-in
@@ -270,8 +272,17 @@ static Geom make_geom(u64 d, u64 r, u64 k)
     g.U = g.W < kMaxUnits ? g.W : kMaxUnits;
     g.UC = kUnitChunks;
     g.G3 = (g.U + kWalkWaves - 1) / kWalkWaves;       // (the layout is sized for this many)
-    const u64 loc = (d + 3) / 4;
-    g.L = (u32)(loc < kSampleLoc ? loc : kSampleLoc);
+    // A bracket as wide as twice r (80 samples or more in the top r) is enough for a short
+    // vector, whose few candidates cost the walking kernels nothing, and the estimate's one
+    // workgroup is a good part of its time: 4-6 instead of 10 us with a quarter of the samples.
+    u64 loc = (d + 3) / 4, want = kSampleLoc;
+    if (d < kShortVector) {
+        want = kEstThreads;
+        while (want < kSampleLoc && want * 4 * r < 80 * d) want *= 2;
+    }
+    g.L = (u32)(loc < want ? loc : want);
+    g.est_vecs = 1;
+    while (g.est_vecs * kEstThreads < g.L) g.est_vecs *= 2;
     // Every workgroup of the streaming kernel stores its whole histogram: few
     // bins when r is small (the list B of the deciding bin then holds a few
     // hundred entries anyway), more when r is large.
@@ -395,9 +406,8 @@ __device__ __forceinline__ u64 stratum_start(const Geom &g, u32 j)
 {
     // strata of (almost) equal length; only monotonicity and the two ends matter
     if (j >= g.L) return g.d;
-    static_assert((kSampleLoc & (kSampleLoc - 1)) == 0, "the usual count of strata is a power of two");
-    const u64 x = g.L == kSampleLoc ? (g.d * (u64)j) / kSampleLoc     // d * j < 2^46; a shift
-                                    : (u64)((double)g.d * (double)j / (double)g.L);
+    const u64 x = (g.L & (g.L - 1u)) == 0u ? (g.d * (u64)j) >> (31 - __clz((int)g.L))   // d * j < 2^46
+                                           : (u64)((double)g.d * (double)j / (double)g.L);
     return x < g.d ? x : g.d;
 }
 
@@ -407,7 +417,7 @@ sample_body(const float *__restrict__ grad, const float *__restrict__ residual, 
 {
     const u32 j = blockIdx.x * kSampleThreads + threadIdx.x;
     for (u32 i = j; i < zero_words; i += gridDim.x * kSampleThreads) zero_base[i] = 0u;
-    if (j >= kSampleLoc) return;
+    if (j >= g.est_vecs * kEstThreads) return;
     u32 out[4] = {kNoSample, kNoSample, kNoSample, kNoSample};
     if (j < g.L) {
         const u64 start = stratum_start(g, j), end = stratum_start(g, j + 1);
@@ -509,6 +519,7 @@ __device__ __forceinline__ void wave_pick_from_top(const u32 *hist, u32 top, con
     }
 }
 
+template <u32 kVecs>      // 16-byte sample groups per thread
 __device__ __forceinline__ void
 estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
 {
@@ -521,7 +532,6 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
     __shared__ u32 scan_lds[kEstThreads / kWave + 1];
     __shared__ u32 bin_s[3], before_s[3], top_s;
     const u32 tid = threadIdx.x;
-    constexpr u32 kVecs = kSampleLoc / kEstThreads;       // 16-byte sample groups per thread
     const uint4 *s4 = reinterpret_cast<const uint4 *>(samples);
     uint4 v[kVecs];
 #pragma unroll
@@ -2496,10 +2506,11 @@ __global__ void __launch_bounds__(kSampleThreads) k_sample(Batch B, Geom g, Enco
                 m.at<u32>(L.samples));
 }
 
+template <u32 kVecs>
 __global__ void __launch_bounds__(kEstThreads) k_estimate(Batch B, Geom g, EncodeLayout L)
 {
     const Member m(B);
-    estimate_body(m.at<u32>(L.samples), g, m.at<EncodeCtl>(L.ctl));
+    estimate_body<kVecs>(m.at<u32>(L.samples), g, m.at<EncodeCtl>(L.ctl));
 }
 
 template <bool kAll, int kRows>
@@ -2791,10 +2802,18 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         } else {
             {
                 StageScope sc(trace, RTOPK_STAGE_PREPARE, stream);
-                k_sample<<<dim3(kSampleLoc / kSampleThreads, 1, nb), kSampleThreads, 0, stream>>>(
+                k_sample<<<dim3(g.est_vecs * kEstThreads / kSampleThreads, 1, nb), kSampleThreads, 0, stream>>>(
                     B, gg, L);
                 RTOPK_LAUNCH_CHECK();
-                k_estimate<<<dim3(1, 1, nb), kEstThreads, 0, stream>>>(B, gg, L);
+                const dim3 eg(1, 1, nb);
+                static_assert(kSampleLoc == 16 * kEstThreads, "one kernel for each power of two");
+                switch (g.est_vecs) {
+                case 1: k_estimate<1><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
+                case 2: k_estimate<2><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
+                case 4: k_estimate<4><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
+                case 8: k_estimate<8><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
+                default: k_estimate<16><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
+                }
                 RTOPK_LAUNCH_CHECK();
             }
             {
