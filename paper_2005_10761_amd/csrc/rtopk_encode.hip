@@ -1519,18 +1519,29 @@ struct Wide {
     u32 spin_limit;     // polls before a workgroup gives up at a barrier
 };
 
+// until everything this wavefront has sent to memory is acknowledged
+__device__ __forceinline__ void wait_own_memory()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
+
 // Everything the workgroups exchange goes through device-scope atomic
 // operations (additions to the histograms, atomic stores of the few words
 // workgroup 0 reads at the end, atomic loads on the reading side), which are
 // carried out where all compute units see them. The barrier therefore only has
 // to order them: every thread waits until its own operations are acknowledged
-// (a workgroup-scope release does that) before its workgroup checks in. A
+// before its workgroup checks in. (The wait is explicit: neither a workgroup-scope
+// release nor the workgroup barrier waits for device memory, as the wavefronts of
+// one workgroup share a cache.) A
 // device-scope fence per thread, which writes back and invalidates the L2 of
 // the XCD, made a barrier of 256 workgroups cost ~100 us.
 __device__ __forceinline__ bool grid_barrier(Wide &w, u32 *lds_flag)
 {
     if (!w.alive) return false;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    wait_own_memory();
     __syncthreads();
     ++w.epoch;
     if (threadIdx.x == 0) {
