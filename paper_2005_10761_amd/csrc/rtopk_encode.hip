@@ -138,7 +138,11 @@ constexpr u32 kWindowBits = 12;
 constexpr int kFinThreads = 1024;
 constexpr u32 kFinWaves = kFinThreads / kWave;
 constexpr u32 kSlabs = kTargetChunks / (4 * kFinThreads);  // 16-byte groups of chunk counters per thread
-constexpr u32 kStageB = 2048, kStageM = 4096; // short lists that fit are selected in LDS (cfg3: 600 and 2,700 entries)
+// Short lists that fit are selected in LDS (600 and 2,700 entries at r = 127,786,
+// k = 25,558). Up to kStageM keys a thread holds four of them, up to kStageMLarge
+// eight (k = 111,740: 4,700 keys of random-k 16.9 instead of 22.4 us from memory;
+// holding eight always costs the smaller lists 0.5-1 us).
+constexpr u32 kStageB = 2048, kStageM = 4096, kStageMLarge = 8192;
 
 constexpr u32 kErrSelect = 2u;                // a selection found no element of the requested rank
 constexpr u32 kErrCount = 4u;                 // the winners did not add up to k
@@ -1720,8 +1724,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     __shared__ u64 scratch[2];
     __shared__ u64 st_b_key[kStageB];
     __shared__ u32 st_b_idx[kStageB];
-    __shared__ u64 st_m_key[kStageM];
-    __shared__ u32 st_m_idx[kStageM];
+    __shared__ u64 st_m_key[kStageMLarge];
+    __shared__ u32 st_m_idx[kStageMLarge];
     __shared__ u32 extra_m, sure_extra;
     __shared__ unsigned long long gt_extra;
     __shared__ u32 run_chunk, run_before, run_index, run_found;
@@ -1982,15 +1986,17 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         }
     }
 
-    // The short-list path. It is compiled twice: once with both lists in LDS
+    // The short-list path. It is compiled three times: with both lists in LDS
     // (the usual case; the compiler then knows the address space of every list
-    // access and overlaps the loads that fill the lists) and once with the
-    // lists wherever they fit.
-    auto short_lists = [&](u64 *bk, u32 *bi, u64 *mk, u32 *mi, auto all_lds_tag) {
-        constexpr bool kAllLds = decltype(all_lds_tag)::value;
+    // access and overlaps the loads that fill the lists), the key list up to
+    // kStageM or up to kStageMLarge entries, and once with the lists wherever
+    // they fit.
+    auto short_lists = [&](u64 *bk, u32 *bi, u64 *mk, u32 *mi, auto in_lds_tag) {
+        constexpr u32 kInLds = decltype(in_lds_tag)::value;          // entries of M in LDS, 0: lists anywhere
+        constexpr bool kAllLds = kInLds != 0u;
         const u32 n_b_use = lists ? n_bd : 0u;
-        const bool m_lds = kAllLds || (lists && n_m0 + n_b_use <= kStageM);
-        const u32 m_cap = m_lds ? kStageM : 2u * g.G3 * kListCap;
+        const bool m_lds = kAllLds || (lists && n_m0 + n_b_use <= kStageMLarge);
+        const u32 m_cap = kAllLds ? kInLds : m_lds ? kStageMLarge : 2u * g.G3 * kListCap;
         auto barrier = [&] { if (kAllLds) lds_barrier(); else __syncthreads(); };
         // Entry j of classify workgroup t lives at [j][t]. First every thread
         // notes where the entries of its workgroup are (no memory latency in
@@ -2000,7 +2006,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         for (u32 j = 0; j < vm; ++j) mi[em + j] = j * g.G3 + tid;
         barrier();
         if (kAllLds) {
-            constexpr u32 kB = kStageB / kFinThreads, kM = kStageM / kFinThreads;
+            constexpr u32 kB = kStageB / kFinThreads, kM = kAllLds ? kInLds / kFinThreads : 1u;
             u32 b_m[kB], b_i[kB], m_i[kM];
             u64 m_k[kM];
 #pragma unroll
@@ -2185,7 +2191,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             barrier();
             count_greater = c_def + gt_extra;
             n_mm = n_m0 + extra_m;
-            if (__builtin_expect(tie_run && n_mm <= kStageM && n_mm <= m_cap, 0)) {
+            if (__builtin_expect(tie_run && n_mm <= kStageMLarge && n_mm <= m_cap, 0)) {
                 // short after all: the selection below reads it several times, from LDS then
                 for (u32 p = tid; p < n_mm; p += kFinThreads) { st_m_key[p] = mk[p]; st_m_idx[p] = mi[p]; }
                 mk = st_m_key;
@@ -2197,7 +2203,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 have_k = true;
             } else if (n_mm <= m_cap && c_klo < g.k && g.k - c_klo <= n_mm) {
                 // (in LDS a thread's entries, four at most, stay in registers over the rounds)
-                constexpr u32 kM = kAllLds ? kStageM / kFinThreads : 1u;
+                constexpr u32 kM = kAllLds ? kInLds / kFinThreads : 1u;
                 u64 rm_k[kM];
                 u32 rm_i[kM];
                 if (kAllLds) {
@@ -2233,12 +2239,14 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         const u32 n_b_use = lists ? n_bd : 0u;
         const bool b_lds = n_b_use <= kStageB;
         // (a run of equal magnitudes may add any number of keys: the large array then)
-        const bool m_lds = lists && n_m0 + n_b_use <= kStageM;
-        if (b_lds && m_lds)
-            short_lists(st_b_key, st_b_idx, st_m_key, st_m_idx, std::true_type{});
+        const bool m_lds = lists && n_m0 + n_b_use <= kStageMLarge;
+        if (b_lds && lists && n_m0 + n_b_use <= kStageM)
+            short_lists(st_b_key, st_b_idx, st_m_key, st_m_idx, std::integral_constant<u32, kStageM>{});
+        else if (b_lds && m_lds)
+            short_lists(st_b_key, st_b_idx, st_m_key, st_m_idx, std::integral_constant<u32, kStageMLarge>{});
         else
             short_lists(b_lds ? st_b_key : db_key, b_lds ? st_b_idx : db_idx,
-                        m_lds ? st_m_key : dm_key, m_lds ? st_m_idx : dm_idx, std::false_type{});
+                        m_lds ? st_m_key : dm_key, m_lds ? st_m_idx : dm_idx, std::integral_constant<u32, 0u>{});
     }
 
     if (!have_t || (!have_k && !g.take_all)) {
