@@ -204,16 +204,20 @@ struct EncodeCtl {
     // written by k_estimate
     Bins bins;
     u32 n_samples;
-    // written by k_pick (dense also by k_finalize when r == d and the key window missed)
+    // written by k_pick
     u32 dense;          // S does not hold what is needed: walk the vector itself
-    u32 missed;         // ... because the estimate (r == d: the key window) missed
+    u32 missed;         // ... because the estimate missed (k_finalize: r == d and the key window missed)
     u32 bd_lo, bd_hi;   // pattern range of the deciding bin
     u32 bd_bits;        // bit width of bd_hi - bd_lo
     u64 c_def;          // entries above bd_hi
     // written by k_classify
     u32 overflow;       // a short-list region of some classify workgroup was full
     u32 overflow_m;     // ... and it was a region of the key list M
-    // written by k_finalize
+    // Written by k_finalize, by workgroup 0 while others of the grid may only just start: none
+    // of these may be a word that k_finalize reads. (A workgroup that starts late must decide
+    // from the same words as the ones before it whether it stays for the selection over all
+    // candidates; one that stays alone waits at check-in for workgroups that have left.)
+    u32 emit_dense;     // k_emit walks the vector itself, as it does when `dense` is set
     u32 T, I_star;      // last member of the top-r set in (magnitude desc, index asc) order
     u64 K_star;         // last winner in (key asc, index asc) order
     u32 J_star;
@@ -2002,7 +2006,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         have_t = true;
         have_k = true;
         if (cand.dense && tid == 0) {
-            ctl->dense = 1u;
+            ctl->emit_dense = 1u;
             if (g.all_members) ctl->missed = 1u;
         }
     }
@@ -2277,7 +2281,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         // the emit kernel.
         cand.dense = true;
         if (tid == 0) {
-            ctl->dense = 1u;
+            ctl->emit_dense = 1u;
             if (g.all_members) ctl->missed = 1u;
         }
     }
@@ -2425,7 +2429,8 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
     const u32 u = blockIdx.x * kWalkWaves + threadIdx.x / kWave;
     if (u >= g.U) return;
     const u32 lane = lane_id();
-    const Candidates cand{seg_count, s_ent, residual, g.d, g.C, g.U, g.UC, g.cap, ctl->dense != 0u};
+    const Candidates cand{seg_count, s_ent, residual, g.d, g.C, g.U, g.UC, g.cap,
+                          (ctl->dense | ctl->emit_dense) != 0u};
     const UnitWalk walk(cand, u < g.U ? u : g.W, g.U, g.W);
     const u32 my_chunk = u + lane * g.U;
     const u32 my_base = (lane < g.UC && my_chunk < g.W) ? chunk_base[my_chunk] : 0u;
