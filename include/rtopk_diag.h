@@ -40,7 +40,8 @@ typedef struct rtopk_encode_stats {
     uint64_t ties_taken;         /* r - count_greater, taken from the lowest indices */
     uint64_t superset_size;      /* entries compacted before the exact selection (candidates that
                                     certainly belong to the top r and whose key is above the
-                                    a-priori window are not among them) */
+                                    a-priori window are not among them, unless the selection over
+                                    all candidates needed them and put them there) */
     uint64_t key_list_size;      /* members whose sampling key fell inside the a-priori window */
 } rtopk_encode_stats_t;
 

@@ -47,8 +47,10 @@
 //              rank in index order and is located from the per-chunk counts.
 //              When a short list overflowed otherwise or the key window
 //              missed, the same quantities are found by radix selection over
-//              S or, where S is not enough, the vector (exact; on all workgroups of the kernel's
-//              grid when the vector is long, see grid_select96)
+//              S (exact; on all workgroups of the kernel's grid when the vector is
+//              long, see grid_select96). Where members that were not to be sent
+//              decide after all (the window missed high, the threshold lies above
+//              the bracket), one pass over the vector puts them into S first
 //   emit       entries of S that are members and winners -> the message in
 //              index order, starting at the chunk's prefix; residual at the
 //              sent positions <- a - a
@@ -205,8 +207,8 @@ struct EncodeCtl {
     Bins bins;
     u32 n_samples;
     // written by k_pick
-    u32 dense;          // S does not hold what is needed: walk the vector itself
-    u32 missed;         // ... because the estimate missed (k_finalize: r == d and the key window missed)
+    u32 dense;          // the estimate missed, S holds fewer than r entries: walk the vector itself
+    u32 partial;        // the deciding bin lies above the bracket, where S only holds what may be sent
     u32 bd_lo, bd_hi;   // pattern range of the deciding bin
     u32 bd_bits;        // bit width of bd_hi - bd_lo
     u64 c_def;          // entries above bd_hi
@@ -217,7 +219,7 @@ struct EncodeCtl {
     // of these may be a word that k_finalize reads. (A workgroup that starts late must decide
     // from the same words as the ones before it whether it stays for the selection over all
     // candidates; one that stays alone waits at check-in for workgroups that have left.)
-    u32 emit_dense;     // k_emit walks the vector itself, as it does when `dense` is set
+    u32 emit_dense;     // r == d and the key window missed: k_emit walks the vector itself
     u32 T, I_star;      // last member of the top-r set in (magnitude desc, index asc) order
     u64 K_star;         // last winner in (key asc, index asc) order
     u32 J_star;
@@ -686,7 +688,7 @@ struct Ring {
     // Up to 64 entries leave the ring. A candidate above the bracket is a certain member,
     // and one whose key lies above the window is certainly not sent: it is needed by
     // nobody and does not reach the slice (should the estimate or the window have missed,
-    // the vector itself is walked). In a layer that holds most of the top r, where nearly
+    // finalize fills the slices again). In a layer that holds most of the top r, where nearly
     // all candidates lie above the bracket, four fifths of them go this way.
     __device__ __forceinline__ void take(u64 c0, const Geom &g, const PhiloxSeed &seed, u32 bracket_hi,
                                          uint2 *__restrict__ my_ent)
@@ -890,7 +892,8 @@ struct Candidates {
     const float *__restrict__ a;
     u64 d;
     u32 C, U, UC, cap;
-    bool dense;         // every chunk is read from the vector (the estimate kept too little)
+    bool dense;         // every chunk is read from the vector (the estimate kept too little; r == d
+                        // and the key window missed)
 
     __device__ __forceinline__ u32 length(u32 s) const
     {
@@ -1177,14 +1180,13 @@ constexpr u32 kPickRows = 128, kPickMembers = 2;   // up to here the classify wo
 
 // the deciding bin: its pattern range and the entries above it
 struct Picked {
-    u32 dense;          // S does not hold what is needed: walk the vector itself
-    u32 missed;         // ... because the estimate kept fewer than r candidates
+    u32 dense, partial; // see EncodeCtl
     u32 bd_lo, bd_hi;
     u64 c_def;
     __device__ __forceinline__ void store(EncodeCtl *ctl) const
     {
         ctl->dense = dense;
-        ctl->missed = missed;
+        ctl->partial = partial;
         ctl->bd_lo = bd_lo;
         ctl->bd_hi = bd_hi;
         ctl->bd_bits = bd_hi > bd_lo ? 32u - (u32)__clz(bd_hi - bd_lo) : 1u;
@@ -1300,9 +1302,10 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
     if (tid == 0) {
         u32 bd_lo = 0, bd_hi = 0;
         if (!dense) bin_range(bins, bin_s, &bd_lo, &bd_hi);
-        // above the bracket S only holds what may be sent: no short list can decide there
-        const bool above = !dense && bin_s >= bins.nfine;
-        picked = Picked{(dense || above) ? 1u : 0u, dense ? 1u : 0u, bd_lo, bd_hi, before_s};
+        // above the bracket S only holds what may be sent (everything when k == r): no short
+        // list can decide there
+        const bool partial = !dense && bin_s >= bins.nfine && g.take_all == 0u;
+        picked = Picked{dense ? 1u : 0u, partial ? 1u : 0u, bd_lo, bd_hi, before_s};
     }
     lds_barrier();
     return picked;
@@ -1332,9 +1335,9 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
     const u32 wave = threadIdx.x / kWave, lane = lane_id();
     const u32 u = blockIdx.x * kWalkWaves + wave;
-    const bool dense = (now ? now->dense : ctl->dense) != 0u;
+    const bool undecided = (now ? now->dense | now->partial : ctl->dense | ctl->partial) != 0u;
     const u32 bd_lo = now ? now->bd_lo : ctl->bd_lo, bd_hi = now ? now->bd_hi : ctl->bd_hi;
-    if (dense) {
+    if (undecided) {
         if (threadIdx.x == 0) {
             blk_sure[blockIdx.x] = 0u; n_m[blockIdx.x] = 0u; n_b[blockIdx.x] = 0u;
             blk_bmin[blockIdx.x] = 0xFFFFFFFFu; blk_bmax[blockIdx.x] = 0u;
@@ -1734,8 +1737,7 @@ __device__ __forceinline__ Selected grid_select96(ForEach &&for_each, u64 rank, 
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void
 finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
-           const float *__restrict__ a,
-           const u32 *__restrict__ seg_count, const uint2 *__restrict__ s_ent,
+           const float *__restrict__ a, u32 *seg_count, uint2 *s_ent,
            u32 *win_cnt, const u32 *__restrict__ bd_cnt, const u32 *__restrict__ blk_sure,
            const u32 *__restrict__ n_m, const u32 *__restrict__ n_b,
            const u32 *__restrict__ blk_bmin, const u32 *__restrict__ blk_bmax,
@@ -1758,8 +1760,69 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
 
     const u32 tid = threadIdx.x;
     const u32 wave = tid / kWave, lane = lane_id();
-    const bool dense = ctl->dense != 0u;
+    const bool dense = ctl->dense != 0u, partial = ctl->partial != 0u;
+    const u32 bd_lo = ctl->bd_lo, bd_hi = ctl->bd_hi, bd_bits = ctl->bd_bits;
+    const u64 c_def = ctl->c_def;
     Candidates cand{seg_count, s_ent, a, g.d, g.C, g.U, g.UC, g.cap, dense};
+    // What is walked holds every member of the top-r set. Otherwise (S as the streaming kernel
+    // left it) the members above the bracket whose key lies above the window are missing.
+    bool whole = dense || g.take_all != 0u;
+    // Fills the slices of chunks first, first + step, ... again, from the vector and with every
+    // element at or above the deciding bin: one pass over the vector (four rows of a chunk in
+    // flight), after which S will do for all the passes of an exact selection and for emit. The
+    // keys are left to be computed. (By one wavefront, which sees what it wrote itself.)
+    auto complete_slices = [&](u32 first, u32 step) {
+        constexpr u32 kRows = 4;
+        const u64 below = lanes_below();
+        for (u32 sc = first; sc < g.W; sc += step) {
+            const float *chunk = a + (u64)sc * g.C;
+            const u32 len = cand.length(sc);
+            uint2 *slice = s_ent + (u64)sc * g.cap;
+            u32 kept = 0;
+            for (u32 r0 = 0; r0 < len; r0 += kRows * kChunkQuantum) {
+                u32 bits[kRows][4];
+                if (r0 + kRows * kChunkQuantum <= len) {
+                    const f32x4u *row = reinterpret_cast<const f32x4u *>(chunk + r0) + lane;
+#pragma unroll
+                    for (u32 q = 0; q < kRows; ++q) {
+                        const f32x4 v = row[q * kWave];
+#pragma unroll
+                        for (u32 e = 0; e < 4; ++e) bits[q][e] = __float_as_uint(v[e]);
+                    }
+                } else {
+#pragma unroll
+                    for (u32 q = 0; q < kRows; ++q)
+#pragma unroll
+                        for (u32 e = 0; e < 4; ++e) {
+                            const u32 at = r0 + q * kChunkQuantum + 4u * lane + e;
+                            bits[q][e] = at < len ? __float_as_uint(chunk[at]) : 0u;
+                        }
+                }
+#pragma unroll
+                for (u32 q = 0; q < kRows; ++q) {
+                    const u32 place = r0 + q * kChunkQuantum + 4u * lane;
+                    bool hit[4];
+                    u64 b[4];
+#pragma unroll
+                    for (u32 e = 0; e < 4; ++e) {
+                        hit[e] = place + e < len && mag_of(bits[q][e]) >= bd_lo;
+                        b[e] = __ballot(hit[e]);
+                    }
+                    u32 p = kept + popc64(b[0] & below) + popc64(b[1] & below) + popc64(b[2] & below) +
+                            popc64(b[3] & below);
+#pragma unroll
+                    for (u32 e = 0; e < 4; ++e)
+                        if (hit[e]) {
+                            if (p < g.cap) slice[p] = make_uint2((kKeyUnknown << 30) | (place + e), bits[q][e]);
+                            ++p;
+                        }
+                    kept += popc64(b[0]) + popc64(b[1]) + popc64(b[2]) + popc64(b[3]);
+                }
+            }
+            if (lane == 0) seg_count[chunk_slot(sc, g.U, g.UC)] = kept;
+        }
+        wait_own_memory();
+    };
     // every candidate, split wavefront by chunk; f(index, pattern, chunk)
     auto each_s = [&](auto &&f) {
         // kWave consecutive chunks per wavefront at a time: their sizes in one round of
@@ -1780,8 +1843,6 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     const bool in_grid = tid < g.G3;
     const u32 vm = in_grid ? n_m[tid] : 0u, vb = in_grid ? n_b[tid] : 0u;
     const u32 vs = in_grid ? blk_sure[tid] : 0u;
-    const u32 bd_lo = ctl->bd_lo, bd_hi = ctl->bd_hi, bd_bits = ctl->bd_bits;
-    const u64 c_def = ctl->c_def;
     const bool overflow = ctl->overflow != 0u, overflow_m = ctl->overflow_m != 0u;
     if (tid == 0) { extra_m = 0u; sure_extra = 0u; gt_extra = 0ull; run_found = 0u; }
     // The three totals (every workgroup of the grid needs them to decide whether
@@ -1818,7 +1879,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         T = 0u;
         I_star = 0xFFFFFFFFu;
     }
-    const bool lists = !dense && !overflow && (g.all_members || (c_def < g.r && need2 <= n_bd));
+    const bool lists = !dense && !partial && !overflow && (g.all_members || (c_def < g.r && need2 <= n_bd));
     // The list B overflowed but M did not, and every entry of the deciding bin has
     // the same magnitude: the last member is the need2-th of them in index order.
     bool tie_run = false;
@@ -1835,9 +1896,11 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     }
     // ---- many workgroups or one? Every workgroup of the grid decides alike,
     //      from what classify and pick left: the lists cannot give the
-    //      threshold (the estimate kept too little; the deciding bin crowded by
-    //      several magnitudes), or the key window certainly missed.
+    //      threshold (the estimate kept too little; it lies above the bracket; the
+    //      deciding bin crowded by several magnitudes), or the key window certainly missed.
     bool wide = false;
+    // the lists are complete and fewer than k members have a key at or below the window's upper end
+    const bool missed_high = lists && !g.take_all && sure_walk + n_m0 + (g.all_members ? 0ull : need2) < g.k;
     if (gridDim.x > 1u) {
         const bool slow_t = !g.all_members && !lists && !tie_run;
         bool slow_k = false;
@@ -1864,9 +1927,9 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         // (diagnostics: with no patience at all the barriers time out, the kernel ends
         // with the error flag set and every workgroup still leaves normally)
         Wide w{wide_ws, gridDim.x, 1u, 0u, true, g.force_timeout != 0u ? 0u : kWideSpinLimit};
-        // r == d: S only holds the coordinates inside the key window, which
-        // missed: the vector itself is walked, here and by the emit kernel
-        if (g.all_members) cand.dense = true;
+        // r == d: S only holds the coordinates whose key the window admits, and every
+        // coordinate is a member: the vector itself is walked, here and by the emit kernel
+        if (g.all_members) { cand.dense = true; whole = true; }
         const bool vec16 = (reinterpret_cast<uintptr_t>(a) & 15u) == 0;
         const u32 n_waves = gridDim.x * kFinWaves;
         // f(valid, index, pattern) for every entry of this workgroup's chunks, all lanes
@@ -1916,7 +1979,12 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         path = 1u | 8u;
         // where whoever comes across a selected string in a later pass leaves it whole
         u64 *found_t = w.ws->found[kWidePasses - 2], *found_k = w.ws->found[kWidePasses - 1];
-        const bool in_bin_only = !g.all_members && !cand.dense;
+        const bool in_bin_only = !g.all_members && !dense;
+        auto complete = [&] {
+            complete_slices(blockIdx.x * kFinWaves + wave, n_waves);     // the chunks wide_each gives this wavefront
+            whole = true;
+        };
+        if (!whole && (partial || missed_high)) complete();
         const u32 top = in_bin_only ? bd_hi : 0x7FFFFFFFu;
         Selected sel_t{0ull, 0u, 12}, sel_k{0ull, 0u, 12};
         Pair96 tbound{~0ull, 0xFFFFFFFFu}, kbound{~0ull, 0xFFFFFFFFu};
@@ -1946,18 +2014,25 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             if (in_bin_only && m < bd_lo) return false;
             return pair_le((u64)(top - m), idx, tbound);
         };
-        // the keys above the window are not in S
-        if (!g.take_all) cand.dense = true;
         if (!g.take_all && w.alive) {
+            // Members whose key the window admits are all in S: where they number k or more
+            // (a list overflowed, the window missed low) they decide; their number shows in
+            // the first pass.
             auto each_key = [&](auto &&f2) {
                 wide_each([&](bool valid, u32 idx, u32 bits) {
-                    const bool on = valid && is_member_w(idx, bits);
-                    f2(on, on ? sample_key(idx, seed) : 0ull, idx);
+                    bool on = valid && is_member_w(idx, bits);
+                    const u64 key = on ? sample_key(idx, seed) : 0ull;
+                    on = on && (whole || key <= g.K_hi);
+                    f2(on, key, idx);
                 }, nothing);
             };
-            u64 less = 0;
             bool ok_k = true;
-            sel_k = grid_select96(each_key, g.k, 0, w, h, &less, &ok_k);
+            for (;;) {
+                u64 less = 0;
+                sel_k = grid_select96(each_key, g.k, 0, w, h, &less, &ok_k);
+                if (ok_k || whole || !w.alive) break;
+                complete();
+            }
             if (!ok_k) err |= kErrSelect;
             kbound = sel_k.bound();
         }
@@ -2005,10 +2080,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         if (blockIdx.x != 0u) return;
         have_t = true;
         have_k = true;
-        if (cand.dense && tid == 0) {
-            ctl->emit_dense = 1u;
-            if (g.all_members) ctl->missed = 1u;
-        }
+        if (g.all_members && tid == 0) ctl->emit_dense = 1u;
     }
 
     // The short-list path. It is compiled three times: with both lists in LDS
@@ -2274,30 +2346,40 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                         m_lds ? st_m_key : dm_key, m_lds ? st_m_idx : dm_idx, std::integral_constant<u32, 0u>{});
     }
 
-    if (!have_t || (!have_k && !g.take_all)) {
-        // A short list overflowed or the key window missed: S does not hold the
-        // candidates above the bracket whose keys lie above the window (r == d: any key
-        // above it), so the exact selection below walks the vector itself, and so does
-        // the emit kernel.
+    if (g.all_members && !have_k) {
+        // r == d and a short list overflowed or the key window missed: as above
         cand.dense = true;
-        if (tid == 0) {
-            ctl->emit_dense = 1u;
-            if (g.all_members) ctl->missed = 1u;
-        }
+        whole = true;
+        if (tid == 0) ctl->emit_dense = 1u;
     }
+    auto complete_alone = [&] {
+        __syncthreads();
+        complete_slices(wave, kFinWaves);
+        __syncthreads();
+        whole = true;
+    };
     if (!have_t) {
-        // ---- exact threshold by selection over all candidates -----------
+        // ---- exact threshold by selection over all candidates: those of the deciding
+        //      bin, or the whole vector when the estimate had kept too little ----------
         path |= 1u;
+        if (partial && !whole) complete_alone();
+        const u32 top = dense ? 0x7FFFFFFFu : bd_hi;
         auto each_mag = [&](auto &&f) {
-            each_s([&](u32 idx, u32 bits, u32) { f((u64)(0x7FFFFFFFu - mag_of(bits)), idx); });
+            each_s([&](u32 idx, u32 bits, u32) {
+                const u32 m = mag_of(bits);
+                if (dense || (m >= bd_lo && m <= bd_hi)) f((u64)(top - m), idx);
+            });
         };
-        const Pair96 tb = block_select96(each_mag, g.r, 4, h, scratch, &ok);
+        const Pair96 tb = block_select96(each_mag, dense ? g.r : need2, 4, h, scratch, &ok);
         if (!ok) err |= kErrSelect;
-        T = 0x7FFFFFFFu - (u32)tb.hi;
+        T = top - (u32)tb.hi;
         I_star = tb.lo;
         u32 my_gt = 0;
-        each_s([&](u32, u32 bits, u32) { if (mag_of(bits) > T) ++my_gt; });
-        count_greater = block_sum(my_gt, scan32);
+        each_s([&](u32, u32 bits, u32) {
+            const u32 m = mag_of(bits);
+            if (m > T && m <= top) ++my_gt;
+        });
+        count_greater = (dense ? 0ull : c_def) + block_sum(my_gt, scan32);
     }
     auto is_member = [&](u32 idx, u32 bits) {
         const u32 m = mag_of(bits);
@@ -2309,12 +2391,20 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         __syncthreads();
         for (u32 s = tid; s < g.W; s += kFinThreads) win_cnt[s] = 0u;
         if (!g.take_all) {
+            // (members whose key the window admits first, as above)
             auto each_key = [&](auto &&f) {
                 each_s([&](u32 idx, u32 bits, u32) {
-                    if (is_member(idx, bits)) f(sample_key(idx, seed), idx);
+                    if (!is_member(idx, bits)) return;
+                    const u64 key = sample_key(idx, seed);
+                    if (whole || key <= g.K_hi) f(key, idx);
                 });
             };
-            const Pair96 kb = block_select96(each_key, g.k, 0, h, scratch, &ok);
+            Pair96 kb{0ull, 0u};
+            for (;;) {
+                kb = block_select96(each_key, g.k, 0, h, scratch, &ok);
+                if (ok || whole) break;
+                complete_alone();
+            }
             if (!ok) err |= kErrSelect;
             K_star = kb.hi;
             J_star = kb.lo;
@@ -2990,7 +3080,7 @@ extern "C" int rtopk_encode_stats(const void *workspace, void *stream_v,
         for (u32 s2 = 0; s2 < c.W; ++s2) superset += counts[chunk_slot(s2, c.U, c.UC)];
     }
     host_out->error_flags = c.err;
-    host_out->path = c.path | (c.missed ? 2u : 0u);
+    host_out->path = c.path | ((c.dense | c.emit_dense) != 0u ? 2u : 0u);
     host_out->threshold_bits = c.T;
     host_out->boundary_list_size = c.n_b;
     host_out->count_greater = c.count_greater;
