@@ -251,6 +251,7 @@ struct Geom {
                         // had underestimated the r-th largest magnitude: it then lies above the linear bins
     u32 take_all;       // k == r: every member is sent, keys are never looked at
     u32 all_members;    // r == d: every coordinate is a member, magnitudes are never looked at
+    u32 keyed;          // the streaming kernel keys the candidates (not those of a short vector)
     u32 k_nlz;          // leading zeros of K_hi - K_lo
     u64 K_lo, K_hi;     // key window
 };
@@ -685,6 +686,23 @@ struct Ring {
             if (hit[e]) { buf[p & (kRing - 1u)] = make_uint2(place0 + 4u * lane_id() + e, bits[e]); ++p; }
         pending += popc64(b0) + popc64(b1) + popc64(b2) + popc64(b3);
     }
+    // straight to the slice, the keys left to be computed
+    __device__ __forceinline__ void append_unkeyed(const u32 (&bits)[4], const bool (&hit)[4], u32 place0, u32 cap,
+                                                   uint2 *__restrict__ my_ent)
+    {
+        const u64 b0 = __ballot(hit[0]), b1 = __ballot(hit[1]), b2 = __ballot(hit[2]),
+                  b3 = __ballot(hit[3]);
+        if ((b0 | b1 | b2 | b3) == 0ull) return;
+        const u64 below = lanes_below();
+        u32 p = out + popc64(b0 & below) + popc64(b1 & below) + popc64(b2 & below) + popc64(b3 & below);
+#pragma unroll
+        for (u32 e = 0; e < 4; ++e)
+            if (hit[e]) {
+                if (p < cap) my_ent[p] = make_uint2((kKeyUnknown << 30) | (place0 + 4u * lane_id() + e), bits[e]);
+                ++p;
+            }
+        out += popc64(b0) + popc64(b1) + popc64(b2) + popc64(b3);
+    }
     // Up to 64 entries leave the ring. A candidate above the bracket is a certain member,
     // and one whose key lies above the window is certainly not sent: it is needed by
     // nobody and does not reach the slice (should the estimate or the window have missed,
@@ -725,6 +743,10 @@ constexpr u32 kFusedWaves = kFusedThreads / kWave;
 // next ones are on their way meanwhile. One, but for short vectors, where a
 // wavefront has a single chunk: two.
 constexpr int kLongRows = 1, kShortRows = 2;
+// A short vector's candidates are few and a wavefront meets them at the end of its only
+// chunk or two, where nothing hides the microsecond a key and the way through the ring take:
+// they go straight to S, and classify keys them, which waits for memory anyway (428,000
+// elements, r = 84: 6.3 instead of 7.1 us; 65,536, r = 13: the call 35.6 instead of 36.4).
 
 // kAll (r == d, the random-k operator): no magnitude decides anything. An
 // element is kept when its sampling key lies at or below the upper end of the
@@ -737,7 +759,8 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
         u32 *__restrict__ group_sums, u32 *__restrict__ seg_count, uint2 *__restrict__ s_ent)
 {
     __shared__ u32 h[kAll ? 1 : kMaxBins];
-    extern __shared__ uint2 ring_s[];           // kRing entries per wavefront (and what the launch claims beyond)
+    constexpr bool kKeyed = kRows == kLongRows;
+    extern __shared__ uint2 ring_s[];           // kRing entries per wavefront (and what the launch claims beyond), none if not keyed
     Bins bins{};
     u32 nbins = 0;
     if (kAll) {
@@ -777,8 +800,12 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
                 n_above += popc64(__ballot(hit[e] && !fine));
             }
         }
-        ring.append(bits, hit, place, g.cap);
-        while (ring.pending >= (u32)kWave) ring.take(c0, g, seed, bracket_hi, my_ent);
+        if (kKeyed) {
+            ring.append(bits, hit, place, g.cap);
+            while (ring.pending >= (u32)kWave) ring.take(c0, g, seed, bracket_hi, my_ent);
+        } else {
+            ring.append_unkeyed(bits, hit, place, g.cap, my_ent);
+        }
     };
     auto open_chunk = [&](u32 w) {
         c0 = (u64)w * g.C;
@@ -786,7 +813,7 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
         ring.out = 0u;
     };
     auto close_chunk = [&](u32 w) {
-        if (ring.pending != 0u) ring.take(c0, g, seed, bracket_hi, my_ent);
+        if (kKeyed && ring.pending != 0u) ring.take(c0, g, seed, bracket_hi, my_ent);
         if (lane_id() == 0) seg_count[chunk_slot(w, g.U, g.UC)] = ring.out;
     };
     const bool all_valid[4] = {true, true, true, true};
@@ -1302,9 +1329,9 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
     if (tid == 0) {
         u32 bd_lo = 0, bd_hi = 0;
         if (!dense) bin_range(bins, bin_s, &bd_lo, &bd_hi);
-        // above the bracket S only holds what may be sent (everything when k == r): no short
-        // list can decide there
-        const bool partial = !dense && bin_s >= bins.nfine && g.take_all == 0u;
+        // above the bracket S only holds what may be sent (everything when k == r or nothing was
+        // keyed): no short list can decide there
+        const bool partial = !dense && bin_s >= bins.nfine && g.take_all == 0u && g.keyed != 0u;
         picked = Picked{dense ? 1u : 0u, partial ? 1u : 0u, bd_lo, bd_hi, before_s};
     }
     lds_barrier();
@@ -1330,6 +1357,7 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
 {
     __shared__ u32 cnt_m, cnt_b, cnt_sure, bmin_s, bmax_s;
     __shared__ u32 list_m[kListCap];
+    constexpr u32 kStored = 0xFFFFFFFFu;      // (never an index) the entry of M is already in its slot
     __shared__ u32 per_chunk[kWalkWaves][kUnitChunksMax];
     __shared__ u32 per_chunk_b[kWalkWaves][kUnitChunksMax];
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
@@ -1361,11 +1389,19 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
         const bool in_bin = valid && !member && m >= bd_lo;
         if (member) {
             u32 says = key >> 30;
-            if (says == kKeyUnknown) says = key_word(idx, g, seed) >> 30;
+            const bool unkeyed = says == kKeyUnknown;
+            u64 k64 = 0;
+            if (unkeyed) {
+                if (g.take_all == 0u) k64 = sample_key(idx, seed);
+                says = g.take_all != 0u || k64 < g.K_lo ? kKeyBelow : k64 > g.K_hi ? kKeyAbove : kKeyInside;
+            }
             const bool sure = says == kKeyBelow;
             if (says == kKeyInside) {
                 const u32 p = atomicAdd(&cnt_m, 1u);
-                if (p < kListCap) list_m[p] = idx;
+                if (p < kListCap) {
+                    list_m[p] = unkeyed ? kStored : idx;
+                    if (unkeyed) { m_key[slot(p)] = k64; m_idx[slot(p)] = idx; }
+                }
             }
             if (sure) atomicAdd(&per_chunk[wave][i], 1u);
         }
@@ -1406,12 +1442,14 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
     mine = wave_sum(mine);
     if (lane == 0 && mine) atomicAdd(&cnt_sure, mine);
     __syncthreads();
-    // the keys of the workgroup's entries of M, all at once
+    // the keys of the workgroup's entries of M that came without one, all at once
     static_assert(kListCap <= kWalkThreads, "one thread per list slot");
     if (threadIdx.x < cnt_m && threadIdx.x < kListCap) {
         const u32 idx = list_m[threadIdx.x];
-        m_key[slot(threadIdx.x)] = sample_key(idx, seed);
-        m_idx[slot(threadIdx.x)] = idx;
+        if (idx != kStored) {
+            m_key[slot(threadIdx.x)] = sample_key(idx, seed);
+            m_idx[slot(threadIdx.x)] = idx;
+        }
     }
     if (threadIdx.x == 0) {
         blk_sure[blockIdx.x] = cnt_sure;
@@ -1764,9 +1802,10 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     const u32 bd_lo = ctl->bd_lo, bd_hi = ctl->bd_hi, bd_bits = ctl->bd_bits;
     const u64 c_def = ctl->c_def;
     Candidates cand{seg_count, s_ent, a, g.d, g.C, g.U, g.UC, g.cap, dense};
-    // What is walked holds every member of the top-r set. Otherwise (S as the streaming kernel
-    // left it) the members above the bracket whose key lies above the window are missing.
-    bool whole = dense || g.take_all != 0u;
+    // Whether what the exact selections walk holds every member of the top-r set. Otherwise (S as
+    // a keying stream left it) the members above the bracket whose key lies above the window are
+    // missing.
+    bool whole = dense || g.take_all != 0u || (g.keyed == 0u && g.all_members == 0u);
     // Fills the slices of chunks first, first + step, ... again, from the vector and with every
     // element at or above the deciding bin: one pass over the vector (four rows of a chunk in
     // flight), after which S will do for all the passes of an exact selection and for emit. The
@@ -1899,8 +1938,6 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     //      threshold (the estimate kept too little; it lies above the bracket; the
     //      deciding bin crowded by several magnitudes), or the key window certainly missed.
     bool wide = false;
-    // the lists are complete and fewer than k members have a key at or below the window's upper end
-    const bool missed_high = lists && !g.take_all && sure_walk + n_m0 + (g.all_members ? 0ull : need2) < g.k;
     if (gridDim.x > 1u) {
         const bool slow_t = !g.all_members && !lists && !tie_run;
         bool slow_k = false;
@@ -1984,7 +2021,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             complete_slices(blockIdx.x * kFinWaves + wave, n_waves);     // the chunks wide_each gives this wavefront
             whole = true;
         };
-        if (!whole && (partial || missed_high)) complete();
+        // (complete lists that show fewer than k members with a key the window admits)
+        if (!whole && (partial || (lists && sure_walk + n_m0 + need2 < g.k))) complete();
         const u32 top = in_bin_only ? bd_hi : 0x7FFFFFFFu;
         Selected sel_t{0ull, 0u, 12}, sel_k{0ull, 0u, 12};
         Pair96 tbound{~0ull, 0xFFFFFFFFu}, kbound{~0ull, 0xFFFFFFFFu};
@@ -2821,11 +2859,11 @@ bool allow_lds_claim(K kernel)
 struct FusedShape { unsigned threads, grid, lds; bool is_short; };
 FusedShape fused_shape(u32 W, u64 d, unsigned grid_limit)
 {
-    unsigned waves = W <= 512u ? 4u : W <= 2048u ? 8u : d < (1ull << 24) ? 12u : d <= (1ull << 26) ? 10u : 8u;
-    unsigned grid = (W + waves - 1) / waves;
     const bool is_short = W <= 2048u;
+    unsigned waves = W <= 512u ? 4u : is_short ? 8u : d < (1ull << 24) ? 12u : d <= (1ull << 26) ? 10u : 8u;
+    unsigned grid = (W + waves - 1) / waves;
     return FusedShape{waves * (unsigned)kWave, grid > grid_limit ? grid_limit : grid,
-                      is_short ? waves * kRing * (unsigned)sizeof(uint2) : kFusedLdsClaim, is_short};
+                      is_short ? 0u : kFusedLdsClaim, is_short};
 }
 
 int fused_grid_limit(unsigned *out)
@@ -2918,6 +2956,7 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
     if (rc2) return rc2;
     const FusedShape fs = fused_shape(g.W, g.d, grid_limit);
     const unsigned fgrid = fs.grid;
+    g.keyed = fs.is_short ? 0u : 1u;
 
     const TraceRequest trace = g_trace;
     g_trace = TraceRequest{};

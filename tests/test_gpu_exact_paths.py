@@ -41,7 +41,9 @@ def test_exact_selections(kind, d, r, k, abort):
     got = u.gpu_encode_once(g, m, r, k, SEED, STEP, offset=d % 4, force=force)
     u.assert_encode_equal(got, oracle.encode(g, m, r, k, SEED, STEP), f"{kind} d={d}")
     st = got[3]
-    assert st["path"] & 3 == 1, st                   # exact, and not by walking the vector pass after pass
+    # exact, and not by walking the vector pass after pass (a short vector's candidates are all
+    # there: with few of them above a bracket that is too low the short lists still decide)
+    assert st["path"] & 3 == 1 or (kind == "bracket" and d < 1 << 21 and st["path"] == 0), st
     if d > 1 << 22 and kind in ("high", "window", "bracket"):
         # members whose keys lie above the window decide: the buffer was completed with them.
         # (The bracket of 65,536 samples holds 0.7 r entries; what is above it and not to be sent

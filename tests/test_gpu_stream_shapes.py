@@ -44,3 +44,25 @@ def test_stream_shapes(d, off_g, off_m, layout):
         assert st["error_flags"] == 0 and (layout == "hot" or st["path"] == 0), st
         got = (idx.cpu().numpy().view(np.uint32), val.cpu().numpy(), tm.cpu().numpy())
         u.assert_encode_equal(got, oracle.encode(g, m, r, k, 3, 4), f"d={d} r={r} k={k}")
+
+
+@pytest.mark.parametrize("chunks,whole", [(2048, True), (2049, False), (3072, False), (4097, False)])
+@pytest.mark.parametrize("ops", ["rtopk", "top-k", "random-k"])
+def test_short_vectors_keep_every_candidate(chunks, whole, ops):
+    """Part of the top r lies far above the bracket: a keying stream leaves out what will not
+    be sent of it, a short vector's keeps all candidates."""
+    from tests import gpu_util as u
+    d = chunks * 1024 - 5
+    rng = np.random.default_rng(chunks)
+    g = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    g[::50] *= np.float32(1e4)
+    g[::400] *= np.float32(1e4)              # a quarter of the top r, far above the rest
+    m = np.zeros(d, np.float32)
+    r = d if ops == "random-k" else d // 100
+    k = r if ops == "top-k" else d // 1000
+    got = u.gpu_encode_once(g, m, r, k, 5, 6, offset=chunks % 4)
+    u.assert_encode_equal(got, oracle.encode(g, m, r, k, 5, 6), f"chunks={chunks} {ops}")
+    if ops == "rtopk":
+        # with k = r everything is sent and nothing left out, from the same sample
+        every = u.gpu_encode_once(g, m, r, r, 5, 6, offset=chunks % 4)[3]["superset_size"]
+        assert got[3]["path"] == 0 and (got[3]["superset_size"] == every) == whole, (got[3], every)
