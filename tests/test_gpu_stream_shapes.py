@@ -66,3 +66,20 @@ def test_short_vectors_keep_every_candidate(chunks, whole, ops):
         # with k = r everything is sent and nothing left out, from the same sample
         every = u.gpu_encode_once(g, m, r, r, 5, 6, offset=chunks % 4)[3]["superset_size"]
         assert got[3]["path"] == 0 and (got[3]["superset_size"] == every) == whole, (got[3], every)
+
+
+@pytest.mark.parametrize("d", [2_000_003, 3_000_001, 4_000_000])
+def test_short_vectors_sample_enough_for_a_heavy_tail(d):
+    """Below 2^22 elements the estimate takes as many samples as put 160 into the top r: its
+    bracket then ends at a sample of rank 50 or so and not at the largest one or two, which
+    in a heavy-tailed vector lie far above. About 1.4 r entries lie in the bracket, over 256
+    linear bins of which rounding to a power of two leaves half: 3 r / 256 in the deciding
+    bin, and not twice that (80 samples: 7 r / 256)."""
+    from tests import gpu_util as u
+    rng = np.random.default_rng(d)
+    g = rng.standard_t(3, d).astype(np.float32)
+    m = np.zeros(d, np.float32)
+    r, k = d // 100, d // 1000
+    got = u.gpu_encode_once(g, m, r, k, 42, 1)
+    u.assert_encode_equal(got, oracle.encode(g, m, r, k, 42, 1), f"d={d}")
+    assert got[3]["path"] == 0 and got[3]["boundary_list_size"] <= 5 * r // 256, got[3]
