@@ -2855,15 +2855,23 @@ bool allow_lds_claim(K kernel)
                                (int)kFusedLdsClaim) == hipSuccess;
 }
 
-// Wavefronts per workgroup of the streaming kernel, and its grid. Measured (us, a
+// Wavefronts per workgroup of the streaming kernel, and its grid. A vector of up to 2048
+// chunks is one chunk per wavefront. Above, short vectors are a few rounds of chunks (more
+// wavefronts, fewer rounds), long ones stream best with least in flight. Measured (us, a
 // launch with 8, 10, 12 wavefronts): five vectors of 11.2 M elements 131, 123, 116;
 // eight of 25.6 M 419, 391, 399; four of 66 M 534, 524, 550; four of 134 M 1067, 1117,
-// 1112; four of 2^28 2372, 2510, 2554. Short vectors are a few rounds of chunks (more
-// wavefronts, fewer rounds), long ones stream best with least in flight.
+// 1112; four of 2^28 2372, 2510, 2554. Whole calls for one vector: 3 M 54.6, 57.0, 53.1;
+// 11.2 M 74.7, 72.6, 70.4; 40 M 140, 134.5, 142; 66 M 199, 194, 199; 100 M 276, 283, 281.5;
+// 134 M 353, 364, 368. (What fits exactly is a saw-tooth in the number of chunks: 13 M runs 3%
+// faster with 10, 134 M + 1 and 180 M 3% faster with 10 than with 8.)
+// Between one round of 12 wavefronts (3072 chunks) and two of 8 (4096), a second round that is
+// a third full or less costs more than the shape of the short vectors with two chunks per
+// wavefront: one vector of 3.5 M 53.9 / 50.4 (r = d: 38.5 / 33.6), of 4 M 52.7 / 51.8, sixteen
+// of 4 M 210.6 / 202.4, four of 4 M 88.9 / 91.1; just above 3072 chunks 47.3 / 49.3.
 struct FusedShape { unsigned threads, grid, lds; bool is_short; };
 FusedShape fused_shape(u32 W, u64 d, unsigned grid_limit)
 {
-    const bool is_short = W <= 2048u;
+    const bool is_short = W <= 2048u || (W > 3072u && W <= 4096u);
     unsigned waves = W <= 512u ? 4u : is_short ? 8u : d < (1ull << 24) ? 12u : d <= (1ull << 26) ? 10u : 8u;
     unsigned grid = (W + waves - 1) / waves;
     return FusedShape{waves * (unsigned)kWave, grid > grid_limit ? grid_limit : grid,

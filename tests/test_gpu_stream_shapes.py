@@ -46,7 +46,8 @@ def test_stream_shapes(d, off_g, off_m, layout):
         u.assert_encode_equal(got, oracle.encode(g, m, r, k, 3, 4), f"d={d} r={r} k={k}")
 
 
-@pytest.mark.parametrize("chunks,whole", [(2048, True), (2049, False), (3072, False), (4097, False)])
+@pytest.mark.parametrize("chunks,whole", [(2048, True), (2049, False), (3072, False), (3073, True), (4096, True),
+                                          (4097, False)])
 @pytest.mark.parametrize("ops", ["rtopk", "top-k", "random-k"])
 def test_short_vectors_keep_every_candidate(chunks, whole, ops):
     """Part of the top r lies far above the bracket: a keying stream leaves out what will not
