@@ -2374,12 +2374,12 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             }
         }
     };
-    if (!wide && (lists || tie_run)) {
+    if (__builtin_expect(!wide && (lists || tie_run), 1)) {
         const u32 n_b_use = lists ? n_bd : 0u;
         const bool b_lds = n_b_use <= kStageB;
         // (a run of equal magnitudes may add any number of keys: the large array then)
         const bool m_lds = lists && n_m0 + n_b_use <= kStageMLarge;
-        if (b_lds && lists && n_m0 + n_b_use <= kStageM)
+        if (__builtin_expect(b_lds && lists && n_m0 + n_b_use <= kStageM, 1))
             short_lists(st_b_key, st_b_idx, st_m_key, st_m_idx, std::integral_constant<u32, kStageM>{});
         else if (b_lds && m_lds)
             short_lists(st_b_key, st_b_idx, st_m_key, st_m_idx, std::integral_constant<u32, kStageMLarge>{});
@@ -2400,7 +2400,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         __syncthreads();
         whole = true;
     };
-    if (!have_t) {
+    if (__builtin_expect(!have_t, 0)) {
         // ---- exact threshold by selection over all candidates: those of the deciding
         //      bin, or the whole vector when the estimate had kept too little ----------
         path |= 1u;
@@ -2427,7 +2427,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         const u32 m = mag_of(bits);
         return m > T || (m == T && idx <= I_star);
     };
-    if (!have_k) {
+    if (__builtin_expect(!have_k, 0)) {
         // ---- exact key cut and winners per chunk by selection over all candidates
         path |= 1u;
         __syncthreads();
