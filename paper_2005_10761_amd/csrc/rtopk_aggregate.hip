@@ -52,11 +52,18 @@ constexpr unsigned kAggMaxWaves = 4096;
 // The sparse weight step takes k_weights (one kernel) where the vector is long and the
 // messages are sparse: from kWeightsTiles tiles on, up to kWeightsWorkers workers and
 // kWeightsPerTile entries per tile; k_tile_starts + k_update elsewhere. Measured (us,
-// k_weights / the pair): four workers of 66 M coordinates, 8 entries per tile,
-// 19.5 / 38.7; eight of 2^28, 2 per tile, 21 / 131; two of 2^28, 8 per tile, 62 / 116;
-// eight of 25.6 M, 16 per tile, 19.6 / 19.7; five of 11.2 M, 10 per tile, 14.5 / 10.0;
-// five of 11.2 M, 102 per tile, 27.8 / 22.3; sixteen of 25.6 M (a table twice as
-// large, half the workgroups) 51 / 36.
+// k_weights / the pair), messages crowded towards one end of the vector:
+//   2^25, two and eight workers: 1 entry per tile 9 / 16, 14 / 22; 12: 11 / 27, 18 / 41;
+//     100: 36 / 52, 42 / 135
+//   2^26: 1: 9 / 26, 15 / 36; 12: 19 / 40, 24 / 73; 100: 65 / 67, 74 / 146
+//   2^28: 1: 11 / 83, 16 / 111; 12: 56 / 106, 68 / 165; 50: 218 / 214, 236 / 258;
+//     100: 347 / 334, 367 / 326
+//   2^30: 1: 26 / 312, 31 / 427; 12: 274 / 490, 300 / 744.
+// From 2^25 to 2^30, one to eight workers, 0.25 to 12 entries per tile, evenly spread,
+// crowded, in stretches of their own or in a twentieth of the vector, k_weights is never the
+// slower one; the line at 12 leaves out what it would still gain up to 50. Shorter vectors:
+// five workers of 11.2 M coordinates, 10 per tile, 14.5 / 10.0; sixteen workers of 25.6 M (a
+// table twice as large, half the workgroups) 51 / 36.
 constexpr u64 kWeightsTiles = 1u << 14;
 constexpr u32 kWeightsWorkers = 8;
 constexpr u32 kWeightsPerTile = 12;
@@ -492,12 +499,18 @@ k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64
                     if (in) sum[slot[q]] += e_v[q];
                     lds_barrier();
                 } else {
-                    // repeated indices inside one message: in position order
+                    // repeated indices inside one message: in position order, one wavefront
+                    // after the other; the first entries of all runs of equal indices
+                    // together, then the second ones, ...
+                    const u32 before = lane_left(e_i[q], left[q]);
+                    const u64 heads = __ballot(in && (lane == 0 || before != e_i[q]));
+                    const u32 rank = in ? lane - (63u - (u32)__clzll(heads & (lanes_below() | (1ull << lane)))) : 0u;
+                    const u32 most = wave_max(rank);
                     for (u32 wv = 0; wv < (u32)kAggWaves; ++wv) {
                         if (wave == wv)
-                            for (u64 rest = __ballot(in); rest; rest &= rest - 1) {
-                                const int src = __ffsll((unsigned long long)rest) - 1;
-                                if ((int)lane == src) sum[slot[q]] += e_v[q];
+                            for (u32 s = 0; s <= most; ++s) {
+                                if (in && rank == s) sum[slot[q]] += e_v[q];
+                                wave_lds_fence();
                             }
                         lds_barrier();
                     }
@@ -516,17 +529,35 @@ k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64
         }
         if (!cut) break;
         if (__builtin_expect(seen == 0u, 0)) {
-            // Nothing lies below the bound: a window holds one coordinate only (an index
-            // that occurs more than 255 times in one message). One thread takes it.
-            if (tid == 0) {
-                float s = 0.0f;
-                u32 moved = 0;
-                for (u32 q = 0; q < n; ++q)
-                    for (u64 p = pos[q]; p < k && idx[q * k + p] == bound; ++p) {
-                        s += val[q * k + p];
-                        pos[q] = p + 1;
-                        moved = 1;
+            // Nothing lies below the bound: a window holds one coordinate only, the bound (an index
+            // that occurs more than 255 times in one message). Its entries, worker after worker:
+            // the workgroup fetches 256 at a time, one thread adds them up in position order.
+            // (20,000 entries on one coordinate: 0.74 ms; 2.5 when that thread fetched them too, and
+            // 1.5 on the pair of kernels.)
+            float s = 0.0f;
+            bool moved = false;
+            for (u32 q = 0; q < n; ++q) {
+                u32 c;
+                do {
+                    const u64 from = pos[q], j = from + tid;
+                    const bool on = j < k && idx[q * k + j] == bound;
+                    sum[tid] = on ? val[q * k + j] : 0.0f;
+                    const u64 m = __ballot(on);
+                    if (lane == 0) key[wave] = popc_mask(m);
+                    lds_barrier();
+                    c = 0;
+                    for (u32 wv = 0; wv < (u32)kAggWaves; ++wv) c += key[wv];
+                    moved = moved || c != 0u;
+                    if (tid == 0) {
+                        for (u32 t = 0; t < c; ++t) s += sum[t];
+                        pos[q] = from + c;
                     }
+                    lds_barrier();
+                } while (c == (u32)kAggThreads);
+            }
+            sum[tid] = 0.0f;
+            if (tid < (u32)kAggWaves) key[tid] = kEmpty;
+            if (tid == 0) {
                 const float avg = average(s);
                 if (avg != 0.0f && bound >= base) omega[bound] = fmaf(neg_step, avg, omega[bound]);
                 // (a list that is not sorted, a broken precondition: the loop ends all the same)

@@ -129,6 +129,16 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Orders one wavefront's own LDS accesses: what its lanes wrote before is what
+// its lanes read after (the hardware keeps a wavefront's LDS operations in
+// order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 __host__ __device__ constexpr u64 align_up(u64 x, u64 a) { return (x + a - 1) / a * a; }
 
 }  // namespace rtopk

@@ -370,16 +370,6 @@ static EncodeLayout make_layout(const Geom &g)
 __device__ __forceinline__ u32 mag_of(u32 bits) { return bits & 0x7FFFFFFFu; }
 __device__ __forceinline__ u32 popc64(u64 m) { return (u32)__popcll((unsigned long long)m); }
 
-// Orders one wavefront's own LDS accesses: what its lanes wrote before is what
-// its lanes read after (the hardware keeps a wavefront's LDS operations in
-// order; this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
 // ---------------------------------------------------------------------------
 // workgroup-wide sums of one value per thread (thread order); the second
 // level is a wavefront scan, not a serial loop: LDS round trips are slow
