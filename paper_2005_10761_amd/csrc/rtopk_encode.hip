@@ -826,6 +826,17 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
             mv[q] = __builtin_nontemporal_load(mp + q * kWave);
         }
     };
+    // the sum of the group at `base`, which has been loaded, stored and handed on as patterns
+    auto add = [&](u64 base, u32 (&bits)[kRows][4]) {
+        f32x4u *mp = reinterpret_cast<f32x4u *>(residual + base) + lane_id();
+#pragma unroll
+        for (int q = 0; q < kRows; ++q) {
+            const f32x4 a = gv[q] + mv[q];
+            __builtin_nontemporal_store((f32x4u)a, mp + q * kWave);
+            bits[q][0] = __float_as_uint(a.x); bits[q][1] = __float_as_uint(a.y);
+            bits[q][2] = __float_as_uint(a.z); bits[q][3] = __float_as_uint(a.w);
+        }
+    };
     // The chunks that are whole: the next group is on its way while this one's
     // candidates are looked for.
     const u32 w_first = blockIdx.x * n_waves + threadIdx.x / kWave;
@@ -837,14 +848,7 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
         load(base);
         for (;;) {
             u32 bits[kRows][4];
-            f32x4u *mp = reinterpret_cast<f32x4u *>(residual + base) + lane_id();
-#pragma unroll
-            for (int q = 0; q < kRows; ++q) {
-                const f32x4 a = gv[q] + mv[q];
-                __builtin_nontemporal_store((f32x4u)a, mp + q * kWave);
-                bits[q][0] = __float_as_uint(a.x); bits[q][1] = __float_as_uint(a.y);
-                bits[q][2] = __float_as_uint(a.z); bits[q][3] = __float_as_uint(a.w);
-            }
+            add(base, bits);
             const u32 place = (u32)(base - c0);
             const bool last = place + kGroup >= g.C;
             const u32 w_next = last ? w + wave_stride : w;
@@ -863,10 +867,25 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
         }
         while (w < w_full) w += wave_stride;
     }
-    // the ragged end of the vector: one chunk, of some wavefront
+    // The ragged end of the vector: one chunk, of some wavefront. It may be nearly C elements
+    // long: its groups go the same way (read row by row without the next one on its way, it
+    // held a call of 2^30 - 1 elements up by 3%, one of 3 * 2^30 - 1 by 6%).
     if (w == w_full && w < g.W) {
         open_chunk(w);
-        for (u64 base = c0; base < g.d; base += kChunkQuantum) {
+        u64 base = c0;
+        bool more = base + kGroup <= g.d;
+        if (more) load(base);
+        while (more) {
+            u32 bits[kRows][4];
+            add(base, bits);
+            const u32 place = (u32)(base - c0);
+            base += kGroup;
+            more = base + kGroup <= g.d;
+            if (more) load(base);
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) keep(bits[u], all_valid, place + u * kChunkQuantum);
+        }
+        for (; base < g.d; base += kChunkQuantum) {
             u32 bits[4];
             bool valid[4];
 #pragma unroll

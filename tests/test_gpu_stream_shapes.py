@@ -15,6 +15,10 @@ pytestmark = pytest.mark.gpu
     (1024 * 1024, 0, 1), (1024 * 1024 + 1, 0, 0),            # one more chunk than 4 wavefronts x 256
     (2048 * 1024, 2, 0), (2048 * 1024 + 257, 0, 3),          # the last length with two rows at a time
     ((1 << 24) - 1, 0, 0), ((1 << 24) + 5, 1, 1),            # 12 and 10 wavefronts per workgroup
+    # what the last chunk holds, around whole groups of one row and of two
+    (5120 + 255, 0, 0), (5120 + 511, 0, 1), (5120 + 512, 1, 0), (5120 + 513, 0, 0), (5120 + 1023, 2, 2),
+    (2099 * 1024 + 255, 0, 0), (2099 * 1024 + 256, 0, 0), (2099 * 1024 + 511, 3, 1), (2099 * 1024 + 512, 0, 0),
+    (2099 * 1024 + 1023, 0, 2), ((1 << 25) + 1700, 1, 0),
 ])
 @pytest.mark.parametrize("layout", ["even", "hot"])
 def test_stream_shapes(d, off_g, off_m, layout):
