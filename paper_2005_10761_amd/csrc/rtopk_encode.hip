@@ -251,7 +251,7 @@ struct Geom {
                         // had underestimated the r-th largest magnitude: it then lies above the linear bins
     u32 take_all;       // k == r: every member is sent, keys are never looked at
     u32 all_members;    // r == d: every coordinate is a member, magnitudes are never looked at
-    u32 keyed;          // the streaming kernel keys the candidates (not those of a short vector)
+    u32 keyed;          // the streaming kernel keys the candidates (of a short vector only if they are many)
     u32 k_nlz;          // leading zeros of K_hi - K_lo
     u64 K_lo, K_hi;     // key window
 };
@@ -737,23 +737,23 @@ constexpr u32 kFusedWaves = kFusedThreads / kWave;
 // next ones are on their way meanwhile. One, but for short vectors, where a
 // wavefront has a single chunk: two.
 constexpr int kLongRows = 1, kShortRows = 2;
-// A short vector's candidates are few and a wavefront meets them at the end of its only
-// chunk or two, where nothing hides the microsecond a key and the way through the ring take:
-// they go straight to S, and classify keys them, which waits for memory anyway (428,000
-// elements, r = 84: 6.3 instead of 7.1 us; 65,536, r = 13: the call 35.6 instead of 36.4).
+// kKeyed: the candidates are keyed, by way of a ring in LDS. A short vector's are few, as a
+// rule, and a wavefront meets them at the end of its only chunk or two, where nothing hides the
+// microsecond a key and the way through the ring take: they then go straight to S, and
+// classify keys them, which waits for memory anyway (428,000 elements, r = 84: 6.3 instead of
+// 7.1 us; 65,536, r = 13: the call 35.6 instead of 36.4). See keys_in_stream.
 
 // kAll (r == d, the random-k operator): no magnitude decides anything. An
 // element is kept when its sampling key lies at or below the upper end of the
 // a-priori window (all of them when k == r as well); no histogram is made and
 // the control block, which no earlier kernel has touched, is cleared here.
-template <bool kAll, int kRows>
+template <bool kAll, int kRows, bool kKeyed>
 __device__ __forceinline__ void
 fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g, PhiloxSeed seed,
         EncodeCtl *__restrict__ ctl, u32 zero_words, u32 *__restrict__ partials,
         u32 *__restrict__ group_sums, u32 *__restrict__ seg_count, uint2 *__restrict__ s_ent)
 {
     __shared__ u32 h[kAll ? 1 : kMaxBins];
-    constexpr bool kKeyed = kRows == kLongRows;
     extern __shared__ uint2 ring_s[];           // kRing entries per wavefront (and what the launch claims beyond), none if not keyed
     Bins bins{};
     u32 nbins = 0;
@@ -2701,11 +2701,11 @@ __global__ void __launch_bounds__(kEstThreads) k_estimate(Batch B, Geom g, Encod
     estimate_body<kVecs>(m.at<u32>(L.samples), g, m.at<EncodeCtl>(L.ctl));
 }
 
-template <bool kAll, int kRows>
+template <bool kAll, int kRows, bool kKeyed>
 __global__ void __launch_bounds__(kFusedThreads) k_fused(Batch B, Geom g, EncodeLayout L)
 {
     const Member m(B);
-    fused_body<kAll, kRows>(m.grad, m.residual, g, m.seed, m.at<EncodeCtl>(L.ctl),
+    fused_body<kAll, kRows, kKeyed>(m.grad, m.residual, g, m.seed, m.at<EncodeCtl>(L.ctl),
                             (u32)(L.zero_bytes / 4), m.at<u32>(L.partials), m.at<u32>(L.group_sums), m.at<u32>(L.seg_count),
                             m.at<uint2>(L.s_ent));
 }
@@ -2876,7 +2876,8 @@ bool allow_lds_claim(K kernel)
 // Between one round of 12 wavefronts (3072 chunks) and two of 8 (4096), a second round that is
 // a third full or less costs more than the shape of the short vectors with two chunks per
 // wavefront: one vector of 3.5 M 53.9 / 50.4 (r = d: 38.5 / 33.6), of 4 M 52.7 / 51.8, sixteen
-// of 4 M 210.6 / 202.4, four of 4 M 88.9 / 91.1; just above 3072 chunks 47.3 / 49.3.
+// of 4 M 210.6 / 202.4, four of 4 M 88.9 / 91.1 (none of them keyed); just above 3072 chunks
+// 47.3 / 49.3.
 struct FusedShape { unsigned threads, grid, lds; bool is_short; };
 FusedShape fused_shape(u32 W, u64 d, unsigned grid_limit)
 {
@@ -2884,7 +2885,22 @@ FusedShape fused_shape(u32 W, u64 d, unsigned grid_limit)
     unsigned waves = W <= 512u ? 4u : is_short ? 8u : d < (1ull << 24) ? 12u : d <= (1ull << 26) ? 10u : 8u;
     unsigned grid = (W + waves - 1) / waves;
     return FusedShape{waves * (unsigned)kWave, grid > grid_limit ? grid_limit : grid,
-                      is_short ? 0u : kFusedLdsClaim, is_short};
+                      is_short ? waves * kRing * (unsigned)sizeof(uint2) : kFusedLdsClaim, is_short};
+}
+
+// Whether the stream computes the candidates' keys (and leaves out what will not be sent).
+// Those of a long vector always: they take the time in which the stream waits for memory. A
+// short vector's stream has nothing to hide them behind, but where a launch's members have
+// many, the classify and emit kernels do less for it. us, unkeyed / keyed: one vector of
+// 300,007 elements, r = 1%, 36.9 / 37.9; eight of 2 M, r = 1% (160,000 in all), 85.2 / 83.4;
+// five of 950,000, r = 5% (238,000), 57.6 / 56.3; sixteen of 2 M, r = 10%, 176 / 155. Layered
+// vectors, in which most chunks with candidates overflow their slice, lose up to 4% by keys
+// between 130,000 and a million candidates. From an eighth of the vector on every chunk does
+// (sixteen of 2 M, r = 20%: 198.1 / 198.4).
+constexpr u64 kKeyedMembers = 1u << 17;
+bool keys_in_stream(const Geom &g, bool is_short, unsigned nb)
+{
+    return !is_short || (g.all_members == 0u && nb * g.r >= kKeyedMembers && g.r * kSliceDiv < g.d);
 }
 
 int fused_grid_limit(unsigned *out)
@@ -2894,14 +2910,14 @@ int fused_grid_limit(unsigned *out)
     std::lock_guard<std::mutex> lock(g_device_mutex);
     if (g_fused_grid[dev] == 0) {
         int cus = 0, fit_t = 0, fit_f = 0;
-        if (!allow_lds_claim(k_fused<false, kLongRows>) || !allow_lds_claim(k_fused<false, kShortRows>) ||
-            !allow_lds_claim(k_fused<true, kLongRows>) || !allow_lds_claim(k_fused<true, kShortRows>))
+        if (!allow_lds_claim(k_fused<false, kLongRows, true>) || !allow_lds_claim(k_fused<false, kShortRows, true>) ||
+            !allow_lds_claim(k_fused<true, kLongRows, true>))
             return RTOPK_EHIP;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_t, k_fused<false, kShortRows>,
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_t, k_fused<false, kShortRows, true>,
                                                          (int)kFusedThreads,
                                                          kFusedLdsClaim) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_f, k_fused<true, kShortRows>,
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_f, k_fused<true, kLongRows, true>,
                                                          (int)kFusedThreads,
                                                          kFusedLdsClaim) != hipSuccess)
             return RTOPK_EHIP;
@@ -2977,7 +2993,6 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
     if (rc2) return rc2;
     const FusedShape fs = fused_shape(g.W, g.d, grid_limit);
     const unsigned fgrid = fs.grid;
-    g.keyed = fs.is_short ? 0u : 1u;
 
     const TraceRequest trace = g_trace;
     g_trace = TraceRequest{};
@@ -2987,6 +3002,7 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         const unsigned nb = n - first < kMaxBatch ? n - first : kMaxBatch;
         Geom gg = g;                    // this launch group's share-out of the walking kernels
         set_units(gg, nb);
+        gg.keyed = keys_in_stream(gg, fs.is_short, nb) ? 1u : 0u;
         Batch B{};
         for (unsigned i = 0; i < nb; ++i) {
             B.grad[i] = grad[first + i];
@@ -3006,9 +3022,9 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
             // r == d (random-k): no estimate, no histogram, no threshold
             StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
             if (fs.is_short)
-                k_fused<true, kShortRows><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
+                k_fused<true, kShortRows, false><<<fg, fs.threads, 0, stream>>>(B, gg, L);
             else
-                k_fused<true, kLongRows><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
+                k_fused<true, kLongRows, true><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
             RTOPK_LAUNCH_CHECK();
         } else {
             {
@@ -3029,10 +3045,12 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
             }
             {
                 StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
-                if (fs.is_short)
-                    k_fused<false, kShortRows><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
+                if (fs.is_short && !gg.keyed)
+                    k_fused<false, kShortRows, false><<<fg, fs.threads, 0, stream>>>(B, gg, L);
+                else if (fs.is_short)
+                    k_fused<false, kShortRows, true><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
                 else
-                    k_fused<false, kLongRows><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
+                    k_fused<false, kLongRows, true><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
                 RTOPK_LAUNCH_CHECK();
             }
         }

@@ -73,6 +73,38 @@ def test_short_vectors_keep_every_candidate(chunks, whole, ops):
         assert got[3]["path"] == 0 and (got[3]["superset_size"] == every) == whole, (got[3], every)
 
 
+@pytest.mark.parametrize("d,r,whole", [(1 << 21, (1 << 17) - 1, True), (1 << 21, 1 << 17, False),
+                                       (1 << 20, 1 << 17, True), ((1 << 20) + 1, 1 << 17, False),
+                                       (4096 * 1024, 1 << 17, False)])
+def test_short_vectors_with_many_candidates_are_keyed(d, r, whole):
+    """From 2^17 members per launch on a short vector's stream keys its candidates, unless
+    they are an eighth of the vector; two vectors with half of them each do so together."""
+    import torch
+
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    rng = np.random.default_rng(d + r)
+    g = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    g[::50] *= np.float32(1e4)                       # far above the rest
+    m = np.zeros(d, np.float32)
+    k = r // 10
+    got = u.gpu_encode_once(g, m, r, k, 5, 6)
+    u.assert_encode_equal(got, oracle.encode(g, m, r, k, 5, 6), f"d={d} r={r}")
+    every = u.gpu_encode_once(g, m, r, r, 5, 6)[3]["superset_size"]
+    assert got[3]["path"] == 0 and (got[3]["superset_size"] == every) == whole, (got[3], every)
+    r, k = (r + 1) // 2, r // 20
+    grads = [torch.from_numpy(g).to(u.DEV) for _ in range(2)]
+    res = [torch.zeros(d, device=u.DEV) for _ in range(2)]
+    idx = [torch.empty(k, dtype=torch.int32, device=u.DEV) for _ in range(2)]
+    val = [torch.empty(k, device=u.DEV) for _ in range(2)]
+    ws = torch.empty(2 * rt.encode_workspace_bytes(d, r, k), dtype=torch.uint8, device=u.DEV).fill_(0xA5)
+    rt.encode_batch(grads, res, r, k, [5, 8], 6, idx, val, ws)
+    torch.cuda.synchronize()
+    for w, seed in enumerate((5, 8)):
+        got = (idx[w].cpu().numpy().view(np.uint32), val[w].cpu().numpy(), res[w].cpu().numpy())
+        u.assert_encode_equal(got, oracle.encode(g, m, r, k, seed, 6), f"batch of two, d={d} member {w}")
+
+
 @pytest.mark.parametrize("d", [2_000_003, 3_000_001, 4_000_000])
 def test_short_vectors_sample_enough_for_a_heavy_tail(d):
     """Below 2^22 elements the estimate takes as many samples as put 160 into the top r: its
