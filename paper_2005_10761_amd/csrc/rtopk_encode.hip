@@ -103,6 +103,7 @@ constexpr u32 kSampleThreads = 256;
 constexpr u32 kEstThreads = 1024;
 constexpr u32 kNoSample = 0xFFFFFFFFu;
 constexpr u64 kShortVector = 1u << 22;
+constexpr u64 kHeavyTail = 1u << 14;          // (see make_geom)
 
 constexpr u32 kChunkQuantum = 256;            // one wavefront iteration: 64 lanes x 4 elements
 constexpr u32 kMinChunk = 4 * kChunkQuantum;  // short vectors: chunks of four iterations
@@ -288,15 +289,18 @@ static Geom make_geom(u64 d, u64 r, u64 k)
     g.G3 = (g.U + kWalkWaves - 1) / kWalkWaves;       // (the layout is sized for this many)
     // A wide bracket is enough for a short vector, whose few candidates cost the walking
     // kernels nothing, and the estimate's one workgroup is a good part of its time: 4-6
-    // instead of 10 us with a quarter of the samples. 160 samples or more in the top r: with
-    // 80 the bracket's upper end is the largest sample or two, a heavy-tailed vector's deciding
-    // bin then crowds the short lists. One call, us, 80 / 160 / 320 samples, r = 1%: Student-t
-    // values 48.8 / 44.1 / 45.9 at 2^21 elements, 63.5 / 54.5 / 55.5 at 3.5 M; values spread
-    // evenly over three decades 35.6 / 35.9 / 37.1 at 200,003, 40.5 / 40.4 / 41.1 at 2^20.
+    // instead of 10 us with a quarter of the samples. With 80 samples in the top r the
+    // bracket's upper end is the largest sample or two, and a heavy-tailed vector's deciding
+    // bin holds r / 35 entries; from kHeavyTail on that costs finalize more than twice the
+    // samples cost (as long as those are few: they cost every member of a batch). One call,
+    // us, 80 / 160 / 320 samples, r = 1%: Student-t values 48.8 / 44.1 / 45.9 at 2^21 elements,
+    // 63.5 / 54.5 / 55.5 at 3.5 M; values spread evenly over three decades 44.3 / 44.4 / 45.6 at
+    // 2^21; sixteen layered vectors of 2 M, r = 5,046 134 / 155.
     u64 loc = (d + 3) / 4, want = kSampleLoc;
     if (d < kShortVector) {
         want = kEstThreads;
-        while (want < kSampleLoc && want * 4 * r < 160 * d) want *= 2;
+        while (want < kSampleLoc && want * 4 * r < 80 * d) want *= 2;
+        if (r >= kHeavyTail && want <= kSampleLoc / 4 && want * 4 * r < 160 * d) want *= 2;
     }
     g.L = (u32)(loc < want ? loc : want);
     g.est_vecs = 1;
