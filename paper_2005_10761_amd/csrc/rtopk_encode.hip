@@ -2900,11 +2900,15 @@ FusedShape fused_shape(u32 W, u64 d, unsigned grid_limit)
 // five of 950,000, r = 5% (238,000), 57.6 / 56.3; sixteen of 2 M, r = 10%, 176 / 155. Layered
 // vectors, in which most chunks with candidates overflow their slice, lose up to 4% by keys
 // between 130,000 and a million candidates. From an eighth of the vector on every chunk does
-// (sixteen of 2 M, r = 20%: 198.1 / 198.4).
-constexpr u64 kKeyedMembers = 1u << 17;
+// (sixteen of 2 M, r = 20%: 198.1 / 198.4). r == d, where the stream computes every element's
+// key to know the candidates: one vector of 300,007 24.5 / 24.6, two of 3.5 M 43.4 / 44.0;
+// eight of 2 M, k = 1%, 72.5 / 70.9, sixteen of 1 M 72.3 / 70.8.
+constexpr u64 kKeyedMembers = 1u << 17, kKeyedElements = 1u << 23;
 bool keys_in_stream(const Geom &g, bool is_short, unsigned nb)
 {
-    return !is_short || (g.all_members == 0u && nb * g.r >= kKeyedMembers && g.r * kSliceDiv < g.d);
+    if (!is_short) return true;
+    if (g.all_members) return nb * g.d >= kKeyedElements;
+    return nb * g.r >= kKeyedMembers && g.r * kSliceDiv < g.d;
 }
 
 int fused_grid_limit(unsigned *out)
@@ -3025,8 +3029,10 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         if (g.all_members) {
             // r == d (random-k): no estimate, no histogram, no threshold
             StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
-            if (fs.is_short)
+            if (fs.is_short && !gg.keyed)
                 k_fused<true, kShortRows, false><<<fg, fs.threads, 0, stream>>>(B, gg, L);
+            else if (fs.is_short)
+                k_fused<true, kShortRows, true><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
             else
                 k_fused<true, kLongRows, true><<<fg, fs.threads, fs.lds, stream>>>(B, gg, L);
             RTOPK_LAUNCH_CHECK();

@@ -105,6 +105,32 @@ def test_short_vectors_with_many_candidates_are_keyed(d, r, whole):
         u.assert_encode_equal(got, oracle.encode(g, m, r, k, seed, 6), f"batch of two, d={d} member {w}")
 
 
+@pytest.mark.parametrize("n", [15, 16])
+def test_short_random_k_batches_on_both_sides_of_keying(n):
+    """r == d: from 2^23 elements per launch on a short vector's stream leaves the keys it
+    computes anyway in the candidate buffer."""
+    import torch
+
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    d, k = 1 << 19, 5000
+    rng = np.random.default_rng(n)
+    g = rng.standard_normal(d).astype(np.float32)
+    m = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    grad = torch.from_numpy(g).to(u.DEV)
+    res = [torch.from_numpy(m).to(u.DEV) for _ in range(n)]
+    idx = [torch.empty(k, dtype=torch.int32, device=u.DEV) for _ in range(n)]
+    val = [torch.empty(k, device=u.DEV) for _ in range(n)]
+    stride = rt.encode_workspace_bytes(d, d, k)
+    ws = torch.empty(n * stride, dtype=torch.uint8, device=u.DEV).fill_(0xA5)
+    rt.encode_batch([grad] * n, res, d, k, list(range(n)), 6, idx, val, ws)
+    torch.cuda.synchronize()
+    for w in range(n):
+        assert rt.encode_stats(ws[w * stride:(w + 1) * stride])["path"] == 0
+        got = (idx[w].cpu().numpy().view(np.uint32), val[w].cpu().numpy(), res[w].cpu().numpy())
+        u.assert_encode_equal(got, oracle.encode(g, m, d, k, w, 6), f"member {w} of {n}")
+
+
 @pytest.mark.parametrize("d", [2_000_003, 3_000_001, 4_000_000])
 def test_short_vectors_sample_enough_for_a_heavy_tail(d):
     """Below 2^22 elements the estimate takes as many samples as put 160 into the top r: its
