@@ -736,7 +736,6 @@ struct Ring {
 // 4 KB pieces of each array.
 // ---------------------------------------------------------------------------
 constexpr u32 kFusedThreads = 768;            // at most; a launch takes 4 to 12 wavefronts, see fused_waves
-constexpr u32 kFusedWaves = kFusedThreads / kWave;
 // kRows: rows of 256 elements a wavefront adds, stores and looks at together; the
 // next ones are on their way meanwhile. One, but for short vectors, where a
 // wavefront has a single chunk: two.
@@ -2766,31 +2765,64 @@ __global__ void __launch_bounds__(kWalkThreads) k_emit(Batch B, Geom g, EncodeLa
 
 // ---------------------------------------------------------------------------
 // Calibration (diagnostics): a = g + m into the residual buffer and nothing
-// else, over the same chunks, with the same accesses and the same grid as
-// the fused kernel: the speed of the bare read-read-write stream.
+// else, over the same chunks, with the same accesses, in the same order and
+// on the same grid as the fused kernel: the speed of the bare read-read-write
+// stream.
 // ---------------------------------------------------------------------------
+template <int kRows>
 __global__ void __launch_bounds__(kFusedThreads)
 k_stream_add(const float *__restrict__ grad, float *__restrict__ residual, u64 d, u32 C, u32 W)
 {
+    constexpr u32 kGroup = kRows * kChunkQuantum;
     const u32 n_waves = blockDim.x / kWave, wave_stride = gridDim.x * n_waves;
-    for (u32 w = blockIdx.x * n_waves + threadIdx.x / kWave; w < W; w += wave_stride) {
-        const u64 c0 = (u64)w * C;
-        const u64 c1 = c0 + C < d ? c0 + C : d;
-        u64 base = c0;
-        constexpr int NR = 2;
-        for (; base + NR * kChunkQuantum <= c1; base += NR * kChunkQuantum) {
-            const f32x4 *g4 = reinterpret_cast<const f32x4 *>(grad + base) + lane_id();
-            f32x4 *m4 = reinterpret_cast<f32x4 *>(residual + base) + lane_id();
-            f32x4 gv[NR], mv[NR];
+    f32x4 gv[kRows], mv[kRows];
+    auto load = [&](u64 base) {
+        const f32x4u *gp = reinterpret_cast<const f32x4u *>(grad + base) + lane_id();
+        const f32x4u *mp = reinterpret_cast<const f32x4u *>(residual + base) + lane_id();
 #pragma unroll
-            for (int u = 0; u < NR; ++u) {
-                gv[u] = __builtin_nontemporal_load(g4 + u * kWave);
-                mv[u] = __builtin_nontemporal_load(m4 + u * kWave);
-            }
-#pragma unroll
-            for (int u = 0; u < NR; ++u) __builtin_nontemporal_store(gv[u] + mv[u], m4 + u * kWave);
+        for (int q = 0; q < kRows; ++q) {
+            gv[q] = __builtin_nontemporal_load(gp + q * kWave);
+            mv[q] = __builtin_nontemporal_load(mp + q * kWave);
         }
-        for (u64 i = base + lane_id(); i < c1; i += kWave) residual[i] = grad[i] + residual[i];
+    };
+    auto add = [&](u64 base, f32x4 (&a)[kRows]) {
+#pragma unroll
+        for (int q = 0; q < kRows; ++q) a[q] = gv[q] + mv[q];
+        f32x4u *mp = reinterpret_cast<f32x4u *>(residual + base) + lane_id();
+#pragma unroll
+        for (int q = 0; q < kRows; ++q) __builtin_nontemporal_store((f32x4u)a[q], mp + q * kWave);
+    };
+    const u32 w_full = (u32)(d / C);
+    u32 w = blockIdx.x * n_waves + threadIdx.x / kWave;
+    if (w < w_full) {
+        u64 c0 = (u64)w * C, base = c0;
+        load(base);
+        for (;;) {
+            f32x4 a[kRows];
+            add(base, a);
+            const bool last = base - c0 + kGroup >= C;
+            const u32 w_next = last ? w + wave_stride : w;
+            const u64 next = last ? (u64)w_next * C : base + kGroup;
+            if (w_next >= w_full) break;
+            load(next);
+            if (last) c0 = next;
+            w = w_next;
+            base = next;
+        }
+        while (w < w_full) w += wave_stride;
+    }
+    if (w == w_full && w < W) {
+        u64 base = (u64)w * C;
+        bool more = base + kGroup <= d;
+        if (more) load(base);
+        while (more) {
+            f32x4 a[kRows];
+            add(base, a);
+            base += kGroup;
+            more = base + kGroup <= d;
+            if (more) load(base);
+        }
+        for (u64 i = base + lane_id(); i < d; i += kWave) residual[i] = grad[i] + residual[i];
     }
 }
 
@@ -2919,7 +2951,7 @@ int fused_grid_limit(unsigned *out)
     if (g_fused_grid[dev] == 0) {
         int cus = 0, fit_t = 0, fit_f = 0;
         if (!allow_lds_claim(k_fused<false, kLongRows, true>) || !allow_lds_claim(k_fused<false, kShortRows, true>) ||
-            !allow_lds_claim(k_fused<true, kLongRows, true>))
+            !allow_lds_claim(k_fused<true, kLongRows, true>) || !allow_lds_claim(k_stream_add<kLongRows>))
             return RTOPK_EHIP;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_t, k_fused<false, kShortRows, true>,
@@ -3141,8 +3173,10 @@ extern "C" int rtopk_diag_stream_add(const float *grad, float *residual, uint64_
     const int rc = fused_grid_limit(&grid_limit);
     if (rc) return rc;
     const FusedShape fs = fused_shape(g.W, g.d, grid_limit);
-    const unsigned fgrid = fs.grid;
-    k_stream_add<<<fgrid, fs.threads, 0, (hipStream_t)stream_v>>>(grad, residual, d, g.C, g.W);
+    if (fs.is_short)
+        k_stream_add<kShortRows><<<fs.grid, fs.threads, 0, (hipStream_t)stream_v>>>(grad, residual, d, g.C, g.W);
+    else
+        k_stream_add<kLongRows><<<fs.grid, fs.threads, fs.lds, (hipStream_t)stream_v>>>(grad, residual, d, g.C, g.W);
     RTOPK_LAUNCH_CHECK();
     return RTOPK_OK;
 }

@@ -146,3 +146,18 @@ def test_short_vectors_sample_enough_for_a_heavy_tail(d):
     got = u.gpu_encode_once(g, m, r, k, 42, 1)
     u.assert_encode_equal(got, oracle.encode(g, m, r, k, 42, 1), f"d={d}")
     assert got[3]["path"] == 0 and got[3]["boundary_list_size"] <= 5 * r // 256, got[3]
+
+
+@pytest.mark.parametrize("d", [1, 1023, 1024, 1025, 100_003, 2049 * 1024, 2050 * 1024 - 1, 3500 * 1024 + 511,
+                               4097 * 1024 + 1, (1 << 25) + 1700])
+def test_the_calibration_add_covers_every_element_once(d):
+    import torch
+
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    gen = torch.Generator(device=u.DEV).manual_seed(d)
+    g, m = (torch.randn(d + 64, generator=gen, device=u.DEV) for _ in range(2))
+    want = m.clone()
+    want[:d] += g[:d]
+    rt.diag_stream_add(g[:d], m[:d])
+    assert torch.equal(m, want)
