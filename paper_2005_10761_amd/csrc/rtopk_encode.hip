@@ -15,7 +15,7 @@
 // dense in candidates is shared by all wavefronts.
 //
 // Pipeline:
-//   sample     a = g + m at 16384 jittered, stratified locations (4 elements
+//   sample     a = g + m at up to 16384 jittered, stratified locations (4 elements
 //              each); clears the control block
 //   estimate   one workgroup: from the sample's order statistics, a lower
 //              bound t_lo that the r-th largest magnitude exceeds and an upper
@@ -30,6 +30,7 @@
 //              a-priori window [K_lo, K_hi] around the k-th smallest of r
 //              uniform keys; an entry above the fine range whose key lies above
 //              the window will not be sent, the others -> S with what the key said
+//              (a short vector with few candidates: all of them -> S, unkeyed)
 //   pick       one workgroup (short vectors: every classify workgroup for itself):
 //              the group sums of all rows -> the group that
 //              holds the r-th largest magnitude; that group's bins of all
@@ -480,7 +481,8 @@ sample_body(const float *__restrict__ grad, const float *__restrict__ residual, 
 // that holds the sample of rank np - 4 sd - 8 (fewer than r entries lie
 // above it). Four of these doubled deviations are six to eight true ones; a
 // miss (at worst 3 in 100,000 per side, were the clusters to rise and fall
-// entirely together) costs a fifth of a millisecond, while six of them kept a
+// entirely together) costs 0.14 ms above the bracket and 0.35 ms below it at
+// 25.6 M elements, 0.4 and 3.2 ms at 2^28, while six of them kept a
 // fifth more candidates on every call (eight vectors of 25.6 M: classify 24.0
 // instead of 17.8 us, emit 20.7 instead of 17.0).
 // ---------------------------------------------------------------------------
@@ -972,7 +974,7 @@ struct Candidates {
 
 // One wavefront walks chunks u, u + U, u + 2U, ... as one flat sequence: lane
 // i first fetches the size of the i-th of them (there are at most
-// kUnitChunks), a prefix sum turns flat positions into (chunk, entry) pairs,
+// kUnitChunksMax), a prefix sum turns flat positions into (chunk, entry) pairs,
 // and every iteration of the walk hands 64 consecutive positions to the 64
 // lanes; the entries of one chunk stay in index order. f(valid, i, index,
 // pattern, first, p0) is called by all lanes in every iteration, so it may use
@@ -2353,7 +2355,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             if (g.take_all) {
                 have_k = true;
             } else if (n_mm <= m_cap && c_klo < g.k && g.k - c_klo <= n_mm) {
-                // (in LDS a thread's entries, four at most, stay in registers over the rounds)
+                // (in LDS a thread's entries, four or eight at most, stay in registers over the rounds)
                 constexpr u32 kM = kAllLds ? kInLds / kFinThreads : 1u;
                 u64 rm_k[kM];
                 u32 rm_i[kM];
@@ -2722,10 +2724,11 @@ __global__ void __launch_bounds__(kPickThreads) k_pick(Batch B, u32 n_rows, Geom
 }
 
 // kPick: every workgroup picks the deciding bin for itself, from the few histogram rows of a
-// short vector (128 at most: 32 KB of them per workgroup), and there is no k_pick: one call
-// of 200,003 elements 36.2 instead of 38.2 us, of 1 M 41.1 instead of 41.8. With 256
-// rows and a thousand workgroups
-// the rows would cost more than the kernel.
+// short vector (kPickRows at most: 32 KB of them per workgroup), and there is no k_pick. One
+// call, us, with k_pick / without: one vector of 200,003 elements 37.1 / 35.3, of 2^20 (128 rows)
+// 42.2 / 41.5, of 2^20 + 1 41.5 / 41.8, of 1.6 M (196 rows) 47.1 / 48.1, of 2^21 (256) 44.1 /
+// 45.4; two of 2^20 43.9 / 43.4, of 1.6 M 49.5 / 52.1; four of 2^20 51.6 / 51.6, of 2^21 64.7 /
+// 75.0; eight of 2^20 67.1 / 71.3. (Three to eight members gain up to 64 rows; they keep k_pick.)
 template <bool kPick>
 __global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, u32 n_rows, Geom g, EncodeLayout L)
 {
@@ -2874,10 +2877,11 @@ struct StageScope {
 };
 
 // Workgroups of the streaming kernel: one per compute unit (all start
-// together and share the chunks evenly, so none waits for a slot). Eight
-// wavefronts per compute unit with 8 x 16 bytes in flight per lane saturate
-// HBM; two or three workgroups per unit stream no faster, leave three times
-// the histogram rows to add up and less room for kernels of other streams.
+// together and share the chunks evenly, so none waits for a slot) of 4 to 12
+// wavefronts (fused_shape), each with one row of 256 elements of both arrays on
+// its way, two rows in a short vector. Two or three workgroups per unit stream
+// no faster, leave three times the histogram rows to add up and less room for
+// kernels of other streams.
 // The count of units is looked up at the first call on the device.
 constexpr int kMaxDevices = 64;
 constexpr int kFusedBlocksPerCU = 1;
