@@ -209,8 +209,8 @@ struct EncodeCtl {
     Bins bins;
     u32 n_samples;
     // written by k_pick
-    u32 dense;          // the estimate missed, S holds fewer than r entries: walk the vector itself
-    u32 partial;        // the deciding bin lies above the bracket, where S only holds what may be sent
+    u32 mode;           // bit 0: the estimate missed, S holds fewer than r entries: walk the vector itself;
+                        // bit 1: the deciding bin lies above the bracket, where S only holds what may be sent
     u32 bd_lo, bd_hi;   // pattern range of the deciding bin
     u32 bd_bits;        // bit width of bd_hi - bd_lo
     u64 c_def;          // entries above bd_hi
@@ -1225,13 +1225,12 @@ constexpr u32 kPickRows = 128, kPickMembers = 2;   // up to here the classify wo
 
 // the deciding bin: its pattern range and the entries above it
 struct Picked {
-    u32 dense, partial; // see EncodeCtl
+    u32 mode;           // see EncodeCtl
     u32 bd_lo, bd_hi;
     u64 c_def;
     __device__ __forceinline__ void store(EncodeCtl *ctl) const
     {
-        ctl->dense = dense;
-        ctl->partial = partial;
+        ctl->mode = mode;
         ctl->bd_lo = bd_lo;
         ctl->bd_hi = bd_hi;
         ctl->bd_bits = bd_hi > bd_lo ? 32u - (u32)__clz(bd_hi - bd_lo) : 1u;
@@ -1350,7 +1349,7 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
         // above the bracket S only holds what may be sent (everything when k == r or nothing was
         // keyed): no short list can decide there
         const bool partial = !dense && bin_s >= bins.nfine && g.take_all == 0u && g.keyed != 0u;
-        picked = Picked{dense ? 1u : 0u, partial ? 1u : 0u, bd_lo, bd_hi, before_s};
+        picked = Picked{(dense ? 1u : 0u) | (partial ? 2u : 0u), bd_lo, bd_hi, before_s};
     }
     lds_barrier();
     return picked;
@@ -1365,6 +1364,7 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
 // short list cannot hold it, but the last member is then simply the entry of
 // a known rank in index order, which those counts locate.
 // ---------------------------------------------------------------------------
+template <bool kKeyed>      // S holds keyed entries (what is read from the vector itself never is)
 __device__ __forceinline__ void
 classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const float *__restrict__ a,
            const u32 *__restrict__ seg_count, const uint2 *__restrict__ s_ent,
@@ -1374,14 +1374,13 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
            u32 *__restrict__ b_mag, u32 *__restrict__ b_idx)
 {
     __shared__ u32 cnt_m, cnt_b, cnt_sure, bmin_s, bmax_s;
-    __shared__ u32 list_m[kListCap];
-    constexpr u32 kStored = 0xFFFFFFFFu;      // (never an index) the entry of M is already in its slot
+    __shared__ u32 list_m[kKeyed ? kListCap : 1u];
     __shared__ u32 per_chunk[kWalkWaves][kUnitChunksMax];
     __shared__ u32 per_chunk_b[kWalkWaves][kUnitChunksMax];
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
     const u32 wave = threadIdx.x / kWave, lane = lane_id();
     const u32 u = blockIdx.x * kWalkWaves + wave;
-    const bool undecided = (now ? now->dense | now->partial : ctl->dense | ctl->partial) != 0u;
+    const bool undecided = (now ? now->mode : ctl->mode) != 0u;
     const u32 bd_lo = now ? now->bd_lo : ctl->bd_lo, bd_hi = now ? now->bd_hi : ctl->bd_hi;
     if (undecided) {
         if (threadIdx.x == 0) {
@@ -1407,9 +1406,10 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
         const bool in_bin = valid && !member && m >= bd_lo;
         if (member) {
             u32 says = key >> 30;
-            const bool unkeyed = says == kKeyUnknown;
             u64 k64 = 0;
-            if (unkeyed) {
+            if (kKeyed) {
+                if (says == kKeyUnknown) says = key_word(idx, g, seed) >> 30;
+            } else {
                 if (g.take_all == 0u) k64 = sample_key(idx, seed);
                 says = g.take_all != 0u || k64 < g.K_lo ? kKeyBelow : k64 > g.K_hi ? kKeyAbove : kKeyInside;
             }
@@ -1417,8 +1417,8 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
             if (says == kKeyInside) {
                 const u32 p = atomicAdd(&cnt_m, 1u);
                 if (p < kListCap) {
-                    list_m[p] = unkeyed ? kStored : idx;
-                    if (unkeyed) { m_key[slot(p)] = k64; m_idx[slot(p)] = idx; }
+                    if (kKeyed) list_m[p] = idx;
+                    else { m_key[slot(p)] = k64; m_idx[slot(p)] = idx; }
                 }
             }
             if (sure) atomicAdd(&per_chunk[wave][i], 1u);
@@ -1460,14 +1460,12 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
     mine = wave_sum(mine);
     if (lane == 0 && mine) atomicAdd(&cnt_sure, mine);
     __syncthreads();
-    // the keys of the workgroup's entries of M that came without one, all at once
+    // the keys of the workgroup's entries of M, all at once
     static_assert(kListCap <= kWalkThreads, "one thread per list slot");
-    if (threadIdx.x < cnt_m && threadIdx.x < kListCap) {
+    if (kKeyed && threadIdx.x < cnt_m && threadIdx.x < kListCap) {
         const u32 idx = list_m[threadIdx.x];
-        if (idx != kStored) {
-            m_key[slot(threadIdx.x)] = sample_key(idx, seed);
-            m_idx[slot(threadIdx.x)] = idx;
-        }
+        m_key[slot(threadIdx.x)] = sample_key(idx, seed);
+        m_idx[slot(threadIdx.x)] = idx;
     }
     if (threadIdx.x == 0) {
         blk_sure[blockIdx.x] = cnt_sure;
@@ -1816,14 +1814,15 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
 
     const u32 tid = threadIdx.x;
     const u32 wave = tid / kWave, lane = lane_id();
-    const bool dense = ctl->dense != 0u, partial = ctl->partial != 0u;
+    const u32 mode = ctl->mode;
+    const bool dense = (mode & 1u) != 0u, partial = (mode & 2u) != 0u;
     const u32 bd_lo = ctl->bd_lo, bd_hi = ctl->bd_hi, bd_bits = ctl->bd_bits;
     const u64 c_def = ctl->c_def;
     Candidates cand{seg_count, s_ent, a, g.d, g.C, g.U, g.UC, g.cap, dense};
     // Whether what the exact selections walk holds every member of the top-r set. Otherwise (S as
     // a keying stream left it) the members above the bracket whose key lies above the window are
     // missing.
-    bool whole = dense || g.take_all != 0u || (g.keyed == 0u && g.all_members == 0u);
+    auto holds_all = [&] { return dense || g.take_all != 0u || g.keyed == 0u || g.all_members != 0u; };
     // Fills the slices of chunks first, first + step, ... again, from the vector and with every
     // element at or above the deciding bin: one pass over the vector (four rows of a chunk in
     // flight), after which S will do for all the passes of an exact selection and for emit. The
@@ -1984,7 +1983,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         Wide w{wide_ws, gridDim.x, 1u, 0u, true, g.force_timeout != 0u ? 0u : kWideSpinLimit};
         // r == d: S only holds the coordinates whose key the window admits, and every
         // coordinate is a member: the vector itself is walked, here and by the emit kernel
-        if (g.all_members) { cand.dense = true; whole = true; }
+        if (g.all_members) cand.dense = true;
+        bool whole = holds_all();
         const bool vec16 = (reinterpret_cast<uintptr_t>(a) & 15u) == 0;
         const u32 n_waves = gridDim.x * kFinWaves;
         // f(valid, index, pattern) for every entry of this workgroup's chunks, all lanes
@@ -2405,9 +2405,9 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     if (g.all_members && !have_k) {
         // r == d and a short list overflowed or the key window missed: as above
         cand.dense = true;
-        whole = true;
         if (tid == 0) ctl->emit_dense = 1u;
     }
+    bool whole = holds_all();
     auto complete_alone = [&] {
         __syncthreads();
         complete_slices(wave, kFinWaves);
@@ -2576,7 +2576,7 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
     if (u >= g.U) return;
     const u32 lane = lane_id();
     const Candidates cand{seg_count, s_ent, residual, g.d, g.C, g.U, g.UC, g.cap,
-                          (ctl->dense | ctl->emit_dense) != 0u};
+                          ((ctl->mode & 1u) | ctl->emit_dense) != 0u};
     const UnitWalk walk(cand, u < g.U ? u : g.W, g.U, g.W);
     const u32 my_chunk = u + lane * g.U;
     const u32 my_base = (lane < g.UC && my_chunk < g.W) ? chunk_base[my_chunk] : 0u;
@@ -2729,7 +2729,7 @@ __global__ void __launch_bounds__(kPickThreads) k_pick(Batch B, u32 n_rows, Geom
 // 42.2 / 41.5, of 2^20 + 1 41.5 / 41.8, of 1.6 M (196 rows) 47.1 / 48.1, of 2^21 (256) 44.1 /
 // 45.4; two of 2^20 43.9 / 43.4, of 1.6 M 49.5 / 52.1; four of 2^20 51.6 / 51.6, of 2^21 64.7 /
 // 75.0; eight of 2^20 67.1 / 71.3. (Three to eight members gain up to 64 rows; they keep k_pick.)
-template <bool kPick>
+template <bool kPick, bool kKeyed>
 __global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, u32 n_rows, Geom g, EncodeLayout L)
 {
     const Member m(B);
@@ -2739,7 +2739,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, u32 n_rows, 
         p = pick_body<kWalkThreads>(m.at<u32>(L.partials), m.at<u32>(L.group_sums), n_rows, g, ctl);
         if (blockIdx.x == 0 && threadIdx.x == 0) p.store(ctl);
     }
-    classify_body(g, m.seed, ctl, kPick ? &p : nullptr, m.residual, m.at<u32>(L.seg_count),
+    classify_body<kKeyed>(g, m.seed, ctl, kPick ? &p : nullptr, m.residual, m.at<u32>(L.seg_count),
                   m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt), m.at<u32>(L.bd_cnt),
                   m.at<u32>(L.blk_sure), m.at<u32>(L.n_m), m.at<u32>(L.n_b), m.at<u32>(L.blk_bmin),
                   m.at<u32>(L.blk_bmax), m.at<u64>(L.m_key), m.at<u32>(L.m_idx),
@@ -3107,10 +3107,16 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
                 k_pick<<<dim3(1, 1, nb), kPickThreads, 0, stream>>>(B, fgrid, gg, L);
                 RTOPK_LAUNCH_CHECK();
             }
-            if (!g.all_members && few_rows)
-                k_classify<true><<<dim3(gg.G3, 1, nb), kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
+            const dim3 cg(gg.G3, 1, nb);
+            const bool picks = !g.all_members && few_rows;
+            if (picks && gg.keyed)
+                k_classify<true, true><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
+            else if (picks)
+                k_classify<true, false><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
+            else if (gg.keyed)
+                k_classify<false, true><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
             else
-                k_classify<false><<<dim3(gg.G3, 1, nb), kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
+                k_classify<false, false><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
             RTOPK_LAUNCH_CHECK();
         }
         {
@@ -3206,7 +3212,7 @@ extern "C" int rtopk_encode_stats(const void *workspace, void *stream_v,
         for (u32 s2 = 0; s2 < c.W; ++s2) superset += counts[chunk_slot(s2, c.U, c.UC)];
     }
     host_out->error_flags = c.err;
-    host_out->path = c.path | ((c.dense | c.emit_dense) != 0u ? 2u : 0u);
+    host_out->path = c.path | (((c.mode & 1u) | c.emit_dense) != 0u ? 2u : 0u);
     host_out->threshold_bits = c.T;
     host_out->boundary_list_size = c.n_b;
     host_out->count_greater = c.count_greater;

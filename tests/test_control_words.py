@@ -27,5 +27,5 @@ def test_finalize_reads_no_control_word_that_it_writes():
     fields = re.findall(r"ctl->(\w+)(\s*=(?!=))?", body)
     written = {name for name, assigned in fields if assigned}
     read = {name for name, assigned in fields if not assigned}
-    assert {"dense", "overflow", "bd_lo", "c_def"} <= read and {"T", "K_star", "err"} <= written
+    assert {"mode", "overflow", "bd_lo", "c_def"} <= read and {"T", "K_star", "err"} <= written
     assert not read & written, read & written
