@@ -116,10 +116,17 @@ constexpr u32 kUnitChunks = kTargetChunks / kMaxUnits;   // chunks one of them w
 // entry: half as many wavefronts then walk twice as many chunks each. With fewer
 // vectors the longest wavefront decides (the one that holds a chunk of a hot
 // layer). classify / emit with 4096 and 2048 wavefronts per vector, us: eight of
-// 25.6 M elements 24.8 / 21.7 and 19.8 / 17.8; five of 11.2 M 30.2 / 28.7 and
-// 32.5 / 33.9; four of 2^28 105 / 501 and 102 / 524.
+// 25.6 M elements 24.8 / 21.7 and 19.8 / 17.8; five of 11.2 M, r = 5%, 30.2 / 28.7 and
+// 32.5 / 33.9; four of 2^28 105 / 501 and 102 / 524. Where the wavefronts are short (chunks of
+// kMinChunk) and their chunks sparse, four members are many: five of 4.3 M, r = 0.4%, 12.0 / 9.3
+// and 8.5 / 6.7. Whole calls of four to six members, 2048 against 4096 wavefronts: r = 0.5 to 2%
+// of 3.4 to 4.3 M 0-9% faster (one layered vector of 4.15 M 1-7% slower), of 11.2 M 2-4%, of 25.6 M
+// 0-2%; r = 5% 0-5% slower from 6 M on; 2.2 M and 3.1 M (hardly more chunks than wavefronts, some of
+// which walk two) 11% slower to 5% faster, 50 M 0-3% slower.
 constexpr u32 kBatchUnits = 2048;
-constexpr u32 kBatchMembers = 7;              // ... from this many members per launch on
+constexpr u32 kBatchMembers = 7;              // ... from this many members per launch on,
+constexpr u32 kSparseMembers = 4;             // ... or this many with few candidates and
+constexpr u32 kSparseChunks = 3328;           // at least this many chunks (set_units)
 constexpr u32 kUnitChunksMax = kTargetChunks / kBatchUnits;
 constexpr u32 kWalkThreads = 256;             // fused / classify / emit workgroups: 4 wavefronts
 constexpr u32 kWalkWaves = kWalkThreads / kWave;
@@ -332,9 +339,11 @@ static Geom make_geom(u64 d, u64 r, u64 k)
 // the walking kernels' share-out for a launch that serves nb vectors (see kBatchUnits)
 static void set_units(Geom &g, unsigned nb)
 {
-    const u32 units = nb >= kBatchMembers ? kBatchUnits : kMaxUnits;
+    const bool sparse = g.C == kMinChunk && g.W >= kSparseChunks && g.r * 32 <= g.d;
+    const bool batch = nb >= kBatchMembers || (nb >= kSparseMembers && sparse);
+    const u32 units = batch ? kBatchUnits : kMaxUnits;
     g.U = g.W < units ? g.W : units;
-    g.UC = nb >= kBatchMembers ? kUnitChunksMax : kUnitChunks;
+    g.UC = batch ? kUnitChunksMax : kUnitChunks;
     g.G3 = (g.U + kWalkWaves - 1) / kWalkWaves;
 }
 

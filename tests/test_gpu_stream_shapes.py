@@ -131,6 +131,36 @@ def test_short_random_k_batches_on_both_sides_of_keying(n):
         u.assert_encode_equal(got, oracle.encode(g, m, d, k, w, 6), f"member {w} of {n}")
 
 
+@pytest.mark.parametrize("n,d,r", [(4, 2303 * 1024, 9000), (4, 2303 * 1024 + 1, 9000), (3, 3072 * 1024, 9000),
+                                   (3, 3071 * 1024, 9000), (4, 3327 * 1024, 20000), (4, 3327 * 1024 + 1, 20000),
+                                   (4, 4500 * 1024, 4500 * 32), (4, 4500 * 1024, 4500 * 32 + 1), (6, 4500 * 1024, 9000)])
+def test_batches_around_the_changes_of_shape_and_share_out(n, d, r):
+    """Chunks in all, and chunks, candidates and members per launch, on both sides of
+    where the streaming kernel changes its shape and the walking kernels their share-out."""
+    import torch
+
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    k = r // 7
+    rng = np.random.default_rng(d + n)
+    gs = [(rng.standard_normal(d) * 10.0 ** rng.uniform(-3, 0, d)).astype(np.float32) for _ in range(2)]
+    m = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    dev = [torch.from_numpy(g).to(u.DEV) for g in gs]
+    res = [torch.from_numpy(m).to(u.DEV) for _ in range(n)]
+    idx = [torch.empty(k, dtype=torch.int32, device=u.DEV) for _ in range(n)]
+    val = [torch.empty(k, device=u.DEV) for _ in range(n)]
+    stride = rt.encode_workspace_bytes(d, r, k)
+    ws = torch.empty(n * stride, dtype=torch.uint8, device=u.DEV).fill_(0xA5)
+    rt.encode_batch([dev[w % 2] for w in range(n)], res, r, k, list(range(n)), 3, idx, val, ws)
+    torch.cuda.synchronize()
+    for w in range(n):
+        st = rt.encode_stats(ws[w * stride:(w + 1) * stride])
+        assert st["path"] == 0 and st["error_flags"] == 0, (w, st)
+        got = (idx[w].cpu().numpy().view(np.uint32), val[w].cpu().numpy(), res[w].cpu().numpy())
+        if w in (0, n - 1):
+            u.assert_encode_equal(got, oracle.encode(gs[w % 2], m, r, k, w, 3), f"member {w} of {n}, d={d} r={r}")
+
+
 @pytest.mark.parametrize("d", [2_000_003, 3_000_001, 4_000_000])
 def test_short_vectors_sample_enough_for_a_heavy_tail(d):
     """Below 2^22 elements the estimate takes as many samples as put 160 into the top r: its
