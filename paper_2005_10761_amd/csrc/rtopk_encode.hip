@@ -2926,11 +2926,14 @@ bool allow_lds_claim(K kernel)
 // a third full or less costs more than the shape of the short vectors with two chunks per
 // wavefront: one vector of 3.5 M 53.9 / 50.4 (r = d: 38.5 / 33.6), of 4 M 52.7 / 51.8, sixteen
 // of 4 M 210.6 / 202.4, four of 4 M 88.9 / 91.1 (none of them keyed); just above 3072 chunks
-// 47.3 / 49.3.
+// 47.3 / 49.3. A batch gains by that shape below 3072 chunks too, as its members run side by
+// side: from kShortBatch chunks in all. k_fused of four vectors of 2.4 M 28.2 / 23.5; calls of
+// sixteen of 2.2 M 7% faster, of four of 2.6 M 2-5%, of three 0-4% slower.
+constexpr u32 kShortBatch = 9216;
 struct FusedShape { unsigned threads, grid, lds; bool is_short; };
-FusedShape fused_shape(u32 W, u64 d, unsigned grid_limit)
+FusedShape fused_shape(u32 W, u64 d, unsigned nb, unsigned grid_limit)
 {
-    const bool is_short = W <= 2048u || (W > 3072u && W <= 4096u);
+    const bool is_short = W <= 2048u || (W > 3072u && W <= 4096u) || (W <= 3072u && nb * W >= kShortBatch);
     unsigned waves = W <= 512u ? 4u : is_short ? 8u : d < (1ull << 24) ? 12u : d <= (1ull << 26) ? 10u : 8u;
     unsigned grid = (W + waves - 1) / waves;
     return FusedShape{waves * (unsigned)kWave, grid > grid_limit ? grid_limit : grid,
@@ -3044,9 +3047,6 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
     unsigned grid_limit = 0;
     const int rc2 = fused_grid_limit(&grid_limit);
     if (rc2) return rc2;
-    const FusedShape fs = fused_shape(g.W, g.d, grid_limit);
-    const unsigned fgrid = fs.grid;
-
     const TraceRequest trace = g_trace;
     g_trace = TraceRequest{};
     StageScope whole(trace, RTOPK_STAGE_ALL, stream);
@@ -3055,6 +3055,8 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         const unsigned nb = n - first < kMaxBatch ? n - first : kMaxBatch;
         Geom gg = g;                    // this launch group's share-out of the walking kernels
         set_units(gg, nb);
+        const FusedShape fs = fused_shape(g.W, g.d, nb, grid_limit);
+        const unsigned fgrid = fs.grid;
         gg.keyed = keys_in_stream(gg, fs.is_short, nb) ? 1u : 0u;
         Batch B{};
         for (unsigned i = 0; i < nb; ++i) {
@@ -3191,7 +3193,7 @@ extern "C" int rtopk_diag_stream_add(const float *grad, float *residual, uint64_
     unsigned grid_limit = 0;
     const int rc = fused_grid_limit(&grid_limit);
     if (rc) return rc;
-    const FusedShape fs = fused_shape(g.W, g.d, grid_limit);
+    const FusedShape fs = fused_shape(g.W, g.d, 1u, grid_limit);
     if (fs.is_short)
         k_stream_add<kShortRows><<<fs.grid, fs.threads, 0, (hipStream_t)stream_v>>>(grad, residual, d, g.C, g.W);
     else
