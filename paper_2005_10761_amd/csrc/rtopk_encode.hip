@@ -3,12 +3,14 @@
 // gfx950 kernels that stream the gradient and the residual exactly once
 // (12d bytes). All cross-kernel state lives in the caller's workspace.
 //
-// The vector is cut into W short contiguous chunks, and every chunk owns a
-// slice of the candidate buffer S an eighth as long as the chunk (one byte of
-// workspace per element). The wavefront that streams a chunk appends the
-// entries it keeps to the chunk's slice in index order and finally stores how
-// many it kept. S is therefore ordered by index without any cross-workgroup
-// scan, ticket or fence. A chunk that would keep more than its slice holds is
+// The vector is cut into W short contiguous chunks. Every wavefront of the
+// streaming kernel owns a piece of the candidate buffer S an eighth as long as the
+// chunks it streams (one byte of workspace per element). It appends the entries
+// it keeps, chunk after chunk and in index order, and stores for each chunk where
+// its slice starts and how many entries it holds. A chunk's entries are therefore
+// in index order without any cross-workgroup scan, ticket or fence, and a chunk that is
+// dense in candidates takes the room that the wavefront's others leave. A chunk
+// that would keep more than there is room for is
 // marked; the later kernels read it from the residual buffer, which holds a by
 // then. Later kernels walk S chunk by chunk; each of their
 // wavefronts takes every U-th chunk, so that a region of the vector that is
@@ -138,7 +140,8 @@ constexpr u32 kMaxWalkBlocks = kMaxUnits / kWalkWaves;
 // separate cache lines.
 __host__ __device__ inline u32 chunk_slot(u32 s, u32 U, u32 UC) { return (s % U) * UC + s / U; }
 constexpr u32 kListCap = 128;                 // short-list slots per classify workgroup
-constexpr u32 kSliceDiv = 8;                  // a chunk's slice of S holds a kSliceDiv-th of the chunk
+constexpr u32 kSliceDiv = 8;                  // S holds a kSliceDiv-th as many entries as there are elements
+constexpr u32 kSliceFull = 1u << 31;          // (in a chunk's count) the chunk kept more than its slice could hold
 
 // An entry of S: the binary32 pattern, and one word with the element's place in
 // its chunk (18 bits), what its sampling key says (2 bits) and, for a key inside
@@ -244,8 +247,7 @@ static_assert(offsetof(EncodeCtl, err) == 0, "the error flags lead the control b
 struct Geom {
     u64 d, r, k;
     u32 C;              // elements per chunk (a power of two, at least 1024)
-    u32 cap;            // entries a chunk's slice of S holds (C / kSliceDiv); a chunk that keeps
-                        // more is read from the vector itself by the later kernels
+    u32 cap;            // entries of S per chunk (C / kSliceDiv)
     u32 W;              // chunks
     u32 U;              // wavefronts of classify / emit; wavefront u walks chunks u, u + U, ...
     u32 UC;             // ... at most this many of them (W <= U * UC)
@@ -267,7 +269,7 @@ struct Geom {
 
 struct EncodeLayout {
     u64 ctl, wide, zero_bytes, partials, group_sums;
-    u64 samples, seg_count, win_cnt, bd_cnt, chunk_base, blk_sure, n_m, n_b, blk_bmin, blk_bmax;
+    u64 samples, seg, win_cnt, bd_cnt, chunk_base, blk_sure, n_m, n_b, blk_bmin, blk_bmax;
     u64 m_key, m_idx, b_mag, b_idx;
     u64 dm_key, dm_idx, db_key, db_idx;
     u64 s_ent;
@@ -358,7 +360,7 @@ static EncodeLayout make_layout(const Geom &g)
     L.partials = take((u64)kMaxFusedBlocks * kMaxBins * 4);
     L.group_sums = take((u64)kMaxFusedBlocks * kMaxGroups * 4);
     L.samples = take((u64)kSampleLoc * 16);
-    L.seg_count = take((u64)kTargetChunks * 4);      // fixed size: its offset depends on nothing
+    L.seg = take((u64)kTargetChunks * 8);            // fixed size: its offset depends on nothing
     L.win_cnt = take((u64)kTargetChunks * 4);
     L.bd_cnt = take((u64)kTargetChunks * 4);
     L.chunk_base = take((u64)kTargetChunks * 4);
@@ -679,14 +681,15 @@ constexpr u32 kRing = 512;                    // a power of two >= 63 waiting + 
 struct Ring {
     uint2 *buf;         // kRing entries owned by this wavefront: (place in the chunk, pattern)
     u32 head, pending;  // (head is reduced where it is used)
-    u32 out;            // entries of the chunk's slice so far (above its capacity: it overflowed)
+    u32 room;           // entries the chunk's slice may hold
+    u32 out;            // entries of it so far (above room: it overflowed)
 
-    __device__ __forceinline__ void append(const u32 (&bits)[4], const bool (&hit)[4], u32 place0, u32 cap)
+    __device__ __forceinline__ void append(const u32 (&bits)[4], const bool (&hit)[4], u32 place0)
     {
         const u64 b0 = __ballot(hit[0]), b1 = __ballot(hit[1]), b2 = __ballot(hit[2]),
                   b3 = __ballot(hit[3]);
         if ((b0 | b1 | b2 | b3) == 0ull) return;
-        if (out > cap) return;        // the slice overflowed: the chunk will be read from the vector itself
+        if (out > room) return;       // the slice overflowed: the chunk will be read from the vector itself
         const u64 below = lanes_below();
         const u32 at = head + pending;
         u32 p = at + popc64(b0 & below) + popc64(b1 & below) + popc64(b2 & below) + popc64(b3 & below);
@@ -696,7 +699,7 @@ struct Ring {
         pending += popc64(b0) + popc64(b1) + popc64(b2) + popc64(b3);
     }
     // straight to the slice, the keys left to be computed
-    __device__ __forceinline__ void append_unkeyed(const u32 (&bits)[4], const bool (&hit)[4], u32 place0, u32 cap,
+    __device__ __forceinline__ void append_unkeyed(const u32 (&bits)[4], const bool (&hit)[4], u32 place0,
                                                    uint2 *__restrict__ my_ent)
     {
         const u64 b0 = __ballot(hit[0]), b1 = __ballot(hit[1]), b2 = __ballot(hit[2]),
@@ -707,7 +710,7 @@ struct Ring {
 #pragma unroll
         for (u32 e = 0; e < 4; ++e)
             if (hit[e]) {
-                if (p < cap) my_ent[p] = make_uint2((kKeyUnknown << 30) | (place0 + 4u * lane_id() + e), bits[e]);
+                if (p < room) my_ent[p] = make_uint2((kKeyUnknown << 30) | (place0 + 4u * lane_id() + e), bits[e]);
                 ++p;
             }
         out += popc64(b0) + popc64(b1) + popc64(b2) + popc64(b3);
@@ -732,7 +735,7 @@ struct Ring {
         wave_lds_fence();
         const u64 mask = __ballot(stays);
         const u32 pos = out + popc64(mask & lanes_below());
-        if (stays && pos < g.cap) my_ent[pos] = e;
+        if (stays && pos < room) my_ent[pos] = e;
         head += n;
         pending -= n;
         out += popc64(mask);
@@ -765,7 +768,7 @@ template <bool kAll, int kRows, bool kKeyed>
 __device__ __forceinline__ void
 fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g, PhiloxSeed seed,
         EncodeCtl *__restrict__ ctl, u32 zero_words, u32 *__restrict__ partials,
-        u32 *__restrict__ group_sums, u32 *__restrict__ seg_count, uint2 *__restrict__ s_ent)
+        u32 *__restrict__ group_sums, uint2 *__restrict__ seg, uint2 *__restrict__ s_ent)
 {
     __shared__ u32 h[kAll ? 1 : kMaxBins];
     extern __shared__ uint2 ring_s[];           // kRing entries per wavefront (and what the launch claims beyond), none if not keyed
@@ -785,7 +788,7 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
 
     const u32 n_waves = blockDim.x / kWave, wave_stride = gridDim.x * n_waves;
     u32 n_above = 0;        // this wavefront's candidates above the linear bins
-    Ring ring{ring_s + threadIdx.x / kWave * kRing, 0u, 0u, 0u};
+    Ring ring{ring_s + threadIdx.x / kWave * kRing, 0u, 0u, 0u, 0u};
     const u32 bracket_hi = kAll ? 0x7FFFFFFFu : bins.fine_hi;
     u64 c0 = 0;             // the current chunk
     uint2 *my_ent = s_ent;
@@ -809,20 +812,40 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
             }
         }
         if (kKeyed) {
-            ring.append(bits, hit, place, g.cap);
+            ring.append(bits, hit, place);
             while (ring.pending >= (u32)kWave) ring.take(c0, g, seed, bracket_hi, my_ent);
         } else {
-            ring.append_unkeyed(bits, hit, place, g.cap, my_ent);
+            ring.append_unkeyed(bits, hit, place, my_ent);
         }
     };
+    // This wavefront's part of S: the chunks it streams (w_first, w_first + wave_stride, ...) times
+    // g.cap entries. A chunk may take what the ones before it have left and half of what the
+    // ones after it are due (an ordinary chunk needs less than half): a layer that holds much of
+    // the top r is dealt out over many wavefronts, a chunk or two each. With a slice of fixed size per
+    // chunk a tenth of the chunks of layered vectors overflowed and were read again by
+    // both walking kernels: classify / emit of five vectors of 11.2 M elements, r = 5%, 29.1 / 27.5
+    // us, with shared room 16.1 / 17.6; of four of 66 M with a twentieth of the rows
+    // touched 40.0 / 33.0 and 21.0 / 22.1 (the stream, which now stores those entries, 535 and 542).
+    const u32 w_first = blockIdx.x * n_waves + threadIdx.x / kWave;
+    u32 later, at;          // chunks still to come; where in S the next slice starts
+    {
+        const u32 each = g.W / wave_stride, over = g.W % wave_stride;
+        later = each + (w_first < over ? 1u : 0u);
+        at = (w_first * each + (w_first < over ? w_first : over)) * g.cap;
+    }
+    const u32 s_end = at + later * g.cap;
     auto open_chunk = [&](u32 w) {
         c0 = (u64)w * g.C;
-        my_ent = s_ent + (u64)w * g.cap;
+        --later;
+        my_ent = s_ent + at;
+        ring.room = s_end - at - later * (g.cap / 2u);
         ring.out = 0u;
     };
     auto close_chunk = [&](u32 w) {
         if (kKeyed && ring.pending != 0u) ring.take(c0, g, seed, bracket_hi, my_ent);
-        if (lane_id() == 0) seg_count[chunk_slot(w, g.U, g.UC)] = ring.out;
+        const bool full = ring.out > ring.room;
+        if (lane_id() == 0) seg[chunk_slot(w, g.U, g.UC)] = make_uint2(ring.out | (full ? kSliceFull : 0u), at);
+        if (!full) at += ring.out;
     };
     const bool all_valid[4] = {true, true, true, true};
     // Groups of kRows rows. Every element is read once and written once: both
@@ -853,7 +876,6 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
     };
     // The chunks that are whole: the next group is on its way while this one's
     // candidates are looked for.
-    const u32 w_first = blockIdx.x * n_waves + threadIdx.x / kWave;
     const u32 w_full = (u32)(g.d / g.C);
     u32 w = w_first;
     if (w < w_full) {
@@ -873,7 +895,7 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
             for (int u = 0; u < kRows; ++u) keep(bits[u], all_valid, place + u * kChunkQuantum);
             if (last) {
                 close_chunk(w);
-                open_chunk(w_next);
+                if (more) open_chunk(w_next);
             }
             if (!more) break;
             w = w_next;
@@ -941,11 +963,11 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
 // the fused kernel filled; in dense mode it is the chunk of a itself.
 // ---------------------------------------------------------------------------
 struct Candidates {
-    const u32 *__restrict__ seg_count;
+    const uint2 *__restrict__ seg;          // per chunk: entries in its slice of S (kSliceFull: too many), the slice's start
     const uint2 *__restrict__ s_ent;
     const float *__restrict__ a;
     u64 d;
-    u32 C, U, UC, cap;
+    u32 C, U, UC;
     bool dense;         // every chunk is read from the vector (the estimate kept too little; r == d
                         // and the key window missed)
 
@@ -954,21 +976,23 @@ struct Candidates {
         const u64 c0 = (u64)s * C;
         return (u32)(c0 + C < d ? C : d - c0);
     }
-    // entries of chunk s, and whether they are the chunk's elements themselves:
+    // entries of chunk s, where in S they start, and whether they are the chunk's elements themselves:
     // a chunk that kept more than its slice holds is read from the vector (all
     // its elements then count as entries; what lies below the candidates'
     // lower bound is below every threshold the later kernels compare with)
-    __device__ __forceinline__ u32 count(u32 s, bool *from_vector) const
+    __device__ __forceinline__ u32 count(u32 s, u32 *start, bool *from_vector) const
     {
-        const u32 kept = dense ? 0u : seg_count[chunk_slot(s, U, UC)];
-        *from_vector = dense || kept > cap;
-        return *from_vector ? length(s) : kept;
+        const uint2 kept = dense ? make_uint2(kSliceFull, 0u) : seg[chunk_slot(s, U, UC)];
+        *start = kept.y;
+        *from_vector = (kept.x & kSliceFull) != 0u;
+        return *from_vector ? length(s) : kept.x;
     }
+    // entry j of chunk s, whose slice starts at `start`
     // (key: what the streaming kernel left of the sampling key, kKeyUnknown << 30 if nothing)
-    __device__ __forceinline__ void entry(u32 s, u32 j, bool from_vector, u32 *idx, u32 *bits, u32 *key) const
+    __device__ __forceinline__ void entry(u32 s, u32 start, u32 j, bool from_vector, u32 *idx, u32 *bits, u32 *key) const
     {
         if (!from_vector) {
-            const uint2 e = s_ent[(u64)s * cap + j];
+            const uint2 e = s_ent[start + j];
             *idx = s * C + (e.x & kPlaceMask);
             *bits = e.y;
             *key = e.x;
@@ -996,6 +1020,7 @@ struct Candidates {
 template <u32 kChunks>
 struct ChunkWalk {
     u32 u, stride, excl, inc, total;
+    u32 shift;              // (in the chunk's lane) what turns flat positions into places in S
     u64 from_vector;        // bit i: the i-th chunk is read from the vector itself
     static constexpr u32 kRowQueueSize = 512; // a power of two >= 63 entries waiting + one row of 256
 
@@ -1008,11 +1033,13 @@ struct ChunkWalk {
         stride = step;
         const u64 s = (u64)first + (u64)lane * step;
         bool fv = false;
-        u32 cnt = (lane < kChunks && s < n_chunks) ? cand.count((u32)s, &fv) : 0u;
+        u32 start = 0u;
+        u32 cnt = (lane < kChunks && s < n_chunks) ? cand.count((u32)s, &start, &fv) : 0u;
         from_vector = __ballot(fv);
         if (fv) cnt = 0u;           // not part of the flat sequence: see for_each_vector_row
         inc = wave_inclusive_sum(cnt);
         excl = inc - cnt;
+        shift = start - excl;
         total = __shfl(inc, kWave - 1, kWave);
     }
 
@@ -1045,7 +1072,7 @@ struct ChunkWalk {
             for (u32 q = 0; q < kAhead; ++q) {
                 const u32 p = p0 + q * kWave + lane;
                 locate(p, &c[q], &first[q]);
-                cand.entry(u + c[q] * stride, p - first[q], false, &idx[q], &bits[q], &key[q]);
+                cand.entry(u + c[q] * stride, __shfl(shift, c[q], kWave), p, false, &idx[q], &bits[q], &key[q]);
             }
 #pragma unroll
             for (u32 q = 0; q < kAhead; ++q) f(true, c[q], idx[q], bits[q], key[q], first[q], p0 + q * kWave);
@@ -1054,7 +1081,8 @@ struct ChunkWalk {
             const u32 p = p0 + lane;
             u32 c, first, idx = 0, bits = 0, key = 0;
             locate(p, &c, &first);
-            if (p < total) cand.entry(u + c * stride, p - first, false, &idx, &bits, &key);
+            const u32 to_s = __shfl(shift, c, kWave);
+            if (p < total) cand.entry(u + c * stride, to_s, p, false, &idx, &bits, &key);
             f(p < total, c, idx, bits, key, first, p0);
         }
     }
@@ -1376,7 +1404,7 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
 template <bool kKeyed>      // S holds keyed entries (what is read from the vector itself never is)
 __device__ __forceinline__ void
 classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const float *__restrict__ a,
-           const u32 *__restrict__ seg_count, const uint2 *__restrict__ s_ent,
+           const uint2 *__restrict__ seg, const uint2 *__restrict__ s_ent,
            u32 *__restrict__ win_cnt, u32 *__restrict__ bd_cnt, u32 *__restrict__ blk_sure,
            u32 *__restrict__ n_m, u32 *__restrict__ n_b, u32 *__restrict__ blk_bmin,
            u32 *__restrict__ blk_bmax, u64 *__restrict__ m_key, u32 *__restrict__ m_idx,
@@ -1398,7 +1426,7 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
         }
         return;
     }
-    const Candidates cand{seg_count, s_ent, a, g.d, g.C, g.U, g.UC, g.cap, false};
+    const Candidates cand{seg, s_ent, a, g.d, g.C, g.U, g.UC, false};
     const UnitWalk walk(cand, u < g.U ? u : g.W, g.U, g.W);
     if (threadIdx.x == 0) { cnt_m = 0u; cnt_b = 0u; cnt_sure = 0u; bmin_s = 0xFFFFFFFFu; bmax_s = 0u; }
     if (lane < kUnitChunksMax) { per_chunk[wave][lane] = 0u; per_chunk_b[wave][lane] = 0u; }
@@ -1800,7 +1828,7 @@ __device__ __forceinline__ Selected grid_select96(ForEach &&for_each, u64 rank, 
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void
 finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
-           const float *__restrict__ a, u32 *seg_count, uint2 *s_ent,
+           const float *__restrict__ a, uint2 *seg, uint2 *s_ent,
            u32 *win_cnt, const u32 *__restrict__ bd_cnt, const u32 *__restrict__ blk_sure,
            const u32 *__restrict__ n_m, const u32 *__restrict__ n_b,
            const u32 *__restrict__ blk_bmin, const u32 *__restrict__ blk_bmax,
@@ -1827,7 +1855,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     const bool dense = (mode & 1u) != 0u, partial = (mode & 2u) != 0u;
     const u32 bd_lo = ctl->bd_lo, bd_hi = ctl->bd_hi, bd_bits = ctl->bd_bits;
     const u64 c_def = ctl->c_def;
-    Candidates cand{seg_count, s_ent, a, g.d, g.C, g.U, g.UC, g.cap, dense};
+    Candidates cand{seg, s_ent, a, g.d, g.C, g.U, g.UC, dense};
     // Whether what the exact selections walk holds every member of the top-r set. Otherwise (S as
     // a keying stream left it) the members above the bracket whose key lies above the window are
     // missing.
@@ -1842,7 +1870,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         for (u32 sc = first; sc < g.W; sc += step) {
             const float *chunk = a + (u64)sc * g.C;
             const u32 len = cand.length(sc);
-            uint2 *slice = s_ent + (u64)sc * g.cap;
+            const u32 start = sc * g.cap;
+            uint2 *slice = s_ent + start;
             u32 kept = 0;
             for (u32 r0 = 0; r0 < len; r0 += kRows * kChunkQuantum) {
                 u32 bits[kRows][4];
@@ -1884,7 +1913,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                     kept += popc64(b[0]) + popc64(b[1]) + popc64(b[2]) + popc64(b[3]);
                 }
             }
-            if (lane == 0) seg_count[chunk_slot(sc, g.U, g.UC)] = kept;
+            if (lane == 0) seg[chunk_slot(sc, g.U, g.UC)] = make_uint2(kept | (kept > g.cap ? kSliceFull : 0u), start);
         }
         wait_own_memory();
     };
@@ -2003,12 +2032,13 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         auto wide_each = [&](auto &&f, auto &&done) {
             for (u32 sc = blockIdx.x * kFinWaves + wave; sc < g.W; sc += n_waves) {
                 bool fv = false;
-                const u32 n_e = cand.count(sc, &fv);
+                u32 start = 0;
+                const u32 n_e = cand.count(sc, &start, &fv);
                 if (!fv) {
                     for (u32 j0 = 0; j0 < n_e; j0 += kWave) {
                         const u32 j = j0 + lane;
                         u32 idx = 0, bits = 0, key = 0;
-                        if (j < n_e) cand.entry(sc, j, false, &idx, &bits, &key);
+                        if (j < n_e) cand.entry(sc, start, j, false, &idx, &bits, &key);
                         f(j < n_e, idx, bits);
                     }
                 } else {
@@ -2268,14 +2298,15 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 const u32 sc = run_chunk;
                 const u32 want = (u32)(need2 - run_before);      // 1-based, among the chunk's
                 bool sc_vec = false;
-                const u32 n_e = cand.count(sc, &sc_vec);
+                u32 start = 0;
+                const u32 n_e = cand.count(sc, &start, &sc_vec);
                 lds_barrier();
                 if (tid == 0) run_found = 0u;
                 u32 seen = 0;
                 for (u32 j0 = 0; j0 < n_e && seen < want; j0 += kFinThreads) {
                     const u32 j = j0 + tid;
                     u32 idx = 0, bits = 0, key = 0;
-                    if (j < n_e) cand.entry(sc, j, sc_vec, &idx, &bits, &key);
+                    if (j < n_e) cand.entry(sc, start, j, sc_vec, &idx, &bits, &key);
                     const u32 m = mag_of(bits);
                     const u32 flag = (j < n_e && m >= bd_lo && m <= bd_hi) ? 1u : 0u;
                     const u32 excl = block_exclusive_sum(flag, scan32);
@@ -2576,7 +2607,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void
 emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
-       const u32 *__restrict__ seg_count, const uint2 *__restrict__ s_ent,
+       const uint2 *__restrict__ seg, const uint2 *__restrict__ s_ent,
        const u32 *__restrict__ chunk_base,
        u32 *__restrict__ out_idx, float *__restrict__ out_val, float *residual)
 {
@@ -2584,7 +2615,7 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
     const u32 u = blockIdx.x * kWalkWaves + threadIdx.x / kWave;
     if (u >= g.U) return;
     const u32 lane = lane_id();
-    const Candidates cand{seg_count, s_ent, residual, g.d, g.C, g.U, g.UC, g.cap,
+    const Candidates cand{seg, s_ent, residual, g.d, g.C, g.U, g.UC,
                           ((ctl->mode & 1u) | ctl->emit_dense) != 0u};
     const UnitWalk walk(cand, u < g.U ? u : g.W, g.U, g.W);
     const u32 my_chunk = u + lane * g.U;
@@ -2720,7 +2751,7 @@ __global__ void __launch_bounds__(kFusedThreads) k_fused(Batch B, Geom g, Encode
 {
     const Member m(B);
     fused_body<kAll, kRows, kKeyed>(m.grad, m.residual, g, m.seed, m.at<EncodeCtl>(L.ctl),
-                            (u32)(L.zero_bytes / 4), m.at<u32>(L.partials), m.at<u32>(L.group_sums), m.at<u32>(L.seg_count),
+                            (u32)(L.zero_bytes / 4), m.at<u32>(L.partials), m.at<u32>(L.group_sums), m.at<uint2>(L.seg),
                             m.at<uint2>(L.s_ent));
 }
 
@@ -2748,7 +2779,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, u32 n_rows, 
         p = pick_body<kWalkThreads>(m.at<u32>(L.partials), m.at<u32>(L.group_sums), n_rows, g, ctl);
         if (blockIdx.x == 0 && threadIdx.x == 0) p.store(ctl);
     }
-    classify_body<kKeyed>(g, m.seed, ctl, kPick ? &p : nullptr, m.residual, m.at<u32>(L.seg_count),
+    classify_body<kKeyed>(g, m.seed, ctl, kPick ? &p : nullptr, m.residual, m.at<uint2>(L.seg),
                   m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt), m.at<u32>(L.bd_cnt),
                   m.at<u32>(L.blk_sure), m.at<u32>(L.n_m), m.at<u32>(L.n_b), m.at<u32>(L.blk_bmin),
                   m.at<u32>(L.blk_bmax), m.at<u64>(L.m_key), m.at<u32>(L.m_idx),
@@ -2759,7 +2790,7 @@ __global__ void __launch_bounds__(kFinThreads) k_finalize(Batch B, Geom g, Encod
 {
     const Member m(B);
     finalize_body(g, m.seed, m.at<EncodeCtl>(L.ctl), m.at<WideScratch>(L.wide), m.residual,
-                  m.at<u32>(L.seg_count),
+                  m.at<uint2>(L.seg),
                   m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt), m.at<u32>(L.bd_cnt),
                   m.at<u32>(L.blk_sure), m.at<u32>(L.n_m), m.at<u32>(L.n_b),
                   m.at<u32>(L.blk_bmin), m.at<u32>(L.blk_bmax), m.at<u64>(L.m_key),
@@ -2771,7 +2802,7 @@ __global__ void __launch_bounds__(kFinThreads) k_finalize(Batch B, Geom g, Encod
 __global__ void __launch_bounds__(kWalkThreads) k_emit(Batch B, Geom g, EncodeLayout L)
 {
     const Member m(B);
-    emit_body(g, m.seed, m.at<EncodeCtl>(L.ctl), m.at<u32>(L.seg_count), m.at<uint2>(L.s_ent),
+    emit_body(g, m.seed, m.at<EncodeCtl>(L.ctl), m.at<uint2>(L.seg), m.at<uint2>(L.s_ent),
               m.at<u32>(L.chunk_base), m.out_idx, m.out_val, m.residual);
 }
 
@@ -3215,12 +3246,12 @@ extern "C" int rtopk_encode_stats(const void *workspace, void *stream_v,
     uint64_t superset = 0;
     if (c.W > 0 && c.W <= kTargetChunks && c.U > 0 && c.UC > 0 && (u64)c.U * c.UC <= kTargetChunks &&
         c.W <= c.U * c.UC) {
-        const EncodeLayout L = make_layout(Geom{});   // the offset of seg_count is fixed
-        std::vector<u32> counts(kTargetChunks);
-        if (hipMemcpy(counts.data(), (const char *)workspace + L.seg_count,
-                      (size_t)kTargetChunks * 4, hipMemcpyDeviceToHost) != hipSuccess)
+        const EncodeLayout L = make_layout(Geom{});   // the offset of seg is fixed
+        std::vector<uint2> slices(kTargetChunks);
+        if (hipMemcpy(slices.data(), (const char *)workspace + L.seg,
+                      (size_t)kTargetChunks * sizeof(uint2), hipMemcpyDeviceToHost) != hipSuccess)
             return RTOPK_EHIP;
-        for (u32 s2 = 0; s2 < c.W; ++s2) superset += counts[chunk_slot(s2, c.U, c.UC)];
+        for (u32 s2 = 0; s2 < c.W; ++s2) superset += slices[chunk_slot(s2, c.U, c.UC)].x & ~kSliceFull;
     }
     host_out->error_flags = c.err;
     host_out->path = c.path | (((c.mode & 1u) | c.emit_dense) != 0u ? 2u : 0u);
