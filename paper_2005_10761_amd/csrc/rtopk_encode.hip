@@ -383,6 +383,11 @@ static EncodeLayout make_layout(const Geom &g)
     return L;
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// the same four floats at any address a float may have: the memory instructions of 16
+// bytes only ask for 4-byte alignment
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
 __device__ __forceinline__ u32 mag_of(u32 bits) { return bits & 0x7FFFFFFFu; }
 __device__ __forceinline__ u32 popc64(u64 m) { return (u32)__popcll((unsigned long long)m); }
 
@@ -435,6 +440,45 @@ __device__ __forceinline__ u64 stratum_start(const Geom &g, u32 j)
     return x < g.d ? x : g.d;
 }
 
+// A first element inside stratum [start, start + len), len > 4. The offset depends on the
+// stratum AND on (seed, step): a vector whose layout happens to mislead one set of offsets (a
+// period close to the stratum length) does not mislead the next step's or another worker's.
+// Which elements are sampled never changes the result, only the path.
+__device__ __forceinline__ u64 sample_place(u32 j, u64 start, u64 len, const PhiloxSeed &seed)
+{
+    u32 hsh = (j + 1u) * 0x9E3779B1u;
+    hsh ^= seed.seed_lo * 0x85EBCA77u + seed.step_lo * 0xC2B2AE3Du +
+           (seed.seed_hi ^ seed.step_hi) * 0x27D4EB2Fu;
+    hsh ^= hsh >> 15; hsh *= 0x85EBCA77u; hsh ^= hsh >> 13;
+    hsh *= 0xC2B2AE3Du; hsh ^= hsh >> 16;
+    // offset in [0, len - 4], scaled from the hash instead of a remainder
+    return start + (u64)(((u64)hsh * (u64)(len - 3)) >> 32);
+}
+
+// the samples of location j
+__device__ __forceinline__ uint4 take_samples(const float *__restrict__ grad, const float *__restrict__ residual,
+                                              const Geom &g, const PhiloxSeed &seed, u32 j)
+{
+    u32 v[4] = {kNoSample, kNoSample, kNoSample, kNoSample};
+    if (j >= g.L) return make_uint4(v[0], v[1], v[2], v[3]);
+    const u64 start = stratum_start(g, j), end = stratum_start(g, j + 1);
+    if (end - start > 4) {
+        // One 16-byte load per array, at whatever alignment the pointers have (word by word, a vector of
+        // 11.2 M elements off 16 bytes took 6.8 us, now 4.8). The four elements may start up to
+        // three before the stratum: it stays a spread-out sample.
+        const u64 p = sample_place(j, start, end - start, seed) & ~3ull;
+        const f32x4 gv = *reinterpret_cast<const f32x4u *>(grad + p);
+        const f32x4 mv = *reinterpret_cast<const f32x4u *>(residual + p);
+#pragma unroll
+        for (u32 e = 0; e < 4; ++e) v[e] = mag_of(__float_as_uint(gv[e] + mv[e]));
+    } else {
+#pragma unroll
+        for (u32 e = 0; e < 4; ++e)
+            if (start + e < end) v[e] = mag_of(__float_as_uint(grad[start + e] + residual[start + e]));
+    }
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 __device__ __forceinline__ void
 sample_body(const float *__restrict__ grad, const float *__restrict__ residual, Geom g,
          PhiloxSeed seed, u32 *__restrict__ zero_base, u32 zero_words, u32 *__restrict__ samples)
@@ -442,44 +486,7 @@ sample_body(const float *__restrict__ grad, const float *__restrict__ residual, 
     const u32 j = blockIdx.x * kSampleThreads + threadIdx.x;
     for (u32 i = j; i < zero_words; i += gridDim.x * kSampleThreads) zero_base[i] = 0u;
     if (j >= g.est_vecs * kEstThreads) return;
-    u32 out[4] = {kNoSample, kNoSample, kNoSample, kNoSample};
-    if (j < g.L) {
-        const u64 start = stratum_start(g, j), end = stratum_start(g, j + 1);
-        const u64 len = end - start;
-        u64 p = start;
-        if (len > 4) {
-            // The offset depends on the stratum AND on (seed, step): a vector whose
-            // layout happens to mislead one set of offsets (a period close to the
-            // stratum length) does not mislead the next step's or another worker's.
-            // Which elements are sampled never changes the result, only the path.
-            u32 hsh = (j + 1u) * 0x9E3779B1u;
-            hsh ^= seed.seed_lo * 0x85EBCA77u + seed.step_lo * 0xC2B2AE3Du +
-                   (seed.seed_hi ^ seed.step_hi) * 0x27D4EB2Fu;
-            hsh ^= hsh >> 15; hsh *= 0x85EBCA77u; hsh ^= hsh >> 13;
-            hsh *= 0xC2B2AE3Du; hsh ^= hsh >> 16;
-            // offset in [0, len - 4], scaled from the hash instead of a remainder
-            p += (u64)(((u64)hsh * (u64)(len - 3)) >> 32);
-        }
-        const bool aligned = (((uintptr_t)grad | (uintptr_t)residual) & 15u) == 0;
-        if (aligned && len > 4 && (p & ~3ull) + 4 <= g.d) {
-            // one 16-byte load per array, from one cache line each (the four elements
-            // may start up to three before the stratum: it stays a spread-out sample)
-            p &= ~3ull;
-            const float4 gv = *reinterpret_cast<const float4 *>(grad + p);
-            const float4 mv = *reinterpret_cast<const float4 *>(residual + p);
-            out[0] = mag_of(__float_as_uint(gv.x + mv.x));
-            out[1] = mag_of(__float_as_uint(gv.y + mv.y));
-            out[2] = mag_of(__float_as_uint(gv.z + mv.z));
-            out[3] = mag_of(__float_as_uint(gv.w + mv.w));
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const u64 i = p + e;
-                if (i < end) out[e] = mag_of(__float_as_uint(grad[i] + residual[i]));
-            }
-        }
-    }
-    reinterpret_cast<uint4 *>(samples)[j] = make_uint4(out[0], out[1], out[2], out[3]);
+    reinterpret_cast<uint4 *>(samples)[j] = take_samples(grad, residual, g, seed, j);
 }
 
 // ---------------------------------------------------------------------------
@@ -657,10 +664,6 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
 // access per array). Kept entries are appended to the chunk's slice of S in index
 // order.
 // ---------------------------------------------------------------------------
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-// the same four floats at any address a float may have: the memory instructions of 16
-// bytes only ask for 4-byte alignment
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ u64 elem_index(u64 base, int e) { return base + 4ull * lane_id() + (u64)e; }
 
@@ -1117,9 +1120,8 @@ struct ChunkWalk {
                                              u32 (&bits)[4], bool (&valid)[4]) const
     {
         const u32 off = rc.r0 + 4u * lane_id();
-        const bool vec16 = (reinterpret_cast<uintptr_t>(cand.a) & 15u) == 0;
-        if (vec16 && rc.r0 + kChunkQuantum <= rc.len) {
-            const f32x4 v = *reinterpret_cast<const f32x4 *>(cand.a + rc.c0 + off);
+        if (rc.r0 + kChunkQuantum <= rc.len) {
+            const f32x4 v = *reinterpret_cast<const f32x4u *>(cand.a + rc.c0 + off);
             bits[0] = __float_as_uint(v.x); bits[1] = __float_as_uint(v.y);
             bits[2] = __float_as_uint(v.z); bits[3] = __float_as_uint(v.w);
 #pragma unroll
@@ -1168,7 +1170,6 @@ struct ChunkWalk {
         typedef u32 u32x16 __attribute__((ext_vector_type(4 * kRows)));
         const u32 lane = lane_id();
         const u64 below = lanes_below();
-        const bool vec16 = (reinterpret_cast<uintptr_t>(cand.a) & 15u) == 0;
         u32 head = 0, pending = 0;
         for (u64 rest = from_vector; rest != 0ull; rest &= rest - 1ull) {
             const u32 i = (u32)__ffsll((unsigned long long)rest) - 1u;
@@ -1177,10 +1178,10 @@ struct ChunkWalk {
             const u32 len = cand.length(sc);
             for (u32 r0 = 0; r0 < len || pending != 0u; r0 += kRows * kChunkQuantum) {
                 u32x16 bits;
-                if (vec16 && r0 + kRows * kChunkQuantum <= len) {
+                if (r0 + kRows * kChunkQuantum <= len) {
 #pragma unroll
                     for (u32 q = 0; q < kRows; ++q) {
-                        const f32x4 v = *reinterpret_cast<const f32x4 *>(cand.a + c0 + r0 + q * kChunkQuantum + 4u * lane);
+                        const f32x4 v = *reinterpret_cast<const f32x4u *>(cand.a + c0 + r0 + q * kChunkQuantum + 4u * lane);
 #pragma unroll
                         for (u32 e = 0; e < 4; ++e) bits[4 * q + e] = __float_as_uint(v[e]);
                     }
@@ -2023,7 +2024,6 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         // coordinate is a member: the vector itself is walked, here and by the emit kernel
         if (g.all_members) cand.dense = true;
         bool whole = holds_all();
-        const bool vec16 = (reinterpret_cast<uintptr_t>(a) & 15u) == 0;
         const u32 n_waves = gridDim.x * kFinWaves;
         // f(valid, index, pattern) for every entry of this workgroup's chunks, all lanes
         // together; done(s) after the last entry of chunk s. Wavefront v of the grid takes
@@ -2044,20 +2044,18 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 } else {
                     const u64 c0 = (u64)sc * g.C;
                     u32 j0 = 0;
-                    if (vec16) {
-                        for (; j0 + 4 * kChunkQuantum <= n_e; j0 += 4 * kChunkQuantum) {
-                            const f32x4 *p4 = reinterpret_cast<const f32x4 *>(a + c0 + j0) + lane;
-                            f32x4 v[4];
+                    for (; j0 + 4 * kChunkQuantum <= n_e; j0 += 4 * kChunkQuantum) {
+                        const f32x4u *p4 = reinterpret_cast<const f32x4u *>(a + c0 + j0) + lane;
+                        f32x4 v[4];
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) v[q] = p4[q * kWave];
+                        for (int q = 0; q < 4; ++q) v[q] = p4[q * kWave];
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const u32 i0 = (u32)(c0 + j0) + (u32)q * kChunkQuantum + 4u * lane;
-                                f(true, i0, __float_as_uint(v[q].x));
-                                f(true, i0 + 1u, __float_as_uint(v[q].y));
-                                f(true, i0 + 2u, __float_as_uint(v[q].z));
-                                f(true, i0 + 3u, __float_as_uint(v[q].w));
-                            }
+                        for (int q = 0; q < 4; ++q) {
+                            const u32 i0 = (u32)(c0 + j0) + (u32)q * kChunkQuantum + 4u * lane;
+                            f(true, i0, __float_as_uint(v[q].x));
+                            f(true, i0 + 1u, __float_as_uint(v[q].y));
+                            f(true, i0 + 2u, __float_as_uint(v[q].z));
+                            f(true, i0 + 3u, __float_as_uint(v[q].w));
                         }
                     }
                     for (; j0 < n_e; j0 += kWave) {
@@ -3117,11 +3115,11 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         } else {
             {
                 StageScope sc(trace, RTOPK_STAGE_PREPARE, stream);
+                const dim3 eg(1, 1, nb);
+                static_assert(kSampleLoc == 16 * kEstThreads, "one kernel for each power of two");
                 k_sample<<<dim3(g.est_vecs * kEstThreads / kSampleThreads, 1, nb), kSampleThreads, 0, stream>>>(
                     B, gg, L);
                 RTOPK_LAUNCH_CHECK();
-                const dim3 eg(1, 1, nb);
-                static_assert(kSampleLoc == 16 * kEstThreads, "one kernel for each power of two");
                 switch (g.est_vecs) {
                 case 1: k_estimate<1><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
                 case 2: k_estimate<2><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
