@@ -44,7 +44,7 @@
 //   finalize   one workgroup: exact r-th largest (magnitude, lower index
 //              first) inside B -> (T, I*); members of B join the key lists;
 //              exact (k - #certain)-th smallest (key, index) in M -> (K*, J*);
-//              prefix sum of the winners per chunk. When B overflowed because
+//              prefix sum of the winners per quad of chunks. When B overflowed because
 //              the deciding bin is one long run of equal magnitudes (zeros,
 //              signs, a few levels), the last member is the entry of a known
 //              rank in index order and is located from the per-chunk counts.
@@ -55,7 +55,8 @@
 //              decide after all (the window missed high, the threshold lies above
 //              the bracket), one pass over the vector puts them into S first
 //   emit       entries of S that are members and winners -> the message in
-//              index order, starting at the chunk's prefix; residual at the
+//              index order, starting at the quad's prefix plus the winners of the quad's
+//              earlier chunks; residual at the
 //              sent positions <- a - a
 // Two special cases of Definition 3 take shortcuts: with k == r (top-k) no
 // sampling key is ever computed, and with r == d (random-k) no magnitude is
@@ -154,12 +155,20 @@ constexpr u32 kKeyUnknown = 3u;               // (entries read from the vector i
 constexpr u32 kWindowBits = 12;
 constexpr int kFinThreads = 1024;
 constexpr u32 kFinWaves = kFinThreads / kWave;
-constexpr u32 kSlabs = kTargetChunks / (4 * kFinThreads);  // 16-byte groups of chunk counters per thread
-// Short lists that fit are selected in LDS (600 and 2,700 entries at r = 127,786,
-// k = 25,558). Up to kStageM keys a thread holds four of them, up to kStageMLarge
-// eight (k = 111,740: 4,700 keys of random-k 16.9 instead of 22.4 us from memory;
-// holding eight always costs the smaller lists 0.5-1 us).
-constexpr u32 kStageB = 2048, kStageM = 4096, kStageMLarge = 8192;
+constexpr u32 kSlabs = kTargetChunks / (16 * kFinThreads); // 16-byte groups of quad counters per thread
+// Short lists that fit are selected in LDS (270 and 2,000 entries at r = 127,786, k = 25,558;
+// 4,400 and 20,800 at 2^28, r = 5%, k = 1%): of B an entry's magnitude and index, of M one word with
+// where in the window its key lies and its chunk.
+constexpr u32 kStageB = 4608, kStageM = 20992;
+constexpr u32 kJoinCap = 512;                 // members of the deciding bin whose keys join M
+constexpr u32 kStageRun = 8192;               // keys of a run of equal magnitudes that are selected in LDS
+constexpr u32 kChunkBits = 15;
+static_assert(kTargetChunks == 1u << kChunkBits && kChunkBits + kWindowBits <= 32, "an entry of M is one word");
+// A selection in the lists counts strings in bins by their leading bits, kWave groups of bins.
+constexpr u32 kCutB = 1024, kCutM = 1u << kWindowBits;
+// The winners per chunk are added up chunk by chunk only by emit; finalize goes by quads of them.
+constexpr u32 kQuad = 4;
+constexpr u32 kQuads = kTargetChunks / kQuad;
 
 constexpr u32 kErrSelect = 2u;                // a selection found no element of the requested rank
 constexpr u32 kErrCount = 4u;                 // the winners did not add up to k
@@ -269,8 +278,8 @@ struct Geom {
 
 struct EncodeLayout {
     u64 ctl, wide, zero_bytes, partials, group_sums;
-    u64 samples, seg, win_cnt, bd_cnt, chunk_base, blk_sure, n_m, n_b, blk_bmin, blk_bmax;
-    u64 m_key, m_idx, b_mag, b_idx;
+    u64 samples, seg, win_cnt, bd_cnt, quad_win, quad_base, blk_lists, blk_bmin, blk_bmax;
+    u64 m_ent, b_ent;
     u64 dm_key, dm_idx, db_key, db_idx;
     u64 s_ent;
     u64 total;
@@ -363,17 +372,14 @@ static EncodeLayout make_layout(const Geom &g)
     L.seg = take((u64)kTargetChunks * 8);            // fixed size: its offset depends on nothing
     L.win_cnt = take((u64)kTargetChunks * 4);
     L.bd_cnt = take((u64)kTargetChunks * 4);
-    L.chunk_base = take((u64)kTargetChunks * 4);
-    L.blk_sure = take((u64)g.G3 * 4);
-    L.n_m = take((u64)g.G3 * 4);
-    L.n_b = take((u64)g.G3 * 4);
+    L.quad_win = take((u64)kQuads * 4);
+    L.quad_base = take((u64)kQuads * 4);
+    L.blk_lists = take((u64)g.G3 * 8);
     L.blk_bmin = take((u64)g.G3 * 4);
     L.blk_bmax = take((u64)g.G3 * 4);
     const u64 slots = (u64)g.G3 * kListCap;
-    L.m_key = take(slots * 8);
-    L.m_idx = take(slots * 4);
-    L.b_mag = take(slots * 4);
-    L.b_idx = take(slots * 4);
+    L.m_ent = take(slots * 8);
+    L.b_ent = take(slots * 8);
     L.dm_key = take(2 * slots * 8);
     L.dm_idx = take(2 * slots * 4);
     L.db_key = take(slots * 8);
@@ -1402,17 +1408,14 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
 // short list cannot hold it, but the last member is then simply the entry of
 // a known rank in index order, which those counts locate.
 // ---------------------------------------------------------------------------
-template <bool kKeyed>      // S holds keyed entries (what is read from the vector itself never is)
 __device__ __forceinline__ void
 classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const float *__restrict__ a,
            const uint2 *__restrict__ seg, const uint2 *__restrict__ s_ent,
-           u32 *__restrict__ win_cnt, u32 *__restrict__ bd_cnt, u32 *__restrict__ blk_sure,
-           u32 *__restrict__ n_m, u32 *__restrict__ n_b, u32 *__restrict__ blk_bmin,
-           u32 *__restrict__ blk_bmax, u64 *__restrict__ m_key, u32 *__restrict__ m_idx,
-           u32 *__restrict__ b_mag, u32 *__restrict__ b_idx)
+           u32 *__restrict__ win_cnt, u32 *__restrict__ bd_cnt, u32 *__restrict__ quad_win,
+           uint2 *__restrict__ blk_lists, u32 *__restrict__ blk_bmin,
+           u32 *__restrict__ blk_bmax, uint2 *__restrict__ m_ent, uint2 *__restrict__ b_ent)
 {
     __shared__ u32 cnt_m, cnt_b, cnt_sure, bmin_s, bmax_s;
-    __shared__ u32 list_m[kKeyed ? kListCap : 1u];
     __shared__ u32 per_chunk[kWalkWaves][kUnitChunksMax];
     __shared__ u32 per_chunk_b[kWalkWaves][kUnitChunksMax];
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
@@ -1422,7 +1425,7 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
     const u32 bd_lo = now ? now->bd_lo : ctl->bd_lo, bd_hi = now ? now->bd_hi : ctl->bd_hi;
     if (undecided) {
         if (threadIdx.x == 0) {
-            blk_sure[blockIdx.x] = 0u; n_m[blockIdx.x] = 0u; n_b[blockIdx.x] = 0u;
+            blk_lists[blockIdx.x] = make_uint2(0u, 0u);
             blk_bmin[blockIdx.x] = 0xFFFFFFFFu; blk_bmax[blockIdx.x] = 0u;
         }
         return;
@@ -1443,21 +1446,11 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
         const bool member = valid && (g.all_members != 0u || m > bd_hi);
         const bool in_bin = valid && !member && m >= bd_lo;
         if (member) {
-            u32 says = key >> 30;
-            u64 k64 = 0;
-            if (kKeyed) {
-                if (says == kKeyUnknown) says = key_word(idx, g, seed) >> 30;
-            } else {
-                if (g.take_all == 0u) k64 = sample_key(idx, seed);
-                says = g.take_all != 0u || k64 < g.K_lo ? kKeyBelow : k64 > g.K_hi ? kKeyAbove : kKeyInside;
-            }
-            const bool sure = says == kKeyBelow;
-            if (says == kKeyInside) {
+            if (key >> 30 == kKeyUnknown) key = key_word(idx, g, seed);
+            const bool sure = key >> 30 == kKeyBelow;
+            if (key >> 30 == kKeyInside) {
                 const u32 p = atomicAdd(&cnt_m, 1u);
-                if (p < kListCap) {
-                    if (kKeyed) list_m[p] = idx;
-                    else { m_key[slot(p)] = k64; m_idx[slot(p)] = idx; }
-                }
+                if (p < kListCap) m_ent[slot(p)] = make_uint2((key >> kPlaceBits) & (kCutM - 1u), idx);
             }
             if (sure) atomicAdd(&per_chunk[wave][i], 1u);
         }
@@ -1469,7 +1462,7 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
             if ((here & below) == 0ull) base = atomicAdd(&cnt_b, popc64(here));
             base = (u32)__builtin_amdgcn_readfirstlane((int)base);
             const u32 p = base + popc64(here & below);
-            if (p < kListCap) { b_mag[slot(p)] = m; b_idx[slot(p)] = idx; }
+            if (p < kListCap) b_ent[slot(p)] = make_uint2(m, idx);
             atomicAdd(&per_chunk_b[wave][i], 1u);
             if (m < lane_bmin) { lane_bmin = m; atomicMin(&bmin_s, m); }
             if (m > lane_bmax) { lane_bmax = m; atomicMax(&bmax_s, m); }
@@ -1498,17 +1491,17 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
     mine = wave_sum(mine);
     if (lane == 0 && mine) atomicAdd(&cnt_sure, mine);
     __syncthreads();
-    // the keys of the workgroup's entries of M, all at once
-    static_assert(kListCap <= kWalkThreads, "one thread per list slot");
-    if (kKeyed && threadIdx.x < cnt_m && threadIdx.x < kListCap) {
-        const u32 idx = list_m[threadIdx.x];
-        m_key[slot(threadIdx.x)] = sample_key(idx, seed);
-        m_idx[slot(threadIdx.x)] = idx;
+    // chunks u, u + 1, ... of the workgroup's wavefronts are neighbours: a quad in each round
+    static_assert(kWalkWaves == kQuad, "the chunks of a round are a quad");
+    if (threadIdx.x < g.UC && blockIdx.x * kQuad + threadIdx.x * g.U < g.W) {
+        u32 sum = 0;
+#pragma unroll
+        for (u32 w = 0; w < kWalkWaves; ++w) sum += per_chunk[w][threadIdx.x];
+        quad_win[blockIdx.x + threadIdx.x * (g.U / kQuad)] = sum;
     }
     if (threadIdx.x == 0) {
-        blk_sure[blockIdx.x] = cnt_sure;
-        n_m[blockIdx.x] = cnt_m < kListCap ? cnt_m : kListCap;
-        n_b[blockIdx.x] = cnt_b < kListCap ? cnt_b : kListCap;
+        const u32 in_m = cnt_m < kListCap ? cnt_m : kListCap, in_b = cnt_b < kListCap ? cnt_b : kListCap;
+        blk_lists[blockIdx.x] = make_uint2(in_m | in_b << 16, cnt_sure);
         blk_bmin[blockIdx.x] = bmin_s;
         blk_bmax[blockIdx.x] = bmax_s;
         if (cnt_m > kListCap || cnt_b > kListCap) ctl->overflow = 1u;
@@ -1622,6 +1615,62 @@ __device__ __forceinline__ Pair96 block_select96(ForEach &&for_each, u64 rank, i
 __device__ __forceinline__ bool pair_le(u64 hi, u32 lo, const Pair96 &p)
 {
     return hi < p.hi || (hi == p.hi && lo <= p.lo);
+}
+
+// ---------------------------------------------------------------------------
+// Selection among the short lists' strings: they have been counted in kWave * kPer bins
+// (kPer a divisor of kWave) by their leading bits, and group by group of kPer bins. Every wavefront finds
+// the bin of the rank-th string for itself (one group per lane, then one bin per lane: no barrier in
+// between); the strings in that bin, a handful, are gathered, and every wavefront ranks them
+// for itself, one per lane. (Byte by byte, as block_select96 goes, each byte takes two barriers of sixteen
+// wavefronts and a walk over the bins, and the string left over one more round.)
+// ---------------------------------------------------------------------------
+template <u32 kPer>
+struct CutBins {
+    u32 *bin, *group;       // counters in LDS
+    __device__ __forceinline__ void add(u32 b) const
+    {
+        atomicAdd(&bin[b], 1u);
+        atomicAdd(&group[b / kPer], 1u);
+    }
+    // the bin that holds the rank-th string (1 <= rank <= strings added), the rank inside it and the strings in it
+    __device__ __forceinline__ void find(u32 rank, u32 *at, u32 *rank_in, u32 *here) const
+    {
+        const u32 lane = lane_id();
+        u32 c = group[lane], inc = wave_inclusive_sum(c);
+        u64 owner = __ballot(inc - c < rank && rank <= inc);
+        const int g0 = owner != 0ull ? __ffsll((unsigned long long)owner) - 1 : 0;
+        rank -= (u32)__builtin_amdgcn_readlane((int)(inc - c), g0);
+        c = lane < kPer ? bin[(u32)g0 * kPer + lane] : 0u;
+        inc = wave_inclusive_sum(c);
+        owner = __ballot(inc - c < rank && rank <= inc);
+        const int b0 = owner != 0ull ? __ffsll((unsigned long long)owner) - 1 : 0;
+        *at = (u32)g0 * kPer + (u32)b0;
+        *rank_in = rank - (u32)__builtin_amdgcn_readlane((int)(inc - c), b0);
+        *here = (u32)__builtin_amdgcn_readlane((int)c, b0);
+    }
+};
+
+// the rank-th (1-based) of n <= kWave distinct strings, one per lane; *up_to: the lane's
+// string is it or comes before it
+__device__ __forceinline__ Pair96 wave_rank(u64 hi, u32 lo, u32 n, u32 rank, bool *up_to)
+{
+    const u32 lane = lane_id();
+    u32 smaller = 0;
+#pragma unroll 1
+    for (u32 j = 0; j < n; ++j) {
+        const u32 h1 = (u32)__builtin_amdgcn_readlane((int)(u32)(hi >> 32), (int)j);
+        const u32 h0 = (u32)__builtin_amdgcn_readlane((int)(u32)hi, (int)j);
+        const u32 l = (u32)__builtin_amdgcn_readlane((int)lo, (int)j);
+        const u64 h = ((u64)h1 << 32) | h0;
+        smaller += (h < hi || (h == hi && l < lo)) ? 1u : 0u;
+    }
+    const u64 owner = __ballot(lane < n && smaller + 1u == rank);
+    const int src = owner != 0ull ? __ffsll((unsigned long long)owner) - 1 : 0;
+    *up_to = lane < n && smaller < rank;
+    const u32 h1 = (u32)__builtin_amdgcn_readlane((int)(u32)(hi >> 32), src);
+    const u32 h0 = (u32)__builtin_amdgcn_readlane((int)(u32)hi, src);
+    return Pair96{((u64)h1 << 32) | h0, (u32)__builtin_amdgcn_readlane((int)lo, src)};
 }
 
 // ---------------------------------------------------------------------------
@@ -1830,21 +1879,26 @@ __device__ __forceinline__ Selected grid_select96(ForEach &&for_each, u64 rank, 
 __device__ __forceinline__ void
 finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
            const float *__restrict__ a, uint2 *seg, uint2 *s_ent,
-           u32 *win_cnt, const u32 *__restrict__ bd_cnt, const u32 *__restrict__ blk_sure,
-           const u32 *__restrict__ n_m, const u32 *__restrict__ n_b,
-           const u32 *__restrict__ blk_bmin, const u32 *__restrict__ blk_bmax,
-           const u64 *__restrict__ m_key, const u32 *__restrict__ m_idx,
-           const u32 *__restrict__ b_mag, const u32 *__restrict__ b_idx, u64 *dm_key,
-           u32 *dm_idx, u64 *db_key, u32 *db_idx, u32 *__restrict__ chunk_base)
+           u32 *win_cnt, const u32 *__restrict__ bd_cnt, const u32 *__restrict__ quad_win,
+           const uint2 *__restrict__ blk_lists, const u32 *__restrict__ blk_bmin,
+           const u32 *__restrict__ blk_bmax, const uint2 *__restrict__ m_ent,
+           const uint2 *__restrict__ b_ent, u64 *dm_key,
+           u32 *dm_idx, u64 *db_key, u32 *db_idx, u32 *__restrict__ quad_base)
 {
     static_assert(kMaxWalkBlocks <= (u32)kFinThreads, "one thread per classify workgroup");
-    __shared__ u32 h[4][256];
-    __shared__ u32 scan32[kSlabs * kFinWaves + 1];
+    // The short lists in LDS (see kStageB): counters of the two cuts, winners the lists add per quad
+    // (two to a word, at most a workgroup's lists), what shares a cut's bin. A run of equal magnitudes: its keys.
+    struct Lists {
+        u32 bin_b[kCutB], bin_m[kCutM], group_b[kWave], group_m[kWave], won[kQuads / 2];
+        u32 b_x[kStageB], b_idx[kStageB], m[kStageM], joined[kJoinCap];
+        u32 cand[kWave], cand_idx[kWave], n_cand_b, n_cand_m;
+    };
+    struct Run { u32 h[4][256]; u64 key[kStageRun]; u32 idx[kStageRun]; };
+    static_assert(offsetof(Lists, bin_b) == 0 && kCutB >= 4 * 256, "the histograms of block_select96 take the place of bin_b");
+    __shared__ union { Lists lists; Run run; } lds;
+    u32 (*h)[256] = lds.run.h;
+    __shared__ u32 scan32[3 * kFinWaves + 1];
     __shared__ u64 scratch[2];
-    __shared__ u64 st_b_key[kStageB];
-    __shared__ u32 st_b_idx[kStageB];
-    __shared__ u64 st_m_key[kStageMLarge];
-    __shared__ u32 st_m_idx[kStageMLarge];
     __shared__ u32 extra_m, sure_extra;
     __shared__ unsigned long long gt_extra;
     __shared__ u32 run_chunk, run_before, run_index, run_found;
@@ -1936,8 +1990,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
 
     // ---- everything the short-list path needs, fetched in one round ------
     const bool in_grid = tid < g.G3;
-    const u32 vm = in_grid ? n_m[tid] : 0u, vb = in_grid ? n_b[tid] : 0u;
-    const u32 vs = in_grid ? blk_sure[tid] : 0u;
+    const uint2 counts = in_grid ? blk_lists[tid] : make_uint2(0u, 0u);
+    const u32 vm = counts.x & 0xFFFFu, vb = counts.x >> 16, vs = counts.y;
     const bool overflow = ctl->overflow != 0u, overflow_m = ctl->overflow_m != 0u;
     if (tid == 0) { extra_m = 0u; sure_extra = 0u; gt_extra = 0ull; run_found = 0u; }
     // The three totals (every workgroup of the grid needs them to decide whether
@@ -1949,7 +2003,6 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     {
         const u32 im = wave_inclusive_sum(vm), ib = wave_inclusive_sum(vb), wsure = wave_sum(vs);
         if (lane == kWave - 1) { scan32[wave] = im; scan32[kFinWaves + wave] = ib; scan32[2 * kFinWaves + wave] = wsure; }
-        static_assert(3 * kFinWaves <= kSlabs * kFinWaves + 1, "room for three partial sums per wavefront");
         static_assert(kFinWaves <= kWave, "one lane per wavefront's partial sum");
         lds_barrier();
         const u32 pm = lane < kFinWaves ? scan32[lane] : 0u;
@@ -2176,82 +2229,207 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         if (g.all_members && tid == 0) ctl->emit_dense = 1u;
     }
 
-    // The short-list path. It is compiled three times: with both lists in LDS
-    // (the usual case; the compiler then knows the address space of every list
-    // access and overlaps the loads that fill the lists), the key list up to
-    // kStageM or up to kStageMLarge entries, and once with the lists wherever
-    // they fit.
-    auto short_lists = [&](u64 *bk, u32 *bi, u64 *mk, u32 *mi, auto in_lds_tag) {
-        constexpr u32 kInLds = decltype(in_lds_tag)::value;          // entries of M in LDS, 0: lists anywhere
-        constexpr bool kAllLds = kInLds != 0u;
-        const u32 n_b_use = lists ? n_bd : 0u;
-        const bool m_lds = kAllLds || (lists && n_m0 + n_b_use <= kStageMLarge);
-        const u32 m_cap = kAllLds ? kInLds : m_lds ? kStageMLarge : 2u * g.G3 * kListCap;
-        auto barrier = [&] { if (kAllLds) lds_barrier(); else __syncthreads(); };
-        // Entry j of classify workgroup t lives at [j][t]. First every thread
-        // notes where the entries of its workgroup are (no memory latency in
-        // that loop), then the entries are fetched position by position, all
-        // loads of a thread in flight together.
+    // ---- the short lists decide, in LDS. What bounds this is latency: one workgroup's chain of trips
+    //      to memory and barriers, and the few hundred cold lines that one compute unit fetches at
+    //      0.4 a ns. So an entry of a list is 8 bytes (M: where in the window its key lies, not the key,
+    //      which only the entries in the cut's own bin need), winners per chunk are read and added up by
+    //      quads of chunks, and either cut is one pass over bins. Kernel, us, against lists of keys
+    //      (16 and 12 bytes an entry, more than 8,192 keys in memory), a counter per chunk and a radix selection byte by
+    //      byte: one vector of 200,003 elements 12.2 -> 10.4, of 2^20 13.9 -> 11.1, of 25.6 M 18.2 -> 13.4, top-k
+    //      and random-k of 11.2 M 12.2 -> 8.8 and 17.0 -> 12.4, four of 2^28 (20,700 keys) 105 -> 37.
+    uint4 qw[kSlabs];
+    auto load_quads = [&](auto &&load) {
+#pragma unroll
+        for (u32 q = 0; q < kSlabs; ++q) {
+            const u32 x = 4u * (q * kFinThreads + tid);
+            qw[q] = make_uint4(0u, 0u, 0u, 0u);
+            if (x * kQuad < g.W) qw[q] = load(x);
+        }
+    };
+    bool quick = false;         // what the lists add to the quads is in lds.lists.won
+    if (__builtin_expect(!wide && lists && n_bd <= kStageB && n_m0 <= kStageM, 1)) {
+        Lists &ls = lds.lists;
+        const bool with_b = !g.all_members;
+        for (u32 i = tid; i < kCutM; i += kFinThreads) ls.bin_m[i] = 0u;
+        if (tid < kCutB) ls.bin_b[tid] = 0u;
+        for (u32 i = tid; i < (g.W + 2u * kQuad - 1u) / (2u * kQuad) + 1u && i < kQuads / 2u; i += kFinThreads) ls.won[i] = 0u;
+        if (tid < (u32)kWave) { ls.group_b[tid] = 0u; ls.group_m[tid] = 0u; }
+        if (tid == 0) { ls.n_cand_b = 0u; ls.n_cand_m = 0u; }
+        // Entry j of classify workgroup t lives at [j][t]. First every thread notes where the
+        // entries of its workgroup are (a hot layer may sit in one workgroup's lists), then all fetch them.
+#pragma unroll 1
+        for (u32 j = 0; j < vb; ++j) ls.b_idx[eb + j] = j * g.G3 + tid;
+#pragma unroll 1
+        for (u32 j = 0; j < vm; ++j) ls.m[em + j] = j * g.G3 + tid;
+        lds_barrier();
+        const CutBins<kCutB / kWave> cut_b{ls.bin_b, ls.group_b};
+        const CutBins<kCutM / kWave> cut_m{ls.bin_m, ls.group_m};
+        const u32 chunk_shift = 31u - (u32)__clz((int)g.C), shift_b = bd_bits > 10u ? bd_bits - 10u : 0u;
+        static_assert(kCutB == 1u << 10, "bits of a bin of B");
+        auto word_m = [&](u32 at, u32 idx) { return at << kChunkBits | idx >> chunk_shift; };
+        constexpr u32 kAhead = 4;
+#pragma unroll 1
+        for (u32 p0 = tid; p0 < n_m0; p0 += kAhead * kFinThreads) {
+            uint2 e[kAhead];
+#pragma unroll
+            for (u32 q = 0; q < kAhead; ++q) {
+                const u32 p = p0 + q * kFinThreads;
+                e[q] = m_ent[p < n_m0 ? ls.m[p] : 0u];
+            }
+#pragma unroll
+            for (u32 q = 0; q < kAhead; ++q) {
+                const u32 p = p0 + q * kFinThreads;
+                if (p < n_m0) { ls.m[p] = word_m(e[q].x, e[q].y); cut_m.add(e[q].x); }
+            }
+        }
+        if (with_b)
+#pragma unroll 1
+            for (u32 p = tid; p < n_bd; p += kFinThreads) {
+                const uint2 e = b_ent[ls.b_idx[p]];
+                const u32 x = bd_hi - e.x;
+                ls.b_x[p] = x;
+                ls.b_idx[p] = e.y;
+                cut_b.add(x >> shift_b);
+            }
+        load_quads([&](u32 x) { return reinterpret_cast<const uint4 *>(quad_win)[x / 4u]; });
+        lds_barrier();
+        // ---- exact threshold inside the deciding bin
+        Pair96 tb{~0ull, 0xFFFFFFFFu};
+        if (with_b) {
+            u32 at, rank, here;
+            cut_b.find((u32)need2, &at, &rank, &here);
+            auto each_here = [&](auto &&f) {
+#pragma unroll 1
+                for (u32 p = tid; p < n_bd; p += kFinThreads)
+                    if (ls.b_x[p] >> shift_b == at) f(p);
+            };
+            if (__builtin_expect(here <= (u32)kWave, 1)) {
+                each_here([&](u32 p) { ls.cand[atomicAdd(&ls.n_cand_b, 1u)] = p; });
+                lds_barrier();
+                const u32 p = lane < here ? ls.cand[lane] : 0u;
+                bool up_to;
+                tb = wave_rank(ls.b_x[p], ls.b_idx[p], here, rank, &up_to);
+                lds_barrier();                  // (the candidates of the key cut come next)
+            } else {
+                // many share it (a few levels): byte by byte, the bits that differ only
+                lds_barrier();
+                const u64 low = (1ull << shift_b) - 1ull;
+                const u32 idx_shift = g.d > 1ull ? (u32)__clz((int)(u32)(g.d - 1ull)) : 31u;
+                tb = block_select96([&](auto &&f) {
+                    each_here([&](u32 p) { f((u64)ls.b_x[p] & low, ls.b_idx[p] << idx_shift); });
+                }, rank, (64 - (int)shift_b) / 8, h, scratch, &ok);
+                if (!ok) err |= kErrSelect;
+                tb = Pair96{(u64)at << shift_b | tb.hi, tb.lo >> idx_shift};
+            }
+            T = bd_hi - (u32)tb.hi;
+            I_star = tb.lo;
+            // ---- its members: a key decides between certain winner, one more entry of M, and nothing
+            u32 my_gt = 0, my_sure = 0;
+#pragma unroll 1
+            for (u32 p = tid; p < n_bd; p += kFinThreads) {
+                const u32 x = ls.b_x[p], idx = ls.b_idx[p];
+                bool sure = pair_le((u64)x, idx, tb);
+                my_gt += (u64)x < tb.hi ? 1u : 0u;
+                if (sure && g.take_all == 0u) {
+                    const u64 key = sample_key(idx, seed);
+                    sure = key < g.K_lo;
+                    if (!sure && key <= g.K_hi) {
+                        const u32 q = atomicAdd(&extra_m, 1u);
+                        const u32 at = (u32)(((key - g.K_lo) << g.k_nlz) >> (64 - kWindowBits));
+                        if (q < kJoinCap && n_m0 + q < kStageM) {
+                            ls.joined[q] = idx;
+                            ls.m[n_m0 + q] = word_m(at, idx);
+                            cut_m.add(at);
+                        }
+                    }
+                }
+                if (sure) ++my_sure;
+                ls.b_x[p] = sure ? 1u : 0u;     // from here on: whether it is a certain winner
+            }
+            my_gt = wave_sum(my_gt);
+            my_sure = wave_sum(my_sure);
+            if (lane == 0 && my_gt) atomicAdd(&gt_extra, (unsigned long long)my_gt);
+            if (lane == 0 && my_sure) atomicAdd(&sure_extra, my_sure);
+            lds_barrier();
+        }
+        have_t = true;
+        count_greater = c_def + gt_extra;
+        n_mm = n_m0 + extra_m;
+        const u64 c_klo = sure_walk + sure_extra;
+        u32 at = 0, rank = 0, here = 0;
+        if (g.take_all) {
+            quick = true;
+        } else if (c_klo < g.k && g.k - c_klo <= n_mm && extra_m <= kJoinCap && n_mm <= kStageM) {
+            cut_m.find((u32)(g.k - c_klo), &at, &rank, &here);
+            quick = here <= (u32)kWave;         // (a 4096th of the window with more keys: as if the lists had not fitted)
+        }
+        if (__builtin_expect(quick, 1)) {
+            // a winner of chunk sc: one more in its quad and (for emit) in the chunk
+            auto won = [&](u32 sc) {
+                const u32 x = sc / kQuad;
+                atomicAdd(&ls.won[x / 2u], 1u << (16u * (x & 1u)));
+                atomicAdd(&win_cnt[sc], 1u);
+            };
+            if (with_b)
+#pragma unroll 1
+                for (u32 p = tid; p < n_bd; p += kFinThreads)
+                    if (ls.b_x[p] != 0u) won(ls.b_idx[p] >> chunk_shift);
+            if (!g.take_all) {
+#pragma unroll 1
+                for (u32 p = tid; p < n_mm; p += kFinThreads) {
+                    const u32 w = ls.m[p];
+                    if (w >> kChunkBits == at) ls.cand[atomicAdd(&ls.n_cand_m, 1u)] = p;
+                    else if (w >> kChunkBits < at) won(w & ((1u << kChunkBits) - 1u));
+                }
+                lds_barrier();
+                // the candidates' indices: whoever has the candidate's list fetches its entry again
+#pragma unroll 1
+                for (u32 j = 0; j < here; ++j) {
+                    const u32 p = ls.cand[j];
+                    if (p >= n_m0) { if (tid == 0) ls.cand_idx[j] = ls.joined[p - n_m0]; }
+                    else if (p - em < vm) ls.cand_idx[j] = m_ent[(u64)(p - em) * g.G3 + tid].y;
+                }
+                lds_barrier();
+                const u32 idx = lane < here ? ls.cand_idx[lane] : 0u;
+                bool up_to;
+                const Pair96 kb = wave_rank((sample_key(idx, seed) - g.K_lo) << g.k_nlz, idx, here, rank, &up_to);
+                if (wave == 0 && up_to) won(idx >> chunk_shift);
+                K_star = (kb.hi >> g.k_nlz) + g.K_lo;
+                J_star = kb.lo;
+            }
+            have_k = true;
+        } else {
+            have_t = false;
+            ok = true;
+            lds_barrier();                      // (everybody has read the counts)
+            if (tid == 0) { extra_m = 0u; sure_extra = 0u; gt_extra = 0ull; }
+        }
+        lds_barrier();
+    }
+
+    // The lists that do not fit LDS, and a run of equal magnitudes at the threshold: in memory.
+    if (__builtin_expect(!wide && !quick && (lists || tie_run), 0)) {
+        u64 *bk = db_key, *mk = dm_key;
+        u32 *bi = db_idx, *mi = dm_idx;
+        const u32 m_cap = 2u * g.G3 * kListCap;
+        // as above: where the entries are, then the entries (M's keys are made here)
         if (lists) for (u32 j = 0; j < vb; ++j) bi[eb + j] = j * g.G3 + tid;
         for (u32 j = 0; j < vm; ++j) mi[em + j] = j * g.G3 + tid;
-        barrier();
-        if (kAllLds) {
-            constexpr u32 kB = kStageB / kFinThreads, kM = kAllLds ? kInLds / kFinThreads : 1u;
-            u32 b_m[kB], b_i[kB], m_i[kM];
-            u64 m_k[kM];
-#pragma unroll
-            for (u32 q = 0; q < kB; ++q) {
-                const u32 p = q * kFinThreads + tid;
-                if (p < n_b_use) { const u32 at = bi[p]; b_m[q] = b_mag[at]; b_i[q] = b_idx[at]; }
+        __syncthreads();
+        if (lists)
+            for (u32 p = tid; p < n_bd; p += kFinThreads) {
+                const uint2 e = b_ent[bi[p]];
+                bk[p] = (u64)(bd_hi - e.x);
+                bi[p] = e.y;
             }
-#pragma unroll
-            for (u32 q = 0; q < kM; ++q) {
-                const u32 p = q * kFinThreads + tid;
-                if (p < n_m0) { const u32 at = mi[p]; m_k[q] = m_key[at]; m_i[q] = m_idx[at]; }
-            }
-#pragma unroll
-            for (u32 q = 0; q < kB; ++q) {
-                const u32 p = q * kFinThreads + tid;
-                if (p < n_b_use) { bk[p] = (u64)(bd_hi - b_m[q]); bi[p] = b_i[q]; }
-            }
-#pragma unroll
-            for (u32 q = 0; q < kM; ++q) {
-                const u32 p = q * kFinThreads + tid;
-                if (p < n_m0) { mk[p] = (m_k[q] - g.K_lo) << g.k_nlz; mi[p] = m_i[q]; }
-            }
-        } else {
-            for (u32 p = tid; p < n_b_use; p += kFinThreads) {
-                const u32 at = bi[p];
-                bk[p] = (u64)(bd_hi - b_mag[at]);
-                bi[p] = b_idx[at];
-            }
-            for (u32 p = tid; p < n_m0; p += kFinThreads) {
-                const u32 at = mi[p];
-                mk[p] = (m_key[at] - g.K_lo) << g.k_nlz;
-                mi[p] = m_idx[at];
-            }
+        for (u32 p = tid; p < n_m0; p += kFinThreads) {
+            const u32 idx = m_ent[mi[p]].y;
+            mk[p] = (sample_key(idx, seed) - g.K_lo) << g.k_nlz;
+            mi[p] = idx;
         }
-        barrier();
-        // (in LDS a thread's entries, two at most, stay in registers over the rounds)
-        constexpr u32 kB = kAllLds ? kStageB / kFinThreads : 1u;
-        u64 rb_k[kB];
-        u32 rb_i[kB];
-        if (kAllLds) {
-#pragma unroll
-            for (u32 q = 0; q < kB; ++q) {
-                const u32 p = q * kFinThreads + tid;
-                rb_k[q] = p < n_bd ? bk[p] : 0ull;
-                rb_i[q] = p < n_bd ? bi[p] : 0u;
-            }
-        }
+        __syncthreads();
         auto each_b = [&](auto &&f) {
-            if (kAllLds) {
-#pragma unroll
-                for (u32 q = 0; q < kB; ++q)
-                    if (q * kFinThreads + tid < n_bd) f(rb_k[q], rb_i[q]);
-            } else {
-                for (u32 p = tid; p < n_bd; p += kFinThreads) f(bk[p], bi[p]);
-            }
+            for (u32 p = tid; p < n_bd; p += kFinThreads) f(bk[p], bi[p]);
         };
         Pair96 tb{0ull, 0u};
         if (__builtin_expect(tie_run, 0)) {
@@ -2379,40 +2557,22 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 if (lane == 0 && my_sure) atomicAdd(&sure_extra, my_sure);
             }
             if (my_gt) atomicAdd(&gt_extra, (unsigned long long)my_gt);
-            barrier();
+            __syncthreads();
             count_greater = c_def + gt_extra;
             n_mm = n_m0 + extra_m;
-            if (__builtin_expect(tie_run && n_mm <= kStageMLarge && n_mm <= m_cap, 0)) {
+            if (n_mm <= kStageRun && n_mm <= m_cap) {
                 // short after all: the selection below reads it several times, from LDS then
-                for (u32 p = tid; p < n_mm; p += kFinThreads) { st_m_key[p] = mk[p]; st_m_idx[p] = mi[p]; }
-                mk = st_m_key;
-                mi = st_m_idx;
+                for (u32 p = tid; p < n_mm; p += kFinThreads) { lds.run.key[p] = mk[p]; lds.run.idx[p] = mi[p]; }
+                mk = lds.run.key;
+                mi = lds.run.idx;
                 lds_barrier();
             }
             const u64 c_klo = sure_walk + sure_extra;
             if (g.take_all) {
                 have_k = true;
             } else if (n_mm <= m_cap && c_klo < g.k && g.k - c_klo <= n_mm) {
-                // (in LDS a thread's entries, four or eight at most, stay in registers over the rounds)
-                constexpr u32 kM = kAllLds ? kInLds / kFinThreads : 1u;
-                u64 rm_k[kM];
-                u32 rm_i[kM];
-                if (kAllLds) {
-#pragma unroll
-                    for (u32 q = 0; q < kM; ++q) {
-                        const u32 p = q * kFinThreads + tid;
-                        rm_k[q] = p < n_mm ? mk[p] : 0ull;
-                        rm_i[q] = p < n_mm ? mi[p] : 0u;
-                    }
-                }
                 auto each_m = [&](auto &&f) {
-                    if (kAllLds) {
-#pragma unroll
-                        for (u32 q = 0; q < kM; ++q)
-                            if (q * kFinThreads + tid < n_mm) f(rm_k[q], rm_i[q]);
-                    } else {
-                        for (u32 p = tid; p < n_mm; p += kFinThreads) f(mk[p], mi[p]);
-                    }
+                    for (u32 p = tid; p < n_mm; p += kFinThreads) f(mk[p], mi[p]);
                 };
                 const Pair96 kb = block_select96(each_m, g.k - c_klo, 0, h, scratch, &ok);
                 if (ok) {
@@ -2425,19 +2585,6 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 }
             }
         }
-    };
-    if (__builtin_expect(!wide && (lists || tie_run), 1)) {
-        const u32 n_b_use = lists ? n_bd : 0u;
-        const bool b_lds = n_b_use <= kStageB;
-        // (a run of equal magnitudes may add any number of keys: the large array then)
-        const bool m_lds = lists && n_m0 + n_b_use <= kStageMLarge;
-        if (__builtin_expect(b_lds && lists && n_m0 + n_b_use <= kStageM, 1))
-            short_lists(st_b_key, st_b_idx, st_m_key, st_m_idx, std::integral_constant<u32, kStageM>{});
-        else if (b_lds && m_lds)
-            short_lists(st_b_key, st_b_idx, st_m_key, st_m_idx, std::integral_constant<u32, kStageMLarge>{});
-        else
-            short_lists(b_lds ? st_b_key : db_key, b_lds ? st_b_idx : db_idx,
-                        m_lds ? st_m_key : dm_key, m_lds ? st_m_idx : dm_idx, std::integral_constant<u32, 0u>{});
     }
 
     if (g.all_members && !have_k) {
@@ -2516,66 +2663,65 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     }
     __syncthreads();
 
-    // ---- output offset of every chunk: thread t holds the counters of chunks
+    // ---- output offset of every quad of chunks: thread t holds the winners of quads
     //      4*(1024*q + t) .. +3, q < kSlabs; prefix sums run slab after slab.
-    //      This is the workgroup's first read of the counters, after the
-    //      barrier that follows its atomics on them.
-    u32 c[kSlabs][4], s4[kSlabs], inc[kSlabs];
+    if (__builtin_expect(quick, 1)) {
+#pragma unroll
+        for (u32 q = 0; q < kSlabs; ++q) {
+            const u32 x = 4u * (q * kFinThreads + tid);
+            if (x * kQuad >= g.W) continue;
+            const u32 w01 = lds.lists.won[x / 2u], w23 = lds.lists.won[x / 2u + 1u];
+            qw[q].x += w01 & 0xFFFFu;
+            qw[q].y += w01 >> 16;
+            qw[q].z += w23 & 0xFFFFu;
+            qw[q].w += w23 >> 16;
+        }
+    } else {
+        // from the chunks' counters: the workgroup's first read of them, after the barrier that
+        // follows its atomics on them (wide: written by other workgroups of this grid, read where they
+        // were written)
+        auto quad = [&](u32 x) {
+            u32 sum = 0;
+#pragma unroll
+            for (u32 e = 0; e < kQuad; ++e) {
+                const u32 sc = x * kQuad + e;
+                if (sc < g.W) sum += wide ? __hip_atomic_load(&win_cnt[sc], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : win_cnt[sc];
+            }
+            return sum;
+        };
+        load_quads([&](u32 x) { return make_uint4(quad(x), quad(x + 1u), quad(x + 2u), quad(x + 3u)); });
+    }
+    u32 s4[kSlabs], inc[kSlabs];
 #pragma unroll
     for (u32 q = 0; q < kSlabs; ++q) {
-        const u32 s = 4u * (q * kFinThreads + tid);
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (s < g.W) {
-            if (__builtin_expect(wide, 0)) {
-                // written by other workgroups of this grid: read where they were written
-                v.x = __hip_atomic_load(&win_cnt[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                v.y = __hip_atomic_load(&win_cnt[s + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                v.z = __hip_atomic_load(&win_cnt[s + 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                v.w = __hip_atomic_load(&win_cnt[s + 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                v = reinterpret_cast<const uint4 *>(win_cnt)[q * kFinThreads + tid];
-            }
-        }
-        c[q][0] = v.x;
-        c[q][1] = s + 1 < g.W ? v.y : 0u;
-        c[q][2] = s + 2 < g.W ? v.z : 0u;
-        c[q][3] = s + 3 < g.W ? v.w : 0u;
-        s4[q] = c[q][0] + c[q][1] + c[q][2] + c[q][3];
+        // (quads beyond the last chunk)
+        const u32 x = 4u * (q * kFinThreads + tid);
+        if ((x + 1u) * kQuad >= g.W) qw[q].y = 0u;
+        if ((x + 2u) * kQuad >= g.W) qw[q].z = 0u;
+        if ((x + 3u) * kQuad >= g.W) qw[q].w = 0u;
+        s4[q] = qw[q].x + qw[q].y + qw[q].z + qw[q].w;
+        inc[q] = wave_inclusive_sum(s4[q]);
     }
-#pragma unroll
-    for (u32 q = 0; q < kSlabs; ++q) inc[q] = wave_inclusive_sum(s4[q]);
+    static_assert(kSlabs * kFinWaves <= kWave, "one partial sum per lane");
     if (lane == kWave - 1) {
 #pragma unroll
         for (u32 q = 0; q < kSlabs; ++q) scan32[q * kFinWaves + wave] = inc[q];
     }
-    __syncthreads();
-    {
-        constexpr u32 n = kSlabs * kFinWaves;          // partial sums, a few per lane of wave 0
-        constexpr u32 kEach = n / kWave;
-        static_assert(n % kWave == 0 && kEach >= 1, "whole partial sums per lane");
-        if (wave == 0) {
-            u32 part[kEach], sum = 0;
-#pragma unroll
-            for (u32 j = 0; j < kEach; ++j) { part[j] = scan32[kEach * lane + j]; sum += part[j]; }
-            const u32 xi = wave_inclusive_sum(sum);
-            u32 running = xi - sum;
-#pragma unroll
-            for (u32 j = 0; j < kEach; ++j) { scan32[kEach * lane + j] = running; running += part[j]; }
-            if (lane == kWave - 1) scan32[n] = xi;
-        }
-    }
-    __syncthreads();
-    const u64 total = scan32[kSlabs * kFinWaves];
+    lds_barrier();
+    const u32 part = lane < kSlabs * kFinWaves ? scan32[lane] : 0u;
+    const u32 up_to_here = wave_inclusive_sum(part);
+    const u64 total = (u32)__builtin_amdgcn_readlane((int)up_to_here, kWave - 1);
 #pragma unroll
     for (u32 q = 0; q < kSlabs; ++q) {
-        const u32 s = 4u * (q * kFinThreads + tid);
-        if (s < g.W) {
+        const u32 x = 4u * (q * kFinThreads + tid);
+        const u32 before = (u32)__builtin_amdgcn_readlane((int)(up_to_here - part), (int)(q * kFinWaves + wave));
+        if (x * kQuad < g.W) {
             uint4 o;
-            o.x = scan32[q * kFinWaves + wave] + inc[q] - s4[q];
-            o.y = o.x + c[q][0];
-            o.z = o.y + c[q][1];
-            o.w = o.z + c[q][2];
-            reinterpret_cast<uint4 *>(chunk_base)[q * kFinThreads + tid] = o;
+            o.x = before + inc[q] - s4[q];
+            o.y = o.x + qw[q].x;
+            o.z = o.y + qw[q].y;
+            o.w = o.z + qw[q].z;
+            reinterpret_cast<uint4 *>(quad_base)[x / 4u] = o;
         }
     }
     if (total != g.k) err |= kErrCount;
@@ -2606,7 +2752,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
 __device__ __forceinline__ void
 emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
        const uint2 *__restrict__ seg, const uint2 *__restrict__ s_ent,
-       const u32 *__restrict__ chunk_base,
+       const u32 *__restrict__ win_cnt, const u32 *__restrict__ quad_base,
        u32 *__restrict__ out_idx, float *__restrict__ out_val, float *residual)
 {
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
@@ -2617,7 +2763,15 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
                           ((ctl->mode & 1u) | ctl->emit_dense) != 0u};
     const UnitWalk walk(cand, u < g.U ? u : g.W, g.U, g.W);
     const u32 my_chunk = u + lane * g.U;
-    const u32 my_base = (lane < g.UC && my_chunk < g.W) ? chunk_base[my_chunk] : 0u;
+    // where the chunk's winners go: after those of the quads before it and of the chunks before it
+    // in its own quad
+    u32 my_base = 0;
+    if (lane < g.UC && my_chunk < g.W) {
+        const uint4 v = reinterpret_cast<const uint4 *>(win_cnt)[my_chunk / kQuad];
+        const u32 in_quad = my_chunk % kQuad;
+        my_base = quad_base[my_chunk / kQuad] + (in_quad > 0u ? v.x : 0u) + (in_quad > 1u ? v.y : 0u) +
+                  (in_quad > 2u ? v.z : 0u);
+    }
     const u32 T = ctl->T, I_star = ctl->I_star;
     const Pair96 kcut{ctl->K_star, ctl->J_star};
     const u64 below = lanes_below();
@@ -2767,7 +2921,7 @@ __global__ void __launch_bounds__(kPickThreads) k_pick(Batch B, u32 n_rows, Geom
 // 42.2 / 41.5, of 2^20 + 1 41.5 / 41.8, of 1.6 M (196 rows) 47.1 / 48.1, of 2^21 (256) 44.1 /
 // 45.4; two of 2^20 43.9 / 43.4, of 1.6 M 49.5 / 52.1; four of 2^20 51.6 / 51.6, of 2^21 64.7 /
 // 75.0; eight of 2^20 67.1 / 71.3. (Three to eight members gain up to 64 rows; they keep k_pick.)
-template <bool kPick, bool kKeyed>
+template <bool kPick>
 __global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, u32 n_rows, Geom g, EncodeLayout L)
 {
     const Member m(B);
@@ -2777,31 +2931,28 @@ __global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, u32 n_rows, 
         p = pick_body<kWalkThreads>(m.at<u32>(L.partials), m.at<u32>(L.group_sums), n_rows, g, ctl);
         if (blockIdx.x == 0 && threadIdx.x == 0) p.store(ctl);
     }
-    classify_body<kKeyed>(g, m.seed, ctl, kPick ? &p : nullptr, m.residual, m.at<uint2>(L.seg),
-                  m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt), m.at<u32>(L.bd_cnt),
-                  m.at<u32>(L.blk_sure), m.at<u32>(L.n_m), m.at<u32>(L.n_b), m.at<u32>(L.blk_bmin),
-                  m.at<u32>(L.blk_bmax), m.at<u64>(L.m_key), m.at<u32>(L.m_idx),
-                  m.at<u32>(L.b_mag), m.at<u32>(L.b_idx));
+    classify_body(g, m.seed, ctl, kPick ? &p : nullptr, m.residual, m.at<uint2>(L.seg),
+                  m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt), m.at<u32>(L.bd_cnt), m.at<u32>(L.quad_win),
+                  m.at<uint2>(L.blk_lists), m.at<u32>(L.blk_bmin), m.at<u32>(L.blk_bmax),
+                  m.at<uint2>(L.m_ent), m.at<uint2>(L.b_ent));
 }
 
 __global__ void __launch_bounds__(kFinThreads) k_finalize(Batch B, Geom g, EncodeLayout L)
 {
     const Member m(B);
     finalize_body(g, m.seed, m.at<EncodeCtl>(L.ctl), m.at<WideScratch>(L.wide), m.residual,
-                  m.at<uint2>(L.seg),
-                  m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt), m.at<u32>(L.bd_cnt),
-                  m.at<u32>(L.blk_sure), m.at<u32>(L.n_m), m.at<u32>(L.n_b),
-                  m.at<u32>(L.blk_bmin), m.at<u32>(L.blk_bmax), m.at<u64>(L.m_key),
-                  m.at<u32>(L.m_idx), m.at<u32>(L.b_mag), m.at<u32>(L.b_idx), m.at<u64>(L.dm_key),
+                  m.at<uint2>(L.seg), m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt), m.at<u32>(L.bd_cnt),
+                  m.at<u32>(L.quad_win), m.at<uint2>(L.blk_lists), m.at<u32>(L.blk_bmin), m.at<u32>(L.blk_bmax),
+                  m.at<uint2>(L.m_ent), m.at<uint2>(L.b_ent), m.at<u64>(L.dm_key),
                   m.at<u32>(L.dm_idx), m.at<u64>(L.db_key), m.at<u32>(L.db_idx),
-                  m.at<u32>(L.chunk_base));
+                  m.at<u32>(L.quad_base));
 }
 
 __global__ void __launch_bounds__(kWalkThreads) k_emit(Batch B, Geom g, EncodeLayout L)
 {
     const Member m(B);
     emit_body(g, m.seed, m.at<EncodeCtl>(L.ctl), m.at<uint2>(L.seg), m.at<uint2>(L.s_ent),
-              m.at<u32>(L.chunk_base), m.out_idx, m.out_val, m.residual);
+              m.at<u32>(L.win_cnt), m.at<u32>(L.quad_base), m.out_idx, m.out_val, m.residual);
 }
 
 // ---------------------------------------------------------------------------
@@ -3149,14 +3300,10 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
             }
             const dim3 cg(gg.G3, 1, nb);
             const bool picks = !g.all_members && few_rows;
-            if (picks && gg.keyed)
-                k_classify<true, true><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
-            else if (picks)
-                k_classify<true, false><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
-            else if (gg.keyed)
-                k_classify<false, true><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
+            if (picks)
+                k_classify<true><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
             else
-                k_classify<false, false><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
+                k_classify<false><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
             RTOPK_LAUNCH_CHECK();
         }
         {
