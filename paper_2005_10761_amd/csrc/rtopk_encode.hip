@@ -105,7 +105,9 @@ static_assert(kMaxBins % kCoarseSpan == 0 && kCoarseSpan == 64, "one lane per bi
 constexpr u32 kSampleLoc = 16384;             // sampled locations, 4 consecutive elements each
 constexpr u32 kSampleThreads = 256;
 constexpr u32 kEstThreads = 1024;
-constexpr u32 kNoSample = 0xFFFFFFFFu;
+// A sample is the leading 15 bits of a magnitude (the estimate needs 12): the one workgroup of the
+// estimate fetches cold lines at 0.4 a ns, and four bytes a sample were 2,048 of them.
+constexpr u32 kSampleShift = 16, kBucketShift = 3, kNoSample = 0xFFFFu;
 constexpr u64 kShortVector = 1u << 22;
 constexpr u64 kHeavyTail = 1u << 14;          // (see make_geom)
 
@@ -368,7 +370,7 @@ static EncodeLayout make_layout(const Geom &g)
     L.zero_bytes = o;                       // cleared at the start of every call
     L.partials = take((u64)kMaxFusedBlocks * kMaxBins * 4);
     L.group_sums = take((u64)kMaxFusedBlocks * kMaxGroups * 4);
-    L.samples = take((u64)kSampleLoc * 16);
+    L.samples = take((u64)kSampleLoc * 8);
     L.seg = take((u64)kTargetChunks * 8);            // fixed size: its offset depends on nothing
     L.win_cnt = take((u64)kTargetChunks * 4);
     L.bd_cnt = take((u64)kTargetChunks * 4);
@@ -461,28 +463,29 @@ __device__ __forceinline__ u64 sample_place(u32 j, u64 start, u64 len, const Phi
     return start + (u64)(((u64)hsh * (u64)(len - 3)) >> 32);
 }
 
-// the samples of location j
-__device__ __forceinline__ uint4 take_samples(const float *__restrict__ grad, const float *__restrict__ residual,
+// the samples of location j, two to a word
+__device__ __forceinline__ uint2 take_samples(const float *__restrict__ grad, const float *__restrict__ residual,
                                               const Geom &g, const PhiloxSeed &seed, u32 j)
 {
     u32 v[4] = {kNoSample, kNoSample, kNoSample, kNoSample};
-    if (j >= g.L) return make_uint4(v[0], v[1], v[2], v[3]);
-    const u64 start = stratum_start(g, j), end = stratum_start(g, j + 1);
-    if (end - start > 4) {
-        // One 16-byte load per array, at whatever alignment the pointers have (word by word, a vector of
-        // 11.2 M elements off 16 bytes took 6.8 us, now 4.8). The four elements may start up to
-        // three before the stratum: it stays a spread-out sample.
-        const u64 p = sample_place(j, start, end - start, seed) & ~3ull;
-        const f32x4 gv = *reinterpret_cast<const f32x4u *>(grad + p);
-        const f32x4 mv = *reinterpret_cast<const f32x4u *>(residual + p);
+    if (j < g.L) {
+        const u64 start = stratum_start(g, j), end = stratum_start(g, j + 1);
+        if (end - start > 4) {
+            // One 16-byte load per array, at whatever alignment the pointers have (word by word, a vector of
+            // 11.2 M elements off 16 bytes took 6.8 us, now 4.8). The four elements may start up to
+            // three before the stratum: it stays a spread-out sample.
+            const u64 p = sample_place(j, start, end - start, seed) & ~3ull;
+            const f32x4 gv = *reinterpret_cast<const f32x4u *>(grad + p);
+            const f32x4 mv = *reinterpret_cast<const f32x4u *>(residual + p);
 #pragma unroll
-        for (u32 e = 0; e < 4; ++e) v[e] = mag_of(__float_as_uint(gv[e] + mv[e]));
-    } else {
+            for (u32 e = 0; e < 4; ++e) v[e] = mag_of(__float_as_uint(gv[e] + mv[e])) >> kSampleShift;
+        } else {
 #pragma unroll
-        for (u32 e = 0; e < 4; ++e)
-            if (start + e < end) v[e] = mag_of(__float_as_uint(grad[start + e] + residual[start + e]));
+            for (u32 e = 0; e < 4; ++e)
+                if (start + e < end) v[e] = mag_of(__float_as_uint(grad[start + e] + residual[start + e])) >> kSampleShift;
+        }
     }
-    return make_uint4(v[0], v[1], v[2], v[3]);
+    return make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16);
 }
 
 __device__ __forceinline__ void
@@ -492,7 +495,7 @@ sample_body(const float *__restrict__ grad, const float *__restrict__ residual, 
     const u32 j = blockIdx.x * kSampleThreads + threadIdx.x;
     for (u32 i = j; i < zero_words; i += gridDim.x * kSampleThreads) zero_base[i] = 0u;
     if (j >= g.est_vecs * kEstThreads) return;
-    reinterpret_cast<uint4 *>(samples)[j] = take_samples(grad, residual, g, seed, j);
+    reinterpret_cast<uint2 *>(samples)[j] = take_samples(grad, residual, g, seed, j);
 }
 
 // ---------------------------------------------------------------------------
@@ -557,32 +560,34 @@ __device__ __forceinline__ void wave_pick_from_top(const u32 *hist, u32 top, con
     }
 }
 
-template <u32 kVecs>      // 16-byte sample groups per thread
+template <u32 kVecs>      // locations (8 bytes, four samples) per thread
 __device__ __forceinline__ void
 estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
 {
-    // One compute unit looks at 65,536 samples: the work per sample is what this
-    // kernel costs, so the two passes over them are a handful of instructions per
-    // 16-byte group. A sample is a magnitude pattern (< 2^31) or kNoSample
-    // (all ones): as signed integers the missing ones are -1, below every real one.
+    // One compute unit looks at 65,536 samples: the lines it fetches and the work per
+    // sample are what this kernel costs, so the two passes over them are a handful of
+    // instructions per location. A sample has 15 bits or is kNoSample
+    // (all ones): as signed 16-bit integers the missing ones are -1, below every real one.
     __shared__ u32 h_max[4096];                           // buckets of the per-thread maxima
     __shared__ u32 h[4096];                               // buckets of the samples that matter
     __shared__ u32 scan_lds[kEstThreads / kWave + 1];
     __shared__ u32 bin_s[3], before_s[3], top_s;
     const u32 tid = threadIdx.x;
-    const uint4 *s4 = reinterpret_cast<const uint4 *>(samples);
-    uint4 v[kVecs];
+    const uint2 *s2 = reinterpret_cast<const uint2 *>(samples);
+    uint2 v[kVecs];
 #pragma unroll
-    for (u32 q = 0; q < kVecs; ++q) v[q] = s4[q * kEstThreads + tid];
+    for (u32 q = 0; q < kVecs; ++q) v[q] = s2[q * kEstThreads + tid];
     for (u32 b = tid; b < 4096u; b += kEstThreads) { h[b] = 0u; h_max[b] = 0u; }
     if (tid < 3u) { bin_s[tid] = 0u; before_s[tid] = 0u; }
     if (tid == 0) top_s = 0u;
     auto smax = [](int a, int b) { return a > b ? a : b; };
-    int gmax[kVecs];                                      // largest of each group, -1 if none
+    auto low = [](u32 w) { return (int)(short)(w & 0xFFFFu); };
+    auto high = [](u32 w) { return (int)w >> 16; };
+    int gmax[kVecs];                                      // largest of each location, -1 if none
     int tmax = -1;
 #pragma unroll
     for (u32 q = 0; q < kVecs; ++q) {
-        gmax[q] = smax(smax((int)v[q].x, (int)v[q].y), smax((int)v[q].z, (int)v[q].w));
+        gmax[q] = smax(smax(low(v[q].x), high(v[q].x)), smax(low(v[q].y), high(v[q].y)));
         tmax = smax(tmax, gmax[q]);
     }
     // Number of samples: four per location once every stratum is longer than
@@ -595,8 +600,7 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
         u32 nvalid = 0;
 #pragma unroll
         for (u32 q = 0; q < kVecs; ++q)
-            nvalid += (v[q].x != kNoSample) + (v[q].y != kNoSample) + (v[q].z != kNoSample) +
-                      (v[q].w != kNoSample);
+            nvalid += (low(v[q].x) >= 0) + (high(v[q].x) >= 0) + (low(v[q].y) >= 0) + (high(v[q].y) >= 0);
         n = block_sum(nvalid, scan_lds);
     }
 
@@ -610,15 +614,23 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
 
     // Only the top s_lo samples matter. At most s_lo - 1 threads hold a sample
     // above the s_lo-th largest one, so the s_lo-th largest of the per-thread
-    // maxima is not above it: buckets below that maximum's bucket need no count.
+    // maxima (of which there must be that many) is not above it: buckets below that maximum's bucket need no count.
     // (the bucket of the largest sample of all is where every walk starts)
     {
-        const u32 wmax = wave_max_dpp(tmax >= 0 ? (u32)tmax >> 19 : 0u);
+        const u32 wmax = wave_max_dpp(tmax >= 0 ? (u32)tmax >> kBucketShift : 0u);
         if (lane_id() == 0 && wmax) atomicMax(&top_s, wmax);
     }
+    // (Where the top holds more samples than there are threads, the same with the maxima of the
+    // locations: every sample counted, five vectors of 11.2 M elements, r = 5%, took 11.4 us, now 9.3)
     u32 cut_bucket = 0;
-    if (s_lo < kEstThreads) {
-        if (tmax >= 0) atomicAdd(&h_max[(u32)tmax >> 19], 1u);
+    if (s_lo < g.L) {
+        if (s_lo < kEstThreads) {
+            if (tmax >= 0) atomicAdd(&h_max[(u32)tmax >> kBucketShift], 1u);
+        } else {
+#pragma unroll
+            for (u32 q = 0; q < kVecs; ++q)
+                if (gmax[q] >= 0) atomicAdd(&h_max[(u32)gmax[q] >> kBucketShift], 1u);
+        }
         lds_barrier();
         if (tid < kWave) {
             const u32 want_cut[1] = {s_lo};
@@ -627,17 +639,18 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
         lds_barrier();
         cut_bucket = bin_s[2];                     // stays 0 when fewer than s_lo threads hold samples
     }
-    const int cut = (int)(cut_bucket << 19);       // >= 0: missing samples never pass
+    const int cut = (int)(cut_bucket << kBucketShift);    // >= 0: missing samples never pass
     u32 nzero = 0;
-    auto count = [&](u32 m) {
-        if ((int)m < cut) return;
-        if (m == 0u) ++nzero;                     // exact zeros come in long runs: count them aside
-        else atomicAdd(&h[m >> 19], 1u);
+    auto count = [&](int m) {
+        if (m < cut) return;
+        const u32 b = (u32)m >> kBucketShift;
+        if (b == 0u) ++nzero;                     // zeros come in long runs: count them aside
+        else atomicAdd(&h[b], 1u);
     };
 #pragma unroll
     for (u32 q = 0; q < kVecs; ++q) {
-        if (gmax[q] < cut) continue;               // nearly every group
-        count(v[q].x); count(v[q].y); count(v[q].z); count(v[q].w);
+        if (gmax[q] < cut) continue;               // nearly every location
+        count(low(v[q].x)); count(high(v[q].x)); count(low(v[q].y)); count(high(v[q].y));
     }
     nzero = wave_sum(nzero);
     if (lane_id() == 0 && nzero) atomicAdd(&h[0], nzero);
