@@ -68,7 +68,7 @@ constexpr u64 kWeightsTiles = 1u << 14;
 constexpr u32 kWeightsWorkers = 8;
 constexpr u32 kWeightsPerTile = 12;
 constexpr u32 kWeightsBlocks = 1024;      // four workgroups per compute unit
-constexpr unsigned kMomentumLdsClaim = 30u * 1024u;   // with the 32 KB of tiles: two workgroups per unit
+constexpr unsigned kMomentumLdsClaim = 16u * 1024u;   // with the 32 KB of tiles: three workgroups per unit
 
 __device__ __forceinline__ u32 popc_mask(u64 m) { return (u32)__popcll((unsigned long long)m); }
 
@@ -908,14 +908,15 @@ extern "C" int rtopk_aggregate_update_momentum(const uint32_t *idx, const float 
     hipStream_t stream = (hipStream_t)stream_v;
     if (const int rc = debug_check_messages(idx, n, k, d, stream)) return rc;
     const u64 tiles = (d + kAggTile - 1) / kAggTile;
-    const u32 tiles_per_wave = (u32)((tiles + kAggMaxWaves - 1) / kAggMaxWaves);
-    const u64 waves = (tiles + tiles_per_wave - 1) / tiles_per_wave;
-    const unsigned grid = (unsigned)((waves + kAggWaves - 1) / kAggWaves);
-    // This form streams 16 bytes per coordinate and is bound by HBM alone: two
-    // workgroups per compute unit (eight wavefronts) stream 6% faster than the five
-    // that fit, so each workgroup also claims LDS it does not use.
+    const unsigned grid = (unsigned)((tiles + kAggWaves - 1) / kAggWaves);
+    // This form streams 16 bytes per coordinate: one tile per wavefront, in order, so that the
+    // wavefronts that search and those that stream overlap, and three workgroups per
+    // compute unit (each claims LDS it does not use). us, 4096 wavefronts of runs of tiles with two
+    // workgroups per unit / one tile and two / three / five: eight workers of 25.6 M 80.9 / 76.7 / 74.4 / 75.6, sixteen, k = 1%,
+    // 145 / 112 / 99 / 98; five of 11.2 M 45.3 / 39.2 / 38.8 / 38.9; eight of 100 M 357 / 275 / 269 / 274; two of
+    // 200 M, k = 1%, 681 / 546 / 570 / 573; four of 66 M 200 / 182 / 185 / 184.
     k_aggregate<true><<<grid, kAggThreads, kMomentumLdsClaim, stream>>>(
-        idx, val, n, k, d, tiles, tiles_per_wave, omega, Momentum{scale, mu, -eta, velocity});
+        idx, val, n, k, d, tiles, 1u, omega, Momentum{scale, mu, -eta, velocity});
     if (hipGetLastError() != hipSuccess) return RTOPK_EHIP;
     return RTOPK_OK;
 }
