@@ -48,7 +48,16 @@ constexpr int kAggWaves = kAggThreads / kWave;
 constexpr int kAggTile = 2048;
 constexpr int kAggAhead = 8;              // workers whose next pairs are fetched together
 constexpr int kAggMore = 8;               // further slices of one crowded message fetched together
+// Tiles per wavefront of the dense average: as many as give kAggMaxWaves wavefronts, at most
+// kAggRun, and one where the messages hold kAggDense entries per tile or more (a wavefront's chain of
+// trips per tile is then what counts, not the search for its first one). us, one / two / four / eight tiles:
+//   25.6 M, 16 entries per tile 25.8 / 24.9 / 24.5 / 35.5, evenly spread 29.2 / 25.4 / 23.8 / 29.7; 327
+//   per tile 59.7 / 67.8 / 97.3; 11.2 M, 102 per tile 21.5 / 24.2 / 38.3; 66 M, 8 per tile 53.8 / 53.9 / 52.5 / 56.4;
+//   100 M, 16 per tile 113 / 106 / 109 / 133 (twelve: 166), 1.6 per tile 109 / 91 / 78 / 80; 200 M, two
+//   workers, 41 per tile 194 / 172 / 168 / 193 (24: 238).
 constexpr unsigned kAggMaxWaves = 4096;
+constexpr u32 kAggRun = 4;
+constexpr u64 kAggDense = 64;
 // The sparse weight step takes k_weights (one kernel) where the vector is long and the
 // messages are sparse: from kWeightsTiles tiles on, up to kWeightsWorkers workers and
 // kWeightsPerTile entries per tile; k_tile_starts + k_update elsewhere. Measured (us,
@@ -885,7 +894,10 @@ extern "C" int rtopk_aggregate(const uint32_t *idx, const float *val, uint32_t n
     hipStream_t stream = (hipStream_t)stream_v;
     if (const int rc = debug_check_messages(idx, n, k, d, stream)) return rc;
     const u64 tiles = (d + kAggTile - 1) / kAggTile;
-    const u32 tiles_per_wave = (u32)((tiles + kAggMaxWaves - 1) / kAggMaxWaves);
+    u64 run = (tiles + kAggMaxWaves - 1) / kAggMaxWaves;
+    if (run > kAggRun) run = kAggRun;
+    if (k >= (kAggDense * tiles + n - 1) / n) run = 1;
+    const u32 tiles_per_wave = (u32)run;
     const u64 waves = (tiles + tiles_per_wave - 1) / tiles_per_wave;
     const unsigned grid = (unsigned)((waves + kAggWaves - 1) / kAggWaves);
     k_aggregate<false><<<grid, kAggThreads, 0, stream>>>(idx, val, n, k, d, tiles, tiles_per_wave,
