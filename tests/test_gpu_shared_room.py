@@ -1,0 +1,73 @@
+"""Where the rules around the candidate buffer, the short lists and the dense
+average's runs of tiles change over. Bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _encode(g, r, k, seed, steps=2, offset=0):
+    from tests import gpu_util as u
+    d = len(g)
+    w, res, paths = u.GpuWorker(d, r, k, offset=offset), np.zeros(d, np.float32), []
+    for t in range(steps):
+        got = w.encode(g, seed, t)
+        oi, ov, res = oracle.encode(g, res, r, k, seed, t)
+        u.assert_encode_equal(got, (oi, ov, res), f"d={d} r={r} k={k} step {t}")
+        paths.append(w.stats["path"])
+    return paths
+
+
+@pytest.mark.parametrize("d", [3_200_000, 6_300_001, 9_500_123])      # 1 to 2, 2 to 3, 3 to 4 chunks per wavefront of 3072
+@pytest.mark.parametrize("hot", ["first", "last", "ragged", "same_wavefront", "all_of_one"])
+@pytest.mark.parametrize("k_of_r", [1, 2, 5])
+def test_chunks_share_their_wavefronts_room(d, hot, k_of_r):
+    """Chunks that are members throughout, at the ends of a wavefront's part of the buffer, two of one
+    wavefront, and all of one wavefront's: with k = r none fits, with k = r / 5 one takes the others' room."""
+    stride = 3072 * 1024
+    rng = np.random.default_rng(d + k_of_r)
+    g = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    starts = {"first": [0], "last": [(d // 1024 - 1) * 1024], "ragged": [d // 1024 * 1024],
+              "same_wavefront": [5 * 1024, 5 * 1024 + stride], "all_of_one": range(7 * 1024, d, stride)}[hot]
+    for s in starts:
+        n = len(g[s:s + 1024])
+        g[s:s + 1024] = rng.standard_normal(n).astype(np.float32) * 5.0 + np.float32(20.0)
+    r = 5_000
+    print(f"shared room d={d} hot={hot} r={r} k={r // k_of_r}", flush=True)
+    _encode(g, r, r // k_of_r, 3, offset=d % 4)
+
+
+@pytest.mark.parametrize("d,r,k,levels", [(200_003, 4_000, 900, 64), (200_003, 12_000, 1_500, 8), (1_048_576, 10_485, 1_048, 4),
+                                          (1_500_000, 1_500, 1_500, 4), (70_001, 300, 60, 1024), (4_200_000, 40_000, 8_000, 16)])
+def test_deciding_bin_of_a_few_levels(d, r, k, levels):
+    """Quantised values: from a handful to thousands of equal magnitudes share the bin of the cut, in lists
+    that fit the staging area and lists that do not."""
+    g = (np.round(np.random.default_rng(d + r).standard_normal(d) * levels) / levels).astype(np.float32)
+    print(f"levels d={d} r={r} k={k} levels={levels}", flush=True)
+    assert not any(p & 2 for p in _encode(g, r, k, 11))
+
+
+def test_more_keys_than_the_staging_area_holds():
+    """Random-k whose key window holds 21,400 keys (20,992 are staged)."""
+    d, k = 40_000_003, 2_500_000
+    g = np.random.default_rng(4).standard_normal(d).astype(np.float32)
+    print(f"key list d={d} k={k}", flush=True)
+    assert _encode(g, d, k, 5, steps=1) == [0]
+
+
+@pytest.mark.parametrize("tiles", [4096, 4097, 8193, 12289, 16385])   # runs of one, two, three, four and four tiles
+@pytest.mark.parametrize("per_tile", [1, 63, 64])                     # ... and of one from 64 entries per tile on
+@pytest.mark.parametrize("n", [1, 5])
+def test_dense_average_over_the_runs_of_tiles(tiles, per_tile, n):
+    from tests import gpu_util as u
+    d = (tiles - 1) * 2048 + 7
+    k = tiles * per_tile // n + 1
+    rng = np.random.default_rng(tiles + per_tile + n)
+    idx = np.stack([np.unique(rng.integers(0, d, 2 * k))[:k] for _ in range(n)]).astype(np.uint32)
+    idx[:, -1] = d - 1
+    val = rng.standard_normal((n, k)).astype(np.float32)
+    print(f"average tiles={tiles} per tile {per_tile} n={n}", flush=True)
+    out = u.gpu_aggregate(idx, val, n, d)
+    assert np.array_equal(u.bits(out), u.bits(oracle.aggregate_f32(idx, val, n, d)))
