@@ -48,16 +48,15 @@ constexpr int kAggWaves = kAggThreads / kWave;
 constexpr int kAggTile = 2048;
 constexpr int kAggAhead = 8;              // workers whose next pairs are fetched together
 constexpr int kAggMore = 8;               // further slices of one crowded message fetched together
-// Tiles per wavefront of the dense average: as many as give kAggMaxWaves wavefronts, at most
-// kAggRun, and one where the messages hold kAggDense entries per tile or more (a wavefront's chain of
-// trips per tile is then what counts, not the search for its first one). us, one / two / four / eight tiles:
-//   25.6 M, 16 entries per tile 25.8 / 24.9 / 24.5 / 35.5, evenly spread 29.2 / 25.4 / 23.8 / 29.7; 327
-//   per tile 59.7 / 67.8 / 97.3; 11.2 M, 102 per tile 21.5 / 24.2 / 38.3; 66 M, 8 per tile 53.8 / 53.9 / 52.5 / 56.4;
-//   100 M, 16 per tile 113 / 106 / 109 / 133 (twelve: 166), 1.6 per tile 109 / 91 / 78 / 80; 200 M, two
-//   workers, 41 per tile 194 / 172 / 168 / 193 (24: 238).
+// Tiles per wavefront of the dense average: as many as give kAggMaxWaves wavefronts; where that is twice
+// kAggRun or more and the workers are few, so that the search for the first tile is short, kAggRun. us, long
+// runs / runs of four, evenly spread messages and messages clustered in forty places, k = 0.1%: two workers of 100 M
+// 83.3 / 71.9 and 95.2 / 77.0, four 84.3 / 73.9 and 98.3 / 81.2, of 2^28 210 / 191 and 262 / 197 (k = 1%: 310 / 236
+// and 363 / 276). Not with more workers: sixteen of 2^28, even messages, 238 / 283 (k = 0.01%); and not for runs of
+// five: four workers of 40 M 28.0 / 31.1.
 constexpr unsigned kAggMaxWaves = 4096;
 constexpr u32 kAggRun = 4;
-constexpr u64 kAggDense = 64;
+constexpr u32 kAggFewWorkers = 4;
 // The sparse weight step takes k_weights (one kernel) where the vector is long and the
 // messages are sparse: from kWeightsTiles tiles on, up to kWeightsWorkers workers and
 // kWeightsPerTile entries per tile; k_tile_starts + k_update elsewhere. Measured (us,
@@ -895,8 +894,7 @@ extern "C" int rtopk_aggregate(const uint32_t *idx, const float *val, uint32_t n
     if (const int rc = debug_check_messages(idx, n, k, d, stream)) return rc;
     const u64 tiles = (d + kAggTile - 1) / kAggTile;
     u64 run = (tiles + kAggMaxWaves - 1) / kAggMaxWaves;
-    if (run > kAggRun) run = kAggRun;
-    if (k >= (kAggDense * tiles + n - 1) / n) run = 1;
+    if (n <= kAggFewWorkers && run >= 2 * kAggRun) run = kAggRun;
     const u32 tiles_per_wave = (u32)run;
     const u64 waves = (tiles + tiles_per_wave - 1) / tiles_per_wave;
     const unsigned grid = (unsigned)((waves + kAggWaves - 1) / kAggWaves);

@@ -57,9 +57,9 @@ def test_more_keys_than_the_staging_area_holds():
     assert _encode(g, d, k, 5, steps=1) == [0]
 
 
-@pytest.mark.parametrize("tiles", [4096, 4097, 8193, 12289, 16385])   # runs of one, two, three, four and four tiles
-@pytest.mark.parametrize("per_tile", [1, 63, 64])                     # ... and of one from 64 entries per tile on
-@pytest.mark.parametrize("n", [1, 5])
+@pytest.mark.parametrize("tiles", [4096, 4097, 12289, 28672, 28673])  # runs of one, two, four and seven tiles; of eight,
+@pytest.mark.parametrize("per_tile", [1, 64])                         # which up to four workers cut to four
+@pytest.mark.parametrize("n", [1, 4, 5])
 def test_dense_average_over_the_runs_of_tiles(tiles, per_tile, n):
     from tests import gpu_util as u
     d = (tiles - 1) * 2048 + 7
