@@ -22,7 +22,8 @@ extern "C" {
 typedef struct rtopk_encode_stats {
     uint32_t error_flags;        /* 0 = clean; bit 1: a selection found no element of the requested
                                     rank; bit 2: the winners did not add up to k; bit 3: a workgroup
-                                    of the many-workgroup selection gave up waiting for the others
+                                    of the many-workgroup selection gave up waiting for the others:
+                                    the message is left as it was, the residual holds g + m
                                     (any bit set: results invalid) */
     uint32_t path;               /* 0: both cut points came from the short lists; bit 0: at least one
                                     came from the slow selection over all candidates; bit 1: the
@@ -90,8 +91,8 @@ int rtopk_trace_next_encode(int stage, void *ev_begin, void *ev_end);
  *                                waits between the workgroups of the
  *                                many-workgroup selection give up at their
  *                                first poll: every kernel still ends normally,
- *                                error_flags reports bit 3, and the outputs of
- *                                that call are invalid. Only has an effect
+ *                                error_flags reports bit 3, and the call
+ *                                writes no message (the residual holds g + m). Only has an effect
  *                                together with a condition that needs the
  *                                selection on a vector of 256 chunks or more.
  * Passing 0 cancels a pending request.

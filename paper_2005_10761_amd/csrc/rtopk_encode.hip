@@ -1932,6 +1932,11 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     // element at or above the deciding bin: one pass over the vector (four rows of a chunk in
     // flight), after which S will do for all the passes of an exact selection and for emit. The
     // keys are left to be computed. (By one wavefront, which sees what it wrote itself.)
+    // A chunk's slice goes back to its fixed place, over whatever slices the stream left there: this
+    // may only run where nobody reads a slice of the stream's any more, that is after a barrier that
+    // all readers have passed, and all chunks have to be refilled. Where some workgroups give up at a
+    // barrier and others go on to refill, both layouts overlap: the call then ends with kErrBarrier (workgroup
+    // 0 misses those that left at the next barrier, if it did not give up itself) and emit reads nothing.
     auto complete_slices = [&](u32 first, u32 step) {
         constexpr u32 kRows = 4;
         const u64 below = lanes_below();
@@ -2771,6 +2776,9 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
     const u32 u = blockIdx.x * kWalkWaves + threadIdx.x / kWave;
     if (u >= g.U) return;
+    // A wait between workgroups of the selection that gave up: there are no cut points, and S may
+    // be half refilled (see complete_slices), so that an entry need not lie inside its chunk.
+    if ((ctl->err & kErrBarrier) != 0u) return;
     const u32 lane = lane_id();
     const Candidates cand{seg, s_ent, residual, g.d, g.C, g.U, g.UC,
                           ((ctl->mode & 1u) | ctl->emit_dense) != 0u};

@@ -1190,6 +1190,28 @@ def test_a_barrier_that_gives_up_ends_the_call_with_the_error_flag():
     assert w.stats["error_flags"] == 0 and w.stats["path"] == 0, w.stats
 
 
+@pytest.mark.parametrize("miss", ["KEY_WINDOW_MISS", "ESTIMATE_MISS", "BRACKET_LOW"])
+@pytest.mark.parametrize("all_members", [False, True])
+def test_a_barrier_that_gives_up_writes_no_message(miss, all_members):
+    """Workgroups that gave up and workgroups that went on may leave the candidate buffer with entries that
+    belong to other chunks: nothing of it may reach the message or the residual, which keeps g + m."""
+    u = _u()
+    rt = u.rt
+    d = 1_500_007                                        # a ragged last chunk
+    wl = Workload(3, d=d)
+    r, k = (d if all_members else wl.r), wl.k
+    if all_members and miss == "BRACKET_LOW":
+        pytest.skip("r == d has no bracket")
+    g = wl.gradient(0, 0)
+    m = (np.random.default_rng(5).standard_normal(d) * 1e-3).astype(np.float32)
+    w = u.GpuWorker(d, r, k, residual=m)
+    idx, val, res = w.encode(g, 5, 0, check_stats=False,
+                             force=getattr(rt, "FORCE_" + miss) | rt.FORCE_BARRIER_TIMEOUT)
+    assert w.stats["error_flags"] & 8, w.stats
+    assert np.all(idx == 0xFFFFFFFF) and np.all(np.isnan(val))          # as the buffers were
+    assert np.array_equal(u.bits(res), u.bits(g + m))
+
+
 def test_test_hooks_belong_to_the_calling_host_thread():
     """rtopk_force_next_encode (like rtopk_trace_next_encode) is remembered per
     host thread: a request made on one thread must not reach another thread's
