@@ -76,6 +76,17 @@ constexpr u64 kWeightsTiles = 1u << 14;
 constexpr u32 kWeightsWorkers = 8;
 constexpr u32 kWeightsPerTile = 12;
 constexpr u32 kWeightsBlocks = 1024;      // four workgroups per compute unit
+// Tiles per wavefront of the momentum step: one, but with 17 to 64 workers two from
+// kMomentumTwo tiles on and four from kMomentumFour on. The search for a wavefront's first tile
+// has 64 lanes for n workers: up to sixteen it takes a few probes, with 33 it is a binary search of fifteen, and a run
+// of tiles makes it once. (More than 64 workers are searched for every tile anyway.) us, runs of one / two / four,
+// evenly spread messages, k = 0.1%: 33 workers of 20 M 95 / 86 / 87, of 25.6 M 117 / 116 / 124, of 33.5 M
+// 145 / 134 / 139, of 66 M 268 / 242 / 232, of 2^28 1078 / 947 / 850, seventeen of 33.5 M 117 / 113 / 113, twenty of 2^28
+// 836 / 780 / 734. The other side: sixteen of 25.6 M 84 / 88 / 94, of 66 M 193 / 192 / 186 (k = 0.01%: 181 / 186 /
+// 183), 33 of 16.8 M 79 / 79 / 72, 65 of 66 M, k = 1%, 489 / 502 / 536. (Between 28 and
+// 33.5 M, 4096 wavefronts of runs of four at two workgroups per unit come out exactly even: seventeen of 33.5 M 110.)
+constexpr u32 kMomentumSearch = 16;
+constexpr u64 kMomentumTwo = (1u << 13) + 1, kMomentumFour = (1u << 14) + 1;
 constexpr unsigned kMomentumLdsClaim = 16u * 1024u;   // with the 32 KB of tiles: three workgroups per unit
 
 __device__ __forceinline__ u32 popc_mask(u64 m) { return (u32)__popcll((unsigned long long)m); }
@@ -918,15 +929,18 @@ extern "C" int rtopk_aggregate_update_momentum(const uint32_t *idx, const float 
     hipStream_t stream = (hipStream_t)stream_v;
     if (const int rc = debug_check_messages(idx, n, k, d, stream)) return rc;
     const u64 tiles = (d + kAggTile - 1) / kAggTile;
-    const unsigned grid = (unsigned)((tiles + kAggWaves - 1) / kAggWaves);
-    // This form streams 16 bytes per coordinate: one tile per wavefront, in order, so that the
+    const bool runs = n > kMomentumSearch && n <= (u32)kWave;
+    const u32 run = !runs ? 1u : tiles >= kMomentumFour ? 4u : tiles >= kMomentumTwo ? 2u : 1u;
+    const u64 waves = (tiles + run - 1) / run;
+    const unsigned grid = (unsigned)((waves + kAggWaves - 1) / kAggWaves);
+    // This form streams 16 bytes per coordinate: few tiles per wavefront, in order, so that the
     // wavefronts that search and those that stream overlap, and three workgroups per
     // compute unit (each claims LDS it does not use). us, 4096 wavefronts of runs of tiles with two
     // workgroups per unit / one tile and two / three / five: eight workers of 25.6 M 80.9 / 76.7 / 74.4 / 75.6, sixteen, k = 1%,
     // 145 / 112 / 99 / 98; five of 11.2 M 45.3 / 39.2 / 38.8 / 38.9; eight of 100 M 357 / 275 / 269 / 274; two of
     // 200 M, k = 1%, 681 / 546 / 570 / 573; four of 66 M 200 / 182 / 185 / 184.
     k_aggregate<true><<<grid, kAggThreads, kMomentumLdsClaim, stream>>>(
-        idx, val, n, k, d, tiles, 1u, omega, Momentum{scale, mu, -eta, velocity});
+        idx, val, n, k, d, tiles, run, omega, Momentum{scale, mu, -eta, velocity});
     if (hipGetLastError() != hipSuccess) return RTOPK_EHIP;
     return RTOPK_OK;
 }

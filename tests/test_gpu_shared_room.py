@@ -71,3 +71,21 @@ def test_dense_average_over_the_runs_of_tiles(tiles, per_tile, n):
     print(f"average tiles={tiles} per tile {per_tile} n={n}", flush=True)
     out = u.gpu_aggregate(idx, val, n, d)
     assert np.array_equal(u.bits(out), u.bits(oracle.aggregate_f32(idx, val, n, d)))
+
+
+@pytest.mark.parametrize("tiles", [8192, 8193, 16384, 16385, 16386])  # runs of one, two and four tiles, whole and not
+@pytest.mark.parametrize("n", [16, 17, 33, 64, 65])
+def test_momentum_step_over_the_runs_of_tiles(tiles, n):
+    from tests import gpu_util as u
+    d = (tiles - 1) * 2048 + 7
+    k = 2 * tiles // n + 1
+    rng = np.random.default_rng(tiles + n)
+    idx = np.stack([np.unique(rng.integers(0, d, 2 * k))[:k] for _ in range(n)]).astype(np.uint32)
+    idx[:, -1] = d - 1
+    val = rng.standard_normal((n, k)).astype(np.float32)
+    omega = rng.standard_normal(d, dtype=np.float32)
+    vel = rng.standard_normal(d, dtype=np.float32) * np.float32(0.01)
+    print(f"momentum tiles={tiles} n={n}", flush=True)
+    gw, gv = u.gpu_aggregate_update_momentum(idx, val, n, d, 0.1, 1.0, 0.9, omega, vel)
+    ww, wv = oracle.aggregate_update_momentum_f32(idx, val, n, d, 0.1, 1.0, 0.9, omega, vel)
+    assert np.array_equal(u.bits(gv), u.bits(wv)) and np.array_equal(u.bits(gw), u.bits(ww))
