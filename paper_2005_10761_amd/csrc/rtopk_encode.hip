@@ -2776,25 +2776,26 @@ emit_body(Geom g, PhiloxSeed seed, const EncodeCtl *__restrict__ ctl,
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
     const u32 u = blockIdx.x * kWalkWaves + threadIdx.x / kWave;
     if (u >= g.U) return;
-    // A wait between workgroups of the selection that gave up: there are no cut points, and S may
-    // be half refilled (see complete_slices), so that an entry need not lie inside its chunk.
-    if ((ctl->err & kErrBarrier) != 0u) return;
     const u32 lane = lane_id();
     const Candidates cand{seg, s_ent, residual, g.d, g.C, g.U, g.UC,
                           ((ctl->mode & 1u) | ctl->emit_dense) != 0u};
-    const UnitWalk walk(cand, u < g.U ? u : g.W, g.U, g.W);
+    // where the lane's chunk's winners go: after those of the quads before it and of the chunks before it
+    // in its own quad. (Loaded by all lanes, those without a chunk the first quad's, before
+    // anything that waits: behind a branch the two loads held the walk up for 0.1 to 0.5 us.)
     const u32 my_chunk = u + lane * g.U;
-    // where the chunk's winners go: after those of the quads before it and of the chunks before it
-    // in its own quad
-    u32 my_base = 0;
-    if (lane < g.UC && my_chunk < g.W) {
-        const uint4 v = reinterpret_cast<const uint4 *>(win_cnt)[my_chunk / kQuad];
-        const u32 in_quad = my_chunk % kQuad;
-        my_base = quad_base[my_chunk / kQuad] + (in_quad > 0u ? v.x : 0u) + (in_quad > 1u ? v.y : 0u) +
-                  (in_quad > 2u ? v.z : 0u);
-    }
-    const u32 T = ctl->T, I_star = ctl->I_star;
+    const bool has_chunk = lane < g.UC && my_chunk < g.W;
+    const u32 quad = has_chunk ? my_chunk / kQuad : 0u, in_quad = my_chunk % kQuad;
+    const uint4 in_front = reinterpret_cast<const uint4 *>(win_cnt)[quad];
+    const u32 of_quad = quad_base[quad];
+    const u32 T = ctl->T, I_star = ctl->I_star, err = ctl->err;
     const Pair96 kcut{ctl->K_star, ctl->J_star};
+    const UnitWalk walk(cand, u < g.U ? u : g.W, g.U, g.W);
+    // A wait between workgroups of the selection that gave up: there are no cut points, and S may
+    // be half refilled (see complete_slices), so that an entry need not lie inside its chunk.
+    // (Looked at with what the first loads bring: a wait of its own at the start cost 0.5 us.)
+    if ((err & kErrBarrier) != 0u) return;
+    const u32 my_base = of_quad + (in_quad > 0u ? in_front.x : 0u) + (in_quad > 1u ? in_front.y : 0u) +
+                        (in_quad > 2u ? in_front.z : 0u);
     const u64 below = lanes_below();
     u32 run = 0;          // winners at flat positions before this iteration
     u32 carry = 0;        // winners before the first entry of the chunk that runs into this iteration
