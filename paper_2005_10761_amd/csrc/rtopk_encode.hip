@@ -260,6 +260,7 @@ struct Geom {
     u32 C;              // elements per chunk (a power of two, at least 1024)
     u32 cap;            // entries of S per chunk (C / kSliceDiv)
     u32 W;              // chunks
+    u32 each, over;     // of them per wavefront of the streaming kernel; its first `over` wavefronts stream one more
     u32 U;              // wavefronts of classify / emit; wavefront u walks chunks u, u + U, ...
     u32 UC;             // ... at most this many of them (W <= U * UC)
     u32 G3;             // classify / emit workgroups
@@ -851,9 +852,8 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
     const u32 w_first = blockIdx.x * n_waves + threadIdx.x / kWave;
     u32 later, at;          // chunks still to come; where in S the next slice starts
     {
-        const u32 each = g.W / wave_stride, over = g.W % wave_stride;
-        later = each + (w_first < over ? 1u : 0u);
-        at = (w_first * each + (w_first < over ? w_first : over)) * g.cap;
+        later = g.each + (w_first < g.over ? 1u : 0u);
+        at = (w_first * g.each + (w_first < g.over ? w_first : g.over)) * g.cap;
     }
     const u32 s_end = at + later * g.cap;
     auto open_chunk = [&](u32 w) {
@@ -3260,6 +3260,9 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         const FusedShape fs = fused_shape(g.W, g.d, nb, grid_limit);
         const unsigned fgrid = fs.grid;
         gg.keyed = keys_in_stream(gg, fs.is_short, nb) ? 1u : 0u;
+        const u32 stream_waves = fgrid * (fs.threads / (unsigned)kWave);
+        gg.each = g.W / stream_waves;
+        gg.over = g.W % stream_waves;
         Batch B{};
         for (unsigned i = 0; i < nb; ++i) {
             B.grad[i] = grad[first + i];
