@@ -2275,9 +2275,9 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         if (tid == 0) { ls.n_cand_b = 0u; ls.n_cand_m = 0u; }
         // Entry j of classify workgroup t lives at [j][t]. First every thread notes where the
         // entries of its workgroup are (a hot layer may sit in one workgroup's lists), then all fetch them.
-#pragma unroll 1
+#pragma unroll 4
         for (u32 j = 0; j < vb; ++j) ls.b_idx[eb + j] = j * g.G3 + tid;
-#pragma unroll 1
+#pragma unroll 4
         for (u32 j = 0; j < vm; ++j) ls.m[em + j] = j * g.G3 + tid;
         lds_barrier();
         const CutBins<kCutB / kWave> cut_b{ls.bin_b, ls.group_b};
