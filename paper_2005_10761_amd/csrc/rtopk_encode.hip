@@ -162,7 +162,6 @@ constexpr u32 kSlabs = kTargetChunks / (16 * kFinThreads); // 16-byte groups of 
 // 4,400 and 20,800 at 2^28, r = 5%, k = 1%): of B an entry's magnitude and index, of M one word with
 // where in the window its key lies and its chunk.
 constexpr u32 kStageB = 4608, kStageM = 20992;
-constexpr u32 kJoinCap = 512;                 // members of the deciding bin whose keys join M
 constexpr u32 kStageRun = 8192;               // keys of a run of equal magnitudes that are selected in LDS
 constexpr u32 kChunkBits = 15;
 static_assert(kTargetChunks == 1u << kChunkBits && kChunkBits + kWindowBits <= 32, "an entry of M is one word");
@@ -1903,7 +1902,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     // (two to a word, at most a workgroup's lists), what shares a cut's bin. A run of equal magnitudes: its keys.
     struct Lists {
         u32 bin_b[kCutB], bin_m[kCutM], group_b[kWave], group_m[kWave], won[kQuads / 2];
-        u32 b_x[kStageB], b_idx[kStageB], m[kStageM], joined[kJoinCap];
+        u32 b_x[kStageB], b_idx[kStageB], m[kStageM];
         u32 cand[kWave], cand_idx[kWave], n_cand_b, n_cand_m;
     };
     struct Run { u32 h[4][256]; u64 key[kStageRun]; u32 idx[kStageRun]; };
@@ -2265,6 +2264,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         }
     };
     bool quick = false;         // what the lists add to the quads is in lds.lists.won
+    constexpr u32 kNotSent = 0xFFFFFFFFu, kSurelySent = 0xFFFFFFFEu;
     if (__builtin_expect(!wide && lists && n_bd <= kStageB && n_m0 <= kStageM, 1)) {
         Lists &ls = lds.lists;
         const bool with_b = !g.all_members;
@@ -2342,28 +2342,27 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             T = bd_hi - (u32)tb.hi;
             I_star = tb.lo;
             // ---- its members: a key decides between certain winner, one more entry of M, and nothing
-            u32 my_gt = 0, my_sure = 0;
+            u32 my_gt = 0, my_sure = 0, my_extra = 0;
 #pragma unroll 1
             for (u32 p = tid; p < n_bd; p += kFinThreads) {
                 const u32 x = ls.b_x[p], idx = ls.b_idx[p];
                 bool sure = pair_le((u64)x, idx, tb);
                 my_gt += (u64)x < tb.hi ? 1u : 0u;
+                u32 verdict = kNotSent;
                 if (sure && g.take_all == 0u) {
                     const u64 key = sample_key(idx, seed);
                     sure = key < g.K_lo;
                     if (!sure && key <= g.K_hi) {
-                        const u32 q = atomicAdd(&extra_m, 1u);
-                        const u32 at = (u32)(((key - g.K_lo) << g.k_nlz) >> (64 - kWindowBits));
-                        if (q < kJoinCap && n_m0 + q < kStageM) {
-                            ls.joined[q] = idx;
-                            ls.m[n_m0 + q] = word_m(at, idx);
-                            cut_m.add(at);
-                        }
+                        verdict = (u32)(((key - g.K_lo) << g.k_nlz) >> (64 - kWindowBits));
+                        cut_m.add(verdict);
+                        ++my_extra;
                     }
                 }
-                if (sure) ++my_sure;
-                ls.b_x[p] = sure ? 1u : 0u;     // from here on: whether it is a certain winner
+                if (sure) { verdict = kSurelySent; ++my_sure; }
+                ls.b_x[p] = verdict;            // from here on: these two, or where in the window its key lies
             }
+            my_extra = wave_sum(my_extra);
+            if (lane == 0 && my_extra) atomicAdd(&extra_m, my_extra);
             my_gt = wave_sum(my_gt);
             my_sure = wave_sum(my_sure);
             if (lane == 0 && my_gt) atomicAdd(&gt_extra, (unsigned long long)my_gt);
@@ -2377,7 +2376,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         u32 at = 0, rank = 0, here = 0;
         if (g.take_all) {
             quick = true;
-        } else if (c_klo < g.k && g.k - c_klo <= n_mm && extra_m <= kJoinCap && n_mm <= kStageM) {
+        } else if (c_klo < g.k && g.k - c_klo <= n_mm) {
             cut_m.find((u32)(g.k - c_klo), &at, &rank, &here);
             quick = here <= (u32)kWave;         // (a 4096th of the window with more keys: as if the lists had not fitted)
         }
@@ -2390,11 +2389,19 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             };
             if (with_b)
 #pragma unroll 1
-                for (u32 p = tid; p < n_bd; p += kFinThreads)
-                    if (ls.b_x[p] != 0u) won(ls.b_idx[p] >> chunk_shift);
+                for (u32 p = tid; p < n_bd; p += kFinThreads) {
+                    const u32 verdict = ls.b_x[p], idx = ls.b_idx[p];
+                    if (verdict == kSurelySent || (verdict != kNotSent && verdict < at)) {
+                        won(idx >> chunk_shift);
+                    } else if (verdict != kNotSent && verdict == at) {
+                        const u32 j = atomicAdd(&ls.n_cand_m, 1u);
+                        ls.cand[j] = kNotSent;          // (not in M)
+                        ls.cand_idx[j] = idx;
+                    }
+                }
             if (!g.take_all) {
 #pragma unroll 1
-                for (u32 p = tid; p < n_mm; p += kFinThreads) {
+                for (u32 p = tid; p < n_m0; p += kFinThreads) {
                     const u32 w = ls.m[p];
                     if (w >> kChunkBits == at) ls.cand[atomicAdd(&ls.n_cand_m, 1u)] = p;
                     else if (w >> kChunkBits < at) won(w & ((1u << kChunkBits) - 1u));
@@ -2404,8 +2411,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
 #pragma unroll 1
                 for (u32 j = 0; j < here; ++j) {
                     const u32 p = ls.cand[j];
-                    if (p >= n_m0) { if (tid == 0) ls.cand_idx[j] = ls.joined[p - n_m0]; }
-                    else if (p - em < vm) ls.cand_idx[j] = m_ent[(u64)(p - em) * g.G3 + tid].y;
+                    if (p != kNotSent && p - em < vm) ls.cand_idx[j] = m_ent[(u64)(p - em) * g.G3 + tid].y;
                 }
                 lds_barrier();
                 const u32 idx = lane < here ? ls.cand_idx[lane] : 0u;

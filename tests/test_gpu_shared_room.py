@@ -49,6 +49,19 @@ def test_deciding_bin_of_a_few_levels(d, r, k, levels):
     assert not any(p & 2 for p in _encode(g, r, k, 11))
 
 
+@pytest.mark.parametrize("d,hot,r,k", [(1 << 20, 4600, 4600, 2300), (1 << 20, 4600, 4590, 4000), (1 << 20, 4608, 4608, 2304),
+                                       (1 << 20, 4609, 4609, 2304), (2_000_003, 4600, 4600, 2300), (1 << 20, 4600, 4600, 4600)])
+@pytest.mark.parametrize("seed", [1, 2, 3])
+def test_nearly_all_members_in_the_deciding_bin(d, hot, r, k, seed):
+    """Entries of +-1 at random places over small noise: the top r lies in the deciding bin but for nothing, and
+    some 540 of its keys join those in the window (k = r: none)."""
+    rng = np.random.default_rng(d + hot + seed)
+    g = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    g[rng.permutation(d)[:hot]] = rng.choice(np.array([-1.0, 1.0], np.float32), hot)
+    print(f"deciding bin d={d} hot={hot} r={r} k={k} seed={seed}", flush=True)
+    assert not any(p & 3 for p in _encode(g, r, k, seed, steps=1))
+
+
 def test_more_keys_than_the_staging_area_holds():
     """Random-k whose key window holds 21,400 keys (20,992 are staged)."""
     d, k = 40_000_003, 2_500_000
