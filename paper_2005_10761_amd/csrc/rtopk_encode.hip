@@ -158,10 +158,16 @@ constexpr u32 kWindowBits = 12;
 constexpr int kFinThreads = 1024;
 constexpr u32 kFinWaves = kFinThreads / kWave;
 constexpr u32 kSlabs = kTargetChunks / (16 * kFinThreads); // 16-byte groups of quad counters per thread
-// Short lists that fit are selected in LDS (270 and 2,000 entries at r = 127,786, k = 25,558;
-// 4,400 and 20,800 at 2^28, r = 5%, k = 1%): of B an entry's magnitude and index, of M one word with
-// where in the window its key lies and its chunk.
-constexpr u32 kStageB = 4608, kStageM = 20992;
+// Short lists that fit are selected in LDS (500 and 2,000 entries at r = 127,786, k = 25,558;
+// 4,300 and 20,500 at 2^28, r = 5%, k = 1%): of B an entry's magnitude and index, of M one word with
+// where in the window its key lies and its chunk. How long M gets is known beforehand: its mean and
+// eight standard deviations (staged_keys) are what a call's finalize kernel claims LDS for, as far as there
+// is any: 2^28 elements, k = 1% need 21,800 at r = 5 k, 23,100 at r = 10 k, 24,200 at r = d, which gets seven. With
+// room for 20,992 whatever the call / now, us: k_finalize of four such vectors, r = 5 k, 35 / 36 (but
+// more than 100 where a window held a few hundred keys above its mean), r = d 89 / 31. (r = 10 k 109 / 109: 6,800
+// entries of B, for which there is no room beside M.) Two streams whose exact selections meet, each with a vector of
+// 11.2 M 304 / 293, of 66 M 750 / 728: a unit taken whole has no room for the other stream's kernels.
+constexpr u32 kStageB = 4608, kStageM = 23936;
 constexpr u32 kStageRun = 8192;               // keys of a run of equal magnitudes that are selected in LDS
 constexpr u32 kChunkBits = 15;
 static_assert(kTargetChunks == 1u << kChunkBits && kChunkBits + kWindowBits <= 32, "an entry of M is one word");
@@ -275,6 +281,7 @@ struct Geom {
     u32 all_members;    // r == d: every coordinate is a member, magnitudes are never looked at
     u32 keyed;          // the streaming kernel keys the candidates (of a short vector only if they are many)
     u32 k_nlz;          // leading zeros of K_hi - K_lo
+    u32 stage_m;        // keys in the window that finalize has room for in LDS
     u64 K_lo, K_hi;     // key window
 };
 
@@ -286,6 +293,14 @@ struct EncodeLayout {
     u64 s_ent;
     u64 total;
 };
+
+// Room for the members whose key lies in the window, `mean` of them on average: with eight
+// standard deviations on top, as far as LDS goes.
+static u32 staged_keys(long double mean)
+{
+    const long double room = mean + 8.0L * sqrtl(mean) + 64.0L;
+    return room < (long double)kStageM ? ((u32)room + 63u) / 64u * 64u : kStageM;
+}
 
 static Geom make_geom(u64 d, u64 r, u64 k)
 {
@@ -346,6 +361,7 @@ static Geom make_geom(u64 d, u64 r, u64 k)
     if (g.K_hi < g.K_lo) g.K_hi = g.K_lo;
     const u64 width = g.K_hi - g.K_lo;
     g.k_nlz = width ? (u32)__builtin_clzll(width) : 63u;
+    g.stage_m = g.take_all ? 0u : staged_keys((fminl(hi, 1.0L) - fmaxl(lo, 0.0L)) * rr);
     return g;
 }
 
@@ -1637,13 +1653,18 @@ __device__ __forceinline__ bool pair_le(u64 hi, u32 lo, const Pair96 &p)
 // for itself, one per lane. (Byte by byte, as block_select96 goes, each byte takes two barriers of sixteen
 // wavefronts and a walk over the bins, and the string left over one more round.)
 // ---------------------------------------------------------------------------
-template <u32 kPer>
+template <u32 kPer, bool kTwoToAWord>
 struct CutBins {
     u32 *bin, *group;       // counters in LDS
     __device__ __forceinline__ void add(u32 b) const
     {
-        atomicAdd(&bin[b], 1u);
+        if (kTwoToAWord) atomicAdd(&bin[b / 2u], 1u << (16u * (b & 1u)));
+        else atomicAdd(&bin[b], 1u);
         atomicAdd(&group[b / kPer], 1u);
+    }
+    __device__ __forceinline__ u32 in_bin(u32 b) const
+    {
+        return kTwoToAWord ? bin[b / 2u] >> (16u * (b & 1u)) & 0xFFFFu : bin[b];
     }
     // the bin that holds the rank-th string (1 <= rank <= strings added), the rank inside it and the strings in it
     __device__ __forceinline__ void find(u32 rank, u32 *at, u32 *rank_in, u32 *here) const
@@ -1653,7 +1674,7 @@ struct CutBins {
         u64 owner = __ballot(inc - c < rank && rank <= inc);
         const int g0 = owner != 0ull ? __ffsll((unsigned long long)owner) - 1 : 0;
         rank -= (u32)__builtin_amdgcn_readlane((int)(inc - c), g0);
-        c = lane < kPer ? bin[(u32)g0 * kPer + lane] : 0u;
+        c = lane < kPer ? in_bin((u32)g0 * kPer + lane) : 0u;
         inc = wave_inclusive_sum(c);
         owner = __ballot(inc - c < rank && rank <= inc);
         const int b0 = owner != 0ull ? __ffsll((unsigned long long)owner) - 1 : 0;
@@ -1882,6 +1903,22 @@ __device__ __forceinline__ Selected grid_select96(ForEach &&for_each, u64 rank, 
     return Selected{phi, plo, j};
 }
 
+// What finalize keeps in LDS. The short lists (see kStageB): counters of the two cuts (of M two to
+// a word: M and the members of B that join it are fewer than 2^16), winners the lists add per quad
+// (two to a word, at most a workgroup's lists), what shares a cut's bin. In their place, the keys of a run
+// of equal magnitudes. Behind them, as much as the launch claims, M itself; elsewhere the run's indices or
+// the winners per quad, and the histograms of the selections.
+struct FinalizeLists {
+    u32 bin_b[kCutB], bin_m[kCutM / 2], group_b[kWave], group_m[kWave], won[kQuads / 2];
+    u32 b_x[kStageB], b_idx[kStageB];
+    u32 cand[kWave], cand_idx[kWave], n_cand_b, n_cand_m;
+};
+constexpr u32 kRunWords = kStageRun + 4 * 256;
+static_assert(kStageM + kStageB < 1u << 16, "two counters of M to a word");
+static_assert(sizeof(FinalizeLists) >= 8 * kStageRun && sizeof(FinalizeLists) + 4 * kStageM + 1408 <= 160 * 1024,
+              "the lists beside the kernel's other variables in one unit's LDS");
+static u32 finalize_claim(const Geom &g) { return 4u * (g.stage_m > kRunWords ? g.stage_m : kRunWords); }
+
 // ---------------------------------------------------------------------------
 // finalize: turns the short lists into the two cut points and the output
 // offset of every chunk (workgroup 0; the others leave at once), or, when the
@@ -1898,17 +1935,12 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
            u32 *dm_idx, u64 *db_key, u32 *db_idx, u32 *__restrict__ quad_base)
 {
     static_assert(kMaxWalkBlocks <= (u32)kFinThreads, "one thread per classify workgroup");
-    // The short lists in LDS (see kStageB): counters of the two cuts, winners the lists add per quad
-    // (two to a word, at most a workgroup's lists), what shares a cut's bin. A run of equal magnitudes: its keys.
-    struct Lists {
-        u32 bin_b[kCutB], bin_m[kCutM], group_b[kWave], group_m[kWave], won[kQuads / 2];
-        u32 b_x[kStageB], b_idx[kStageB], m[kStageM];
-        u32 cand[kWave], cand_idx[kWave], n_cand_b, n_cand_m;
-    };
-    struct Run { u32 h[4][256]; u64 key[kStageRun]; u32 idx[kStageRun]; };
-    static_assert(offsetof(Lists, bin_b) == 0 && kCutB >= 4 * 256, "the histograms of block_select96 take the place of bin_b");
-    __shared__ union { Lists lists; Run run; } lds;
-    u32 (*h)[256] = lds.run.h;
+    __shared__ union { FinalizeLists lists; u64 run_key[kStageRun]; } lds;
+    FinalizeLists &ls = lds.lists;
+    u64 *const run_key = lds.run_key;
+    extern __shared__ u32 list_m[];             // finalize_claim(g) bytes
+    u32 *const run_idx = list_m;
+    u32 (*h)[256] = reinterpret_cast<u32 (*)[256]>(list_m + kStageRun);
     __shared__ u32 scan32[3 * kFinWaves + 1];
     __shared__ u64 scratch[2];
     __shared__ u32 extra_m, sure_extra;
@@ -2263,12 +2295,11 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             if (x * kQuad < g.W) qw[q] = load(x);
         }
     };
-    bool quick = false;         // what the lists add to the quads is in lds.lists.won
+    bool quick = false;         // what the lists add to the quads is in ls.won
     constexpr u32 kNotSent = 0xFFFFFFFFu, kSurelySent = 0xFFFFFFFEu;
-    if (__builtin_expect(!wide && lists && n_bd <= kStageB && n_m0 <= kStageM, 1)) {
-        Lists &ls = lds.lists;
+    if (__builtin_expect(!wide && lists && n_bd <= kStageB && n_m0 <= g.stage_m, 1)) {
         const bool with_b = !g.all_members;
-        for (u32 i = tid; i < kCutM; i += kFinThreads) ls.bin_m[i] = 0u;
+        for (u32 i = tid; i < kCutM / 2u; i += kFinThreads) ls.bin_m[i] = 0u;
         if (tid < kCutB) ls.bin_b[tid] = 0u;
         for (u32 i = tid; i < (g.W + 2u * kQuad - 1u) / (2u * kQuad) + 1u && i < kQuads / 2u; i += kFinThreads) ls.won[i] = 0u;
         if (tid < (u32)kWave) { ls.group_b[tid] = 0u; ls.group_m[tid] = 0u; }
@@ -2278,10 +2309,10 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
 #pragma unroll 4
         for (u32 j = 0; j < vb; ++j) ls.b_idx[eb + j] = j * g.G3 + tid;
 #pragma unroll 4
-        for (u32 j = 0; j < vm; ++j) ls.m[em + j] = j * g.G3 + tid;
+        for (u32 j = 0; j < vm; ++j) list_m[em + j] = j * g.G3 + tid;
         lds_barrier();
-        const CutBins<kCutB / kWave> cut_b{ls.bin_b, ls.group_b};
-        const CutBins<kCutM / kWave> cut_m{ls.bin_m, ls.group_m};
+        const CutBins<kCutB / kWave, false> cut_b{ls.bin_b, ls.group_b};
+        const CutBins<kCutM / kWave, true> cut_m{ls.bin_m, ls.group_m};
         const u32 chunk_shift = 31u - (u32)__clz((int)g.C), shift_b = bd_bits > 10u ? bd_bits - 10u : 0u;
         static_assert(kCutB == 1u << 10, "bits of a bin of B");
         auto word_m = [&](u32 at, u32 idx) { return at << kChunkBits | idx >> chunk_shift; };
@@ -2292,12 +2323,12 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
 #pragma unroll
             for (u32 q = 0; q < kAhead; ++q) {
                 const u32 p = p0 + q * kFinThreads;
-                e[q] = m_ent[p < n_m0 ? ls.m[p] : 0u];
+                e[q] = m_ent[p < n_m0 ? list_m[p] : 0u];
             }
 #pragma unroll
             for (u32 q = 0; q < kAhead; ++q) {
                 const u32 p = p0 + q * kFinThreads;
-                if (p < n_m0) { ls.m[p] = word_m(e[q].x, e[q].y); cut_m.add(e[q].x); }
+                if (p < n_m0) { list_m[p] = word_m(e[q].x, e[q].y); cut_m.add(e[q].x); }
             }
         }
         if (with_b)
@@ -2329,13 +2360,15 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 tb = wave_rank(ls.b_x[p], ls.b_idx[p], here, rank, &up_to);
                 lds_barrier();                  // (the candidates of the key cut come next)
             } else {
-                // many share it (a few levels): byte by byte, the bits that differ only
+                // many share it (a few levels): byte by byte, the bits that differ only (with
+                // histograms in the place of the counters of B, which every wavefront has looked at)
+                static_assert(kCutB >= 4 * 256, "histograms of block_select96");
                 lds_barrier();
                 const u64 low = (1ull << shift_b) - 1ull;
                 const u32 idx_shift = g.d > 1ull ? (u32)__clz((int)(u32)(g.d - 1ull)) : 31u;
                 tb = block_select96([&](auto &&f) {
                     each_here([&](u32 p) { f((u64)ls.b_x[p] & low, ls.b_idx[p] << idx_shift); });
-                }, rank, (64 - (int)shift_b) / 8, h, scratch, &ok);
+                }, rank, (64 - (int)shift_b) / 8, reinterpret_cast<u32 (*)[256]>(ls.bin_b), scratch, &ok);
                 if (!ok) err |= kErrSelect;
                 tb = Pair96{(u64)at << shift_b | tb.hi, tb.lo >> idx_shift};
             }
@@ -2402,7 +2435,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             if (!g.take_all) {
 #pragma unroll 1
                 for (u32 p = tid; p < n_m0; p += kFinThreads) {
-                    const u32 w = ls.m[p];
+                    const u32 w = list_m[p];
                     if (w >> kChunkBits == at) ls.cand[atomicAdd(&ls.n_cand_m, 1u)] = p;
                     else if (w >> kChunkBits < at) won(w & ((1u << kChunkBits) - 1u));
                 }
@@ -2586,9 +2619,9 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             n_mm = n_m0 + extra_m;
             if (n_mm <= kStageRun && n_mm <= m_cap) {
                 // short after all: the selection below reads it several times, from LDS then
-                for (u32 p = tid; p < n_mm; p += kFinThreads) { lds.run.key[p] = mk[p]; lds.run.idx[p] = mi[p]; }
-                mk = lds.run.key;
-                mi = lds.run.idx;
+                for (u32 p = tid; p < n_mm; p += kFinThreads) { run_key[p] = mk[p]; run_idx[p] = mi[p]; }
+                mk = run_key;
+                mi = run_idx;
                 lds_barrier();
             }
             const u64 c_klo = sure_walk + sure_extra;
@@ -2694,7 +2727,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         for (u32 q = 0; q < kSlabs; ++q) {
             const u32 x = 4u * (q * kFinThreads + tid);
             if (x * kQuad >= g.W) continue;
-            const u32 w01 = lds.lists.won[x / 2u], w23 = lds.lists.won[x / 2u + 1u];
+            const u32 w01 = ls.won[x / 2u], w23 = ls.won[x / 2u + 1u];
             qw[q].x += w01 & 0xFFFFu;
             qw[q].y += w01 >> 16;
             qw[q].z += w23 & 0xFFFFu;
@@ -2707,7 +2740,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         // nobody reads any more. (A lane per quad, whose loads fetch a line each: 155.7 us instead of
         // 151.4 after a missed key window at 25.6 M.)
         static_assert(kStageRun >= kQuads && kWave % kQuad == 0 && kQuad == 4, "room for the sums, whole quads per wavefront");
-        u32 *sum = lds.run.idx;
+        u32 *sum = run_idx;
         constexpr u32 kAhead = 8;
         for (u32 s0 = 0; s0 < g.W; s0 += kAhead * kFinThreads) {
             u32 c[kAhead];
@@ -3127,11 +3160,10 @@ std::mutex g_device_mutex;
 unsigned g_fused_grid[kMaxDevices];
 
 template <class K>
-bool allow_lds_claim(K kernel)
+bool allow_lds_claim(K kernel, unsigned bytes = kFusedLdsClaim)
 {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)kFusedLdsClaim) == hipSuccess;
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
 }
 
 // Wavefronts per workgroup of the streaming kernel, and its grid. A vector of up to 2048
@@ -3188,7 +3220,8 @@ int fused_grid_limit(unsigned *out)
     if (g_fused_grid[dev] == 0) {
         int cus = 0, fit_t = 0, fit_f = 0;
         if (!allow_lds_claim(k_fused<false, kLongRows, true>) || !allow_lds_claim(k_fused<false, kShortRows, true>) ||
-            !allow_lds_claim(k_fused<true, kLongRows, true>) || !allow_lds_claim(k_stream_add<kLongRows>))
+            !allow_lds_claim(k_fused<true, kLongRows, true>) || !allow_lds_claim(k_stream_add<kLongRows>) ||
+            !allow_lds_claim(k_finalize, 4u * kStageM))
             return RTOPK_EHIP;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_t, k_fused<false, kShortRows, true>,
@@ -3360,7 +3393,7 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
                 fin_grid = 256u / nb;
                 fin_grid = fin_grid > kWideBlocks ? kWideBlocks : (fin_grid < 16u ? 16u : fin_grid);
             }
-            k_finalize<<<dim3(fin_grid, 1, nb), kFinThreads, 0, stream>>>(B, gg, L);
+            k_finalize<<<dim3(fin_grid, 1, nb), kFinThreads, finalize_claim(gg), stream>>>(B, gg, L);
             RTOPK_LAUNCH_CHECK();
         }
         {

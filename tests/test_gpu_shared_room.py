@@ -62,12 +62,22 @@ def test_nearly_all_members_in_the_deciding_bin(d, hot, r, k, seed):
     assert not any(p & 3 for p in _encode(g, r, k, seed, steps=1))
 
 
-def test_more_keys_than_the_staging_area_holds():
-    """Random-k whose key window holds 21,400 keys (20,992 are staged)."""
-    d, k = 40_000_003, 2_500_000
+@pytest.mark.parametrize("k", [2_500_000, 3_500_000])
+def test_more_keys_than_the_staging_area_holds(k):
+    """Random-k whose key window holds 21,500 keys, which nearly fill the staging area, and 25,100 (23,936 are staged)."""
+    d = 40_000_003
     g = np.random.default_rng(4).standard_normal(d).astype(np.float32)
     print(f"key list d={d} k={k}", flush=True)
     assert _encode(g, d, k, 5, steps=1) == [0]
+
+
+@pytest.mark.parametrize("r,k", [(1, 1), (2, 1), (300, 1), (300, 299), (300, 300), (3_000, 40), (60_000, 59_999), (60_000, 30_000),
+                                 (300_007, 1), (300_007, 150_000), (300_007, 300_006)])
+def test_room_for_the_window_as_sizes_go(r, k):
+    """The room for keys follows the window's width: one-sided windows, all but one sent, half, none looked at."""
+    g = np.random.default_rng(r + k).standard_normal(300_007).astype(np.float32)
+    print(f"room r={r} k={k}", flush=True)
+    assert not any(p & 2 for p in _encode(g, r, k, 9))
 
 
 @pytest.mark.parametrize("tiles", [4096, 4097, 12289, 28672, 28673])  # runs of one, two, four and seven tiles; of eight,
