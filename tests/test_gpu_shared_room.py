@@ -20,23 +20,66 @@ def _encode(g, r, k, seed, steps=2, offset=0):
     return paths
 
 
-@pytest.mark.parametrize("d", [3_200_000, 6_300_001, 9_500_123])      # 1 to 2, 2 to 3, 3 to 4 chunks per wavefront of 3072
+def _stride(d):
+    """Elements between two chunks of one streaming wavefront: 2048 wavefronts up to 4096 chunks, 3072 above."""
+    return (2048 if d <= 4096 * 1024 else 3072) * 1024
+
+
+@pytest.mark.parametrize("d", [3_200_700, 6_300_001, 9_500_123])      # 1 to 2 chunks per wavefront of 2048; 2 to 3, 3 to 4 of 3072
 @pytest.mark.parametrize("hot", ["first", "last", "ragged", "same_wavefront", "all_of_one"])
 @pytest.mark.parametrize("k_of_r", [1, 2, 5])
 def test_chunks_share_their_wavefronts_room(d, hot, k_of_r):
     """Chunks that are members throughout, at the ends of a wavefront's part of the buffer, two of one
-    wavefront, and all of one wavefront's: with k = r none fits, with k = r / 5 one takes the others' room."""
-    stride = 3072 * 1024
+    wavefront, and all of one wavefront's. Up to 4096 chunks the stream keeps all of such a chunk, which never
+    fits; above, it keeps what may be sent: all with k = r, a half or a quarter else."""
+    stride = _stride(d)
     rng = np.random.default_rng(d + k_of_r)
     g = (rng.standard_normal(d) * 1e-3).astype(np.float32)
     starts = {"first": [0], "last": [(d // 1024 - 1) * 1024], "ragged": [d // 1024 * 1024],
               "same_wavefront": [5 * 1024, 5 * 1024 + stride], "all_of_one": range(7 * 1024, d, stride)}[hot]
+    hot_chunks = 0
     for s in starts:
         n = len(g[s:s + 1024])
+        assert n > 300                                                # (a hot chunk, also at the ragged end)
         g[s:s + 1024] = rng.standard_normal(n).astype(np.float32) * 5.0 + np.float32(20.0)
+        hot_chunks += 1
+    assert hot_chunks == {"all_of_one": -(-(d - 7 * 1024) // stride), "same_wavefront": 2}.get(hot, 1)
     r = 5_000
     print(f"shared room d={d} hot={hot} r={r} k={r // k_of_r}", flush=True)
     _encode(g, r, r // k_of_r, 3, offset=d % 4)
+
+
+@pytest.mark.parametrize("d", [3_200_700, 6_300_001])                 # candidates without their keys, and with them
+@pytest.mark.parametrize("count", [127, 128, 129, 191, 192, 193, 300])
+def test_room_left_by_the_wavefronts_other_chunk(d, count):
+    """A wavefront's two chunks have room for 2 * 128 entries, of which the first may take 192. The entries of
+    both are looked for in the workspace: what fits is there whole (so a share beyond 128 was taken), and of a
+    first chunk that does not fit, what the second one's slice, which then starts at the same place, left over."""
+    from tests import gpu_util as u
+    torch = u.torch
+    r, k, seed, second_count = 5_000, 2_500, 3, 60
+    rng = np.random.default_rng(d + count)
+    g = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    patterns = []
+    for chunk, n in ((100, count), (100 + _stride(d) // 1024, second_count)):
+        c0 = chunk * 1024
+        # certain winners, which every stream keeps: the window lies around half of the keys
+        sure = [i for i in range(c0, c0 + 1024) if oracle.key64(seed, 0, i) < int(0.4 * 2**64)]
+        places = np.sort(rng.permutation(np.array(sure))[:n])
+        assert len(places) == n
+        g[c0:c0 + 1024] = 0.0
+        # (low bits set: two samples of the estimate, the upper halves of two patterns, make no such word)
+        g[places] = (20.0 + 3 / 2**18 + chunk / 64 + np.arange(n) / 1024).astype(np.float32)
+        assert np.all(g[places].view(np.uint32) & 0xFF != 0)
+        patterns.append(torch.from_numpy(g[places].view(np.int32)).to(u.DEV))
+    print(f"room left d={d} count={count}", flush=True)
+    w = u.GpuWorker(d, r, k)
+    got = w.encode(g, seed, 0)
+    u.assert_encode_equal(got, oracle.encode(g, np.zeros(d, np.float32), r, k, seed, 0), f"d={d} count={count}")
+    words = w.ws.view(torch.int32)
+    first, second = (int(torch.isin(p, words).sum()) for p in patterns)
+    assert second == second_count
+    assert first == (count if count <= 192 else 192 - second_count), (first, count)
 
 
 @pytest.mark.parametrize("d,r,k,levels", [(200_003, 4_000, 900, 64), (200_003, 12_000, 1_500, 8), (1_048_576, 10_485, 1_048, 4),
