@@ -142,8 +142,8 @@ __device__ __forceinline__ u64 wave_lower_bounds(const u32 *__restrict__ idx, u3
 }
 
 // lane l gets lane l - 1's value, lane 0 gets `first` (by DPP: a shuffle goes through the LDS crossbar, and the
-// master kernels look at the neighbour's index once per worker and tile, between dependent LDS accesses. Eight workers
-// of 25.6 M: average 30.9 -> 29.6 us, momentum step 82.3 -> 81.5; k_update, five of 11.2 M, 16.6 -> 15.8)
+// master kernels look at the neighbour's index once per worker and tile, between dependent LDS accesses.
+// k_update, five workers of 11.2 M, 17.0 -> 15.8 us; the average and the momentum step, bound by their streams, the same)
 __device__ __forceinline__ u32 lane_left(u32 v, u32 first)
 {
     return (u32)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);

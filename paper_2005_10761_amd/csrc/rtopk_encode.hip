@@ -88,7 +88,6 @@
 #include <math.h>
 #include <cstddef>
 #include <mutex>
-#include <type_traits>
 #include <vector>
 
 namespace rtopk {
@@ -653,7 +652,7 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
             wave_pick_from_top<1>(h_max, top_s, want_cut, &bin_s[2], &before_s[2]);
         }
         lds_barrier();
-        cut_bucket = bin_s[2];                     // stays 0 when fewer than s_lo threads hold samples
+        cut_bucket = bin_s[2];                     // stays 0 when fewer than s_lo threads (or locations) hold samples
     }
     const int cut = (int)(cut_bucket << kBucketShift);    // >= 0: missing samples never pass
     u32 nzero = 0;
@@ -863,7 +862,8 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
     // chunk a tenth of the chunks of layered vectors overflowed and were read again by
     // both walking kernels: classify / emit of five vectors of 11.2 M elements, r = 5%, 29.1 / 27.5
     // us, with shared room 16.1 / 17.6; of four of 66 M with a twentieth of the rows
-    // touched 40.0 / 33.0 and 21.0 / 22.1 (the stream, which now stores those entries, 535 and 542).
+    // touched 40.0 / 33.0 and 21.0 / 22.1. The stream pays for it, as it stores those entries: the five 115.7 ->
+    // 118.2, the four 530 -> 541; 1% (53.9 -> 54.5 for one of 25.6 M) where hardly a chunk overflowed.
     const u32 w_first = blockIdx.x * n_waves + threadIdx.x / kWave;
     u32 later, at;          // chunks still to come; where in S the next slice starts
     {
@@ -2284,8 +2284,10 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
     //      which only the entries in the cut's own bin need), winners per chunk are read and added up by
     //      quads of chunks, and either cut is one pass over bins. Kernel, us, against lists of keys
     //      (16 and 12 bytes an entry, more than 8,192 keys in memory), a counter per chunk and a radix selection byte by
-    //      byte: one vector of 200,003 elements 12.2 -> 10.4, of 2^20 13.9 -> 11.1, of 25.6 M 18.2 -> 13.4, top-k
-    //      and random-k of 11.2 M 12.2 -> 8.8 and 17.0 -> 12.4, four of 2^28 (20,700 keys) 105 -> 37.
+    //      byte: one vector of 200,003 elements 12.7 -> 10.0, of 2^20 14.0 -> 10.5, of 25.6 M 18.1 -> 12.8, top-k
+    //      and random-k of 11.2 M 12.2 -> 8.5 and 17.2 -> 11.8, four of 2^28 (20,500 keys) 104 -> 35. (The loops
+    //      that note an entry's place, where crowded chunks leave 128 entries to one thread, go four at a
+    //      time: 65,536 elements with touched rows 12.4 -> 10.8, one at a time 12.8.)
     uint4 qw[kSlabs];
     auto load_quads = [&](auto &&load) {
 #pragma unroll
@@ -3197,13 +3199,13 @@ FusedShape fused_shape(u32 W, u64 d, unsigned nb, unsigned grid_limit)
 // Those of a long vector always: they take the time in which the stream waits for memory. A
 // short vector's stream has nothing to hide them behind, but where a launch's members have
 // many, the classify and emit kernels do less for it. us, unkeyed / keyed: one vector of
-// 300,007 elements, r = 1%, 36.9 / 37.9; eight of 2 M, r = 1% (160,000 in all), 85.2 / 83.4;
-// five of 950,000, r = 5% (238,000), 57.6 / 56.3; sixteen of 2 M, r = 10%, 176 / 155. Layered
-// vectors, in which most chunks with candidates overflow their slice, lose up to 4% by keys
-// between 130,000 and a million candidates. From an eighth of the vector on every chunk does
-// (sixteen of 2 M, r = 20%: 198.1 / 198.4). r == d, where the stream computes every element's
-// key to know the candidates: one vector of 300,007 24.5 / 24.6, two of 3.5 M 43.4 / 44.0;
-// eight of 2 M, k = 1%, 72.5 / 70.9, sixteen of 1 M 72.3 / 70.8.
+// 300,007 elements, r = 1%, 34.7 / 36.7; eight of 2 M, r = 1% (160,000 in all), 81.3 / 79.3; five of
+// 950,000, r = 5% (238,000), 53.3 / 51.6; sixteen of 2 M, r = 10%, 170 / 151; touched rows, four of
+// a million, r = 5%, 54.3 / 50.6. Layered vectors, whose crowded chunks have no others of their wavefront to
+// take room from, lose up to 2.5% by keys there (five of 950,000 56.1 / 57.4; four of 2 M, r = 10%, 75.6 / 77.3).
+// From an eighth of the vector on every chunk overflows (sixteen of 2 M, r = 20%: 187.7 / 187.5). r == d,
+// where the stream computes every element's key to know the candidates: one vector of 300,007 23.1 / 25.5, two of
+// 3.5 M 44.5 / 44.9; eight of 2 M, k = 1%, 69.4 / 66.8, sixteen of 1 M 69.8 / 67.5.
 constexpr u64 kKeyedMembers = 1u << 17, kKeyedElements = 1u << 23;
 bool keys_in_stream(const Geom &g, bool is_short, unsigned nb)
 {
