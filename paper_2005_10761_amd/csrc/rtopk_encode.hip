@@ -160,13 +160,15 @@ constexpr u32 kSlabs = kTargetChunks / (16 * kFinThreads); // 16-byte groups of 
 // Short lists that fit are selected in LDS (500 and 2,000 entries at r = 127,786, k = 25,558;
 // 4,300 and 20,500 at 2^28, r = 5%, k = 1%): of B an entry's magnitude and index, of M one word with
 // where in the window its key lies and its chunk. How long M gets is known beforehand: its mean and
-// eight standard deviations (staged_keys) are what a call's finalize kernel claims LDS for, as far as there
-// is any: 2^28 elements, k = 1% need 21,800 at r = 5 k, 23,100 at r = 10 k, 24,200 at r = d, which gets seven. With
-// room for 20,992 whatever the call / now, us: k_finalize of four such vectors, r = 5 k, 35 / 36, r = d 89 / 31.
-// What B needs is not known: about r / 3,000 at this length. At r = 5 k one vector in thirty has more than 4,608
-// entries (sixteen in a launch 53, but 100 to 126 in six launches of sixteen), at r = 10 k all do (6,800; 109 / 109): there
-// is no room for them beside M, and B in the claimed part costs ordinary calls 0.3 to 0.8 us. Two streams whose exact selections meet, each with a vector of
-// 11.2 M 304 / 293, of 66 M 750 / 728: a unit taken whole has no room for the other stream's kernels.
+// eight standard deviations (staged_keys) are what a call's finalize kernel claims LDS for, as far as
+// there is any: 2^28 elements, k = 1% need 21,800 at r = 5 k, 23,100 at r = 10 k, 24,200 at r = d, which
+// gets seven. With room for 20,992 whatever the call / now, us: k_finalize of four such vectors, r = 5 k,
+// 35 / 36, r = d 89 / 31. Two streams whose exact selections meet, each with a vector of 11.2 M 304 / 293,
+// of 66 M 750 / 728: a unit taken whole has no room for the other stream's kernels.
+// What B needs is not known: about r / 3,000 at that length. At r = 5 k one vector in thirty has more than
+// 4,608 entries (sixteen in a launch 53, but 100 to 126 in six launches of sixteen), at r = 10 k all do
+// (6,800; 109 / 109): there is no room for them beside M, and B in the claimed part costs ordinary
+// calls 0.3 to 0.8 us.
 constexpr u32 kStageB = 4608, kStageM = 23936;
 constexpr u32 kStageRun = 8192;               // keys of a run of equal magnitudes that are selected in LDS
 constexpr u32 kChunkBits = 15;
