@@ -2386,18 +2386,18 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 const u32 x = ls.b_x[p], idx = ls.b_idx[p];
                 bool sure = pair_le((u64)x, idx, tb);
                 my_gt += (u64)x < tb.hi ? 1u : 0u;
-                u32 verdict = kNotSent;
+                u32 standing = kNotSent;
                 if (sure && g.take_all == 0u) {
                     const u64 key = sample_key(idx, seed);
                     sure = key < g.K_lo;
                     if (!sure && key <= g.K_hi) {
-                        verdict = (u32)(((key - g.K_lo) << g.k_nlz) >> (64 - kWindowBits));
-                        cut_m.add(verdict);
+                        standing = (u32)(((key - g.K_lo) << g.k_nlz) >> (64 - kWindowBits));
+                        cut_m.add(standing);
                         ++my_extra;
                     }
                 }
-                if (sure) { verdict = kSurelySent; ++my_sure; }
-                ls.b_x[p] = verdict;            // from here on: these two, or where in the window its key lies
+                if (sure) { standing = kSurelySent; ++my_sure; }
+                ls.b_x[p] = standing;            // from here on: these two, or where in the window its key lies
             }
             my_extra = wave_sum(my_extra);
             if (lane == 0 && my_extra) atomicAdd(&extra_m, my_extra);
@@ -2428,10 +2428,10 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             if (with_b)
 #pragma unroll 1
                 for (u32 p = tid; p < n_bd; p += kFinThreads) {
-                    const u32 verdict = ls.b_x[p], idx = ls.b_idx[p];
-                    if (verdict == kSurelySent || (verdict != kNotSent && verdict < at)) {
+                    const u32 standing = ls.b_x[p], idx = ls.b_idx[p];
+                    if (standing == kSurelySent || (standing != kNotSent && standing < at)) {
                         won(idx >> chunk_shift);
-                    } else if (verdict != kNotSent && verdict == at) {
+                    } else if (standing != kNotSent && standing == at) {
                         const u32 j = atomicAdd(&ls.n_cand_m, 1u);
                         ls.cand[j] = kNotSent;          // (not in M)
                         ls.cand_idx[j] = idx;
