@@ -21,6 +21,16 @@ struct PhiloxSeed {
     u32 seed_lo, seed_hi, step_lo, step_hi;
 };
 
+// a ^ b ^ c as one instruction (the compiler makes two v_xor_b32 of it)
+__device__ __forceinline__ u32 xor3(u32 a, u32 b, u32 c)
+{
+    return (u32)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+
+// What bounds the kernels that key every element (r == d) is the issue of these ten rounds: a product
+// holds its SIMD for 16 cycles, an exclusive or for 4. Two of the twenty products and half of the first two
+// rounds belong to the wavefront alone (the step and the seed); the others take one product and one
+// three-way exclusive or per word. k_fused of 11.2 M elements, r = d: see the kernel.
 __device__ __forceinline__ u64 sample_key(u32 index, const PhiloxSeed &s)
 {
     u32 c0 = index, c1 = 0u, c2 = s.step_lo, c3 = s.step_hi;
@@ -31,8 +41,9 @@ __device__ __forceinline__ u64 sample_key(u32 index, const PhiloxSeed &s)
         const u64 p0 = (u64)0xD2511F53u * c0, p1 = (u64)0xCD9E8D57u * c2;
         const u32 hi0 = (u32)(p0 >> 32), lo0 = (u32)p0;
         const u32 hi1 = (u32)(p1 >> 32), lo1 = (u32)p1;
-        const u32 n0 = hi1 ^ c1 ^ k0;
-        const u32 n2 = hi0 ^ c3 ^ k1;
+        // (rounds 0 and 1: what does not depend on the index first, it is scalar)
+        const u32 n0 = i < 2 ? hi1 ^ (c1 ^ k0) : xor3(hi1, c1, k0);
+        const u32 n2 = i < 1 ? hi0 ^ (c3 ^ k1) : xor3(hi0, c3, k1);
         c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;

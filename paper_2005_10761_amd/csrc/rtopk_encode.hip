@@ -837,9 +837,10 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if (kAll) {
+                // (by the key's leading word: one of 2^32 candidates more, which classify leaves out)
                 hit[e] = valid[e] &&
                          (g.take_all != 0u ||
-                          sample_key((u32)elem_index(c0 + place, e), seed) <= g.K_hi);
+                          (u32)(sample_key((u32)elem_index(c0 + place, e), seed) >> 32) <= (u32)(g.K_hi >> 32));
             } else {
                 const u32 m = mag_of(bits[e]);
                 hit[e] = valid[e] && m >= bins.t_lo;
