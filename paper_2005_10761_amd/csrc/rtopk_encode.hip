@@ -268,6 +268,7 @@ struct Geom {
     u32 cap;            // entries of S per chunk (C / kSliceDiv)
     u32 W;              // chunks
     u32 each, over;     // of them per wavefront of the streaming kernel; its first `over` wavefronts stream one more
+    u32 spread;         // neighbouring wavefronts (as the chunks are dealt out) are of different workgroups
     u32 U;              // wavefronts of classify / emit; wavefront u walks chunks u, u + U, ...
     u32 UC;             // ... at most this many of them (W <= U * UC)
     u32 G3;             // classify / emit workgroups
@@ -786,8 +787,8 @@ struct Ring {
 // fused: a = g + m -> residual buffer; candidates -> S and the histogram.
 // Reads g and m once, writes a once: 12d bytes of HBM traffic. The grid is
 // sized to what the device holds at once; wavefront v takes chunks v,
-// v + #wavefronts, ... so that neighbouring wavefronts stream neighbouring
-// 4 KB pieces of each array.
+// v + #wavefronts, ... so that neighbouring wavefronts (deals_across says which those are)
+// stream neighbouring 4 KB pieces of each array.
 // ---------------------------------------------------------------------------
 constexpr u32 kFusedThreads = 768;            // at most; a launch takes 4 to 12 wavefronts, see fused_waves
 // kRows: rows of 256 elements a wavefront adds, stores and looks at together; the
@@ -868,7 +869,8 @@ fused_body(const float *__restrict__ grad, float *__restrict__ residual, Geom g,
     // us, with shared room 16.1 / 17.6; of four of 66 M with a twentieth of the rows
     // touched 40.0 / 33.0 and 21.0 / 22.1. The stream pays for it, as it stores those entries: the five 115.7 ->
     // 118.2, the four 530 -> 541; 1% (53.9 -> 54.5 for one of 25.6 M) where hardly a chunk overflowed.
-    const u32 w_first = blockIdx.x * n_waves + threadIdx.x / kWave;
+    const u32 w_first = g.spread != 0u ? threadIdx.x / kWave * gridDim.x + blockIdx.x
+                                       : blockIdx.x * n_waves + threadIdx.x / kWave;
     u32 later, at;          // chunks still to come; where in S the next slice starts
     {
         later = g.each + (w_first < g.over ? 1u : 0u);
@@ -3218,6 +3220,21 @@ bool keys_in_stream(const Geom &g, bool is_short, unsigned nb)
     return nb * g.r >= kKeyedMembers && g.r * kSliceDiv < g.d;
 }
 
+// How the chunks are dealt to the wavefronts: workgroup by workgroup (neighbouring wavefronts of one
+// workgroup stream neighbouring chunks) or across the workgroups, so that the last, incomplete round of
+// chunks is a few wavefronts of every compute unit and not all wavefronts of some. us, by workgroup /
+// across: one vector of 11.2 M elements 67.0 / 66.2, of 21 M 90.8 / 88.6, of 25.6 M 97.8 / 95.5, of 40 M
+// 131.0 / 128.7, of 66 M 183.7 / 182.6, but of 100 M 263.9 / 271.3 and of 180 M 452 / 457; a batch, which
+// has no incomplete round but the last member's, loses locality: four of 11.2 M 140.4 / 144.0, eight of 5 M
+// 136 / 146, four of 66 M 610 / 623, eight of 25.6 M 472 / 471. With r == d the keys are what a unit is busy with, in
+// a batch too: one of 11.2 M 51.9 / 48.8, of 66 M 206.6 / 197.1, eight of 11.2 M 255.8 / 247.5; four of 6 M 90.2 / 90.7.
+constexpr u64 kAcrossMax = 1u << 26, kAcrossKeyed = 1u << 23;
+bool deals_across(const Geom &g, bool is_short, unsigned nb)
+{
+    if (is_short) return false;
+    return g.all_members ? g.d >= kAcrossKeyed : nb == 1u && g.d <= kAcrossMax;
+}
+
 int fused_grid_limit(unsigned *out)
 {
     int dev = 0;
@@ -3321,6 +3338,7 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         const u32 stream_waves = fgrid * (fs.threads / (unsigned)kWave);
         gg.each = g.W / stream_waves;
         gg.over = g.W % stream_waves;
+        gg.spread = deals_across(gg, fs.is_short, nb) ? 1u : 0u;
         Batch B{};
         for (unsigned i = 0; i < nb; ++i) {
             B.grad[i] = grad[first + i];
