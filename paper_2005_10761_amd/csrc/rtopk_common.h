@@ -9,6 +9,7 @@ namespace rtopk {
 
 constexpr int kWave = 64;
 
+using u16 = uint16_t;
 using u32 = uint32_t;
 using u64 = uint64_t;
 

@@ -1,5 +1,5 @@
 // rtopk_encode: one node-side step of Algorithm 1 (error compensation, the
-// rTop-k operator of Definition 3, residual write-back) as a chain of six or seven
+// rTop-k operator of Definition 3, residual write-back) as a chain of four to seven
 // gfx950 kernels that stream the gradient and the residual exactly once
 // (12d bytes). All cross-kernel state lives in the caller's workspace.
 //
@@ -32,8 +32,8 @@
 //              a-priori window [K_lo, K_hi] around the k-th smallest of r
 //              uniform keys; an entry above the fine range whose key lies above
 //              the window will not be sent, the others -> S with what the key said
-//              (a short vector with few candidates: all of them -> S, unkeyed)
-//   pick       one workgroup (short vectors: every classify workgroup for itself):
+//              (a vector of 3 to 4 M elements with few candidates: all of them -> S, unkeyed)
+//   pick       one workgroup (short vectors: every classify workgroup for itself, as a rule):
 //              the group sums of all rows -> the group that
 //              holds the r-th largest magnitude; that group's bins of all
 //              rows -> the bin that holds it (the deciding bin)
@@ -58,6 +58,9 @@
 //              index order, starting at the quad's prefix plus the winners of the quad's
 //              earlier chunks; residual at the
 //              sent positions <- a - a
+// A short vector (counts_all) has no sample and no estimate: its magnitudes are all
+// counted while they are added (count), and classify, once it has picked the
+// deciding bin, makes S from the vector, which is still in the caches.
 // Two special cases of Definition 3 take shortcuts: with k == r (top-k) no
 // sampling key is ever computed, and with r == d (random-k) no magnitude is
 // ever compared: the streaming kernel then keeps the elements whose key lies
@@ -326,6 +329,7 @@ static Geom make_geom(u64 d, u64 r, u64 k)
     g.U = g.W < kMaxUnits ? g.W : kMaxUnits;
     g.UC = kUnitChunks;
     g.G3 = (g.U + kWalkWaves - 1) / kWalkWaves;       // (the layout is sized for this many)
+    // (Vectors that are counted have no sample, see counts_all.)
     // A wide bracket is enough for a short vector, whose few candidates cost the walking
     // kernels nothing, and the estimate's one workgroup is a good part of its time: 4-6
     // instead of 10 us with a quarter of the samples. With 80 samples in the top r the
@@ -1299,7 +1303,6 @@ __device__ __forceinline__ auto each_of_row(F &&f)
 // above that group), then that group's bins of all rows.
 // ---------------------------------------------------------------------------
 constexpr u32 kPickThreads = 1024;
-constexpr u32 kPickRows = 128, kPickMembers = 2;   // up to here the classify workgroups pick for themselves
 
 // the deciding bin: its pattern range and the entries above it
 struct Picked {
@@ -1333,8 +1336,6 @@ __device__ __forceinline__ void wave_pick_desc(u32 count, u64 need, u64 above_al
     *above = ((u64)b_hi << 32) | b_lo;
 }
 
-// (by all threads of a workgroup of kThreads; every thread gets the result)
-template <u32 kThreads>
 __device__ __forceinline__ Picked
 pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, u32 n_rows, const Geom &g,
           const EncodeCtl *ctl)
@@ -1356,16 +1357,16 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
     {
         constexpr u32 kAhead = 4;
         const u32 words = n_rows * ngroups;
-        for (u32 i0 = tid; i0 < words; i0 += kAhead * kThreads) {
+        for (u32 i0 = tid; i0 < words; i0 += kAhead * kPickThreads) {
             u32 v[kAhead];
 #pragma unroll
             for (u32 q = 0; q < kAhead; ++q) {
-                const u32 i = i0 + q * kThreads;
+                const u32 i = i0 + q * kPickThreads;
                 v[q] = i < words ? group_sums[(u64)(i / ngroups) * kMaxGroups + i % ngroups] : 0u;
             }
 #pragma unroll
             for (u32 q = 0; q < kAhead; ++q) {
-                const u32 i = i0 + q * kThreads;
+                const u32 i = i0 + q * kPickThreads;
                 if (v[q]) atomicAdd(&gtot[i % ngroups], v[q]);
             }
         }
@@ -1395,17 +1396,17 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
         const u32 first_bin = sel_group * kCoarseSpan;
         constexpr u32 kAhead = 16;
         const u32 words = n_rows * kCoarseSpan;
-        for (u32 i0 = tid; i0 < words; i0 += kAhead * kThreads) {
+        for (u32 i0 = tid; i0 < words; i0 += kAhead * kPickThreads) {
             u32 v[kAhead];
 #pragma unroll
             for (u32 q = 0; q < kAhead; ++q) {
-                const u32 i = i0 + q * kThreads;
+                const u32 i = i0 + q * kPickThreads;
                 const u32 b = first_bin + i % kCoarseSpan;
                 v[q] = (i < words && b < nbins) ? partials[(u64)(i / kCoarseSpan) * nbins + b] : 0u;
             }
 #pragma unroll
             for (u32 q = 0; q < kAhead; ++q) {
-                const u32 i = i0 + q * kThreads;
+                const u32 i = i0 + q * kPickThreads;
                 if (v[q]) atomicAdd(&btot[i % kCoarseSpan], v[q]);
             }
         }
@@ -1434,6 +1435,209 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
 }
 
 // ---------------------------------------------------------------------------
+// count: what a short vector has in the place of sample, estimate and fused. a = g + m ->
+// residual buffer, and EVERY magnitude is counted by its leading 15 bits in the workgroup's histogram: no
+// bracket is needed, and no candidates are kept: classify reads the vector again (a few MB, still
+// in the caches) once the deciding bin is known. Two launches and their dependent trips less, for an LDS
+// addition per element, which a short vector's stream (one chunk per wavefront, all its loads in
+// flight at once) waits long enough for.
+//
+// A bin is a 128th of an octave wide; a group of kGroupBins bins is an octave. The row a workgroup
+// stores: the sums of all 256 groups (two bytes each), and the bins of the groups it has anything
+// in. Those lie in kRowSlots slots, group e in slot e mod kRowSlots: of groups that meet there the
+// highest one that is not empty, the others are marked kNotStored in their sums (that takes magnitudes 64
+// octaves apart in one workgroup; should one of those groups decide, the vector itself is walked).
+// Magnitudes in bin 0 (zeros, mostly, which come in long runs) are not counted: what the
+// others do not account for lies there.
+// ---------------------------------------------------------------------------
+constexpr u32 kCountShift = 16, kCountBins = 1u << (31 - kCountShift);
+constexpr u32 kGroupBins = 128, kCountGroups = kCountBins / kGroupBins;
+constexpr u32 kRowSlots = 64, kNotStored = 0x8000u;
+constexpr u32 kRowWords = kRowSlots * kGroupBins / 2;    // of a row's bins, two to a word
+constexpr u32 kCountRows = 128;               // rows at most
+constexpr u32 kCountChunks = 3072;            // chunks of a vector at most
+constexpr u32 kCountThreads = 1024;           // at most
+static_assert((u64)kCountRows * kRowWords * 4 <= (u64)kMaxFusedBlocks * kMaxBins * 4, "the rows lie where the others would");
+static_assert((u64)kCountRows * kCountGroups * 2 <= (u64)kSampleLoc * 8, "the sums lie where the samples would");
+// chunks of a workgroup at most: one per wavefront, or one more for half of them
+constexpr u32 kCountEach = kCountThreads / kWave * 3 / 2;
+static_assert(kCountEach * kMinChunk < kNotStored && kCountEach * kCountRows >= kCountChunks, "sums leave the mark's bit free");
+
+// every lane gets the sum over its row of 16 lanes
+__device__ __forceinline__ u32 row_sum(u32 v)
+{
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x128 /* row_ror:8 */, 0xF, 0xF, false);
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, false);
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xF, 0xF, false);
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xF, 0xF, false);
+    return v;
+}
+
+constexpr u32 kChunkRows = kMinChunk / kChunkQuantum;
+
+__device__ __forceinline__ void
+count_body(const float *__restrict__ grad, float *__restrict__ residual, const Geom &g, u32 *__restrict__ zero_base,
+           u32 zero_words, u16 *__restrict__ sums, uint4 *__restrict__ rows)
+{
+    __shared__ uint4 h4[kCountBins / 8];
+    u32 *const h = reinterpret_cast<u32 *>(h4);
+    const u32 lane = lane_id(), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
+    f32x4 gv[kChunkRows], mv[kChunkRows];
+    auto load = [&](u64 c0) {
+        const f32x4u *gp = reinterpret_cast<const f32x4u *>(grad + c0) + lane, *mp = reinterpret_cast<const f32x4u *>(residual + c0) + lane;
+#pragma unroll
+        for (u32 q = 0; q < kChunkRows; ++q) {
+            gv[q] = __builtin_nontemporal_load(gp + q * kWave);
+            mv[q] = mp[q * kWave];
+        }
+    };
+    const u32 w_full = (u32)(g.d / kMinChunk), stride = gridDim.x * n_waves;
+    u32 w = wave * gridDim.x + blockIdx.x;      // (a second round is a few wavefronts of every workgroup)
+    if (w < w_full) load((u64)w * kMinChunk);
+    for (u32 i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_words; i += gridDim.x * blockDim.x) zero_base[i] = 0u;
+    for (u32 i = threadIdx.x; i < kCountBins / 8; i += blockDim.x) h4[i] = make_uint4(0u, 0u, 0u, 0u);
+    lds_barrier();
+    auto count = [&](float a) {
+        const u32 b = mag_of(__float_as_uint(a)) >> kCountShift;
+        if (b != 0u) atomicAdd(&h[b / 2u], 1u << (16u * (b & 1u)));
+    };
+    for (; w < w_full; w += stride) {
+        f32x4u *mp = reinterpret_cast<f32x4u *>(residual + (u64)w * kMinChunk) + lane;
+        f32x4 a[kChunkRows];
+#pragma unroll
+        for (u32 q = 0; q < kChunkRows; ++q) {
+            a[q] = gv[q] + mv[q];
+            mp[q * kWave] = a[q];
+        }
+        if (w + stride < w_full) load((u64)(w + stride) * kMinChunk);
+#pragma unroll
+        for (u32 q = 0; q < kChunkRows; ++q)
+#pragma unroll
+            for (u32 e = 0; e < 4; ++e) count(a[q][e]);
+    }
+    if (w == w_full)
+        for (u64 i = (u64)w * kMinChunk + lane; i < g.d; i += kWave) {
+            const float a = grad[i] + residual[i];
+            residual[i] = a;
+            count(a);
+        }
+    lds_barrier();
+    // ---- the row: sixteen lanes per slot, the highest group first
+    constexpr u32 kMeet = kCountGroups / kRowSlots;
+    const u32 part = lane % 16u;
+    u16 *my_sums = sums + blockIdx.x * kCountGroups;
+    for (u32 slot = threadIdx.x / 16u; slot < kRowSlots; slot += blockDim.x / 16u) {
+        uint4 c[kMeet];
+#pragma unroll
+        for (u32 x = 0; x < kMeet; ++x) c[x] = h4[(slot + x * kRowSlots) * (kGroupBins / 8u) + part];
+        bool taken = false;
+#pragma unroll
+        for (u32 x = kMeet; x-- > 0;) {
+            const u32 two = c[x].x + c[x].y + c[x].z + c[x].w;
+            u32 sum = row_sum((two & 0xFFFFu) + (two >> 16));
+            if (sum != 0u) {
+                if (!taken) rows[((u64)blockIdx.x * kRowSlots + slot) * (kGroupBins / 8u) + part] = c[x];
+                else sum |= kNotStored;
+                taken = true;
+            }
+            if (part == 0u) my_sums[slot + x * kRowSlots] = (u16)sum;
+        }
+    }
+}
+
+// the deciding bin from those rows, by all threads of a workgroup (every thread gets the result)
+template <u32 kThreads>
+__device__ __forceinline__ Picked
+pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n_rows, const Geom &g)
+{
+    __shared__ u32 gtot[kCountGroups], btot[kGroupBins], lost_s;
+    const u32 tid = threadIdx.x, lane = lane_id();
+    for (u32 i = tid; i < kCountGroups; i += kThreads) gtot[i] = 0u;
+    if (tid < kGroupBins) btot[tid] = 0u;
+    if (tid == 0) lost_s = 0u;
+    // ---- all rows' sums: a thread takes eight groups of every (kThreads / 32)-th row
+    constexpr u32 kAt = kCountGroups / 8u, kAhead = 8;
+    u32 sum[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+    auto add_up = [&](const uint4 &v, u32 mask) {
+        const u32 w[4] = {v.x & mask, v.y & mask, v.z & mask, v.w & mask};
+#pragma unroll
+        for (u32 c = 0; c < 4; ++c) { sum[2 * c] += w[c] & 0xFFFFu; sum[2 * c + 1] += w[c] >> 16; }
+    };
+    const uint4 *s4 = reinterpret_cast<const uint4 *>(sums);
+    for (u32 r0 = tid / kAt; r0 < n_rows; r0 += kAhead * (kThreads / kAt)) {
+        uint4 v[kAhead];
+#pragma unroll
+        for (u32 q = 0; q < kAhead; ++q) {
+            const u32 row = r0 + q * (kThreads / kAt);
+            v[q] = make_uint4(0u, 0u, 0u, 0u);
+            if (row < n_rows) v[q] = s4[row * kAt + tid % kAt];
+        }
+#pragma unroll
+        for (u32 q = 0; q < kAhead; ++q) add_up(v[q], 0x7FFF7FFFu);
+    }
+    lds_barrier();
+#pragma unroll
+    for (u32 c = 0; c < 8; ++c) if (sum[c]) atomicAdd(&gtot[tid % kAt * 8u + c], sum[c]);
+    lds_barrier();
+    // every wavefront finds the group for itself: lane l holds the l-th four groups from the top
+    static_assert(kCountGroups == 4 * kWave && kGroupBins == 2 * kWave, "groups and bins per lane");
+    u32 c4[4], mine = 0;
+#pragma unroll
+    for (u32 q = 0; q < 4; ++q) { c4[q] = gtot[kCountGroups - 1u - 4u * lane - q]; mine += c4[q]; }
+    const u32 need = (u32)g.r;
+    u32 inc = wave_inclusive_sum(mine);
+    u64 owner = __ballot(inc - mine < need && need <= inc);
+    if (owner == 0ull)       // the zeros decide
+        return Picked{0u, 0u, (1u << kCountShift) - 1u, (u32)__builtin_amdgcn_readlane((int)inc, kWave - 1)};
+    u32 group = 0, above = inc - mine;
+#pragma unroll
+    for (u32 q = 0; q < 3; ++q)
+        if (group == q && above + c4[q] < need) { above += c4[q]; ++group; }
+    int src = __ffsll((unsigned long long)owner) - 1;
+    group = kCountGroups - 1u - 4u * (u32)src - (u32)__builtin_amdgcn_readlane((int)group, src);
+    above = (u32)__builtin_amdgcn_readlane((int)above, src);
+    // ---- that group's bins of the rows that have some
+#pragma unroll
+    for (u32 c = 0; c < 8; ++c) sum[c] = 0u;
+    u32 marks = 0;
+    constexpr u32 kOf = kGroupBins / 8u;
+    for (u32 r0 = tid / kOf; r0 < n_rows; r0 += kAhead * (kThreads / kOf)) {
+        uint4 v[kAhead];
+        u32 has[kAhead];
+#pragma unroll
+        for (u32 q = 0; q < kAhead; ++q) {
+            const u32 row = r0 + q * (kThreads / kOf);
+            v[q] = make_uint4(0u, 0u, 0u, 0u);
+            has[q] = 0u;
+            if (row < n_rows) {
+                has[q] = sums[row * kCountGroups + group];
+                v[q] = rows[((u64)row * kRowSlots + group % kRowSlots) * kOf + tid % kOf];
+            }
+        }
+#pragma unroll
+        for (u32 q = 0; q < kAhead; ++q) {
+            marks |= has[q] & kNotStored;
+            add_up(v[q], has[q] != 0u ? ~0u : 0u);
+        }
+    }
+#pragma unroll
+    for (u32 c = 0; c < 8; ++c) if (sum[c]) atomicAdd(&btot[tid % kOf * 8u + c], sum[c]);
+    if (marks != 0u) lost_s = 1u;
+    lds_barrier();
+    if (lost_s != 0u) return Picked{1u, 0u, 0u, 0ull};
+    const u32 b0 = btot[kGroupBins - 1u - 2u * lane], b1 = btot[kGroupBins - 2u - 2u * lane];
+    inc = wave_inclusive_sum(b0 + b1);
+    u32 before = above + inc - b0 - b1;
+    owner = __ballot(before < need && need <= before + b0 + b1);
+    src = owner != 0ull ? __ffsll((unsigned long long)owner) - 1 : 0;
+    u32 bin = group * kGroupBins + kGroupBins - 1u - 2u * lane;
+    if (before + b0 < need) { before += b0; --bin; }
+    bin = (u32)__builtin_amdgcn_readlane((int)bin, src);
+    before = (u32)__builtin_amdgcn_readlane((int)before, src);
+    return Picked{0u, bin << kCountShift, (bin << kCountShift) | ((1u << kCountShift) - 1u), before};
+}
+
+// ---------------------------------------------------------------------------
 // classify: walk S; certain members are keyed against the window, entries
 // of the deciding bin go to the short list B. Of the deciding bin it also
 // leaves the number of entries per chunk and the smallest and largest
@@ -1443,7 +1647,7 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
 // a known rank in index order, which those counts locate.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void
-classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const float *__restrict__ a,
+classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const float *__restrict__ a,
            const uint2 *__restrict__ seg, const uint2 *__restrict__ s_ent,
            u32 *__restrict__ win_cnt, u32 *__restrict__ bd_cnt, u32 *__restrict__ quad_win,
            uint2 *__restrict__ blk_lists, u32 *__restrict__ blk_bmin,
@@ -1455,8 +1659,8 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
     __shared__ uint2 row_queue[kWalkWaves][kRowQueue];
     const u32 wave = threadIdx.x / kWave, lane = lane_id();
     const u32 u = blockIdx.x * kWalkWaves + wave;
-    const bool undecided = (now ? now->mode : ctl->mode) != 0u;
-    const u32 bd_lo = now ? now->bd_lo : ctl->bd_lo, bd_hi = now ? now->bd_hi : ctl->bd_hi;
+    const bool undecided = ctl->mode != 0u;
+    const u32 bd_lo = ctl->bd_lo, bd_hi = ctl->bd_hi;
     if (undecided) {
         if (threadIdx.x == 0) {
             blk_lists[blockIdx.x] = make_uint2(0u, 0u);
@@ -1536,6 +1740,126 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const Picked *now, const 
     if (threadIdx.x == 0) {
         const u32 in_m = cnt_m < kListCap ? cnt_m : kListCap, in_b = cnt_b < kListCap ? cnt_b : kListCap;
         blk_lists[blockIdx.x] = make_uint2(in_m | in_b << 16, cnt_sure);
+        blk_bmin[blockIdx.x] = bmin_s;
+        blk_bmax[blockIdx.x] = bmax_s;
+        if (cnt_m > kListCap || cnt_b > kListCap) ctl->overflow = 1u;
+        if (cnt_m > kListCap) ctl->overflow_m = 1u;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// classify of a counted vector: every wavefront has one chunk of it, whose elements it has loaded
+// before the deciding bin is known. What lies in the deciding bin or above it becomes the
+// chunk's slice of S, keyed, and goes through the short lists and counters as in classify_body: from
+// here on the call goes as any other.
+// ---------------------------------------------------------------------------
+struct ChunkRows {
+    f32x4 v[kChunkRows];
+    u32 len;                // elements of the chunk (0 beyond the vector)
+    __device__ __forceinline__ ChunkRows(const float *__restrict__ a, u64 d, u32 s)
+    {
+        const u64 c0 = (u64)s * kMinChunk;
+        len = c0 >= d ? 0u : d - c0 < kMinChunk ? (u32)(d - c0) : kMinChunk;
+        const float *p = a + c0 + 4u * lane_id();
+        if (len == kMinChunk) {
+#pragma unroll
+            for (u32 q = 0; q < kChunkRows; ++q) v[q] = *reinterpret_cast<const f32x4u *>(p + q * kChunkQuantum);
+        } else {
+#pragma unroll
+            for (u32 q = 0; q < kChunkRows; ++q)
+#pragma unroll
+                for (u32 e = 0; e < 4; ++e) v[q][e] = q * kChunkQuantum + 4u * lane_id() + e < len ? p[q * kChunkQuantum + e] : 0.0f;
+        }
+    }
+};
+
+__device__ __forceinline__ void
+classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, const Picked &now,
+                 uint2 *__restrict__ seg, uint2 *__restrict__ s_ent, u32 *__restrict__ win_cnt,
+                 u32 *__restrict__ bd_cnt, u32 *__restrict__ quad_win, uint2 *__restrict__ blk_lists,
+                 u32 *__restrict__ blk_bmin, u32 *__restrict__ blk_bmax, uint2 *__restrict__ m_ent,
+                 uint2 *__restrict__ b_ent)
+{
+    __shared__ u32 cnt_m, cnt_b, bmin_s, bmax_s, sure_s[kWalkWaves];
+    __shared__ uint2 hits[kWalkWaves][kMinChunk];
+    const u32 wave = threadIdx.x / kWave, lane = lane_id();
+    const u32 s = blockIdx.x * kWalkWaves + wave;
+    const u64 below = lanes_below();
+    if (threadIdx.x == 0) { cnt_m = 0u; cnt_b = 0u; bmin_s = 0xFFFFFFFFu; bmax_s = 0u; }
+    lds_barrier();
+    // ---- the entries, in index order
+    u32 n = 0;
+    if (now.mode == 0u) {
+#pragma unroll
+        for (u32 q = 0; q < kChunkRows; ++q) {
+            const u32 place = q * kChunkQuantum + 4u * lane;
+            bool hit[4];
+            u64 b[4];
+#pragma unroll
+            for (u32 e = 0; e < 4; ++e) {
+                hit[e] = place + e < chunk.len && mag_of(__float_as_uint(chunk.v[q][e])) >= now.bd_lo;
+                b[e] = __ballot(hit[e]);
+            }
+            if ((b[0] | b[1] | b[2] | b[3]) == 0ull) continue;
+            u32 p = n + popc64(b[0] & below) + popc64(b[1] & below) + popc64(b[2] & below) + popc64(b[3] & below);
+#pragma unroll
+            for (u32 e = 0; e < 4; ++e)
+                if (hit[e]) { hits[wave][p] = make_uint2(place + e, __float_as_uint(chunk.v[q][e])); ++p; }
+            n += popc64(b[0]) + popc64(b[1]) + popc64(b[2]) + popc64(b[3]);
+        }
+    }
+    wave_lds_fence();
+    u32 kept = 0;           // entries of the slice (above g.cap: too many, the chunk will be read from the vector)
+    // entry p of this workgroup's short lists lives at [p][workgroup]
+    auto slot = [&](u32 p) { return (u64)p * g.G3 + blockIdx.x; };
+    // places for the lanes that are here in a list of the workgroup: one addition
+    auto places = [&](u32 *count, u64 here) {
+        u32 base = 0;
+        if ((here & below) == 0ull) base = atomicAdd(count, popc64(here));
+        return (u32)__builtin_amdgcn_readfirstlane((int)base) + popc64(here & below);
+    };
+    u32 sure = 0, in_bin = 0, lane_bmin = 0xFFFFFFFFu, lane_bmax = 0u;
+    for (u32 j0 = 0; j0 < n; j0 += kWave) {
+        const u32 j = j0 + lane;
+        const bool valid = j < n;
+        uint2 e = valid ? hits[wave][j] : make_uint2(0u, 0u);
+        const u32 idx = s * kMinChunk + e.x, m = mag_of(e.y);
+        const u32 key = key_word(idx, g, seed);
+        const bool member = valid && m > now.bd_hi, here_b = valid && !member;
+        // (as in Ring::take: of a vector whose members are many, those that will not be sent stay out)
+        const bool stays = valid && (g.keyed == 0u || here_b || key >> 30 != kKeyAbove);
+        const u64 mask = __ballot(stays);
+        const u32 at = kept + popc64(mask & below);
+        if (stays && at < g.cap) s_ent[s * g.cap + at] = make_uint2(key | e.x, e.y);
+        kept += popc64(mask);
+        sure += popc64(__ballot(member && key >> 30 == kKeyBelow));
+        in_bin += popc64(__ballot(here_b));
+        if (member && key >> 30 == kKeyInside) {
+            const u32 p = places(&cnt_m, __ballot(true));
+            if (p < kListCap) m_ent[slot(p)] = make_uint2((key >> kPlaceBits) & (kCutM - 1u), idx);
+        }
+        if (here_b) {
+            const u32 p = places(&cnt_b, __ballot(true));
+            if (p < kListCap) b_ent[slot(p)] = make_uint2(m, idx);
+            if (m < lane_bmin) { lane_bmin = m; atomicMin(&bmin_s, m); }
+            if (m > lane_bmax) { lane_bmax = m; atomicMax(&bmax_s, m); }
+        }
+    }
+    if (lane == 0) {
+        sure_s[wave] = sure;
+        if (s < g.W) {
+            win_cnt[s] = sure;
+            bd_cnt[s] = in_bin;
+            seg[chunk_slot(s, g.U, g.UC)] = make_uint2(kept | (kept > g.cap ? kSliceFull : 0u), s * g.cap);
+        }
+    }
+    lds_barrier();
+    if (threadIdx.x == 0) {
+        static_assert(kWalkWaves == kQuad, "the workgroup's chunks are a quad");
+        const u32 of_quad = sure_s[0] + sure_s[1] + sure_s[2] + sure_s[3];
+        quad_win[blockIdx.x] = of_quad;
+        const u32 in_m = cnt_m < kListCap ? cnt_m : kListCap, in_b = cnt_b < kListCap ? cnt_b : kListCap;
+        blk_lists[blockIdx.x] = make_uint2(in_m | in_b << 16, of_quad);
         blk_bmin[blockIdx.x] = bmin_s;
         blk_bmax[blockIdx.x] = bmax_s;
         if (cnt_m > kListCap || cnt_b > kListCap) ctl->overflow = 1u;
@@ -2993,30 +3317,48 @@ __global__ void __launch_bounds__(kPickThreads) k_pick(Batch B, u32 n_rows, Geom
 {
     const Member m(B);
     EncodeCtl *ctl = m.at<EncodeCtl>(L.ctl);
-    const Picked p = pick_body<kPickThreads>(m.at<u32>(L.partials), m.at<u32>(L.group_sums), n_rows, g, ctl);
+    const Picked p = pick_body(m.at<u32>(L.partials), m.at<u32>(L.group_sums), n_rows, g, ctl);
     if (threadIdx.x == 0) p.store(ctl);
 }
 
-// kPick: every workgroup picks the deciding bin for itself, from the few histogram rows of a
-// short vector (kPickRows at most: 32 KB of them per workgroup), and there is no k_pick. One
-// call, us, with k_pick / without: one vector of 200,003 elements 37.1 / 35.3, of 2^20 (128 rows)
-// 42.2 / 41.5, of 2^20 + 1 41.5 / 41.8, of 1.6 M (196 rows) 47.1 / 48.1, of 2^21 (256) 44.1 /
-// 45.4; two of 2^20 43.9 / 43.4, of 1.6 M 49.5 / 52.1; four of 2^20 51.6 / 51.6, of 2^21 64.7 /
-// 75.0; eight of 2^20 67.1 / 71.3. (Three to eight members gain up to 64 rows; they keep k_pick.)
-template <bool kPick>
-__global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, u32 n_rows, Geom g, EncodeLayout L)
+__global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, Geom g, EncodeLayout L)
 {
     const Member m(B);
-    EncodeCtl *ctl = m.at<EncodeCtl>(L.ctl);
-    Picked p{};
-    if (kPick) {
-        p = pick_body<kWalkThreads>(m.at<u32>(L.partials), m.at<u32>(L.group_sums), n_rows, g, ctl);
-        if (blockIdx.x == 0 && threadIdx.x == 0) p.store(ctl);
-    }
-    classify_body(g, m.seed, ctl, kPick ? &p : nullptr, m.residual, m.at<uint2>(L.seg),
+    classify_body(g, m.seed, m.at<EncodeCtl>(L.ctl), m.residual, m.at<uint2>(L.seg),
                   m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt), m.at<u32>(L.bd_cnt), m.at<u32>(L.quad_win),
                   m.at<uint2>(L.blk_lists), m.at<u32>(L.blk_bmin), m.at<u32>(L.blk_bmax),
                   m.at<uint2>(L.m_ent), m.at<uint2>(L.b_ent));
+}
+
+__global__ void __launch_bounds__(kCountThreads) k_count(Batch B, Geom g, EncodeLayout L)
+{
+    const Member m(B);
+    count_body(m.grad, m.residual, g, m.at<u32>(0), (u32)(L.zero_bytes / 4), m.at<u16>(L.samples), m.at<uint4>(L.partials));
+}
+
+__global__ void __launch_bounds__(kPickThreads) k_pick_counted(Batch B, u32 n_rows, Geom g, EncodeLayout L)
+{
+    const Member m(B);
+    const Picked p = pick_counted<kPickThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g);
+    if (threadIdx.x == 0) p.store(m.at<EncodeCtl>(L.ctl));
+}
+
+template <bool kPick>
+__global__ void __launch_bounds__(kWalkThreads) k_classify_counted(Batch B, u32 n_rows, Geom g, EncodeLayout L)
+{
+    const Member m(B);
+    EncodeCtl *ctl = m.at<EncodeCtl>(L.ctl);
+    const ChunkRows chunk(m.residual, g.d, blockIdx.x * kWalkWaves + threadIdx.x / kWave);
+    Picked p{};
+    if (kPick) {
+        p = pick_counted<kWalkThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g);
+        if (blockIdx.x == 0 && threadIdx.x == 0) p.store(ctl);
+    } else {
+        p = Picked{ctl->mode, ctl->bd_lo, ctl->bd_hi, 0ull};
+    }
+    classify_counted(chunk, g, m.seed, ctl, p, m.at<uint2>(L.seg), m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt),
+                     m.at<u32>(L.bd_cnt), m.at<u32>(L.quad_win), m.at<uint2>(L.blk_lists), m.at<u32>(L.blk_bmin),
+                     m.at<u32>(L.blk_bmax), m.at<uint2>(L.m_ent), m.at<uint2>(L.b_ent));
 }
 
 __global__ void __launch_bounds__(kFinThreads) k_finalize(Batch B, Geom g, EncodeLayout L)
@@ -3235,6 +3577,34 @@ bool deals_across(const Geom &g, bool is_short, unsigned nb)
     return g.all_members ? g.d >= kAcrossKeyed : nb == 1u && g.d <= kAcrossMax;
 }
 
+// Whether a vector's magnitudes are all counted (count_body): short vectors. Whole calls, us, by sample,
+// estimate and candidates / counted: one vector of 65,536 elements 38.9 / 23.9, of 200,003 32.9 / 24.0, of
+// 2^20 36.8 / 28.2, of 2 M, r = 0.5%, 44.7 / 35.8 (layered), r = 50% 58.0 / 50.4, of 3 M 45.8 / 38.9; four of 2 M 61.5 / 52.7,
+// sixteen of 2^20 81.7 / 74.7, of 2 M 120 / 112, of 3 M 158 / 153. A bin is a 128th of an octave and holds up to 4% of the
+// top r: from r = 2^17 on it may hold more than finalize has room for, which costs 15 us. Up to 2^21 elements the
+// rest gains more (2 M touched rows, r = 100,000, 48.0 / 46.0, logscale, r = 500,000, 50.2 / 41.8), above it does not
+// (touched rows of 3 M, r = 150,000, 50.1 / 57.9). Above 3072 chunks the vector's second reading costs what the launches
+// save, and hot chunks want the room that the stream's wavefronts share.
+constexpr u32 kCountAnyR = 2048;              // chunks
+bool counts_all(const Geom &g)
+{
+    return !g.all_members && (g.W <= kCountAnyR || (g.W <= kCountChunks && g.r < kKeyedMembers));
+}
+
+// Workgroups of count: as many wavefronts as chunks, in few rows of bins (every workgroup that picks the deciding
+// bin reads them all). us, 4 / 8 / 16 wavefronts: one vector of 200,003 27.4 / 26.7 / 27.3, of 524,288 30.3 / 29.5 /
+// 30.7, eight of 524,288 45.3 / 41.3 / 40.0; 8 / 16: one of 2^20 30.1 / 30.0, four 42.5 / 39.5.
+struct CountShape { unsigned threads, grid; };
+CountShape count_shape(u32 W)
+{
+    const unsigned waves = W <= 512u ? 8u : kCountThreads / kWave, each = W <= kCountRows * waves ? waves : kCountEach;
+    return CountShape{waves * (unsigned)kWave, (W + each - 1) / each};
+}
+// Every classify workgroup picks for itself up to this many rows over all members, a kernel picks beyond. us, in
+// classify / by a kernel: one of 200,003 (25 rows) 26.7 / 28.9, of 2^21 (128) 37.2 / 38.9; two of 2^21 44.0 / 43.6; four
+// of 2^20 (64) 39.5 / 40.5, of 1.5 M (92) 50.9 / 47.8; eight of 524,288 (64) 41.3 / 41.5, of 2^20 55.1 / 52.6.
+constexpr unsigned kPickRows = 256;
+
 int fused_grid_limit(unsigned *out)
 {
     int dev = 0;
@@ -3320,6 +3690,8 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         g.K_lo = g.K_hi = 0;       // a window that holds no key: the exact selection must run
         g.k_nlz = 63u;
     }
+    // (what a sample or a bracket that misleads does to a call belongs to the path that has them)
+    const unsigned force_general = force & (RTOPK_FORCE_ESTIMATE_MISS | RTOPK_FORCE_BRACKET_LOW);
     hipStream_t stream = (hipStream_t)stream_v;
     unsigned grid_limit = 0;
     const int rc2 = fused_grid_limit(&grid_limit);
@@ -3354,7 +3726,14 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         B.ws = (char *)workspace + (u64)first * L.total;
         B.ws_stride = L.total;
         const dim3 fg(fgrid, 1, nb);
-        if (g.all_members) {
+        const bool counts = force_general == 0u && counts_all(gg);
+        const CountShape cs = count_shape(gg.W);
+        if (counts) set_units(gg, 1u);                  // a chunk per wavefront of the walking kernels
+        if (counts) {
+            StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
+            k_count<<<dim3(cs.grid, 1, nb), cs.threads, 0, stream>>>(B, gg, L);
+            RTOPK_LAUNCH_CHECK();
+        } else if (g.all_members) {
             // r == d (random-k): no estimate, no histogram, no threshold
             StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
             if (fs.is_short && !gg.keyed)
@@ -3394,17 +3773,21 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         }
         {
             StageScope sc(trace, RTOPK_STAGE_CLASSIFY, stream);
-            const bool few_rows = fgrid <= kPickRows && nb <= kPickMembers;
-            if (!g.all_members && !few_rows) {
-                k_pick<<<dim3(1, 1, nb), kPickThreads, 0, stream>>>(B, fgrid, gg, L);
-                RTOPK_LAUNCH_CHECK();
-            }
             const dim3 cg(gg.G3, 1, nb);
-            const bool picks = !g.all_members && few_rows;
-            if (picks)
-                k_classify<true><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
-            else
-                k_classify<false><<<cg, kWalkThreads, 0, stream>>>(B, fgrid, gg, L);
+            const bool each_picks = nb * cs.grid <= kPickRows;
+            if (counts && each_picks) {
+                k_classify_counted<true><<<cg, kWalkThreads, 0, stream>>>(B, cs.grid, gg, L);
+            } else if (counts) {
+                k_pick_counted<<<dim3(1, 1, nb), kPickThreads, 0, stream>>>(B, cs.grid, gg, L);
+                RTOPK_LAUNCH_CHECK();
+                k_classify_counted<false><<<cg, kWalkThreads, 0, stream>>>(B, cs.grid, gg, L);
+            } else {
+                if (!g.all_members) {
+                    k_pick<<<dim3(1, 1, nb), kPickThreads, 0, stream>>>(B, fgrid, gg, L);
+                    RTOPK_LAUNCH_CHECK();
+                }
+                k_classify<<<cg, kWalkThreads, 0, stream>>>(B, gg, L);
+            }
             RTOPK_LAUNCH_CHECK();
         }
         {

@@ -1,0 +1,121 @@
+"""Short vectors, whose magnitudes are all counted by their leading 15 bits while they are added:
+lengths on both sides of every change of launch shape, octaves that meet in one slot of a
+workgroup's row, a cut among zeros and denormals. Bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+CHUNK = 1024
+
+
+def _check(g, m, r, k, seed=5, step=6, offset=0, path=0):
+    from tests import gpu_util as u
+    got = u.gpu_encode_once(g, m, r, k, seed, step, offset=offset)
+    u.assert_encode_equal(got, oracle.encode(g, m, r, k, seed, step), f"d={len(g)} r={r} k={k}")
+    if path is not None:
+        assert got[3]["path"] == path, got[3]
+    return got[3]
+
+
+# 8 and 16 wavefronts per workgroup, a second round of chunks, the last counted length
+@pytest.mark.parametrize("chunks", [1, 7, 8, 9, 512, 513, 2047, 2048, 2049, 2064, 3071, 3072, 3073])
+@pytest.mark.parametrize("ragged", [0, 1, 513])
+@pytest.mark.parametrize("of_r", ["sparse", "dense", "top-k"])
+def test_lengths(chunks, ragged, of_r):
+    d = (chunks - 1) * CHUNK + (ragged or CHUNK)
+    rng = np.random.default_rng(chunks * 3 + ragged)
+    g = (rng.standard_normal(d) * 10.0 ** rng.uniform(-3, 0, d)).astype(np.float32)
+    m = (rng.standard_normal(d) * 1e-4).astype(np.float32)
+    r = min(d, max(2, d // (5 if of_r == "dense" else 90)))
+    k = r if of_r == "top-k" else max(1, r // 6)
+    print(f"counted chunks={chunks} ragged={ragged} r={r} k={k}", flush=True)
+    _check(g, m, r, k, offset=(chunks + ragged) % 4, path=None if chunks < 10 else 0)
+
+
+@pytest.mark.parametrize("d,r", [(2500 * CHUNK, (1 << 17) - 1), (2500 * CHUNK, 1 << 17), (2048 * CHUNK, (1 << 17) + 1),
+                                 (1 << 18, (1 << 18) - 1)])
+def test_large_top_sets(d, r):
+    rng = np.random.default_rng(r)
+    g = rng.standard_normal(d).astype(np.float32)
+    _check(g, np.zeros(d, np.float32), r, r // 20, path=None)
+
+
+# rows of all members up to 256: every classify workgroup picks; beyond: a kernel
+@pytest.mark.parametrize("n,chunks", [(16, 128), (16, 129), (2, 2048), (3, 2048), (17, 100), (7, 2500)])
+def test_batches(n, chunks):
+    import torch
+
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    d = chunks * CHUNK - 3
+    r, k = d // 50, d // 500
+    rng = np.random.default_rng(n + chunks)
+    gs = [(rng.standard_normal(d) * 10.0 ** rng.uniform(-3, 0, d)).astype(np.float32) for _ in range(2)]
+    m = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    dev = [torch.from_numpy(g).to(u.DEV) for g in gs]
+    res = [torch.from_numpy(m).to(u.DEV) for _ in range(n)]
+    idx = [torch.empty(k, dtype=torch.int32, device=u.DEV) for _ in range(n)]
+    val = [torch.empty(k, device=u.DEV) for _ in range(n)]
+    stride = rt.encode_workspace_bytes(d, r, k)
+    ws = torch.empty(n * stride, dtype=torch.uint8, device=u.DEV).fill_(0xA5)
+    print(f"counted batch n={n} chunks={chunks}", flush=True)
+    rt.encode_batch([dev[w % 2] for w in range(n)], res, r, k, list(range(n)), 3, idx, val, ws)
+    torch.cuda.synchronize()
+    for w in range(n):
+        st = rt.encode_stats(ws[w * stride:(w + 1) * stride])
+        assert st["path"] == 0 and st["error_flags"] == 0, (w, st)
+        if w in (0, 1, n - 1):
+            got = (idx[w].cpu().numpy().view(np.uint32), val[w].cpu().numpy(), res[w].cpu().numpy())
+            u.assert_encode_equal(got, oracle.encode(gs[w % 2], m, r, k, w, 3), f"member {w} of {n}")
+
+
+@pytest.mark.parametrize("d", [40_000, 300_007])
+@pytest.mark.parametrize("r,path", [(100, 0), (5_000, 2)])       # the cut among the large ones; among those that lost their slot
+def test_octaves_that_meet_in_a_slot(d, r, path):
+    """A few hundred elements around 2^40, all others 64 octaves below: their bins share a slot of the rows."""
+    rng = np.random.default_rng(d + r)
+    g = (rng.uniform(1.0, 2.0, d) * 2.0 ** -24).astype(np.float32)
+    g[::97] = (rng.uniform(1.0, 2.0, len(g[::97])) * 2.0 ** 40).astype(np.float32)
+    g *= rng.choice(np.array([-1.0, 1.0], np.float32), d)
+    st = _check(g, np.zeros(d, np.float32), r, r // 2, path=None)
+    assert st["path"] & 2 == path, st
+
+
+@pytest.mark.parametrize("d", [5_000, 300_007, 2_500_000])
+@pytest.mark.parametrize("kind", ["zeros decide", "all zero", "denormals", "smallest denormals", "specials", "octaves"])
+def test_where_the_cut_may_lie(d, kind):
+    rng = np.random.default_rng(d)
+    r, k = d // 10, d // 30
+    g = np.zeros(d, np.float32)
+    some = rng.permutation(d)
+    if kind == "zeros decide":
+        g[some[:r // 2]] = rng.standard_normal(r // 2).astype(np.float32)
+        g[some[r // 2:r]] = np.float32(-0.0)
+    elif kind == "denormals":                       # bins 1 to 127: the group of exponent zero
+        g = (rng.integers(1, 1 << 23, d).astype(np.uint32) | (rng.integers(0, 2, d).astype(np.uint32) << 31)).view(np.float32)
+    elif kind == "smallest denormals":              # bin 0 holds distinct magnitudes
+        g = rng.integers(0, 1 << 16, d).astype(np.uint32).view(np.float32)
+    elif kind == "specials":
+        g = rng.standard_normal(d).astype(np.float32)
+        g[some[:20]] = np.float32("inf")
+        g[some[20:30]] = np.float32("-inf")
+        g[some[30:40]] = np.float32("nan")
+    elif kind == "octaves":                         # every binade there is
+        g = (rng.integers(0, 255 << 23, d).astype(np.uint32)).view(np.float32)
+    print(f"cut {kind} d={d}", flush=True)
+    _check(g, np.zeros(d, np.float32), r, k, offset=1, path=None)
+    _check(g, np.zeros(d, np.float32), r, r, path=None)
+
+
+@pytest.mark.parametrize("count", [127, 128, 129, 1024])
+@pytest.mark.parametrize("d", [100_000, 2_600_000])             # all members stay in the buffer; those that may be sent
+def test_chunks_that_fill_their_slice(d, count):
+    rng = np.random.default_rng(d + count)
+    g = (rng.standard_normal(d) * 1e-3).astype(np.float32)
+    for c0 in (0, 5 * CHUNK, d // CHUNK * CHUNK - CHUNK):
+        g[c0 + rng.permutation(CHUNK)[:count]] = (rng.standard_normal(count) + 30.0).astype(np.float32)
+    for r, k in ((3 * count + 500, 300), (3 * count + 500, 3 * count + 500)):
+        _check(g, np.zeros(d, np.float32), r, k, path=None)
