@@ -119,3 +119,26 @@ def test_chunks_that_fill_their_slice(d, count):
         g[c0 + rng.permutation(CHUNK)[:count]] = (rng.standard_normal(count) + 30.0).astype(np.float32)
     for r, k in ((3 * count + 500, 300), (3 * count + 500, 3 * count + 500)):
         _check(g, np.zeros(d, np.float32), r, k, path=None)
+
+
+# 25, 123 and 256 classify workgroups, of which 256, 64 and 32 places per list fit registers (8 fetched at once)
+@pytest.mark.parametrize("d", [100_003, 500_000, 1 << 20, (1 << 20) + 1])
+@pytest.mark.parametrize("hot", [7, 9, 17, 40, 70, 135, 290])
+@pytest.mark.parametrize("where", ["window", "bin", "few levels"])
+def test_lists_in_and_beyond_registers(d, hot, where):
+    """`hot` members in one classify workgroup's chunks: nearly half of their keys lie in the window; or they
+    share the deciding bin, with the cut among them, as distinct magnitudes or as three."""
+    rng = np.random.default_rng(d + hot)
+    g = (rng.standard_normal(d) * 1e-6).astype(np.float32)
+    g[rng.permutation(d)[:200]] = (rng.standard_normal(200) + 9.0).astype(np.float32)
+    at = 8 * CHUNK + rng.permutation(4 * CHUNK)[:hot]
+    if where == "window":
+        g[at] = (rng.standard_normal(hot) + 9.0).astype(np.float32)
+    elif where == "bin":
+        g[at] = (1.0 + rng.permutation(1 << 15)[:hot] / 2.0 ** 23).astype(np.float32)
+    else:
+        g[at] = (1.0 + rng.integers(0, 3, hot) / 2.0 ** 20).astype(np.float32)
+    r = len(np.flatnonzero(np.abs(g) > 0.5)) - (0 if where == "window" else hot // 2)
+    print(f"lists d={d} hot={hot} {where} r={r}", flush=True)
+    for k in (r // 3, r):
+        _check(g, np.zeros(d, np.float32), r, k, path=None)
