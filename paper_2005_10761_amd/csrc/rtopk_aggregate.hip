@@ -75,7 +75,13 @@ constexpr u32 kAggFewWorkers = 4;
 constexpr u64 kWeightsTiles = 1u << 14;
 constexpr u32 kWeightsWorkers = 8;
 constexpr u32 kWeightsPerTile = 12;
-constexpr u32 kWeightsBlocks = 1024;      // four workgroups per compute unit
+// Up to kWeightsFlat entries in all the workgroups learn how many entries they have (k_weights<true>) and are two per
+// compute unit, up to kWeightsFew one: what they do to find their range is a good part of it, and they do it side
+// by side. us, rounds of 256 per worker on four workgroups / now: layered messages, four and eight workers of 35 M,
+// 0.3 entries per tile 10.5 / 8.0 and 13.4 / 9.5, 2 per tile 11.9 / 9.7 and 15.8 / 11.9, 6 per tile 14.8 / 12.5 and 17.5 / 15.3;
+// of 66 M, 2 per tile 12.7 / 10.8 and 16.4 / 13.7. Above, where more is the weights' scattered lines, they lose what
+// they look up twice: eight of 66 M, 6 per tile 25.5 / 27.7, four of 200 M, 12 per tile 67.0 / 70.6.
+constexpr u64 kWeightsFew = 1u << 13, kWeightsFlat = 1u << 17;
 // Tiles per wavefront of the momentum step: one, but with 17 to 64 workers two from
 // kMomentumTwo tiles on and four from kMomentumFour on. The search for a wavefront's first tile
 // has 64 lanes for n workers: up to sixteen it takes a few probes, with 33 it is a binary search of fifteen, and a run
@@ -105,6 +111,8 @@ __device__ __forceinline__ u64 read_lane_u64(u64 v, int lane)
 // remaining range, which shrinks (P + 1)-fold. Returns the result of worker
 // `lane` in lane `lane` (lanes >= nw: unspecified). The lanes of a group bring
 // the range [lo, hi] of positions that is known to hold their worker's result.
+// (kTwo: groups 2w and 2w + 1 belong to worker w, each with an x of its own.)
+template <bool kTwo = false>
 __device__ __forceinline__ u64 wave_lower_bounds(const u32 *__restrict__ idx, u32 w0, u32 nw, u64 k,
                                                  u64 x, u64 lo, u64 hi)
 {
@@ -113,7 +121,7 @@ __device__ __forceinline__ u64 wave_lower_bounds(const u32 *__restrict__ idx, u3
     while (2 * P * nw <= (u32)kWave) P *= 2;
     const u32 w = lane / P, p = lane % P;
     const bool live = w < nw;
-    const u32 *wi = idx + (u64)(w0 + (live ? w : 0)) * k;
+    const u32 *wi = idx + (u64)(w0 + (live ? (kTwo ? w / 2u : w) : 0)) * k;
     if (!live) lo = hi;
     const float inv = 1.0f / (float)(P + 1);
     while (__any(hi > lo)) {
@@ -340,18 +348,19 @@ struct BitExchange {
     }
 };
 
-// The coordinates [x0, x1) of one of the kWeightsBlocks workgroups, and where
-// x0 starts in every worker's list (pos, LDS). Messages cluster (the top
+// The coordinates [x0, x1) of one of the kAggThreads << parts_log workgroups, and where
+// x0 (and, with kEnds, x1) starts in every worker's list (pos and end, LDS). Messages cluster (the top
 // coordinates sit in a few layers), and no two workers' need cluster alike: so
 // evenly spaced entries of EVERY worker, at most 255 in all, cut the coordinates
-// into pieces, and each piece is cut into equal quarters. A piece lies between two
+// into pieces, and each piece is cut into equal parts. A piece lies between two
 // neighbouring samples of any worker: it holds at most an S-th of a
 // message of which S entries were sampled. Where the samples lie in the message
 // also narrows the search for x0 down. lds: 2 * kAggThreads words.
-__device__ __forceinline__ bool weights_range(const u32 *__restrict__ idx, u32 n, u64 k, u64 d, u32 *lds,
-                                              u64 *x0, u64 *x1, u64 *pos)
+template <bool kEnds>
+__device__ __forceinline__ bool weights_range(const u32 *__restrict__ idx, u32 n, u64 k, u64 d, u32 parts_log, u32 *lds,
+                                              u64 *x0, u64 *x1, u64 *pos, u64 *end)
 {
-    static_assert(kWeightsBlocks == 4 * kAggThreads, "a cut per thread, four workgroups between two cuts");
+    // (a cut per thread, 2^parts_log workgroups between two cuts)
     const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     const u32 per = (kAggThreads - 1) / n, cuts = per * n;      // samples of one worker, of all
     // position of worker v's sample s (staggered, or the samples of like messages would coincide)
@@ -379,23 +388,26 @@ __device__ __forceinline__ bool weights_range(const u32 *__restrict__ idx, u32 n
         sorted[rank] = mine;
     }
     lds_barrier();
-    const u32 piece = blockIdx.x / 4u, quarter = blockIdx.x % 4u;
+    const u32 piece = blockIdx.x >> parts_log, part = blockIdx.x & ((1u << parts_log) - 1u);
     u64 lo = piece == 0u || piece > cuts ? 0ull : (u64)sorted[piece - 1u], hi = piece >= cuts ? d : (u64)sorted[piece];
     if (lo > d) lo = d;
     if (hi > d) hi = d;
-    *x0 = lo + (hi - lo) * quarter / 4u;
-    *x1 = lo + (hi - lo) * (quarter + 1u) / 4u;
+    *x0 = lo + ((hi - lo) * part >> parts_log);
+    *x1 = lo + ((hi - lo) * (part + 1u) >> parts_log);
     if (piece > cuts || lo >= hi || *x0 >= *x1) return false;
+    // (with the ends, two searches per worker)
+    constexpr u32 kSides = kEnds ? 2u : 1u;
     const u32 of_wave = (n + kAggWaves - 1) / kAggWaves, first = wave * of_wave;
     if (first < n) {
-        const u32 here = n - first < of_wave ? n - first : of_wave;
+        const u32 here = kSides * (n - first < of_wave ? n - first : of_wave);
         u32 lanes = 1;
         while (2 * lanes * here <= (u32)kWave) lanes *= 2;
-        const u32 v = first + (lane / lanes < here ? lane / lanes : 0u);
-        const u32 c = below(v, *x0);
-        const u64 start = wave_lower_bounds(idx, first, here, k, *x0, c == 0u ? 0ull : at(v, c - 1u) + 1u,
-                                            c == per ? k : at(v, c));
-        if (lane < here) pos[first + lane] = start;
+        const u32 of = lane / lanes < here ? lane / lanes : 0u, v = first + of / kSides;
+        const u64 x = of % kSides == 0u ? *x0 : *x1;
+        const u32 c = below(v, x);
+        const u64 start = wave_lower_bounds<kEnds>(idx, first, here, k, x, c == 0u ? 0ull : at(v, c - 1u) + 1u,
+                                                   c == per ? k : at(v, c));
+        if (lane < here) (lane % kSides == 0u ? pos : end)[first + lane / kSides] = start;
     }
     lds_barrier();                                             // the words are the caller's again
     return true;
@@ -419,8 +431,9 @@ __device__ __forceinline__ bool weights_range(const u32 *__restrict__ idx, u32 n
 // pair of kernels with a wavefront per tile of 2048 coordinates takes 4.8 + 33.8,
 // as its 32,244 tiles walk the same chain in six rounds.
 // ---------------------------------------------------------------------------
+template <bool kFlat>
 __global__ void __launch_bounds__(kAggThreads, 4)
-k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64 k, u64 d,
+k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64 k, u64 d, u32 parts_log,
           float neg_step, float *__restrict__ omega)
 {
     constexpr u32 kWindows = kWeightsWorkers;
@@ -428,19 +441,110 @@ k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64
     constexpr u32 kEmpty = 0xFFFFFFFFu;                    // never a coordinate
     __shared__ u32 key[kSlots];
     __shared__ float sum[kSlots];
-    __shared__ u64 pos[kWindows];
+    __shared__ u64 pos[kWindows], end[kWindows];
     __shared__ u32 word[3];
     __shared__ u32 bound_s;
     const u32 tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
     u64 x0, x1;
-    if (!weights_range(idx, n, k, d, key, &x0, &x1, pos)) return;
+    if (!weights_range<kFlat>(idx, n, k, d, parts_log, key, &x0, &x1, pos, end)) return;
     const float fn = (float)n;
     const bool n_pow2 = (n & (n - 1u)) == 0u;
     const float rn = 1.0f / fn;
     auto average = [&](float s) { return n_pow2 ? s * rn : s / fn; };
-    for (u32 i = tid; i < kSlots; i += kAggThreads) { key[i] = kEmpty; sum[i] = 0.0f; }
     if (tid < 3u) word[tid] = 0u;
     BitExchange exchange{word, 0u};
+    if constexpr (kFlat) {
+        // ---- the usual case: a few hundred entries, whoever sent them. Entry f of the range, worker after
+        //      worker, is thread f % 256's (f / 256)-th; the table is four times as large as the entries need.
+        u32 total = 0;
+        u32 before[kWindows], from_here[kWindows];      // entries of the workers before; what turns f into a position
+#pragma unroll
+        for (u32 q = 0; q < kWindows; ++q) {
+            before[q] = total;
+            from_here[q] = 0u;
+            if (q < n) {
+                from_here[q] = (u32)pos[q] - total;
+                total += (u32)(end[q] > pos[q] ? end[q] - pos[q] : 0ull);
+            }
+        }
+        if (__builtin_expect(total <= kSlots / 2, 1)) {
+            if (total == 0u) return;
+            u32 log_slots = 9u;
+            while (1u << log_slots < 4u * total && 1u << log_slots < kSlots) ++log_slots;
+            const u32 slots = 1u << log_slots;
+            constexpr u32 kMine = kSlots / 2 / kAggThreads;
+            u32 e_i[kMine], e_w[kMine], slot[kMine];
+            float e_v[kMine], w[kMine];
+            u32 leader = 0, mine = 0, valid = 0;
+            const u32 rounds = (total + kAggThreads - 1u) / kAggThreads;
+#pragma unroll
+            for (u32 i = 0; i < kMine; ++i) {
+                if (i >= rounds) break;
+                const u32 f = tid + i * kAggThreads;
+                u32 of = 0, j = f + from_here[0];
+#pragma unroll
+                for (u32 q = 1; q < kWindows; ++q)
+                    if (q < n && f >= before[q]) { of = q; j = f + from_here[q]; }
+                e_w[i] = of;
+                e_i[i] = kEmpty;
+                if (f < total) {
+                    e_i[i] = idx[of * k + j];
+                    e_v[i] = val[of * k + j];
+                    valid |= 1u << i;
+                }
+                // (a message that repeats an index: its entries are added position by position below)
+                u32 left = kEmpty;
+                if (lane == 0u && f != 0u && f < total && j != 0u) left = idx[of * k + j - 1u];
+                left = lane_left(e_i[i], left);
+                const u32 of_left = lane_left(of, of);
+                if (__ballot(f < total && left == e_i[i] && of_left == of) != 0ull) mine |= 2u;
+            }
+            for (u32 i = tid; i < slots; i += kAggThreads) { key[i] = kEmpty; sum[i] = 0.0f; }
+            lds_barrier();
+#pragma unroll
+            for (u32 i = 0; i < kMine; ++i) {
+                if (i >= rounds) break;
+                const bool in = (valid >> i & 1u) != 0u && (u64)e_i[i] >= x0 && (u64)e_i[i] < x1;   // (a list that is not sorted: left out)
+                if (!in) valid &= ~(1u << i);
+                w[i] = in ? omega[e_i[i]] : 0.0f;
+                if (in) {
+                    slot[i] = (e_i[i] * 0x9E3779B1u) >> (32u - log_slots);
+                    u32 was = atomicCAS(&key[slot[i]], kEmpty, e_i[i]);
+                    while (was != kEmpty && was != e_i[i]) {
+                        slot[i] = (slot[i] + 1u) & (slots - 1u);
+                        was = atomicCAS(&key[slot[i]], kEmpty, e_i[i]);
+                    }
+                    if (was == kEmpty) leader |= 1u << i;
+                }
+                if (__ballot(in && (leader >> i & 1u) == 0u) != 0ull) mine |= 1u;
+            }
+            const u32 seen = exchange(mine);
+            if ((seen & 2u) == 0u) {
+                if ((seen & 1u) != 0u) {
+                    // ---- coordinates sent by several workers: sums in worker order
+                    for (u32 q = 0; q < n; ++q) {
+#pragma unroll
+                        for (u32 i = 0; i < kMine; ++i) {
+                            if (i >= rounds) break;
+                            if ((valid >> i & 1u) != 0u && e_w[i] == q) sum[slot[i]] += e_v[i];
+                        }
+                        lds_barrier();
+                    }
+                }
+#pragma unroll
+                for (u32 i = 0; i < kMine; ++i) {
+                    if (i >= rounds) break;
+                    if ((leader >> i & 1u) != 0u) {
+                        const float avg = average((seen & 1u) != 0u ? sum[slot[i]] : 0.0f + e_v[i]);
+                        if (avg != 0.0f) omega[e_i[i]] = fmaf(neg_step, avg, w[i]);
+                    }
+                }
+                return;
+            }
+            lds_barrier();                              // (nobody reads the table any more)
+        }
+    }
+    for (u32 i = tid; i < kSlots; i += kAggThreads) { key[i] = kEmpty; sum[i] = 0.0f; }
     lds_barrier();
 
     for (;;) {
@@ -962,7 +1066,12 @@ static int launch_update(const uint32_t *idx, const float *val, uint32_t n, uint
     if (const int rc = debug_check_messages(idx, n, k, d, stream)) return rc;
     volatile float step = eta * scale;                  // one binary32 rounding, then negated
     if (n <= kWeightsWorkers && d / kAggTile >= kWeightsTiles && (u64)n * k <= d / kAggTile * kWeightsPerTile) {
-        k_weights<<<kWeightsBlocks, kAggThreads, 0, stream>>>(idx, val, n, k, d, -step, omega);
+        const u64 entries = (u64)n * k;
+        const u32 parts_log = entries <= kWeightsFew ? 0u : entries <= kWeightsFlat ? 1u : 2u;
+        if (entries <= kWeightsFlat)
+            k_weights<true><<<kAggThreads << parts_log, kAggThreads, 0, stream>>>(idx, val, n, k, d, parts_log, -step, omega);
+        else
+            k_weights<false><<<kAggThreads << parts_log, kAggThreads, 0, stream>>>(idx, val, n, k, d, parts_log, -step, omega);
         if (hipGetLastError() != hipSuccess) return RTOPK_EHIP;
         return RTOPK_OK;
     }
