@@ -384,6 +384,22 @@ static void set_units(Geom &g, unsigned nb)
     g.G3 = (g.U + kWalkWaves - 1) / kWalkWaves;
 }
 
+// The sample of a launch of nb vectors. One vector of up to kAloneElements elements, of which the top set is a small
+// part, is sampled as a shorter one is: 160 samples in its top r bound the bracket well enough, and the estimate's one
+// workgroup holds the whole call up. us, 65,536 samples / 160 in the top r: Student-t values, 4.3 M elements, r = 1%, 52.2 /
+// 47.5, 8 M 59.9 / 55.3, 11.2 M 66.0 / 62.0; touched rows 61.2 / 58.0, 68.7 / 66.4, 77.5 / 75.2; layers 53.9 / 53.8, 58.7 / 57.1, 66.6 / 65.7; r = k
+// of 11.2 M 65.1 / 62.7. Not longer ones (25.6 M touched rows, r = 1%, 102.4 / 103.9), nor larger top sets (layers of 11.2 M, r = 5%,
+// 77.2 / 80.8), nor batches (four of 11.2 M 139.8 / 142.5, two of 5 M 66.0 / 66.5).
+constexpr u64 kAloneElements = 1u << 24, kAloneShare = 32;
+static void set_samples(Geom &g, unsigned nb)
+{
+    if (nb != 1u || g.d < kShortVector || g.d > kAloneElements || g.r * kAloneShare > g.d) return;
+    u64 want = 2 * kEstThreads;
+    while (want < kSampleLoc && want * 4 * g.r < 160 * g.d) want *= 2;
+    g.L = (u32)want;
+    g.est_vecs = (u32)want / kEstThreads;
+}
+
 static EncodeLayout make_layout(const Geom &g)
 {
     EncodeLayout L{};
@@ -3985,6 +4001,7 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         const unsigned nb = n - first < kMaxBatch ? n - first : kMaxBatch;
         Geom gg = g;                    // this launch group's share-out of the walking kernels
         set_units(gg, nb);
+        set_samples(gg, nb);
         const FusedShape fs = fused_shape(g.W, g.d, nb, grid_limit);
         const unsigned fgrid = fs.grid;
         gg.keyed = keys_in_stream(gg, fs.is_short, nb) ? 1u : 0u;
@@ -4030,10 +4047,10 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
                 StageScope sc(trace, RTOPK_STAGE_PREPARE, stream);
                 const dim3 eg(1, 1, nb);
                 static_assert(kSampleLoc == 16 * kEstThreads, "one kernel for each power of two");
-                k_sample<<<dim3(g.est_vecs * kEstThreads / kSampleThreads, 1, nb), kSampleThreads, 0, stream>>>(
+                k_sample<<<dim3(gg.est_vecs * kEstThreads / kSampleThreads, 1, nb), kSampleThreads, 0, stream>>>(
                     B, gg, L);
                 RTOPK_LAUNCH_CHECK();
-                switch (g.est_vecs) {
+                switch (gg.est_vecs) {
                 case 1: k_estimate<1><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
                 case 2: k_estimate<2><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
                 case 4: k_estimate<4><<<eg, kEstThreads, 0, stream>>>(B, gg, L); break;
