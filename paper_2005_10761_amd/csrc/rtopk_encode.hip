@@ -390,12 +390,24 @@ static void set_units(Geom &g, unsigned nb)
 // 47.5, 8 M 59.9 / 55.3, 11.2 M 66.0 / 62.0; touched rows 61.2 / 58.0, 68.7 / 66.4, 77.5 / 75.2; layers 53.9 / 53.8, 58.7 / 57.1, 66.6 / 65.7; r = k
 // of 11.2 M 65.1 / 62.7. Not longer ones (25.6 M touched rows, r = 1%, 102.4 / 103.9), nor larger top sets (layers of 11.2 M, r = 5%,
 // 77.2 / 80.8), nor batches (four of 11.2 M 139.8 / 142.5, two of 5 M 66.0 / 66.5).
+// Where half the sample puts 1,600 into a top set of up to a sixteenth (r = 5%, the federated setting's), half of it
+// does up to 2^25 elements: the estimate counts what is in the top there. Five vectors of 11.2 M, r = 5%, and the weight
+// step 205.1 / 203.3, one of 11.2 M 77.6 / 75.2 (layers), 78.4 / 73.5 (rows), eight of 5 M 161.5 / 156.3; not r = 10% (layers: one of 25.6 M
+// 114.0 / 119.8, four of 5 M 115.2 / 118.7), nor sixteen vectors (of 4.5 M 243 / 246), nor longer ones (four of 2^28 2938 / 3030).
 constexpr u64 kAloneElements = 1u << 24, kAloneShare = 32;
+constexpr u64 kHalfElements = 1u << 25, kHalfShare = 16, kHalfTop = 1600;
+constexpr unsigned kHalfMembers = 8;
 static void set_samples(Geom &g, unsigned nb)
 {
-    if (nb != 1u || g.d < kShortVector || g.d > kAloneElements || g.r * kAloneShare > g.d) return;
-    u64 want = 2 * kEstThreads;
-    while (want < kSampleLoc && want * 4 * g.r < 160 * g.d) want *= 2;
+    if (g.d < kShortVector) return;
+    u64 want = kSampleLoc;
+    if (nb == 1u && g.d <= kAloneElements && g.r * kAloneShare <= g.d) {
+        want = 2 * kEstThreads;
+        while (want < kSampleLoc && want * 4 * g.r < 160 * g.d) want *= 2;
+    } else if (nb <= kHalfMembers && g.d <= kHalfElements && g.r * kHalfShare <= g.d &&
+               kSampleLoc / 2 * 4 * g.r >= kHalfTop * g.d) {
+        want = kSampleLoc / 2;
+    }
     g.L = (u32)want;
     g.est_vecs = (u32)want / kEstThreads;
 }
