@@ -2982,9 +2982,13 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
             if (__builtin_expect(here <= (u32)kWave, 1)) {
                 each_here([&](u32 p) { ls.cand[atomicAdd(&ls.n_cand_b, 1u)] = p; });
                 lds_barrier();
-                const u32 p = lane < here ? ls.cand[lane] : 0u;
-                bool up_to;
-                tb = wave_rank(ls.b_x[p], ls.b_idx[p], here, rank, &up_to);
+                // (only the wavefronts that hold entries of B, and the first one, need the outcome: with all
+                // sixteen ranking, four to a SIMD, the call waited for the issue of it)
+                if (wave * (u32)kWave < n_bd || wave == 0u) {
+                    const u32 p = lane < here ? ls.cand[lane] : 0u;
+                    bool up_to;
+                    tb = wave_rank(ls.b_x[p], ls.b_idx[p], here, rank, &up_to);
+                }
                 lds_barrier();                  // (the candidates of the key cut come next)
             } else {
                 // many share it (a few levels): byte by byte, the bits that differ only (with
@@ -3074,12 +3078,14 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                     if (p != kNotSent && p - em < vm) ls.cand_idx[j] = m_ent[(u64)(p - em) * g.G3 + tid].y;
                 }
                 lds_barrier();
-                const u32 idx = lane < here ? ls.cand_idx[lane] : 0u;
-                bool up_to;
-                const Pair96 kb = wave_rank((sample_key(idx, seed) - g.K_lo) << g.k_nlz, idx, here, rank, &up_to);
-                if (wave == 0 && up_to) won(idx >> chunk_shift);
-                K_star = (kb.hi >> g.k_nlz) + g.K_lo;
-                J_star = kb.lo;
+                if (wave == 0u) {
+                    const u32 idx = lane < here ? ls.cand_idx[lane] : 0u;
+                    bool up_to;
+                    const Pair96 kb = wave_rank((sample_key(idx, seed) - g.K_lo) << g.k_nlz, idx, here, rank, &up_to);
+                    if (up_to) won(idx >> chunk_shift);
+                    K_star = (kb.hi >> g.k_nlz) + g.K_lo;
+                    J_star = kb.lo;
+                }
             }
             have_k = true;
         } else {
@@ -3345,7 +3351,8 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 atomicAdd(&win_cnt[s], 1u);
         });
     }
-    __syncthreads();
+    // (the lists' winners reach the chunks' counters meanwhile: nobody here reads those then)
+    if (__builtin_expect(quick, 1)) lds_barrier(); else __syncthreads();
 
     // ---- output offset of every quad of chunks: thread t holds the winners of quads
     //      4*(1024*q + t) .. +3, q < kSlabs; prefix sums run slab after slab.
