@@ -82,6 +82,7 @@ constexpr u32 kWeightsPerTile = 12;
 // of 66 M, 2 per tile 12.7 / 10.8 and 16.4 / 13.7. Above, where more is the weights' scattered lines, they lose what
 // they look up twice: eight of 66 M, 6 per tile 25.5 / 27.7, four of 200 M, 12 per tile 67.0 / 70.6.
 constexpr u64 kWeightsFew = 1u << 13, kWeightsFlat = 1u << 17;
+constexpr u32 kPartsLog = 2;              // four workgroups per compute unit otherwise
 // Tiles per wavefront of the momentum step: one, but with 17 to 64 workers two from
 // kMomentumTwo tiles on and four from kMomentumFour on. The search for a wavefront's first tile
 // has 64 lanes for n workers: up to sixteen it takes a few probes, with 33 it is a binary search of fifteen, and a run
@@ -433,9 +434,10 @@ __device__ __forceinline__ bool weights_range(const u32 *__restrict__ idx, u32 n
 // ---------------------------------------------------------------------------
 template <bool kFlat>
 __global__ void __launch_bounds__(kAggThreads, 4)
-k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64 k, u64 d, u32 parts_log,
+k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64 k, u64 d, u32 few_parts_log,
           float neg_step, float *__restrict__ omega)
 {
+    const u32 parts_log = kFlat ? few_parts_log : kPartsLog;
     constexpr u32 kWindows = kWeightsWorkers;
     constexpr u32 kSlots = 2 * kWindows * kAggThreads;     // a power of two
     constexpr u32 kEmpty = 0xFFFFFFFFu;                    // never a coordinate
@@ -1067,7 +1069,7 @@ static int launch_update(const uint32_t *idx, const float *val, uint32_t n, uint
     volatile float step = eta * scale;                  // one binary32 rounding, then negated
     if (n <= kWeightsWorkers && d / kAggTile >= kWeightsTiles && (u64)n * k <= d / kAggTile * kWeightsPerTile) {
         const u64 entries = (u64)n * k;
-        const u32 parts_log = entries <= kWeightsFew ? 0u : entries <= kWeightsFlat ? 1u : 2u;
+        const u32 parts_log = entries <= kWeightsFew ? 0u : entries <= kWeightsFlat ? 1u : kPartsLog;
         if (entries <= kWeightsFlat)
             k_weights<true><<<kAggThreads << parts_log, kAggThreads, 0, stream>>>(idx, val, n, k, d, parts_log, -step, omega);
         else

@@ -401,7 +401,7 @@ static void set_samples(Geom &g, unsigned nb)
 {
     if (g.d < kShortVector) return;
     u64 want = kSampleLoc;
-    if (nb == 1u && g.d <= kAloneElements && g.r * kAloneShare <= g.d) {
+    if (nb == 1u && g.d <= kAloneElements && g.r * kAloneShare < g.d) {
         want = 2 * kEstThreads;
         while (want < kSampleLoc && want * 4 * g.r < 160 * g.d) want *= 2;
     } else if (nb <= kHalfMembers && g.d <= kHalfElements && g.r * kHalfShare <= g.d &&
@@ -3857,6 +3857,8 @@ FusedShape fused_shape(u32 W, u64 d, unsigned nb, unsigned grid_limit)
 // From an eighth of the vector on every chunk overflows (sixteen of 2 M, r = 20%: 187.7 / 187.5). r == d,
 // where the stream computes every element's key to know the candidates: one vector of 300,007 23.1 / 25.5, two of
 // 3.5 M 44.5 / 44.9; eight of 2 M, k = 1%, 69.4 / 66.8, sixteen of 1 M 69.8 / 67.5.
+// (Vectors that are counted go by the same rule: their classify kernel leaves out what a keying stream would. The
+// figures of the shorter ones are those of streams that kept their candidates.)
 constexpr u64 kKeyedMembers = 1u << 17, kKeyedElements = 1u << 23;
 bool keys_in_stream(const Geom &g, bool is_short, unsigned nb)
 {
@@ -4048,6 +4050,7 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         if (counts) set_units(gg, 1u);                  // a chunk per wavefront of the walking kernels
         gg.small = counts && small_lists(gg, nb) ? 1u : 0u;
         if (counts) {
+            { StageScope none(trace, RTOPK_STAGE_PREPARE, stream); }    // (nothing to prepare: the events are recorded all the same)
             StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
             k_count<<<dim3(cs.grid, 1, nb), cs.threads, 0, stream>>>(B, gg, L);
             RTOPK_LAUNCH_CHECK();

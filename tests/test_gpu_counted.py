@@ -22,7 +22,7 @@ def _check(g, m, r, k, seed=5, step=6, offset=0, path=0):
 
 # 8 and 16 wavefronts per workgroup, a second round of chunks, the last counted length
 @pytest.mark.parametrize("chunks", [1, 7, 8, 9, 512, 513, 2047, 2048, 2049, 2064, 3071, 3072, 3073])
-@pytest.mark.parametrize("ragged", [0, 1, 513])
+@pytest.mark.parametrize("ragged", [0, 513])
 @pytest.mark.parametrize("of_r", ["sparse", "dense", "top-k"])
 def test_lengths(chunks, ragged, of_r):
     d = (chunks - 1) * CHUNK + (ragged or CHUNK)
@@ -123,7 +123,7 @@ def test_chunks_that_fill_their_slice(d, count):
 
 # 25, 123 and 256 classify workgroups, of which 256, 64 and 32 places per list fit registers (8 fetched at once)
 @pytest.mark.parametrize("d", [100_003, 500_000, 1 << 20, (1 << 20) + 1])
-@pytest.mark.parametrize("hot", [7, 9, 17, 40, 70, 135, 290])
+@pytest.mark.parametrize("hot", [9, 40, 70, 290])
 @pytest.mark.parametrize("where", ["window", "bin", "few levels"])
 def test_lists_in_and_beyond_registers(d, hot, where):
     """`hot` members in one classify workgroup's chunks: nearly half of their keys lie in the window; or they

@@ -12,15 +12,13 @@ D = (1 << 25) + 5
 
 
 @pytest.mark.parametrize("entries", [8, 8192, 8200, 1 << 17, (1 << 17) + 8])
-@pytest.mark.parametrize("n", [1, 3, 8])
-@pytest.mark.parametrize("layout", ["even", "crowded", "same", "repeats", "ends"])
+@pytest.mark.parametrize("n", [1, 8])
+@pytest.mark.parametrize("layout", ["crowded", "same", "repeats", "ends"])
 def test_totals_and_layouts(entries, n, layout):
     from tests import gpu_util as u
     k = max(1, entries // n)
     rng = np.random.default_rng(entries + n)
-    if layout == "even":
-        idx = np.stack([np.sort(rng.choice(D, k, replace=False)) for _ in range(n)])
-    elif layout == "crowded":                        # half of every message in a stretch of its own length
+    if layout == "crowded":                          # half of every message spread out, half in a stretch of its own length
         def one():
             a = rng.choice(D, k, replace=False)
             at = int(rng.integers(0, D - k))
