@@ -390,24 +390,12 @@ static void set_units(Geom &g, unsigned nb)
 // 47.5, 8 M 59.9 / 55.3, 11.2 M 66.0 / 62.0; touched rows 61.2 / 58.0, 68.7 / 66.4, 77.5 / 75.2; layers 53.9 / 53.8, 58.7 / 57.1, 66.6 / 65.7; r = k
 // of 11.2 M 65.1 / 62.7. Not longer ones (25.6 M touched rows, r = 1%, 102.4 / 103.9), nor larger top sets (layers of 11.2 M, r = 5%,
 // 77.2 / 80.8), nor batches (four of 11.2 M 139.8 / 142.5, two of 5 M 66.0 / 66.5).
-// Where half the sample puts 1,600 into a top set of up to a sixteenth (r = 5%, the federated setting's), half of it
-// does up to 2^25 elements: the estimate counts what is in the top there. Five vectors of 11.2 M, r = 5%, and the weight
-// step 205.1 / 203.3, one of 11.2 M 77.6 / 75.2 (layers), 78.4 / 73.5 (rows), eight of 5 M 161.5 / 156.3; not r = 10% (layers: one of 25.6 M
-// 114.0 / 119.8, four of 5 M 115.2 / 118.7), nor sixteen vectors (of 4.5 M 243 / 246), nor longer ones (four of 2^28 2938 / 3030).
 constexpr u64 kAloneElements = 1u << 24, kAloneShare = 32;
-constexpr u64 kHalfElements = 1u << 25, kHalfShare = 16, kHalfTop = 1600;
-constexpr unsigned kHalfMembers = 8;
 static void set_samples(Geom &g, unsigned nb)
 {
-    if (g.d < kShortVector) return;
-    u64 want = kSampleLoc;
-    if (nb == 1u && g.d <= kAloneElements && g.r * kAloneShare < g.d) {
-        want = 2 * kEstThreads;
-        while (want < kSampleLoc && want * 4 * g.r < 160 * g.d) want *= 2;
-    } else if (nb <= kHalfMembers && g.d <= kHalfElements && g.r * kHalfShare <= g.d &&
-               kSampleLoc / 2 * 4 * g.r >= kHalfTop * g.d) {
-        want = kSampleLoc / 2;
-    }
+    if (nb != 1u || g.d < kShortVector || g.d > kAloneElements || g.r * kAloneShare >= g.d) return;
+    u64 want = 2 * kEstThreads;
+    while (want < kSampleLoc && want * 4 * g.r < 160 * g.d) want *= 2;
     g.L = (u32)want;
     g.est_vecs = (u32)want / kEstThreads;
 }
@@ -3884,16 +3872,20 @@ bool deals_across(const Geom &g, bool is_short, unsigned nb)
 
 // Whether a vector's magnitudes are all counted (count_body): short vectors. Whole calls, us, by sample,
 // estimate and candidates / counted: one vector of 65,536 elements 38.9 / 23.9, of 200,003 32.9 / 24.0, of
-// 2^20 36.8 / 28.2, of 2 M, r = 0.5%, 44.7 / 35.8 (layered), r = 50% 58.0 / 50.4, of 3 M 45.8 / 38.9; four of 2 M 61.5 / 52.7,
-// sixteen of 2^20 81.7 / 74.7, of 2 M 120 / 112, of 3 M 158 / 153. A bin is a 128th of an octave and holds up to 4% of the
-// top r: from r = 2^17 on it may hold more than finalize has room for, which costs 15 us. Up to 2^21 elements the
-// rest gains more (2 M touched rows, r = 100,000, 48.0 / 46.0, logscale, r = 500,000, 50.2 / 41.8), above it does not
-// (touched rows of 3 M, r = 150,000, 50.1 / 57.9). Above 3072 chunks the vector's second reading costs what the launches
+// 2^20 36.8 / 28.2, of 2 M, r = 0.5%, 44.7 / 35.8 (layered), of 3 M 45.8 / 38.9; four of 2 M 61.5 / 52.7,
+// sixteen of 2^20 81.7 / 74.7, of 2 M 120 / 112, of 3 M 158 / 153. A bin is a 128th of an octave and holds 1 to 6% of the
+// top r, by where the threshold lies between two powers of two: a longer list for finalize, and from 4,608 entries on
+// one that does not fit. So r is limited where that costs more than the launches save. Normal values at eight scales, before / now
+// from the least to the most favourable: 3.1 M, r = 32,000 1.10-1.15, 98,000 0.74-0.99; 3 M, r = 60,000 0.84-1.10; 2 M, r = 64,000
+// 1.08-1.20, 130,000 0.80-1.17; 1.5 M, r = 64,000 1.10-1.16; 1.3 M, r = 200,000 0.95-1.16; 2^20, any r 1.17-1.25 (at most 4% of
+// all elements lie in a bin). Above 3072 chunks the vector's second reading costs what the launches
 // save, and hot chunks want the room that the stream's wavefronts share.
-constexpr u32 kCountAnyR = 2048;              // chunks
+constexpr u32 kCountAnyR = 1024, kCountMid = 2048;               // chunks
+constexpr u64 kCountMidMembers = 1u << 16, kCountMembers = 1u << 15;
 bool counts_all(const Geom &g)
 {
-    return !g.all_members && (g.W <= kCountAnyR || (g.W <= kCountChunks && g.r < kKeyedMembers));
+    if (g.all_members || g.W > kCountChunks) return false;
+    return g.W <= kCountAnyR || g.r <= (g.W <= kCountMid ? kCountMidMembers : kCountMembers);
 }
 
 // Workgroups of count: as many wavefronts as chunks, in few rows of bins (every workgroup that picks the deciding

@@ -35,7 +35,8 @@ def test_lengths(chunks, ragged, of_r):
     _check(g, m, r, k, offset=(chunks + ragged) % 4, path=None if chunks < 10 else 0)
 
 
-@pytest.mark.parametrize("d,r", [(2500 * CHUNK, (1 << 17) - 1), (2500 * CHUNK, 1 << 17), (2048 * CHUNK, (1 << 17) + 1),
+@pytest.mark.parametrize("d,r", [(2500 * CHUNK, 1 << 15), (2500 * CHUNK, (1 << 15) + 1), (2048 * CHUNK, 1 << 16),
+                                 (2048 * CHUNK, (1 << 16) + 1), (1024 * CHUNK, 1 << 18), (1025 * CHUNK, 1 << 18),
                                  (1 << 18, (1 << 18) - 1)])
 def test_large_top_sets(d, r):
     rng = np.random.default_rng(r)

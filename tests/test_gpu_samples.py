@@ -9,8 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,d,share", [(1, (1 << 22) - 1, 100), (1, 1 << 22, 100), (1, (1 << 22) + 3, 32), (1, (1 << 22) + 3, 31),
-                                       (1, 6_000_001, 4000), (1, 1 << 24, 100), (1, (1 << 24) + 1, 100), (2, 5_000_001, 100), (1, 5_000_001, 20), (8, 4_300_001, 20), (9, 4_300_001, 20), (2, 5_000_001, 15), (1, 33_000_001, 20),
-                                       (1, 34_000_001, 20)])
+                                       (1, 6_000_001, 4000), (1, 1 << 24, 100), (1, (1 << 24) + 1, 100), (2, 5_000_001, 100)])
 @pytest.mark.parametrize("values", ["layers", "student"])
 def test_sample_by_need(n, d, share, values):
     import torch
