@@ -145,6 +145,9 @@ constexpr u32 kMaxWalkBlocks = kMaxUnits / kWalkWaves;
 // separate cache lines.
 __host__ __device__ inline u32 chunk_slot(u32 s, u32 U, u32 UC) { return (s % U) * UC + s / U; }
 constexpr u32 kListCap = 128;                 // short-list slots per classify workgroup
+// ... of the deciding bin's list of a counted vector: it goes on where else only lists too long for LDS are, M's
+// keys of two lists
+constexpr u32 kLongList = 3 * kListCap;
 constexpr u32 kSliceDiv = 8;                  // S holds a kSliceDiv-th as many entries as there are elements
 constexpr u32 kSliceFull = 1u << 31;          // (in a chunk's count) the chunk kept more than its slice could hold
 
@@ -245,6 +248,7 @@ struct EncodeCtl {
     u32 bd_lo, bd_hi;   // pattern range of the deciding bin
     u32 bd_bits;        // bit width of bd_hi - bd_lo
     u64 c_def;          // entries above bd_hi
+    u32 n_bin, hot;     // (counted vectors) entries of the bin pick found, whether they crowd in few places
     // written by k_classify
     u32 overflow;       // a short-list region of some classify workgroup was full
     u32 overflow_m;     // ... and it was a region of the key list M
@@ -259,7 +263,10 @@ struct EncodeCtl {
     u32 n_b, n_m;
     u32 W, U, UC;       // chunks and their share-out, for the host-side statistics
     u64 count_greater, ties;
+    u32 how;            // kHow...: which lists of a counted vector decided (read by tests)
 };
+static_assert(offsetof(EncodeCtl, how) == 136, "where the tests look");
+constexpr u32 kHowRegisters = 1u, kHowNarrowed = 2u;
 
 // (the error word is the first word of the workspace: callers may read it there)
 static_assert(offsetof(EncodeCtl, err) == 0, "the error flags lead the control block");
@@ -287,6 +294,7 @@ struct Geom {
     u32 all_members;    // r == d: every coordinate is a member, magnitudes are never looked at
     u32 keyed;          // the streaming kernel keys the candidates (of a short vector only if they are many)
     u32 small;          // a counted vector whose short lists finalize keeps in registers, as a rule
+    u32 narrow_from;    // classify narrows a counted vector's deciding bin down from this many entries on (0: never)
     u32 k_nlz;          // leading zeros of K_hi - K_lo
     u32 stage_m;        // keys in the window that finalize has room for in LDS
     u64 K_lo, K_hi;     // key window
@@ -422,6 +430,7 @@ static EncodeLayout make_layout(const Geom &g)
     const u64 slots = (u64)g.G3 * kListCap;
     L.m_ent = take(slots * 8);
     L.b_ent = take(slots * 8);
+    static_assert(kListCap * 8 % 256 == 0 && kLongList <= 3 * kListCap, "B goes on without a gap");
     L.dm_key = take(2 * slots * 8);
     L.dm_idx = take(2 * slots * 4);
     L.db_key = take(slots * 8);
@@ -1326,8 +1335,10 @@ struct Picked {
     u32 mode;           // see EncodeCtl
     u32 bd_lo, bd_hi;
     u64 c_def;
+    u32 n_bin;
     __device__ __forceinline__ void store(EncodeCtl *ctl) const
     {
+        ctl->n_bin = n_bin;
         ctl->mode = mode;
         ctl->bd_lo = bd_lo;
         ctl->bd_hi = bd_hi;
@@ -1445,7 +1456,7 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
         // above the bracket S only holds what may be sent (everything when k == r or nothing was
         // keyed): no short list can decide there
         const bool partial = !dense && bin_s >= bins.nfine && g.take_all == 0u && g.keyed != 0u;
-        picked = Picked{(dense ? 1u : 0u) | (partial ? 2u : 0u), bd_lo, bd_hi, before_s};
+        picked = Picked{(dense ? 1u : 0u) | (partial ? 2u : 0u), bd_lo, bd_hi, before_s, 0u};
     }
     lds_barrier();
     return picked;
@@ -1474,6 +1485,7 @@ constexpr u32 kRowWords = kRowSlots * kGroupBins / 2;    // of a row's bins, two
 constexpr u32 kCountRows = 128;               // rows at most
 constexpr u32 kCountChunks = 3072;            // chunks of a vector at most
 constexpr u32 kCountThreads = 1024;           // at most
+constexpr u32 kPartBits = 8;                  // (see narrow_bin)
 static_assert((u64)kCountRows * kRowWords * 4 <= (u64)kMaxFusedBlocks * kMaxBins * 4, "the rows lie where the others would");
 static_assert((u64)kCountRows * kCountGroups * 2 <= (u64)kSampleLoc * 8, "the sums lie where the samples would");
 // chunks of a workgroup at most: one per wavefront, or one more for half of them
@@ -1494,7 +1506,7 @@ constexpr u32 kChunkRows = kMinChunk / kChunkQuantum;
 
 __device__ __forceinline__ void
 count_body(const float *__restrict__ grad, float *__restrict__ residual, const Geom &g, u32 *__restrict__ zero_base,
-           u32 zero_words, u16 *__restrict__ sums, uint4 *__restrict__ rows)
+           u32 zero_words, u32 *__restrict__ zero_groups, u32 group_words, u16 *__restrict__ sums, uint4 *__restrict__ rows)
 {
     __shared__ uint4 h4[kCountBins / 8];
     u32 *const h = reinterpret_cast<u32 *>(h4);
@@ -1512,6 +1524,7 @@ count_body(const float *__restrict__ grad, float *__restrict__ residual, const G
     u32 w = wave * gridDim.x + blockIdx.x;      // (a second round is a few wavefronts of every workgroup)
     if (w < w_full) load((u64)w * kMinChunk);
     for (u32 i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_words; i += gridDim.x * blockDim.x) zero_base[i] = 0u;
+    for (u32 i = blockIdx.x * blockDim.x + threadIdx.x; i < group_words; i += gridDim.x * blockDim.x) zero_groups[i] = 0u;
     for (u32 i = threadIdx.x; i < kCountBins / 8; i += blockDim.x) h4[i] = make_uint4(0u, 0u, 0u, 0u);
     lds_barrier();
     auto count = [&](float a) {
@@ -1562,16 +1575,18 @@ count_body(const float *__restrict__ grad, float *__restrict__ residual, const G
     }
 }
 
-// the deciding bin from those rows, by all threads of a workgroup (every thread gets the result)
+// the deciding bin from those rows, by all threads of a workgroup (every thread gets the result; whether the
+// bin's entries crowd in few places, *hot in LDS, after the next barrier)
+constexpr u32 kHotRows = 48;
 template <u32 kThreads>
 __device__ __forceinline__ Picked
-pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n_rows, const Geom &g)
+pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n_rows, const Geom &g, u32 *hot)
 {
     __shared__ u32 gtot[kCountGroups], btot[kGroupBins], lost_s;
     const u32 tid = threadIdx.x, lane = lane_id();
     for (u32 i = tid; i < kCountGroups; i += kThreads) gtot[i] = 0u;
     if (tid < kGroupBins) btot[tid] = 0u;
-    if (tid == 0) lost_s = 0u;
+    if (tid == 0) { lost_s = 0u; *hot = 0u; }
     // ---- all rows' sums: a thread takes eight groups of every (kThreads / 32)-th row
     constexpr u32 kAt = kCountGroups / 8u, kAhead = 8;
     u32 sum[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
@@ -1598,15 +1613,15 @@ pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n
     lds_barrier();
     // every wavefront finds the group for itself: lane l holds the l-th four groups from the top
     static_assert(kCountGroups == 4 * kWave && kGroupBins == 2 * kWave, "groups and bins per lane");
-    u32 c4[4], mine = 0;
+    u32 c4[4], four = 0;
 #pragma unroll
-    for (u32 q = 0; q < 4; ++q) { c4[q] = gtot[kCountGroups - 1u - 4u * lane - q]; mine += c4[q]; }
+    for (u32 q = 0; q < 4; ++q) { c4[q] = gtot[kCountGroups - 1u - 4u * lane - q]; four += c4[q]; }
     const u32 need = (u32)g.r;
-    u32 inc = wave_inclusive_sum(mine);
-    u64 owner = __ballot(inc - mine < need && need <= inc);
+    u32 inc = wave_inclusive_sum(four);
+    u64 owner = __ballot(inc - four < need && need <= inc);
     if (owner == 0ull)       // the zeros decide
-        return Picked{0u, 0u, (1u << kCountShift) - 1u, (u32)__builtin_amdgcn_readlane((int)inc, kWave - 1)};
-    u32 group = 0, above = inc - mine;
+        return Picked{0u, 0u, (1u << kCountShift) - 1u, (u32)__builtin_amdgcn_readlane((int)inc, kWave - 1), 0u};
+    u32 group = 0, above = inc - four;
 #pragma unroll
     for (u32 q = 0; q < 3; ++q)
         if (group == q && above + c4[q] < need) { above += c4[q]; ++group; }
@@ -1641,17 +1656,26 @@ pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n
     for (u32 c = 0; c < 8; ++c) if (sum[c]) atomicAdd(&btot[tid % kOf * 8u + c], sum[c]);
     if (marks != 0u) lost_s = 1u;
     lds_barrier();
-    if (lost_s != 0u) return Picked{1u, 0u, 0u, 0ull};
+    if (lost_s != 0u) return Picked{1u, 0u, 0u, 0ull, 0u};
     const u32 b0 = btot[kGroupBins - 1u - 2u * lane], b1 = btot[kGroupBins - 2u - 2u * lane];
     inc = wave_inclusive_sum(b0 + b1);
     u32 before = above + inc - b0 - b1;
     owner = __ballot(before < need && need <= before + b0 + b1);
     src = owner != 0ull ? __ffsll((unsigned long long)owner) - 1 : 0;
-    u32 bin = group * kGroupBins + kGroupBins - 1u - 2u * lane;
-    if (before + b0 < need) { before += b0; --bin; }
+    u32 bin = group * kGroupBins + kGroupBins - 1u - 2u * lane, in_bin = b0;
+    if (before + b0 < need) { before += b0; --bin; in_bin = b1; }
     bin = (u32)__builtin_amdgcn_readlane((int)bin, src);
     before = (u32)__builtin_amdgcn_readlane((int)before, src);
-    return Picked{0u, bin << kCountShift, (bin << kCountShift) | ((1u << kCountShift) - 1u), before};
+    in_bin = (u32)__builtin_amdgcn_readlane((int)in_bin, src);
+    // A classify workgroup's chunks are four rows' here, side by side: where it alone has more of the bin than
+    // its list takes, the rows of some of these threads have far more than the others'.
+    constexpr u32 kParts = kThreads / kOf;
+    const u32 parts = n_rows < kParts ? n_rows : kParts, at = bin % kGroupBins;
+    u32 mine = 0;
+#pragma unroll
+    for (u32 c = 0; c < 8; ++c) mine = at % 8u == c ? sum[c] : mine;
+    if (tid % kOf == at / 8u && mine > kHotRows && in_bin > kLongList && (mine - kHotRows) * parts > in_bin + in_bin / 8u) *hot = 1u;
+    return Picked{0u, bin << kCountShift, (bin << kCountShift) | ((1u << kCountShift) - 1u), before, in_bin};
 }
 
 // ---------------------------------------------------------------------------
@@ -1768,7 +1792,7 @@ classify_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, const float *__restrict__
 // classify of a counted vector: every wavefront has one chunk of it, whose elements it has loaded
 // before the deciding bin is known. What lies in the deciding bin or above it becomes the
 // chunk's slice of S, keyed, and goes through the short lists and counters as in classify_body: from
-// here on the call goes as any other.
+// here on the call goes as any other. A crowded deciding bin is narrowed first.
 // ---------------------------------------------------------------------------
 struct ChunkRows {
     f32x4 v[kChunkRows];
@@ -1790,12 +1814,172 @@ struct ChunkRows {
     }
 };
 
+// until everything this wavefront has sent to memory is acknowledged
+__device__ __forceinline__ void wait_own_memory()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
+
+// A bin of count is a 128th of an octave, whatever the values: of uniform ones the deciding bin may hold d / 256
+// entries, of magnitudes that are nearly equal, or clipped with some noise on top, most of the vector, and no short list
+// takes those. All workgroups know from the pick how many there are, and whether they crowd. From
+// g.narrow_from on, or where they crowd, the workgroups count the bin's entries by their next 8 bits and go on with
+// the one of 256 parts that decides. Calls, us, with sample and bracket / counted, the bin as it is / narrowed, r = 1%:
+// uniform values, 2 M elements 42.9 / 60.6 / 39.5, 3 M 45.4 / 76.7 / 47.1; 1 + 1% normal, 200,003 42.6 / 257 / 32.8, 2^20
+// 46.9 / 83.3 / 38.6; clipped with noise of 1e-3, 200,003 42.8 / 3167 / 32.4, 2^20 70.9 / 124 / 39.2; one layer of 8192
+// in 1..1.05, 200,003 45.0 / 390 / 38.5; eight of 2^20, 1 + 5% normal 69.8 / 82.3 / 69.1. Where nothing
+// narrows the call costs what it did (normal values, 2 M 34.3 / 34.4).
+//
+// For that they have to wait for each other (through device-scope atomics only, see grid_barrier). What bounds it is
+// that additions to one line of memory take 35 ns each: so kPartGroup workgroups share counters and a count of
+// arrivals, the last of them arrives for the group, and the last of all adds up the groups' counters, finds the
+// part and leaves it in every group's word, which only that group polls. (One set of counters and one word for all: uniform
+// values, 2^20 38.2, 2 M 50.8, 3 M 67.3; in groups 31.7, 37.9, 45.4; the look at whether the magnitudes are equal, which
+// saves vectors of signs 2 to 15 us, costs the others 1.5.) A workgroup that has polled kNarrowPolls times in vain calls
+// it off for all (one compare-and-swap stands): two grids of two streams, each holding half of the compute units, would
+// otherwise wait for each other. Finalize then has the crowded bin.
+struct PartGroup {
+    u32 count[1u << kPartBits];
+    u64 found;              // 0, kPartOff, or kPartFound and the part, its entries and the bin's entries above it
+    u32 arrived;
+    u32 pad[61];
+};
+constexpr u32 kPartGroup = 32, kPartGroups = kCountChunks / kWalkWaves / kPartGroup;
+constexpr u64 kPartFound = 1ull, kPartOff = 2ull;
+constexpr u32 kPartEntries = 22;             // bits
+static_assert(kCountChunks * kMinChunk < 1u << kPartEntries && 2u + kPartBits + 2u * kPartEntries <= 64u, "a word holds it all");
+// (the last one is for all groups; in the place of the group sums, which a counted vector has not)
+static_assert((kPartGroups + 1u) * sizeof(PartGroup) <= (u64)kMaxFusedBlocks * kMaxGroups * 4, "room for the counters");
+constexpr u32 kNarrowPolls = 1u << 9;        // (half a millisecond)
+__host__ __device__ constexpr u32 part_groups(u32 G3) { return (G3 + kPartGroup - 1u) / kPartGroup; }
+
+__device__ __forceinline__ Picked
+narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, PartGroup *groups, const Picked &now)
+{
+    __shared__ u32 part[1u << kPartBits], last_s, looked_s, least_s, most_s;
+    __shared__ u64 found_s;
+    static_assert(kWalkThreads == 1u << kPartBits, "a counter per thread");
+    constexpr u32 kShift = kCountShift - kPartBits, kMask = (1u << kPartBits) - 1u, kEntryMask = (1u << kPartEntries) - 1u;
+    const u32 tid = threadIdx.x, lane = lane_id(), bin = now.bd_lo >> kCountShift;
+    const u32 n_groups = part_groups(gridDim.x), group = blockIdx.x / kPartGroup;
+    PartGroup &mine = groups[group], &root = groups[n_groups];
+    // (a look at 1,024 elements, the same ones by all workgroups)
+    const f32x4 some = *reinterpret_cast<const f32x4u *>(a + (u64)tid * (g.d - 4u) / (kWalkThreads - 1u));
+    part[tid] = 0u;
+    if (tid == 0u) { last_s = 0u; found_s = 0ull; looked_s = 0u; least_s = ~0u; most_s = 0u; }
+    lds_barrier();
+#pragma unroll
+    for (u32 q = 0; q < kChunkRows; ++q)
+#pragma unroll
+        for (u32 e = 0; e < 4; ++e) {
+            const u32 m = mag_of(__float_as_uint(chunk.v[q][e])), at = m >> kShift & kMask;
+            const bool in = m >> kCountShift == bin && q * kChunkQuantum + 4u * lane + e < chunk.len;
+            const u64 here = __ballot(in);
+            if (here == 0ull) continue;
+            // (all of one part: one addition serves them)
+            const int src = __ffsll((unsigned long long)here) - 1;
+            const u32 first = (u32)__builtin_amdgcn_readlane((int)at, src);
+            if (__ballot(in && at == first) == here) {
+                if ((int)lane == src) atomicAdd(&part[first], popc64(here));
+            } else if (in) {
+                atomicAdd(&part[at], 1u);
+            }
+        }
+    u32 looked = 0, least = ~0u, most = 0;
+#pragma unroll
+    for (u32 e = 0; e < 4; ++e) {
+        const u32 m = mag_of(__float_as_uint(some[e]));
+        if (m >> kCountShift != bin) continue;
+        ++looked;
+        least = m < least ? m : least;
+        most = m > most ? m : most;
+    }
+    looked = wave_sum(looked);
+    least = ~wave_max_dpp(~least);
+    most = wave_max_dpp(most);
+    if (lane == 0u) { atomicAdd(&looked_s, looked); atomicMin(&least_s, least); atomicMax(&most_s, most); }
+    lds_barrier();
+    // equal magnitudes (signs, a few levels): no part will be smaller
+    if (looked_s > 1u && least_s == most_s) return now;
+    if (part[tid] != 0u) __hip_atomic_fetch_add(&mine.count[tid], part[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wait_own_memory();
+    __syncthreads();
+    if (tid == 0u) {
+        const u32 of_group = gridDim.x - group * kPartGroup < kPartGroup ? gridDim.x - group * kPartGroup : kPartGroup;
+        if (__hip_atomic_fetch_add(&mine.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == of_group)
+            last_s = __hip_atomic_fetch_add(&root.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == n_groups ? 1u : 0u;
+    }
+    __syncthreads();
+    // (by the first lanes of a workgroup: one word stands for all groups)
+    auto decide = [&](u64 word) {
+        u64 expected = 0ull;
+        bool stands = false;
+        if (tid == 0u)
+            stands = __hip_atomic_compare_exchange_strong(&root.found, &expected, word, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT);
+        if (__ballot(stands) != 0ull && lane < n_groups)
+            __hip_atomic_store(&groups[lane].found, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    static_assert(kPartGroups <= (u32)kWave, "a lane per group");
+    if (last_s != 0u) {
+        constexpr u32 kAhead = 12;
+        u32 sum = 0;
+        for (u32 q0 = 0; q0 < n_groups; q0 += kAhead) {
+            u32 c[kAhead];
+#pragma unroll
+            for (u32 q = 0; q < kAhead; ++q)
+                c[q] = __hip_atomic_load(&groups[q0 + q < n_groups ? q0 + q : 0u].count[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (u32 q = 0; q < kAhead; ++q) sum += q0 + q < n_groups ? c[q] : 0u;
+        }
+        part[tid] = sum;
+        __syncthreads();
+        if (tid < (u32)kWave) {
+            // lane l has the l-th four counters from the top
+            u32 c[4], four = 0;
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) { c[q] = part[kMask - 4u * lane - q]; four += c[q]; }
+            const u32 need = (u32)(g.r - now.c_def), inc = wave_inclusive_sum(four);
+            const u64 owner = __ballot(inc - four < need && need <= inc);
+            u32 at = 0, above = inc - four, here = c[0];
+#pragma unroll
+            for (u32 q = 0; q < 3; ++q)
+                if (at == q && above + c[q] < need) { above += c[q]; ++at; here = c[q + 1u]; }
+            const int src = owner != 0ull ? __ffsll((unsigned long long)owner) - 1 : 0;
+            at = kMask - 4u * (u32)src - (u32)__builtin_amdgcn_readlane((int)at, src);
+            above = (u32)__builtin_amdgcn_readlane((int)above, src);
+            here = (u32)__builtin_amdgcn_readlane((int)here, src);
+            // (the bin holds as many as are needed)
+            decide(owner != 0ull ? kPartFound | (u64)at << 2 | (u64)here << (2u + kPartBits) | (u64)above << (2u + kPartBits + kPartEntries)
+                                 : kPartOff);
+        }
+    }
+    if (tid < (u32)kWave) {
+        u64 word = 0ull;
+        u32 polls = 0;
+        while ((word = __hip_atomic_load(&mine.found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0ull) {
+            __builtin_amdgcn_s_sleep(16);
+            if (++polls == kNarrowPolls) decide(kPartOff);
+            if (polls > kWideSpinLimit) { word = kPartOff; break; }      // (cannot happen: somebody decides)
+        }
+        if (tid == 0u) found_s = word;
+    }
+    __syncthreads();
+    const u64 word = found_s;
+    if ((word & kPartFound) == 0ull) return now;
+    const u32 lo = now.bd_lo | ((u32)(word >> 2) & kMask) << kShift;
+    return Picked{0u, lo, lo | ((1u << kShift) - 1u), now.c_def + ((u32)(word >> (2u + kPartBits + kPartEntries)) & kEntryMask),
+                  (u32)(word >> (2u + kPartBits)) & kEntryMask};
+}
+
 __device__ __forceinline__ void
-classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, const Picked &now,
-                 uint2 *__restrict__ seg, uint2 *__restrict__ s_ent, u32 *__restrict__ win_cnt,
-                 u32 *__restrict__ bd_cnt, u32 *__restrict__ quad_win, uint2 *__restrict__ blk_lists,
-                 u32 *__restrict__ blk_bmin, u32 *__restrict__ blk_bmax, uint2 *__restrict__ m_ent,
-                 uint2 *__restrict__ b_ent)
+classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, Picked now, const u32 &hot,
+                 bool picked_here, const float *__restrict__ a, PartGroup *groups, uint2 *__restrict__ seg,
+                 uint2 *__restrict__ s_ent, u32 *__restrict__ win_cnt, u32 *__restrict__ bd_cnt,
+                 u32 *__restrict__ quad_win, uint2 *__restrict__ blk_lists, u32 *__restrict__ blk_bmin,
+                 u32 *__restrict__ blk_bmax, uint2 *__restrict__ m_ent, uint2 *__restrict__ b_ent)
 {
     __shared__ u32 cnt_m, cnt_b, bmin_s, bmax_s, sure_s[kWalkWaves];
     __shared__ uint2 hits[kWalkWaves][kMinChunk];
@@ -1804,6 +1988,10 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
     const u64 below = lanes_below();
     if (threadIdx.x == 0) { cnt_m = 0u; cnt_b = 0u; bmin_s = 0xFFFFFFFFu; bmax_s = 0u; }
     lds_barrier();
+    const bool narrows = g.narrow_from != 0u && (now.n_bin >= g.narrow_from || hot != 0u);
+    if (__builtin_expect(narrows, 0)) now = narrow_bin(chunk, g, a, groups, now);
+    // (once narrowed, nobody reads the words of the kernel that picked any more: all had checked in)
+    if ((picked_here || narrows) && blockIdx.x == 0 && threadIdx.x == 0) now.store(ctl);
     // ---- the entries, in index order
     u32 n = 0;
     if (now.mode == 0u) {
@@ -1835,6 +2023,10 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
         if ((here & below) == 0ull) base = atomicAdd(count, popc64(here));
         return (u32)__builtin_amdgcn_readfirstlane((int)base) + popc64(here & below);
     };
+    // Where finalize has room for the whole bin, in LDS and in memory, a few workgroups may hold most of it (a layer of
+    // like magnitudes).
+    const u32 room = g.G3 * kListCap < kStageB ? g.G3 * kListCap : kStageB;
+    const u32 cap_b = now.n_bin - 1u < room ? kLongList : kListCap;
     u32 sure = 0, in_bin = 0, lane_bmin = 0xFFFFFFFFu, lane_bmax = 0u;
     for (u32 j0 = 0; j0 < n; j0 += kWave) {
         const u32 j = j0 + lane;
@@ -1858,7 +2050,7 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
         if (here_b) {
             const u32 p = places(&cnt_b, __ballot(true));
             // (finalize needs the key's word and, knowing the bin, half of the magnitude)
-            if (p < kListCap) b_ent[slot(p)] = make_uint2((key & ~kPlaceMask) | (m & 0xFFFFu), idx);
+            if (p < cap_b) b_ent[slot(p)] = make_uint2((key & ~kPlaceMask) | (m & 0xFFFFu), idx);
             if (m < lane_bmin) { lane_bmin = m; atomicMin(&bmin_s, m); }
             if (m > lane_bmax) { lane_bmax = m; atomicMax(&bmax_s, m); }
         }
@@ -1876,11 +2068,11 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
         static_assert(kWalkWaves == kQuad, "the workgroup's chunks are a quad");
         const u32 of_quad = sure_s[0] + sure_s[1] + sure_s[2] + sure_s[3];
         quad_win[blockIdx.x] = of_quad;
-        const u32 in_m = cnt_m < kListCap ? cnt_m : kListCap, in_b = cnt_b < kListCap ? cnt_b : kListCap;
+        const u32 in_m = cnt_m < kListCap ? cnt_m : kListCap, in_b = cnt_b < cap_b ? cnt_b : cap_b;
         blk_lists[blockIdx.x] = make_uint2(in_m | in_b << 16, of_quad);
         blk_bmin[blockIdx.x] = bmin_s;
         blk_bmax[blockIdx.x] = bmax_s;
-        if (cnt_m > kListCap || cnt_b > kListCap) ctl->overflow = 1u;
+        if (cnt_m > kListCap || cnt_b > cap_b) ctl->overflow = 1u;
         if (cnt_m > kListCap) ctl->overflow_m = 1u;
     }
 }
@@ -2072,14 +2264,6 @@ struct Wide {
     bool alive;         // false once a barrier timed out
     u32 spin_limit;     // polls before a workgroup gives up at a barrier
 };
-
-// until everything this wavefront has sent to memory is acknowledged
-__device__ __forceinline__ void wait_own_memory()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0);
-    asm volatile("" ::: "memory");
-}
 
 // Everything the workgroups exchange goes through device-scope atomic
 // operations (additions to the histograms, atomic stores of the few words
@@ -2364,7 +2548,7 @@ finalize_small(const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, FinalizeLi
             part[wave][3] = (more != 0ull ? 1u : 0u) | (upper != 0ull ? 2u : 0u);
         }
     }
-    const u32 mode = ctl->mode, overflow = ctl->overflow, bd_hi = ctl->bd_hi;
+    const u32 mode = ctl->mode, overflow = ctl->overflow, bd_hi = ctl->bd_hi, bd_bits = ctl->bd_bits;
     const u64 c_def = ctl->c_def;
     lds_barrier();
     u32 n_m0 = 0, n_bd = 0, sure_walk = 0, more = 0;
@@ -2380,7 +2564,7 @@ finalize_small(const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, FinalizeLi
     if (!g.take_all && (sure_walk >= g.k || sure_walk + n_m0 + need2 < g.k)) return false;     // (the window certainly missed)
     const bool works = wave < kFinWaves / 2u || (more & 2u) != 0u;
     // ---- count. An entry of B is the magnitude's low half (2^16 magnitudes to a bin) and the key's word.
-    constexpr u32 kShiftB = kCountShift - 10u;
+    const u32 shift_b = bd_bits > 10u ? bd_bits - 10u : 0u;
     static_assert(kCutB == 1u << 10 && kCountShift == 16u, "bits of a bin of B");
     const CutBins<kCutB / kWave, false> cut_b{ls.bin_b, ls.group_b};
     const CutBins<kCutM / kWave, true> cut_m{ls.bin_m, ls.group_m};
@@ -2395,11 +2579,11 @@ finalize_small(const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, FinalizeLi
             if (own.place(q) < n) f(q);
         }
     };
-    auto x_of = [&](u32 q) { return ~own.b[q].x & 0xFFFFu; };
+    auto x_of = [&](u32 q) { return (bd_hi - own.b[q].x) & 0xFFFFu; };
     auto place_of = [&](u32 q) { return own.b[q].x >> kPlaceBits & (kCutM - 1u); };
     if (works) {
         each_own(n_m, rounds_m, [&](u32 q) { cut_m.add(own.m[q].x); });
-        each_own(n_b, rounds_b, [&](u32 q) { cut_b.add(x_of(q) >> kShiftB); });
+        each_own(n_b, rounds_b, [&](u32 q) { cut_b.add(x_of(q) >> shift_b); });
     }
     lds_barrier();
     // ---- the cut in B
@@ -2410,7 +2594,7 @@ finalize_small(const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, FinalizeLi
         ok = here <= (u32)kWave;
         if (ok)
             each_own(n_b, rounds_b, [&](u32 q) {
-                if (x_of(q) >> kShiftB == at) {
+                if (x_of(q) >> shift_b == at) {
                     const u32 j = atomicAdd(&ls.n_cand_b, 1u);
                     ls.b_x[j] = x_of(q);
                     ls.b_idx[j] = own.b[q].y;
@@ -2515,6 +2699,7 @@ finalize_small(const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, FinalizeLi
         ctl->UC = g.UC;
         ctl->count_greater = c_def + gt_s;
         ctl->ties = g.r - (c_def + gt_s);
+        ctl->how = kHowRegisters | (bd_bits < kCountShift ? kHowNarrowed : 0u);
     }
     return true;
 }
@@ -3100,6 +3285,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
                 bk[p] = (u64)(bd_hi - mag_in_b(e.x));
                 bi[p] = e.y;
             }
+        if (kCounted) __syncthreads();          // (a long list of B reaches into where M's keys go)
         for (u32 p = tid; p < n_m0; p += kFinThreads) {
             const u32 idx = m_ent[mi[p]].y;
             mk[p] = (sample_key(idx, seed) - g.K_lo) << g.k_nlz;
@@ -3431,6 +3617,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         ctl->UC = g.UC;
         ctl->count_greater = count_greater;
         ctl->ties = g.r - count_greater;
+        ctl->how = kCounted && bd_bits < kCountShift ? kHowNarrowed : 0u;
     }
 }
 
@@ -3623,14 +3810,17 @@ __global__ void __launch_bounds__(kWalkThreads) k_classify(Batch B, Geom g, Enco
 __global__ void __launch_bounds__(kCountThreads) k_count(Batch B, Geom g, EncodeLayout L)
 {
     const Member m(B);
-    count_body(m.grad, m.residual, g, m.at<u32>(0), (u32)(L.zero_bytes / 4), m.at<u16>(L.samples), m.at<uint4>(L.partials));
+    const u32 group_words = (part_groups(g.G3) + 1u) * (u32)(sizeof(PartGroup) / 4u);
+    count_body(m.grad, m.residual, g, m.at<u32>(0), (u32)(L.zero_bytes / 4), m.at<u32>(L.group_sums), group_words, m.at<u16>(L.samples), m.at<uint4>(L.partials));
 }
 
 __global__ void __launch_bounds__(kPickThreads) k_pick_counted(Batch B, u32 n_rows, Geom g, EncodeLayout L)
 {
     const Member m(B);
-    const Picked p = pick_counted<kPickThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g);
-    if (threadIdx.x == 0) p.store(m.at<EncodeCtl>(L.ctl));
+    __shared__ u32 hot;
+    const Picked p = pick_counted<kPickThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g, &hot);
+    lds_barrier();
+    if (threadIdx.x == 0) { p.store(m.at<EncodeCtl>(L.ctl)); m.at<EncodeCtl>(L.ctl)->hot = hot; }
 }
 
 template <bool kPick>
@@ -3639,14 +3829,15 @@ __global__ void __launch_bounds__(kWalkThreads) k_classify_counted(Batch B, u32 
     const Member m(B);
     EncodeCtl *ctl = m.at<EncodeCtl>(L.ctl);
     const ChunkRows chunk(m.residual, g.d, blockIdx.x * kWalkWaves + threadIdx.x / kWave);
+    __shared__ u32 hot;
     Picked p{};
     if (kPick) {
-        p = pick_counted<kWalkThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g);
-        if (blockIdx.x == 0 && threadIdx.x == 0) p.store(ctl);
+        p = pick_counted<kWalkThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g, &hot);
     } else {
-        p = Picked{ctl->mode, ctl->bd_lo, ctl->bd_hi, 0ull};
+        p = Picked{ctl->mode, ctl->bd_lo, ctl->bd_hi, ctl->c_def, ctl->n_bin};
+        if (threadIdx.x == 0) hot = ctl->hot;
     }
-    classify_counted(chunk, g, m.seed, ctl, p, m.at<uint2>(L.seg), m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt),
+    classify_counted(chunk, g, m.seed, ctl, p, hot, kPick, m.residual, m.at<PartGroup>(L.group_sums), m.at<uint2>(L.seg), m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt),
                      m.at<u32>(L.bd_cnt), m.at<u32>(L.quad_win), m.at<uint2>(L.blk_lists), m.at<u32>(L.blk_bmin),
                      m.at<u32>(L.blk_bmax), m.at<uint2>(L.m_ent), m.at<uint2>(L.b_ent));
 }
@@ -3798,7 +3989,7 @@ constexpr int kFusedBlocksPerCU = 1;
 // whose workgroups only hold a chunk per wavefront, run side by side instead.)
 constexpr unsigned kFusedLdsClaim = 96u * 1024u;
 std::mutex g_device_mutex;
-unsigned g_fused_grid[kMaxDevices];
+unsigned g_fused_grid[kMaxDevices], g_classify_grid[kMaxDevices];
 
 template <class K>
 bool allow_lds_claim(K kernel, unsigned bytes = kFusedLdsClaim)
@@ -3873,13 +4064,15 @@ bool deals_across(const Geom &g, bool is_short, unsigned nb)
 // Whether a vector's magnitudes are all counted (count_body): short vectors. Whole calls, us, by sample,
 // estimate and candidates / counted: one vector of 65,536 elements 38.9 / 23.9, of 200,003 32.9 / 24.0, of
 // 2^20 36.8 / 28.2, of 2 M, r = 0.5%, 44.7 / 35.8 (layered), of 3 M 45.8 / 38.9; four of 2 M 61.5 / 52.7,
-// sixteen of 2^20 81.7 / 74.7, of 2 M 120 / 112, of 3 M 158 / 153. A bin is a 128th of an octave and holds 1 to 6% of the
-// top r, by where the threshold lies between two powers of two: a longer list for finalize, and from 4,608 entries on
-// one that does not fit. So r is limited where that costs more than the launches save. Normal values at eight scales, before / now
-// from the least to the most favourable: 3.1 M, r = 32,000 1.10-1.15, 98,000 0.74-0.99; 3 M, r = 60,000 0.84-1.10; 2 M, r = 64,000
-// 1.08-1.20, 130,000 0.80-1.17; 1.5 M, r = 64,000 1.10-1.16; 1.3 M, r = 200,000 0.95-1.16; 2^20, any r 1.17-1.25 (at most 4% of
-// all elements lie in a bin). Above 3072 chunks the vector's second reading costs what the launches
-// save, and hot chunks want the room that the stream's wavefronts share.
+// sixteen of 2^20 81.7 / 74.7, of 2 M 120 / 112, of 3 M 158 / 153. A bin is a 128th of an octave: of normal values at most
+// 0.38% of all elements lie in one, 1 to 6% of the top r by where the threshold lies between two powers of two, which
+// is a longer list for finalize than a bracket's bins leave. So r is limited where that costs more than the launches save.
+// Normal values at eight scales, before / now from the least to the most favourable, without narrow_bin: 3.1 M, r = 32,000
+// 1.10-1.15, 98,000 0.74-0.99; 3 M, r = 60,000 0.84-1.10; 2 M, r = 64,000
+// 1.08-1.20, 130,000 0.80-1.17; 1.5 M, r = 64,000 1.10-1.16; 1.3 M, r = 200,000 0.95-1.16; 2^20, any r 1.17-1.25. Values
+// with lighter tails have no such bound; their bins are narrowed (see there: from 2 M elements on they gain little, at 3 M
+// uniform values lose 4%; a few levels of 2^20, r = 1%, lose 5%, uniform values eight at a time 2%). Above 3072 chunks the vector's second
+// reading costs what the launches save, and hot chunks want the room that the stream's wavefronts share.
 constexpr u32 kCountAnyR = 1024, kCountMid = 2048;               // chunks
 constexpr u64 kCountMidMembers = 1u << 16, kCountMembers = 1u << 15;
 bool counts_all(const Geom &g)
@@ -3898,11 +4091,12 @@ CountShape count_shape(u32 W)
     return CountShape{waves * (unsigned)kWave, (W + each - 1) / each};
 }
 // Whether the short lists are likely to be in reach of OwnEntries: eight times what a classify workgroup leaves on
-// average, of the window's keys (most of stage_m) and of the deciding bin (a twentieth of the top r, as a
-// rule); a batch of many, which the slowest member holds up, only where next to every place is in reach. Calls, us, with
+// average, of the window's keys (most of stage_m) and of the deciding bin (a twentieth of the top r for
+// normal values); a batch of many, which the slowest member holds up, only where next to every place is in reach. Calls, us, with
 // the lists in LDS / in registers: one vector of 65,536 elements 23.6 / 20.8, of 200,003 24.4 / 21.7, layered,
 // r = 2%, 30.1 / 28.4, of 524,288 25.8 / 24.6, of 2^20 28.0 / 25.9, layered 28.0 / 27.3, touched rows 27.7 / 28.4; eight of
-// 200,003 29.0 / 28.1, of 2^20 49.9 / 50.5. Where the attempt fails it costs 0.7 to 1.7: 2^20, r = 2%, 33.0 / 34.6.
+// 200,003 29.0 / 28.1, of 2^20 49.9 / 50.5. Where the attempt fails (touched rows, whose keys are in few workgroups;
+// lighter tails) it costs 0.7 to 1.7: 2^20, r = 2%, 33.0 / 34.6.
 bool small_lists(const Geom &g, unsigned nb)
 {
     if (g.G3 > kSmallBlocks || (nb > 2u && g.G3 > kSmallBlocks / 4u)) return false;
@@ -3910,18 +4104,30 @@ bool small_lists(const Geom &g, unsigned nb)
     return g.r / 20 * 8 <= room && (u64)g.stage_m * 8 <= room;
 }
 
+// The entries of the deciding bin from which on classify narrows it down: more than finalize has room for (4,089 of
+// 2^20 uniform values 34.1, narrowed 31.8, but eight at a time 62.8 and 68.1), or, of a vector of few classify workgroups, so many
+// on average that some lists may not hold theirs (200,003 elements of which 1,229 entries, half of them in one workgroup's
+// chunks, decide: 37.0 narrowed, on the exact selection 388; 1,493 spread ones 29.8, narrowed 30.0).
+u32 narrows_from(u32 G3)
+{
+    const u32 spread = G3 * kListCap * 3u / 16u;
+    return (spread < kStageB ? spread : kStageB) + 1u;
+}
+
 // Every classify workgroup picks for itself up to this many rows over all members, a kernel picks beyond. us, in
 // classify / by a kernel: one of 200,003 (25 rows) 26.7 / 28.9, of 2^21 (128) 37.2 / 38.9; two of 2^21 44.0 / 43.6; four
 // of 2^20 (64) 39.5 / 40.5, of 1.5 M (92) 50.9 / 47.8; eight of 524,288 (64) 41.3 / 41.5, of 2^20 55.1 / 52.6.
 constexpr unsigned kPickRows = 256;
 
-int fused_grid_limit(unsigned *out)
+// workgroups of the streaming kernel in a launch at most, and workgroups of a counted vector's classify that the
+// device holds at once
+int fused_grid_limit(unsigned *out, unsigned *classify_out = nullptr)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return RTOPK_EHIP;
     std::lock_guard<std::mutex> lock(g_device_mutex);
     if (g_fused_grid[dev] == 0) {
-        int cus = 0, fit_t = 0, fit_f = 0;
+        int cus = 0, fit_t = 0, fit_f = 0, fit_c = 0, fit_p = 0;
         if (!allow_lds_claim(k_fused<false, kLongRows, true>) || !allow_lds_claim(k_fused<false, kShortRows, true>) ||
             !allow_lds_claim(k_fused<true, kLongRows, true>) || !allow_lds_claim(k_stream_add<kLongRows>) ||
             !allow_lds_claim(k_finalize<false>, 4u * kStageM) || !allow_lds_claim(k_finalize<true>, 4u * kStageM))
@@ -3932,15 +4138,19 @@ int fused_grid_limit(unsigned *out)
                                                          kFusedLdsClaim) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_f, k_fused<true, kLongRows, true>,
                                                          (int)kFusedThreads,
-                                                         kFusedLdsClaim) != hipSuccess)
+                                                         kFusedLdsClaim) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_c, k_classify_counted<false>, (int)kWalkThreads, 0) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit_p, k_classify_counted<true>, (int)kWalkThreads, 0) != hipSuccess)
             return RTOPK_EHIP;
         int per_cu = fit_t < fit_f ? fit_t : fit_f;
         per_cu = per_cu < kFusedBlocksPerCU ? per_cu : kFusedBlocksPerCU;
         if (cus < 1 || per_cu < 1) return RTOPK_EHIP;
         const unsigned grid = (unsigned)cus * (unsigned)per_cu;
         g_fused_grid[dev] = grid > kMaxFusedBlocks ? kMaxFusedBlocks : grid;
+        g_classify_grid[dev] = (unsigned)cus * (unsigned)(fit_c < fit_p ? fit_c : fit_p);
     }
     *out = g_fused_grid[dev];
+    if (classify_out) *classify_out = g_classify_grid[dev];
     return RTOPK_OK;
 }
 }  // namespace
@@ -4003,8 +4213,8 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
     // (what a sample or a bracket that misleads does to a call belongs to the path that has them)
     const unsigned force_general = force & (RTOPK_FORCE_ESTIMATE_MISS | RTOPK_FORCE_BRACKET_LOW);
     hipStream_t stream = (hipStream_t)stream_v;
-    unsigned grid_limit = 0;
-    const int rc2 = fused_grid_limit(&grid_limit);
+    unsigned grid_limit = 0, classify_limit = 0;
+    const int rc2 = fused_grid_limit(&grid_limit, &classify_limit);
     if (rc2) return rc2;
     const TraceRequest trace = g_trace;
     g_trace = TraceRequest{};
@@ -4041,6 +4251,7 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         const CountShape cs = count_shape(gg.W);
         if (counts) set_units(gg, 1u);                  // a chunk per wavefront of the walking kernels
         gg.small = counts && small_lists(gg, nb) ? 1u : 0u;
+        gg.narrow_from = counts && gg.G3 <= classify_limit && gg.force_abort == 0u ? narrows_from(gg.G3) : 0u;
         if (counts) {
             { StageScope none(trace, RTOPK_STAGE_PREPARE, stream); }    // (nothing to prepare: the events are recorded all the same)
             StageScope sc(trace, RTOPK_STAGE_FUSED, stream);

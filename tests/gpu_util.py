@@ -54,6 +54,12 @@ class GpuWorker:
                 self.residual.cpu().numpy().copy())
 
 
+def lists_that_decided(ws) -> int:
+    """The word of the control block that says which lists of a counted vector decided: bit 0, those in
+    registers; bit 1, the deciding bin had been narrowed."""
+    return int(ws[136:140].view(torch.int32).item())
+
+
 def gpu_encode_once(g, m, r, k, seed, step, offset=0, force=0):
     w = GpuWorker(len(g), r, k, residual=m, offset=offset)
     out = w.encode(g, seed, step, force=force)
