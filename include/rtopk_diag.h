@@ -27,7 +27,8 @@ typedef struct rtopk_encode_stats {
                                     (any bit set: results invalid) */
     uint32_t path;               /* 0: both cut points came from the short lists; bit 0: at least one
                                     came from the slow selection over all candidates; bit 1: the
-                                    sampled estimate failed and the vector itself was walked;
+                                    sampled estimate failed, or (a counted vector, see below) the bins
+                                    that decide were not kept, and the vector itself was walked;
                                     bit 2: the threshold lies in a run of equal magnitudes too long
                                     for the short list (zeros, signs, a few quantisation levels):
                                     its last member was located from per-chunk counts; bit 3: the
@@ -36,7 +37,8 @@ typedef struct rtopk_encode_stats {
     uint32_t threshold_bits;     /* magnitude pattern of the r-th largest |a_i|. With r == d no
                                     magnitude is looked at: threshold_bits and count_greater
                                     are reported as 0 and ties_taken as r */
-    uint32_t boundary_list_size; /* candidates that shared the deciding histogram bin */
+    uint32_t boundary_list_size; /* candidates that shared the deciding histogram bin (of a counted vector
+                                    whose bin was crowded: the part of it that decides) */
     uint64_t count_greater;      /* #{i : mag(a_i) > threshold} */
     uint64_t ties_taken;         /* r - count_greater, taken from the lowest indices */
     uint64_t superset_size;      /* entries compacted before the exact selection (candidates that
@@ -54,10 +56,15 @@ int rtopk_encode_stats(const void *workspace, void *stream, rtopk_encode_stats_t
  * before the kernels of `stage` and `ev_end` right after them; the request is
  * then forgotten. Stage RTOPK_STAGE_ALL brackets the whole call. The events
  * stay owned by the caller. Passing stage 0 cancels a pending request.
+ *
+ * Short vectors (up to about 3 M elements, fewer with large r, and not r == d) are counted: there is
+ * no sample and no estimate, RTOPK_STAGE_PREPARE brackets nothing, RTOPK_STAGE_FUSED counts
+ * all magnitudes by their leading bits and keeps no candidates, and RTOPK_STAGE_CLASSIFY makes
+ * them once the deciding bin is known.
  */
 #define RTOPK_STAGE_PREPARE 1   /* sample a = g + m, estimate the threshold range, clear counters */
 #define RTOPK_STAGE_FUSED 2     /* a = g + m, store, candidates + histogram */
-#define RTOPK_STAGE_CLASSIFY 3  /* certain members, key window, short lists */
+#define RTOPK_STAGE_CLASSIFY 3  /* deciding bin, certain members, key window, short lists */
 #define RTOPK_STAGE_FINALIZE 4  /* exact cut points, output offsets */
 #define RTOPK_STAGE_EMIT 5      /* message + residual write-back */
 #define RTOPK_STAGE_ALL 100
@@ -70,7 +77,8 @@ int rtopk_trace_next_encode(int stage, void *ev_begin, void *ev_end);
  * then forgotten. The results must not change, only rtopk_encode_stats.path
  * (RTOPK_FORCE_BARRIER_TIMEOUT excepted, see there).
  *   RTOPK_FORCE_ESTIMATE_MISS    the sampled threshold estimate keeps no
- *                                candidates: the vector itself is walked
+ *                                candidates (a counted vector: the bins that
+ *                                decide were not kept): the vector itself is walked
  *   RTOPK_FORCE_KEY_WINDOW_MISS  the a-priori window around the k-th smallest
  *                                sampling key is empty: the key cut comes from
  *                                a selection over all candidates
@@ -81,12 +89,15 @@ int rtopk_trace_next_encode(int stage, void *ev_begin, void *ev_end);
  *                                compute units and waits too): one workgroup
  *                                runs the selection alone. Only has an effect
  *                                together with a condition that needs the
- *                                selection.
+ *                                selection, or on a counted vector whose
+ *                                deciding bin is crowded, which is then not
+ *                                narrowed.
  *   RTOPK_FORCE_BRACKET_LOW      the estimate's upper bound is put at its lower
  *                                bound, as if the sample had underestimated
  *                                the r-th largest magnitude: the threshold
  *                                then lies above the finely binned range, in
  *                                the one bin that holds everything above it
+ *                                (a short vector is sampled, not counted, for it)
  *   RTOPK_FORCE_BARRIER_TIMEOUT  (an error path, not a fallback) the bounded
  *                                waits between the workgroups of the
  *                                many-workgroup selection give up at their

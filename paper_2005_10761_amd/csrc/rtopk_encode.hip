@@ -285,7 +285,8 @@ struct Geom {
     u32 L;              // sampled locations
     u32 est_vecs;       // sampled locations per thread of the estimate kernel, a power of two (empty ones included)
     u32 nfine;          // linear histogram bins
-    u32 force_dense;    // diagnostics: make the estimate keep nothing, as if the sample had misled it
+    u32 force_dense;    // diagnostics: make the estimate keep nothing, as if the sample had misled it (of a counted
+                        // vector: as if the deciding bin's row had lost its slot)
     u32 force_abort;    // diagnostics: the workgroups of the wide selection decide "abort" at check-in
     u32 force_timeout;  // diagnostics: the barriers of the wide selection give up at their first poll
     u32 force_low;      // diagnostics: the bracket's upper end is put at its lower end, as if the sample
@@ -1587,6 +1588,7 @@ pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n
     for (u32 i = tid; i < kCountGroups; i += kThreads) gtot[i] = 0u;
     if (tid < kGroupBins) btot[tid] = 0u;
     if (tid == 0) { lost_s = 0u; *hot = 0u; }
+    if (__builtin_expect(g.force_dense != 0u, 0)) return Picked{1u, 0u, 0u, 0ull, 0u};
     // ---- all rows' sums: a thread takes eight groups of every (kThreads / 32)-th row
     constexpr u32 kAt = kCountGroups / 8u, kAhead = 8;
     u32 sum[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
@@ -4210,8 +4212,8 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         g.K_lo = g.K_hi = 0;       // a window that holds no key: the exact selection must run
         g.k_nlz = 63u;
     }
-    // (what a sample or a bracket that misleads does to a call belongs to the path that has them)
-    const unsigned force_general = force & (RTOPK_FORCE_ESTIMATE_MISS | RTOPK_FORCE_BRACKET_LOW);
+    // (a bracket that ends too low belongs to the path that has one)
+    const bool force_bracket = (force & RTOPK_FORCE_BRACKET_LOW) != 0u;
     hipStream_t stream = (hipStream_t)stream_v;
     unsigned grid_limit = 0, classify_limit = 0;
     const int rc2 = fused_grid_limit(&grid_limit, &classify_limit);
@@ -4247,7 +4249,7 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         B.ws = (char *)workspace + (u64)first * L.total;
         B.ws_stride = L.total;
         const dim3 fg(fgrid, 1, nb);
-        const bool counts = force_general == 0u && counts_all(gg);
+        const bool counts = !force_bracket && counts_all(gg);
         const CountShape cs = count_shape(gg.W);
         if (counts) set_units(gg, 1u);                  // a chunk per wavefront of the walking kernels
         gg.small = counts && small_lists(gg, nb) ? 1u : 0u;

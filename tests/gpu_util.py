@@ -60,6 +60,11 @@ def lists_that_decided(ws) -> int:
     return int(ws[136:140].view(torch.int32).item())
 
 
+def estimated_bins(ws) -> int:
+    """The control block's number of histogram bins that an estimate chose (0: there was none)."""
+    return int(ws[20:24].view(torch.int32).item())
+
+
 def gpu_encode_once(g, m, r, k, seed, step, offset=0, force=0):
     w = GpuWorker(len(g), r, k, residual=m, offset=offset)
     out = w.encode(g, seed, step, force=force)

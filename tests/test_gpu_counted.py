@@ -143,3 +143,15 @@ def test_lists_in_and_beyond_registers(d, hot, where):
     print(f"lists d={d} hot={hot} {where} r={r}", flush=True)
     for k in (r // 3, r):
         _check(g, np.zeros(d, np.float32), r, k, path=None)
+
+
+@pytest.mark.parametrize("d", [5_000, 300_007, 2_500_000])
+def test_a_forced_miss_runs_the_counted_chain(d):
+    """What the hook makes happen, happens on the kernels such a vector takes: no estimate has left its bins behind."""
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    g = np.random.default_rng(d).standard_normal(d).astype(np.float32)
+    w = u.GpuWorker(d, d // 100, d // 500)
+    want = oracle.encode(g, np.zeros(d, np.float32), d // 100, d // 500, 1, 2)
+    u.assert_encode_equal(w.encode(g, 1, 2, force=rt.FORCE_ESTIMATE_MISS), want, f"d={d}")
+    assert w.stats["path"] & 3 == 3 and u.estimated_bins(w.ws) == 0
