@@ -1475,7 +1475,7 @@ pick_body(const u32 *__restrict__ partials, const u32 *__restrict__ group_sums, 
 // stores: the sums of all 256 groups (two bytes each), and the bins of the groups it has anything
 // in. Those lie in kRowSlots slots, group e in slot e mod kRowSlots: of groups that meet there the
 // highest one that is not empty, the others are marked kNotStored in their sums (that takes magnitudes 64
-// octaves apart in one workgroup; should one of those groups decide, the vector itself is walked).
+// octaves apart in one workgroup; should one of those groups decide, classify narrows it as a crowded bin).
 // Magnitudes in bin 0 (zeros, mostly, which come in long runs) are not counted: what the
 // others do not account for lies there.
 // ---------------------------------------------------------------------------
@@ -1658,7 +1658,12 @@ pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n
     for (u32 c = 0; c < 8; ++c) if (sum[c]) atomicAdd(&btot[tid % kOf * 8u + c], sum[c]);
     if (marks != 0u) lost_s = 1u;
     lds_barrier();
-    if (lost_s != 0u) return Picked{1u, 0u, 0u, 0ull, 0u};
+    if (__builtin_expect(lost_s != 0u, 0)) {
+        // (the octave decides: classify narrows it, or the vector itself is walked)
+        constexpr u32 kOctave = kGroupBins << kCountShift;
+        *hot = 1u;
+        return Picked{1u, group * kOctave, group * kOctave + (kOctave - 1u), above, gtot[group]};
+    }
     const u32 b0 = btot[kGroupBins - 1u - 2u * lane], b1 = btot[kGroupBins - 2u - 2u * lane];
     inc = wave_inclusive_sum(b0 + b1);
     u32 before = above + inc - b0 - b1;
@@ -1828,7 +1833,7 @@ __device__ __forceinline__ void wait_own_memory()
 // entries, of magnitudes that are nearly equal, or clipped with some noise on top, most of the vector, and no short list
 // takes those. All workgroups know from the pick how many there are, and whether they crowd. From
 // g.narrow_from on, or where they crowd, the workgroups count the bin's entries by their next 8 bits and go on with
-// the one of 256 parts that decides. Calls, us, with sample and bracket / counted, the bin as it is / narrowed, r = 1%:
+// the one of 256 parts that decides. So they do with an octave whose bins some workgroup of count did not keep. Calls, us, with sample and bracket / counted, the bin as it is / narrowed, r = 1%:
 // uniform values, 2 M elements 42.9 / 60.6 / 39.5, 3 M 45.4 / 76.7 / 47.1; 1 + 1% normal, 200,003 42.6 / 257 / 32.8, 2^20
 // 46.9 / 83.3 / 38.6; clipped with noise of 1e-3, 200,003 42.8 / 3167 / 32.4, 2^20 70.9 / 124 / 39.2; one layer of 8192
 // in 1..1.05, 200,003 45.0 / 390 / 38.5; eight of 2^20, 1 + 5% normal 69.8 / 82.3 / 69.1. Where nothing
@@ -1863,8 +1868,11 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
     __shared__ u32 part[1u << kPartBits], last_s, looked_s, least_s, most_s;
     __shared__ u64 found_s;
     static_assert(kWalkThreads == 1u << kPartBits, "a counter per thread");
-    constexpr u32 kShift = kCountShift - kPartBits, kMask = (1u << kPartBits) - 1u, kEntryMask = (1u << kPartEntries) - 1u;
-    const u32 tid = threadIdx.x, lane = lane_id(), bin = now.bd_lo >> kCountShift;
+    constexpr u32 kMask = (1u << kPartBits) - 1u, kEntryMask = (1u << kPartEntries) - 1u;
+    const u32 tid = threadIdx.x, lane = lane_id(), span = now.bd_hi - now.bd_lo;
+    const u32 shift = 32u - kPartBits - (u32)__clz((int)span);
+    // (where there is nothing narrower: the vector itself is walked if the bins were not kept)
+    const Picked as_it_was = now.mode != 0u ? Picked{1u, 0u, 0u, 0ull, 0u} : now;
     const u32 n_groups = part_groups(gridDim.x), group = blockIdx.x / kPartGroup;
     PartGroup &mine = groups[group], &root = groups[n_groups];
     // (a look at 1,024 elements, the same ones by all workgroups)
@@ -1876,8 +1884,8 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
     for (u32 q = 0; q < kChunkRows; ++q)
 #pragma unroll
         for (u32 e = 0; e < 4; ++e) {
-            const u32 m = mag_of(__float_as_uint(chunk.v[q][e])), at = m >> kShift & kMask;
-            const bool in = m >> kCountShift == bin && q * kChunkQuantum + 4u * lane + e < chunk.len;
+            const u32 x = mag_of(__float_as_uint(chunk.v[q][e])) - now.bd_lo, at = x >> shift;
+            const bool in = x <= span && q * kChunkQuantum + 4u * lane + e < chunk.len;
             const u64 here = __ballot(in);
             if (here == 0ull) continue;
             // (all of one part: one addition serves them)
@@ -1893,7 +1901,7 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
 #pragma unroll
     for (u32 e = 0; e < 4; ++e) {
         const u32 m = mag_of(__float_as_uint(some[e]));
-        if (m >> kCountShift != bin) continue;
+        if (m - now.bd_lo > span) continue;
         ++looked;
         least = m < least ? m : least;
         most = m > most ? m : most;
@@ -1904,7 +1912,7 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
     if (lane == 0u) { atomicAdd(&looked_s, looked); atomicMin(&least_s, least); atomicMax(&most_s, most); }
     lds_barrier();
     // equal magnitudes (signs, a few levels): no part will be smaller
-    if (looked_s > 1u && least_s == most_s) return now;
+    if (now.mode == 0u && looked_s > 1u && least_s == most_s) return now;
     if (part[tid] != 0u) __hip_atomic_fetch_add(&mine.count[tid], part[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     wait_own_memory();
     __syncthreads();
@@ -1970,9 +1978,9 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
     }
     __syncthreads();
     const u64 word = found_s;
-    if ((word & kPartFound) == 0ull) return now;
-    const u32 lo = now.bd_lo | ((u32)(word >> 2) & kMask) << kShift;
-    return Picked{0u, lo, lo | ((1u << kShift) - 1u), now.c_def + ((u32)(word >> (2u + kPartBits + kPartEntries)) & kEntryMask),
+    if ((word & kPartFound) == 0ull) return as_it_was;
+    const u32 lo = now.bd_lo | ((u32)(word >> 2) & kMask) << shift;
+    return Picked{0u, lo, lo | ((1u << shift) - 1u), now.c_def + ((u32)(word >> (2u + kPartBits + kPartEntries)) & kEntryMask),
                   (u32)(word >> (2u + kPartBits)) & kEntryMask};
 }
 
@@ -1992,6 +2000,7 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
     lds_barrier();
     const bool narrows = g.narrow_from != 0u && (now.n_bin >= g.narrow_from || hot != 0u);
     if (__builtin_expect(narrows, 0)) now = narrow_bin(chunk, g, a, groups, now);
+    else if (now.mode != 0u) now = Picked{1u, 0u, 0u, 0ull, 0u};
     // (once narrowed, nobody reads the words of the kernel that picked any more: all had checked in)
     if ((picked_here || narrows) && blockIdx.x == 0 && threadIdx.x == 0) now.store(ctl);
     // ---- the entries, in index order
@@ -3619,7 +3628,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         ctl->UC = g.UC;
         ctl->count_greater = count_greater;
         ctl->ties = g.r - count_greater;
-        ctl->how = kCounted && bd_bits < kCountShift ? kHowNarrowed : 0u;
+        ctl->how = kCounted && !dense && bd_bits < kCountShift ? kHowNarrowed : 0u;
     }
 }
 

@@ -11,9 +11,9 @@ pytestmark = pytest.mark.gpu
 CHUNK = 1024
 
 
-def _check(g, m, r, k, seed=5, step=6, offset=0, path=0):
+def _check(g, m, r, k, seed=5, step=6, offset=0, path=0, force=0):
     from tests import gpu_util as u
-    got = u.gpu_encode_once(g, m, r, k, seed, step, offset=offset)
+    got = u.gpu_encode_once(g, m, r, k, seed, step, offset=offset, force=force)
     u.assert_encode_equal(got, oracle.encode(g, m, r, k, seed, step), f"d={len(g)} r={r} k={k}")
     if path is not None:
         assert got[3]["path"] == path, got[3]
@@ -73,16 +73,47 @@ def test_batches(n, chunks):
             u.assert_encode_equal(got, oracle.encode(gs[w % 2], m, r, k, w, 3), f"member {w} of {n}")
 
 
-@pytest.mark.parametrize("d", [40_000, 300_007])
-@pytest.mark.parametrize("r,path", [(100, 0), (5_000, 2)])       # the cut among the large ones; among those that lost their slot
-def test_octaves_that_meet_in_a_slot(d, r, path):
+# the cut among the large ones; among those that lost their slot (their octave is narrowed; unless nobody narrows)
+@pytest.mark.parametrize("d", [40_000, 300_007, 2_097_152])
+@pytest.mark.parametrize("r,force,path", [(100, 0, 0), (5_000, 0, 0), (5_000, "CHECK_IN_ABORT", 2)])
+def test_octaves_that_meet_in_a_slot(d, r, force, path):
     """A few hundred elements around 2^40, all others 64 octaves below: their bins share a slot of the rows."""
+    import paper_2005_10761_amd as rt
+    r = max(r, d // 50) if r != 100 else r
     rng = np.random.default_rng(d + r)
     g = (rng.uniform(1.0, 2.0, d) * 2.0 ** -24).astype(np.float32)
     g[::97] = (rng.uniform(1.0, 2.0, len(g[::97])) * 2.0 ** 40).astype(np.float32)
     g *= rng.choice(np.array([-1.0, 1.0], np.float32), d)
-    st = _check(g, np.zeros(d, np.float32), r, r // 2, path=None)
-    assert st["path"] & 2 == path, st
+    st = _check(g, np.zeros(d, np.float32), r, r // 10, path=None, force=getattr(rt, f"FORCE_{force}") if force else 0)
+    assert st["path"] == 0 if path == 0 else st["path"] & 2, st
+
+
+@pytest.mark.parametrize("n", [3, 16])                          # every classify workgroup picks; a kernel does
+def test_denormals_below_an_octave_that_shares_their_slot(n):
+    """The octave of the denormals, zeros among them, is the one that lost its slot."""
+    import torch
+
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    d = 200_000
+    rng = np.random.default_rng(n)
+    g = (rng.integers(0, 1 << 23, d) * (rng.random(d) < 0.7)).astype(np.uint32)
+    g[::97] = (rng.integers(0, 1 << 23, len(g[::97])) | 64 << 23).astype(np.uint32)
+    g = g.view(np.float32)
+    r, k = d // 2, d // 20
+    grad = torch.from_numpy(g).to(u.DEV)
+    res = [torch.zeros(d, device=u.DEV) for _ in range(n)]
+    idx = [torch.empty(k, dtype=torch.int32, device=u.DEV) for _ in range(n)]
+    val = [torch.empty(k, device=u.DEV) for _ in range(n)]
+    stride = rt.encode_workspace_bytes(d, r, k)
+    ws = torch.empty(n * stride, dtype=torch.uint8, device=u.DEV).fill_(0xA5)
+    rt.encode_batch([grad] * n, res, r, k, list(range(n)), 3, idx, val, ws)
+    torch.cuda.synchronize()
+    for w in (0, n - 1):
+        st = rt.encode_stats(ws[w * stride:(w + 1) * stride])
+        assert st["path"] == 0 and st["error_flags"] == 0, (w, st)
+        got = (idx[w].cpu().numpy().view(np.uint32), val[w].cpu().numpy(), res[w].cpu().numpy())
+        u.assert_encode_equal(got, oracle.encode(g, np.zeros(d, np.float32), r, k, w, 3), f"member {w} of {n}")
 
 
 @pytest.mark.parametrize("d", [5_000, 300_007, 2_500_000])
