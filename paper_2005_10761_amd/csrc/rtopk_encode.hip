@@ -1875,8 +1875,11 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
     const Picked as_it_was = now.mode != 0u ? Picked{1u, 0u, 0u, 0ull, 0u} : now;
     const u32 n_groups = part_groups(gridDim.x), group = blockIdx.x / kPartGroup;
     PartGroup &mine = groups[group], &root = groups[n_groups];
-    // (a look at 1,024 elements, the same ones by all workgroups)
-    const f32x4 some = *reinterpret_cast<const f32x4u *>(a + (u64)tid * (g.d - 4u) / (kWalkThreads - 1u));
+    // (a look at 1,024 elements, the same ones by all workgroups; of a bin, which is crowded, so that there are four.
+    // An octave may be narrowed in a vector of two.)
+    const bool looks = now.mode == 0u && g.d >= 4u;
+    f32x4 some = {};
+    if (looks) some = *reinterpret_cast<const f32x4u *>(a + (u64)tid * (g.d - 4u) / (kWalkThreads - 1u));
     part[tid] = 0u;
     if (tid == 0u) { last_s = 0u; found_s = 0ull; looked_s = 0u; least_s = ~0u; most_s = 0u; }
     lds_barrier();
@@ -1912,7 +1915,7 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
     if (lane == 0u) { atomicAdd(&looked_s, looked); atomicMin(&least_s, least); atomicMax(&most_s, most); }
     lds_barrier();
     // equal magnitudes (signs, a few levels): no part will be smaller
-    if (now.mode == 0u && looked_s > 1u && least_s == most_s) return now;
+    if (looks && looked_s > 1u && least_s == most_s) return now;
     if (part[tid] != 0u) __hip_atomic_fetch_add(&mine.count[tid], part[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     wait_own_memory();
     __syncthreads();

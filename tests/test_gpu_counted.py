@@ -88,6 +88,20 @@ def test_octaves_that_meet_in_a_slot(d, r, force, path):
     assert st["path"] == 0 if path == 0 else st["path"] & 2, st
 
 
+@pytest.mark.parametrize("d", [2, 3, 4, 5, 63, 257, 1025])
+@pytest.mark.parametrize("top", [np.inf, np.nan, 2.0 ** 64])
+def test_octaves_that_meet_in_tiny_vectors(d, top):
+    """The smallest vectors whose deciding octave lost its slot: to infinities, to what is no number, to one value."""
+    rng = np.random.default_rng(d)
+    g = rng.uniform(1.0, 2.0, d).astype(np.float32)
+    g[rng.integers(0, d)] = top
+    for r in {2, d // 2 + 1, d - 1}:
+        if 2 <= r < d:
+            print(f"tiny d={d} r={r} top={top}", flush=True)
+            _check(g, np.zeros(d, np.float32), r, (r + 1) // 2, path=None)
+            _check(g, np.zeros(d, np.float32), r, r, offset=1, path=None)
+
+
 @pytest.mark.parametrize("n", [3, 16])                          # every classify workgroup picks; a kernel does
 def test_denormals_below_an_octave_that_shares_their_slot(n):
     """The octave of the denormals, zeros among them, is the one that lost its slot."""
