@@ -248,7 +248,7 @@ struct EncodeCtl {
     u32 bd_lo, bd_hi;   // pattern range of the deciding bin
     u32 bd_bits;        // bit width of bd_hi - bd_lo
     u64 c_def;          // entries above bd_hi
-    u32 n_bin, hot;     // (counted vectors) entries of the bin pick found, whether they crowd in few places
+    u32 n_bin;          // (counted vectors) entries of the bin pick found, and kCrowds
     // written by k_classify
     u32 overflow;       // a short-list region of some classify workgroup was full
     u32 overflow_m;     // ... and it was a region of the key list M
@@ -265,7 +265,7 @@ struct EncodeCtl {
     u64 count_greater, ties;
     u32 how;            // kHow...: which lists of a counted vector decided (read by tests)
 };
-static_assert(offsetof(EncodeCtl, how) == 136, "where the tests look");
+static_assert(offsetof(EncodeCtl, how) == 128, "where the tests look");
 constexpr u32 kHowRegisters = 1u, kHowNarrowed = 2u;
 
 // (the error word is the first word of the workspace: callers may read it there)
@@ -1578,7 +1578,8 @@ count_body(const float *__restrict__ grad, float *__restrict__ residual, const G
 
 // the deciding bin from those rows, by all threads of a workgroup (every thread gets the result; whether the
 // bin's entries crowd in few places, *hot in LDS, after the next barrier)
-constexpr u32 kHotRows = 48;
+typedef u16 u16x2 __attribute__((ext_vector_type(2)));
+constexpr u32 kCrowds = 1u << 31;
 template <u32 kThreads>
 __device__ __forceinline__ Picked
 pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n_rows, const Geom &g, u32 *hot)
@@ -1590,7 +1591,8 @@ pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n
     if (tid == 0) { lost_s = 0u; *hot = 0u; }
     if (__builtin_expect(g.force_dense != 0u, 0)) return Picked{1u, 0u, 0u, 0ull, 0u};
     // ---- all rows' sums: a thread takes eight groups of every (kThreads / 32)-th row
-    constexpr u32 kAt = kCountGroups / 8u, kAhead = 8;
+    constexpr u32 kAt = kCountGroups / 8u, kOf = kGroupBins / 8u;
+    constexpr u32 kAhead = kCountRows / (kThreads / kAt) < 8u ? kCountRows / (kThreads / kAt) : 8u;
     u32 sum[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
     auto add_up = [&](const uint4 &v, u32 mask) {
         const u32 w[4] = {v.x & mask, v.y & mask, v.z & mask, v.w & mask};
@@ -1633,13 +1635,16 @@ pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n
     // ---- that group's bins of the rows that have some
 #pragma unroll
     for (u32 c = 0; c < 8; ++c) sum[c] = 0u;
+    u16x2 most[4] = {};                    // of any row, in each of the eight bins
     u32 marks = 0;
-    constexpr u32 kOf = kGroupBins / 8u;
-    for (u32 r0 = tid / kOf; r0 < n_rows; r0 += kAhead * (kThreads / kOf)) {
-        uint4 v[kAhead];
-        u32 has[kAhead];
+    constexpr u32 kRounds = kCountRows / (kThreads / kOf);
+    static_assert(kRounds <= 8u, "all rows in one round of loads");
+    const u32 r0 = tid / kOf;
+    {
+        uint4 v[kRounds];
+        u32 has[kRounds];
 #pragma unroll
-        for (u32 q = 0; q < kAhead; ++q) {
+        for (u32 q = 0; q < kRounds; ++q) {
             const u32 row = r0 + q * (kThreads / kOf);
             v[q] = make_uint4(0u, 0u, 0u, 0u);
             has[q] = 0u;
@@ -1649,9 +1654,14 @@ pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n
             }
         }
 #pragma unroll
-        for (u32 q = 0; q < kAhead; ++q) {
+        for (u32 q = 0; q < kRounds; ++q) {
+            if (q * (kThreads / kOf) >= n_rows) break;
             marks |= has[q] & kNotStored;
-            add_up(v[q], has[q] != 0u ? ~0u : 0u);
+            const u32 mask = has[q] != 0u ? ~0u : 0u;
+            add_up(v[q], mask);
+            const u32 w[4] = {v[q].x & mask, v[q].y & mask, v[q].z & mask, v[q].w & mask};
+#pragma unroll
+            for (u32 c = 0; c < 4; ++c) most[c] = __builtin_elementwise_max(most[c], __builtin_bit_cast(u16x2, w[c]));
         }
     }
 #pragma unroll
@@ -1675,13 +1685,13 @@ pick_counted(const u16 *__restrict__ sums, const uint4 *__restrict__ rows, u32 n
     before = (u32)__builtin_amdgcn_readlane((int)before, src);
     in_bin = (u32)__builtin_amdgcn_readlane((int)in_bin, src);
     // A classify workgroup's chunks are four rows' here, side by side: where it alone has more of the bin than
-    // its list takes, the rows of some of these threads have far more than the others'.
-    constexpr u32 kParts = kThreads / kOf;
-    const u32 parts = n_rows < kParts ? n_rows : kParts, at = bin % kGroupBins;
+    // its list takes, one of them has more than a fourth of that. (A row is eight chunks or more, so spread entries may
+    // look the same from 40 per classify workgroup on: up to 524,288 elements they are narrowed from there.)
+    const u32 at = bin % kGroupBins;
     u32 mine = 0;
 #pragma unroll
-    for (u32 c = 0; c < 8; ++c) mine = at % 8u == c ? sum[c] : mine;
-    if (tid % kOf == at / 8u && mine > kHotRows && in_bin > kLongList && (mine - kHotRows) * parts > in_bin + in_bin / 8u) *hot = 1u;
+    for (u32 c = 0; c < 8; ++c) mine = at % 8u == c ? most[c / 2u][c % 2u] : mine;
+    if (tid % kOf == at / 8u && in_bin > kLongList && mine > kLongList / kWalkWaves) *hot = 1u;
     return Picked{0u, bin << kCountShift, (bin << kCountShift) | ((1u << kCountShift) - 1u), before, in_bin};
 }
 
@@ -1987,6 +1997,10 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
                   (u32)(word >> (2u + kPartBits)) & kEntryMask};
 }
 
+// More entries of the bin than this, which only lists in memory would hold, are better off in the selections for lists that
+// overflow where those run on many workgroups (1 - 1e-3 uniform, r = k = 1%, narrowed: 2^20, 16,000 entries, 132 in
+// lists / 127, 2 M, 30,600, 200 / 137, 2.9 M, 44,000, 270 / 159).
+constexpr u32 kMemoryEntries = 3u << 12;
 __device__ __forceinline__ void
 classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, Picked now, const u32 &hot,
                  bool picked_here, const float *__restrict__ a, PartGroup *groups, uint2 *__restrict__ seg,
@@ -2001,7 +2015,9 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
     const u64 below = lanes_below();
     if (threadIdx.x == 0) { cnt_m = 0u; cnt_b = 0u; bmin_s = 0xFFFFFFFFu; bmax_s = 0u; }
     lds_barrier();
-    const bool narrows = g.narrow_from != 0u && (now.n_bin >= g.narrow_from || hot != 0u);
+    const bool crowds = picked_here ? hot != 0u : (now.n_bin & kCrowds) != 0u;
+    now.n_bin &= ~kCrowds;
+    const bool narrows = g.narrow_from != 0u && (now.n_bin >= g.narrow_from || crowds);
     if (__builtin_expect(narrows, 0)) now = narrow_bin(chunk, g, a, groups, now);
     else if (now.mode != 0u) now = Picked{1u, 0u, 0u, 0ull, 0u};
     // (once narrowed, nobody reads the words of the kernel that picked any more: all had checked in)
@@ -2086,7 +2102,7 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
         blk_lists[blockIdx.x] = make_uint2(in_m | in_b << 16, of_quad);
         blk_bmin[blockIdx.x] = bmin_s;
         blk_bmax[blockIdx.x] = bmax_s;
-        if (cnt_m > kListCap || cnt_b > cap_b) ctl->overflow = 1u;
+        if (cnt_m > kListCap || cnt_b > cap_b || (now.n_bin > kMemoryEntries && g.W >= kWideMinChunks)) ctl->overflow = 1u;
         if (cnt_m > kListCap) ctl->overflow_m = 1u;
     }
 }
@@ -3832,9 +3848,10 @@ __global__ void __launch_bounds__(kPickThreads) k_pick_counted(Batch B, u32 n_ro
 {
     const Member m(B);
     __shared__ u32 hot;
-    const Picked p = pick_counted<kPickThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g, &hot);
+    Picked p = pick_counted<kPickThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g, &hot);
     lds_barrier();
-    if (threadIdx.x == 0) { p.store(m.at<EncodeCtl>(L.ctl)); m.at<EncodeCtl>(L.ctl)->hot = hot; }
+    if (hot != 0u) p.n_bin |= kCrowds;
+    if (threadIdx.x == 0) p.store(m.at<EncodeCtl>(L.ctl));
 }
 
 template <bool kPick>
@@ -3845,12 +3862,10 @@ __global__ void __launch_bounds__(kWalkThreads) k_classify_counted(Batch B, u32 
     const ChunkRows chunk(m.residual, g.d, blockIdx.x * kWalkWaves + threadIdx.x / kWave);
     __shared__ u32 hot;
     Picked p{};
-    if (kPick) {
+    if (kPick)
         p = pick_counted<kWalkThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g, &hot);
-    } else {
+    else
         p = Picked{ctl->mode, ctl->bd_lo, ctl->bd_hi, ctl->c_def, ctl->n_bin};
-        if (threadIdx.x == 0) hot = ctl->hot;
-    }
     classify_counted(chunk, g, m.seed, ctl, p, hot, kPick, m.residual, m.at<PartGroup>(L.group_sums), m.at<uint2>(L.seg), m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt),
                      m.at<u32>(L.bd_cnt), m.at<u32>(L.quad_win), m.at<uint2>(L.blk_lists), m.at<u32>(L.blk_bmin),
                      m.at<u32>(L.blk_bmax), m.at<uint2>(L.m_ent), m.at<uint2>(L.b_ent));
@@ -4118,13 +4133,13 @@ bool small_lists(const Geom &g, unsigned nb)
     return g.r / 20 * 8 <= room && (u64)g.stage_m * 8 <= room;
 }
 
-// The entries of the deciding bin from which on classify narrows it down: more than finalize has room for (4,089 of
-// 2^20 uniform values 34.1, narrowed 31.8, but eight at a time 62.8 and 68.1), or, of a vector of few classify workgroups, so many
-// on average that some lists may not hold theirs (200,003 elements of which 1,229 entries, half of them in one workgroup's
-// chunks, decide: 37.0 narrowed, on the exact selection 388; 1,493 spread ones 29.8, narrowed 30.0).
+// The entries of the deciding bin from which on classify narrows it down wherever they are: more than finalize has room
+// for (4,089 of 2^20 uniform values 34.1, narrowed 31.8, but eight at a time 62.8 and 68.1), or, of a vector of few classify
+// workgroups, 96 to each, whose lists hold 384 (200,003 elements, 1,493 entries: 29.8, narrowed 30.0; 20,000 elements, 150
+// entries 26.0, narrowed 29.7).
 u32 narrows_from(u32 G3)
 {
-    const u32 spread = G3 * kListCap * 3u / 16u;
+    const u32 spread = G3 * kListCap * 3u / 4u;
     return (spread < kStageB ? spread : kStageB) + 1u;
 }
 

@@ -57,7 +57,7 @@ class GpuWorker:
 def lists_that_decided(ws) -> int:
     """The word of the control block that says which lists of a counted vector decided: bit 0, those in
     registers; bit 1, the deciding bin had been narrowed."""
-    return int(ws[136:140].view(torch.int32).item())
+    return int(ws[128:132].view(torch.int32).item())
 
 
 def estimated_bins(ws) -> int:

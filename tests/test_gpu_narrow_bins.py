@@ -86,7 +86,7 @@ def test_entries_in_one_workgroups_chunks(layer, count, narrowed):
 
 
 @pytest.mark.parametrize("low", [0, 255])
-@pytest.mark.parametrize("take", [1, 2, 999, 1000])
+@pytest.mark.parametrize("take", [1, 2, 1599, 1600])
 def test_the_first_and_last_part(low, take):
     """All entries of the deciding bin in its lowest or highest part, and the cut at either end of them."""
     d = 50_000
@@ -94,8 +94,8 @@ def test_the_first_and_last_part(low, take):
     g = (rng.standard_normal(d) * 1e-3).astype(np.float32)
     at = rng.permutation(d)
     g[at[:300]] = (rng.standard_normal(300) + 30.0).astype(np.float32)
-    pattern = (0x3F800000 | low << 8) + rng.integers(0, 256, 1000)
-    g[at[300:1300]] = pattern.astype(np.uint32).view(np.float32)
+    pattern = (0x3F800000 | low << 8) + rng.integers(0, 256, 1600)
+    g[at[300:1900]] = pattern.astype(np.uint32).view(np.float32)
     r = 300 + take
     path, how = _check(g, r, r // 3)
     assert path & 3 == 0 and how & NARROWED, (path, how)
