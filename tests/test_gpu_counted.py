@@ -173,7 +173,9 @@ def test_chunks_that_fill_their_slice(d, count):
 @pytest.mark.parametrize("where", ["window", "bin", "few levels"])
 def test_lists_in_and_beyond_registers(d, hot, where):
     """`hot` members in one classify workgroup's chunks: nearly half of their keys lie in the window; or they
-    share the deciding bin, with the cut among them, as distinct magnitudes or as three."""
+    share the deciding bin, with the cut among them, as distinct magnitudes or as three. Few of them are found in
+    registers where there are at most 256 such workgroups; 290 entries of the bin are in no register, but in a list."""
+    from tests import gpu_util as u
     rng = np.random.default_rng(d + hot)
     g = (rng.standard_normal(d) * 1e-6).astype(np.float32)
     g[rng.permutation(d)[:200]] = (rng.standard_normal(200) + 9.0).astype(np.float32)
@@ -187,7 +189,14 @@ def test_lists_in_and_beyond_registers(d, hot, where):
     r = len(np.flatnonzero(np.abs(g) > 0.5)) - (0 if where == "window" else hot // 2)
     print(f"lists d={d} hot={hot} {where} r={r}", flush=True)
     for k in (r // 3, r):
-        _check(g, np.zeros(d, np.float32), r, k, path=None)
+        w = u.GpuWorker(d, r, k, residual=np.zeros(d, np.float32))
+        got = w.encode(g, 5, 6)
+        u.assert_encode_equal(got, oracle.encode(g, np.zeros(d, np.float32), r, k, 5, 6), f"d={d} r={r} k={k}")
+        decided = w.stats["path"], u.lists_that_decided(w.ws)
+        if hot == 9:
+            assert decided == (0, 1 if d <= 1 << 20 else 0), decided
+        elif hot == 290 and where != "window":
+            assert decided == (0, 0), decided
 
 
 @pytest.mark.parametrize("d", [5_000, 300_007, 2_500_000])
