@@ -494,7 +494,8 @@ k_weights(const u32 *__restrict__ idx, const float *__restrict__ val, u32 n, u64
                     e_v[i] = val[of * k + j];
                     valid |= 1u << i;
                 }
-                // (a message that repeats an index: its entries are added position by position below)
+                // (a message that repeats an index: its entries are added position by position below. No encode
+                // sends one; it costs 3-10% more than the rounds at once, eight of 34 M, 64 entries each, 20.9 / 23.1 us)
                 u32 left = kEmpty;
                 if (lane == 0u && f != 0u && f < total && j != 0u) left = idx[of * k + j - 1u];
                 left = lane_left(e_i[i], left);

@@ -31,7 +31,8 @@ __device__ __forceinline__ u32 xor3(u32 a, u32 b, u32 c)
 // What bounds the kernels that key every element (r == d) is the issue of these ten rounds: a product
 // holds its SIMD for 16 cycles, an exclusive or for 4. Two of the twenty products and half of the first two
 // rounds belong to the wavefront alone (the step and the seed); the others take one product and one
-// three-way exclusive or per word: k_fused of 11.2 M elements, r = d, 32.3 -> 28.7 us.
+// three-way exclusive or per word: k_fused of 11.2 M elements, r = d, 32.3 -> 28.7 us (25.3 with its chunks dealt across
+// the workgroups).
 __device__ __forceinline__ u64 sample_key(u32 index, const PhiloxSeed &s)
 {
     u32 c0 = index, c1 = 0u, c2 = s.step_lo, c3 = s.step_hi;

@@ -60,7 +60,7 @@
 //              sent positions <- a - a
 // A short vector (counts_all) has no sample and no estimate: its magnitudes are all
 // counted while they are added (count), and classify, once it has picked the
-// deciding bin, makes S from the vector, which is still in the caches.
+// deciding bin (and narrowed it, where it is crowded), makes S from the vector, which is still in the caches.
 // Two special cases of Definition 3 take shortcuts: with k == r (top-k) no
 // sampling key is ever computed, and with r == d (random-k) no magnitude is
 // ever compared: the streaming kernel then keeps the elements whose key lies
@@ -397,7 +397,8 @@ static void set_units(Geom &g, unsigned nb)
 // part, is sampled as a shorter one is: 160 samples in its top r bound the bracket well enough, and the estimate's one
 // workgroup holds the whole call up. us, 65,536 samples / 160 in the top r: Student-t values, 4.3 M elements, r = 1%, 52.2 /
 // 47.5, 8 M 59.9 / 55.3, 11.2 M 66.0 / 62.0; touched rows 61.2 / 58.0, 68.7 / 66.4, 77.5 / 75.2; layers 53.9 / 53.8, 58.7 / 57.1, 66.6 / 65.7; r = k
-// of 11.2 M 65.1 / 62.7. Not longer ones (25.6 M touched rows, r = 1%, 102.4 / 103.9), nor larger top sets (layers of 11.2 M, r = 5%,
+// of 11.2 M 65.1 / 62.7; uniform and nearly equal values, signs and layers of like magnitudes 4-17% faster too, but eight levels per
+// unit, r = 3%, where the wider bracket reaches one level more, 121 / 136 at 11.2 M. Not longer ones (25.6 M touched rows, r = 1%, 102.4 / 103.9), nor larger top sets (layers of 11.2 M, r = 5%,
 // 77.2 / 80.8), nor batches (four of 11.2 M 139.8 / 142.5, two of 5 M 66.0 / 66.5).
 constexpr u64 kAloneElements = 1u << 24, kAloneShare = 32;
 static void set_samples(Geom &g, unsigned nb)
