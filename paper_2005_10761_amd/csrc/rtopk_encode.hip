@@ -2019,10 +2019,13 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
     const bool crowds = picked_here ? hot != 0u : (now.n_bin & kCrowds) != 0u;
     now.n_bin &= ~kCrowds;
     const bool narrows = g.narrow_from != 0u && (now.n_bin >= g.narrow_from || crowds);
+    const u32 span = now.bd_hi - now.bd_lo;
     if (__builtin_expect(narrows, 0)) now = narrow_bin(chunk, g, a, groups, now);
     else if (now.mode != 0u) now = Picked{1u, 0u, 0u, 0ull, 0u};
-    // (once narrowed, nobody reads the words of the kernel that picked any more: all had checked in)
-    if ((picked_here || narrows) && blockIdx.x == 0 && threadIdx.x == 0) now.store(ctl);
+    // The words of a kernel that picked are replaced by a narrower bin only: then all workgroups have arrived, and
+    // nobody reads them any more. Otherwise one that starts late still may.
+    const bool narrowed = narrows && now.mode == 0u && now.bd_hi - now.bd_lo < span;
+    if ((picked_here || narrowed) && blockIdx.x == 0 && threadIdx.x == 0) now.store(ctl);
     // ---- the entries, in index order
     u32 n = 0;
     if (now.mode == 0u) {
