@@ -97,7 +97,9 @@ int rtopk_trace_next_encode(int stage, void *ev_begin, void *ev_end);
  *                                the r-th largest magnitude: the threshold
  *                                then lies above the finely binned range, in
  *                                the one bin that holds everything above it
- *                                (a short vector is sampled, not counted, for it)
+ *                                (a vector of more than 2^20 elements that
+ *                                would be counted is sampled for it; shorter
+ *                                ones have no bracket, it has no effect)
  *   RTOPK_FORCE_BARRIER_TIMEOUT  (an error path, not a fallback) the bounded
  *                                waits between the workgroups of the
  *                                many-workgroup selection give up at their

@@ -109,8 +109,9 @@ constexpr u32 kSampleThreads = 256;
 constexpr u32 kEstThreads = 1024;
 // A sample is the leading 15 bits of a magnitude (the estimate needs 12): the one workgroup of the
 // estimate fetches cold lines at 0.4 a ns, and four bytes a sample were 2,048 of them.
-constexpr u32 kSampleShift = 16, kBucketShift = 3, kNoSample = 0xFFFFu;
+constexpr u32 kSampleShift = 16, kBucketShift = 3;
 constexpr u64 kShortVector = 1u << 22;
+constexpr u32 kCountAnyR = 1024;              // a vector of up to this many chunks has no sample, whatever r (see counts_all)
 constexpr u64 kHeavyTail = 1u << 14;          // (see make_geom)
 
 constexpr u32 kChunkQuantum = 256;            // one wavefront iteration: 64 lanes x 4 elements
@@ -283,7 +284,7 @@ struct Geom {
     u32 UC;             // ... at most this many of them (W <= U * UC)
     u32 G3;             // classify / emit workgroups
     u32 L;              // sampled locations
-    u32 est_vecs;       // sampled locations per thread of the estimate kernel, a power of two (empty ones included)
+    u32 est_vecs;       // sampled locations per thread of the estimate kernel, a power of two
     u32 nfine;          // linear histogram bins
     u32 force_dense;    // diagnostics: make the estimate keep nothing, as if the sample had misled it (of a counted
                         // vector: as if the deciding bin's row had lost its slot)
@@ -349,15 +350,14 @@ static Geom make_geom(u64 d, u64 r, u64 k)
     // us, 80 / 160 / 320 samples, r = 1%: Student-t values 48.8 / 44.1 / 45.9 at 2^21 elements,
     // 63.5 / 54.5 / 55.5 at 3.5 M; values spread evenly over three decades 44.3 / 44.4 / 45.6 at
     // 2^21; sixteen layered vectors of 2 M, r = 5,046 134 / 155.
-    u64 loc = (d + 3) / 4, want = kSampleLoc;
+    u64 want = kSampleLoc;
     if (d < kShortVector) {
         want = kEstThreads;
         while (want < kSampleLoc && want * 4 * r < 80 * d) want *= 2;
         if (r >= kHeavyTail && want <= kSampleLoc / 4 && want * 4 * r < 160 * d) want *= 2;
     }
-    g.L = (u32)(loc < want ? loc : want);
-    g.est_vecs = 1;
-    while (g.est_vecs * kEstThreads < g.L) g.est_vecs *= 2;
+    g.L = (u32)want;
+    g.est_vecs = (u32)want / kEstThreads;
     // Every workgroup of the streaming kernel stores its whole histogram: few
     // bins when r is small (the list B of the deciding bin then holds a few
     // hundred entries anyway), more when r is large.
@@ -492,14 +492,12 @@ __device__ __forceinline__ u32 block_sum(u32 v, u32 *lds /* >= waves words */)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ u64 stratum_start(const Geom &g, u32 j)
 {
-    // strata of (almost) equal length; only monotonicity and the two ends matter
-    if (j >= g.L) return g.d;
-    const u64 x = (g.L & (g.L - 1u)) == 0u ? (g.d * (u64)j) >> (31 - __clz((int)g.L))   // d * j < 2^46
-                                           : (u64)((double)g.d * (double)j / (double)g.L);
-    return x < g.d ? x : g.d;
+    // strata of (almost) equal length, 64 elements or more: vectors of up to kCountAnyR chunks are counted
+    static_assert((u64)kCountAnyR * kMinChunk >= 64u * (u64)kSampleLoc, "strata of 64 elements");
+    return (g.d * (u64)j) >> (31 - __clz((int)g.L));        // (g.L is a power of two; d * j <= 2^46)
 }
 
-// A first element inside stratum [start, start + len), len > 4. The offset depends on the
+// A first element inside stratum [start, start + len). The offset depends on the
 // stratum AND on (seed, step): a vector whose layout happens to mislead one set of offsets (a
 // period close to the stratum length) does not mislead the next step's or another worker's.
 // Which elements are sampled never changes the result, only the path.
@@ -518,24 +516,16 @@ __device__ __forceinline__ u64 sample_place(u32 j, u64 start, u64 len, const Phi
 __device__ __forceinline__ uint2 take_samples(const float *__restrict__ grad, const float *__restrict__ residual,
                                               const Geom &g, const PhiloxSeed &seed, u32 j)
 {
-    u32 v[4] = {kNoSample, kNoSample, kNoSample, kNoSample};
-    if (j < g.L) {
-        const u64 start = stratum_start(g, j), end = stratum_start(g, j + 1);
-        if (end - start > 4) {
-            // One 16-byte load per array, at whatever alignment the pointers have (word by word, a vector of
-            // 11.2 M elements off 16 bytes took 6.8 us, now 4.8). The four elements may start up to
-            // three before the stratum: it stays a spread-out sample.
-            const u64 p = sample_place(j, start, end - start, seed) & ~3ull;
-            const f32x4 gv = *reinterpret_cast<const f32x4u *>(grad + p);
-            const f32x4 mv = *reinterpret_cast<const f32x4u *>(residual + p);
+    const u64 start = stratum_start(g, j), end = stratum_start(g, j + 1);
+    // One 16-byte load per array, at whatever alignment the pointers have (word by word, a vector of
+    // 11.2 M elements off 16 bytes took 6.8 us, now 4.8). The four elements may start up to
+    // three before the stratum: it stays a spread-out sample.
+    const u64 p = sample_place(j, start, end - start, seed) & ~3ull;
+    const f32x4 gv = *reinterpret_cast<const f32x4u *>(grad + p);
+    const f32x4 mv = *reinterpret_cast<const f32x4u *>(residual + p);
+    u32 v[4];
 #pragma unroll
-            for (u32 e = 0; e < 4; ++e) v[e] = mag_of(__float_as_uint(gv[e] + mv[e])) >> kSampleShift;
-        } else {
-#pragma unroll
-            for (u32 e = 0; e < 4; ++e)
-                if (start + e < end) v[e] = mag_of(__float_as_uint(grad[start + e] + residual[start + e])) >> kSampleShift;
-        }
-    }
+    for (u32 e = 0; e < 4; ++e) v[e] = mag_of(__float_as_uint(gv[e] + mv[e])) >> kSampleShift;
     return make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16);
 }
 
@@ -545,7 +535,7 @@ sample_body(const float *__restrict__ grad, const float *__restrict__ residual, 
 {
     const u32 j = blockIdx.x * kSampleThreads + threadIdx.x;
     for (u32 i = j; i < zero_words; i += gridDim.x * kSampleThreads) zero_base[i] = 0u;
-    if (j >= g.est_vecs * kEstThreads) return;
+    if (j >= g.L) return;
     reinterpret_cast<uint2 *>(samples)[j] = take_samples(grad, residual, g, seed, j);
 }
 
@@ -617,11 +607,9 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
 {
     // One compute unit looks at 65,536 samples: the lines it fetches and the work per
     // sample are what this kernel costs, so the two passes over them are a handful of
-    // instructions per location. A sample has 15 bits or is kNoSample
-    // (all ones): as signed 16-bit integers the missing ones are -1, below every real one.
+    // instructions per location. A sample has 15 bits.
     __shared__ u32 h_max[4096];                           // buckets of the per-thread maxima
     __shared__ u32 h[4096];                               // buckets of the samples that matter
-    __shared__ u32 scan_lds[kEstThreads / kWave + 1];
     __shared__ u32 bin_s[3], before_s[3], top_s;
     const u32 tid = threadIdx.x;
     const uint2 *s2 = reinterpret_cast<const uint2 *>(samples);
@@ -634,26 +622,15 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
     auto smax = [](int a, int b) { return a > b ? a : b; };
     auto low = [](u32 w) { return (int)(short)(w & 0xFFFFu); };
     auto high = [](u32 w) { return (int)w >> 16; };
-    int gmax[kVecs];                                      // largest of each location, -1 if none
-    int tmax = -1;
+    int gmax[kVecs];                                      // largest of each location
+    int tmax = 0;
 #pragma unroll
     for (u32 q = 0; q < kVecs; ++q) {
         gmax[q] = smax(smax(low(v[q].x), high(v[q].x)), smax(low(v[q].y), high(v[q].y)));
         tmax = smax(tmax, gmax[q]);
     }
-    // Number of samples: four per location once every stratum is longer than
-    // four elements; counted otherwise (short vectors).
-    u32 n;
-    if ((u64)g.L * 5ull <= g.d) {
-        n = 4u * g.L;
-        lds_barrier();                                    // orders the clearing of the histograms
-    } else {
-        u32 nvalid = 0;
-#pragma unroll
-        for (u32 q = 0; q < kVecs; ++q)
-            nvalid += (low(v[q].x) >= 0) + (high(v[q].x) >= 0) + (low(v[q].y) >= 0) + (high(v[q].y) >= 0);
-        n = block_sum(nvalid, scan_lds);
-    }
+    const u32 n = 4u * g.L;
+    lds_barrier();                                        // orders the clearing of the histograms
 
     const float p = (float)((double)g.r / (double)g.d);
     const float np = (float)n * p;
@@ -665,10 +642,10 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
 
     // Only the top s_lo samples matter. At most s_lo - 1 threads hold a sample
     // above the s_lo-th largest one, so the s_lo-th largest of the per-thread
-    // maxima (of which there must be that many) is not above it: buckets below that maximum's bucket need no count.
+    // maxima is not above it: buckets below that maximum's bucket need no count.
     // (the bucket of the largest sample of all is where every walk starts)
     {
-        const u32 wmax = wave_max_dpp(tmax >= 0 ? (u32)tmax >> kBucketShift : 0u);
+        const u32 wmax = wave_max_dpp((u32)tmax >> kBucketShift);
         if (lane_id() == 0 && wmax) atomicMax(&top_s, wmax);
     }
     // (Where the top holds more samples than there are threads, the same with the maxima of the
@@ -676,11 +653,10 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
     u32 cut_bucket = 0;
     if (s_lo < g.L) {
         if (s_lo < kEstThreads) {
-            if (tmax >= 0) atomicAdd(&h_max[(u32)tmax >> kBucketShift], 1u);
+            atomicAdd(&h_max[(u32)tmax >> kBucketShift], 1u);
         } else {
 #pragma unroll
-            for (u32 q = 0; q < kVecs; ++q)
-                if (gmax[q] >= 0) atomicAdd(&h_max[(u32)gmax[q] >> kBucketShift], 1u);
+            for (u32 q = 0; q < kVecs; ++q) atomicAdd(&h_max[(u32)gmax[q] >> kBucketShift], 1u);
         }
         lds_barrier();
         if (tid < kWave) {
@@ -688,9 +664,9 @@ estimate_body(const u32 *__restrict__ samples, Geom g, EncodeCtl *ctl)
             wave_pick_from_top<1>(h_max, top_s, want_cut, &bin_s[2], &before_s[2]);
         }
         lds_barrier();
-        cut_bucket = bin_s[2];                     // stays 0 when fewer than s_lo threads (or locations) hold samples
+        cut_bucket = bin_s[2];                     // (bucket 0 where all of them are zero)
     }
-    const int cut = (int)(cut_bucket << kBucketShift);    // >= 0: missing samples never pass
+    const int cut = (int)(cut_bucket << kBucketShift);
     u32 nzero = 0;
     auto count = [&](int m) {
         if (m < cut) return;
@@ -3651,7 +3627,7 @@ finalize_body(Geom g, PhiloxSeed seed, EncodeCtl *ctl, WideScratch *wide_ws,
         ctl->UC = g.UC;
         ctl->count_greater = count_greater;
         ctl->ties = g.r - count_greater;
-        ctl->how = kCounted && !dense && bd_bits < kCountShift ? kHowNarrowed : 0u;
+        if (kCounted) ctl->how = !dense && bd_bits < kCountShift ? kHowNarrowed : 0u;
     }
 }
 
@@ -4106,7 +4082,7 @@ bool deals_across(const Geom &g, bool is_short, unsigned nb)
 // with lighter tails have no such bound; their bins are narrowed (see there: from 2 M elements on they gain little, at 3 M
 // uniform values lose 4%; a few levels of 2^20, r = 1%, lose 5%, uniform values eight at a time 2%). Above 3072 chunks the vector's second
 // reading costs what the launches save, and hot chunks want the room that the stream's wavefronts share.
-constexpr u32 kCountAnyR = 1024, kCountMid = 2048;               // chunks
+constexpr u32 kCountMid = 2048;               // chunks (kCountAnyR: with the sizes of the sample)
 constexpr u64 kCountMidMembers = 1u << 16, kCountMembers = 1u << 15;
 bool counts_all(const Geom &g)
 {
@@ -4243,8 +4219,8 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         g.K_lo = g.K_hi = 0;       // a window that holds no key: the exact selection must run
         g.k_nlz = 63u;
     }
-    // (a bracket that ends too low belongs to the path that has one)
-    const bool force_bracket = (force & RTOPK_FORCE_BRACKET_LOW) != 0u;
+    // (a bracket that ends too low belongs to the path that has one, which vectors of up to kCountAnyR chunks never take)
+    const bool force_bracket = (force & RTOPK_FORCE_BRACKET_LOW) != 0u && g.W > kCountAnyR;
     hipStream_t stream = (hipStream_t)stream_v;
     unsigned grid_limit = 0, classify_limit = 0;
     const int rc2 = fused_grid_limit(&grid_limit, &classify_limit);

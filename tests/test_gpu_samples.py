@@ -37,3 +37,19 @@ def test_sample_by_need(n, d, share, values):
         assert st["path"] == 0 and st["error_flags"] == 0, st
         got = (idx[w].cpu().numpy().view(np.uint32), val[w].cpu().numpy(), res[w].cpu().numpy())
         u.assert_encode_equal(got, oracle.encode(g, np.zeros(d, np.float32), r, k, 4 + w, 6), f"member {w} of {n}")
+
+
+@pytest.mark.parametrize("d,sampled", [(1 << 20, False), ((1 << 20) + 1, True), ((1 << 20) + 1023, True)])
+@pytest.mark.parametrize("r", [40, 20_000, 200_000])
+def test_the_shortest_strata(d, sampled, r):
+    """Vectors of up to 1024 chunks have no sample; the shortest that may (they are counted otherwise) have strata of 64
+    elements: 16,384 locations where r is small, fewer for larger r."""
+    import paper_2005_10761_amd as rt
+    from tests import gpu_util as u
+    rng = np.random.default_rng(d + r)
+    g = rng.standard_normal(d).astype(np.float32)
+    m = (rng.standard_normal(d) * 1e-2).astype(np.float32)
+    w = u.GpuWorker(d, r, r // 4, residual=m, offset=d % 4)
+    got = w.encode(g, 3, 9, force=rt.FORCE_BRACKET_LOW)
+    u.assert_encode_equal(got, oracle.encode(g, m, r, r // 4, 3, 9), f"d={d} r={r}")
+    assert (u.estimated_bins(w.ws) != 0) == sampled
