@@ -249,7 +249,6 @@ struct EncodeCtl {
     u32 bd_lo, bd_hi;   // pattern range of the deciding bin
     u32 bd_bits;        // bit width of bd_hi - bd_lo
     u64 c_def;          // entries above bd_hi
-    u32 n_bin;          // (counted vectors) entries of the bin pick found, and kCrowds
     // written by k_classify
     u32 overflow;       // a short-list region of some classify workgroup was full
     u32 overflow_m;     // ... and it was a region of the key list M
@@ -265,6 +264,7 @@ struct EncodeCtl {
     u32 W, U, UC;       // chunks and their share-out, for the host-side statistics
     u64 count_greater, ties;
     u32 how;            // kHow...: which lists of a counted vector decided (read by tests)
+    u32 n_bin;          // (counted vectors, written by k_pick_counted) entries of the bin pick found, and kCrowds
 };
 static_assert(offsetof(EncodeCtl, how) == 128, "where the tests look");
 constexpr u32 kHowRegisters = 1u, kHowNarrowed = 2u;
@@ -296,7 +296,6 @@ struct Geom {
     u32 all_members;    // r == d: every coordinate is a member, magnitudes are never looked at
     u32 keyed;          // the streaming kernel keys the candidates (of a short vector only if they are many)
     u32 small;          // a counted vector whose short lists finalize keeps in registers, as a rule
-    u32 narrow_from;    // classify narrows a counted vector's deciding bin down from this many entries on (0: never)
     u32 k_nlz;          // leading zeros of K_hi - K_lo
     u32 stage_m;        // keys in the window that finalize has room for in LDS
     u64 K_lo, K_hi;     // key window
@@ -1316,7 +1315,6 @@ struct Picked {
     u32 n_bin;
     __device__ __forceinline__ void store(EncodeCtl *ctl) const
     {
-        ctl->n_bin = n_bin;
         ctl->mode = mode;
         ctl->bd_lo = bd_lo;
         ctl->bd_hi = bd_hi;
@@ -1819,7 +1817,7 @@ __device__ __forceinline__ void wait_own_memory()
 // A bin of count is a 128th of an octave, whatever the values: of uniform ones the deciding bin may hold d / 256
 // entries, of magnitudes that are nearly equal, or clipped with some noise on top, most of the vector, and no short list
 // takes those. All workgroups know from the pick how many there are, and whether they crowd. From
-// g.narrow_from on, or where they crowd, the workgroups count the bin's entries by their next 8 bits and go on with
+// narrow_from on, or where they crowd, the workgroups count the bin's entries by their next 8 bits and go on with
 // the one of 256 parts that decides. So they do with an octave whose bins some workgroup of count did not keep. Calls, us, with sample and bracket / counted, the bin as it is / narrowed, r = 1%:
 // uniform values, 2 M elements 42.9 / 60.6 / 39.5, 3 M 45.4 / 76.7 / 47.1; 1 + 1% normal, 200,003 42.6 / 257 / 32.8, 2^20
 // 46.9 / 83.3 / 38.6; clipped with noise of 1e-3, 200,003 42.8 / 3167 / 32.4, 2^20 70.9 / 124 / 39.2; one layer of 8192
@@ -1980,7 +1978,7 @@ narrow_bin(const ChunkRows &chunk, const Geom &g, const float *__restrict__ a, P
 constexpr u32 kMemoryEntries = 3u << 12;
 __device__ __forceinline__ void
 classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, EncodeCtl *ctl, Picked now, const u32 &hot,
-                 bool picked_here, const float *__restrict__ a, PartGroup *groups, uint2 *__restrict__ seg,
+                 bool picked_here, u32 narrow_from, const float *__restrict__ a, PartGroup *groups, uint2 *__restrict__ seg,
                  uint2 *__restrict__ s_ent, u32 *__restrict__ win_cnt, u32 *__restrict__ bd_cnt,
                  u32 *__restrict__ quad_win, uint2 *__restrict__ blk_lists, u32 *__restrict__ blk_bmin,
                  u32 *__restrict__ blk_bmax, uint2 *__restrict__ m_ent, uint2 *__restrict__ b_ent)
@@ -1994,7 +1992,7 @@ classify_counted(const ChunkRows &chunk, const Geom &g, const PhiloxSeed &seed, 
     lds_barrier();
     const bool crowds = picked_here ? hot != 0u : (now.n_bin & kCrowds) != 0u;
     now.n_bin &= ~kCrowds;
-    const bool narrows = g.narrow_from != 0u && (now.n_bin >= g.narrow_from || crowds);
+    const bool narrows = narrow_from != 0u && (now.n_bin >= narrow_from || crowds);
     const u32 span = now.bd_hi - now.bd_lo;
     if (__builtin_expect(narrows, 0)) now = narrow_bin(chunk, g, a, groups, now);
     else if (now.mode != 0u) now = Picked{1u, 0u, 0u, 0ull, 0u};
@@ -3831,11 +3829,15 @@ __global__ void __launch_bounds__(kPickThreads) k_pick_counted(Batch B, u32 n_ro
     Picked p = pick_counted<kPickThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g, &hot);
     lds_barrier();
     if (hot != 0u) p.n_bin |= kCrowds;
-    if (threadIdx.x == 0) p.store(m.at<EncodeCtl>(L.ctl));
+    if (threadIdx.x == 0) {
+        EncodeCtl *ctl = m.at<EncodeCtl>(L.ctl);
+        p.store(ctl);
+        ctl->n_bin = p.n_bin;
+    }
 }
 
 template <bool kPick>
-__global__ void __launch_bounds__(kWalkThreads) k_classify_counted(Batch B, u32 n_rows, Geom g, EncodeLayout L)
+__global__ void __launch_bounds__(kWalkThreads) k_classify_counted(Batch B, u32 n_rows, u32 narrow_from, Geom g, EncodeLayout L)
 {
     const Member m(B);
     EncodeCtl *ctl = m.at<EncodeCtl>(L.ctl);
@@ -3846,7 +3848,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_classify_counted(Batch B, u32 
         p = pick_counted<kWalkThreads>(m.at<u16>(L.samples), m.at<uint4>(L.partials), n_rows, g, &hot);
     else
         p = Picked{ctl->mode, ctl->bd_lo, ctl->bd_hi, ctl->c_def, ctl->n_bin};
-    classify_counted(chunk, g, m.seed, ctl, p, hot, kPick, m.residual, m.at<PartGroup>(L.group_sums), m.at<uint2>(L.seg), m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt),
+    classify_counted(chunk, g, m.seed, ctl, p, hot, kPick, narrow_from, m.residual, m.at<PartGroup>(L.group_sums), m.at<uint2>(L.seg), m.at<uint2>(L.s_ent), m.at<u32>(L.win_cnt),
                      m.at<u32>(L.bd_cnt), m.at<u32>(L.quad_win), m.at<uint2>(L.blk_lists), m.at<u32>(L.blk_bmin),
                      m.at<u32>(L.blk_bmax), m.at<uint2>(L.m_ent), m.at<uint2>(L.b_ent));
 }
@@ -4260,7 +4262,8 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
         const CountShape cs = count_shape(gg.W);
         if (counts) set_units(gg, 1u);                  // a chunk per wavefront of the walking kernels
         gg.small = counts && small_lists(gg, nb) ? 1u : 0u;
-        gg.narrow_from = counts && gg.G3 <= classify_limit && gg.force_abort == 0u ? narrows_from(gg.G3) : 0u;
+        // (0: never)
+        const u32 narrow_from = counts && gg.G3 <= classify_limit && gg.force_abort == 0u ? narrows_from(gg.G3) : 0u;
         if (counts) {
             { StageScope none(trace, RTOPK_STAGE_PREPARE, stream); }    // (nothing to prepare: the events are recorded all the same)
             StageScope sc(trace, RTOPK_STAGE_FUSED, stream);
@@ -4309,11 +4312,11 @@ static int encode_batch_impl(uint32_t n, const float *const *grad, float *const 
             const dim3 cg(gg.G3, 1, nb);
             const bool each_picks = nb * cs.grid <= kPickRows;
             if (counts && each_picks) {
-                k_classify_counted<true><<<cg, kWalkThreads, 0, stream>>>(B, cs.grid, gg, L);
+                k_classify_counted<true><<<cg, kWalkThreads, 0, stream>>>(B, cs.grid, narrow_from, gg, L);
             } else if (counts) {
                 k_pick_counted<<<dim3(1, 1, nb), kPickThreads, 0, stream>>>(B, cs.grid, gg, L);
                 RTOPK_LAUNCH_CHECK();
-                k_classify_counted<false><<<cg, kWalkThreads, 0, stream>>>(B, cs.grid, gg, L);
+                k_classify_counted<false><<<cg, kWalkThreads, 0, stream>>>(B, cs.grid, narrow_from, gg, L);
             } else {
                 if (!g.all_members) {
                     k_pick<<<dim3(1, 1, nb), kPickThreads, 0, stream>>>(B, fgrid, gg, L);
