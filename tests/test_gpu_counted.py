@@ -102,8 +102,8 @@ def test_octaves_that_meet_in_tiny_vectors(d, top):
             _check(g, np.zeros(d, np.float32), r, r, offset=1, path=None)
 
 
-@pytest.mark.parametrize("n", [3, 16])                          # every classify workgroup picks; a kernel does
-def test_denormals_below_an_octave_that_shares_their_slot(n):
+@pytest.mark.parametrize("n,abort", [(3, False), (16, False), (16, True)])      # every classify workgroup picks; a kernel does, and nobody narrows
+def test_denormals_below_an_octave_that_shares_their_slot(n, abort):
     """The octave of the denormals, zeros among them, is the one that lost its slot."""
     import torch
 
@@ -121,11 +121,13 @@ def test_denormals_below_an_octave_that_shares_their_slot(n):
     val = [torch.empty(k, device=u.DEV) for _ in range(n)]
     stride = rt.encode_workspace_bytes(d, r, k)
     ws = torch.empty(n * stride, dtype=torch.uint8, device=u.DEV).fill_(0xA5)
+    if abort:
+        rt.force_next_encode(rt.FORCE_CHECK_IN_ABORT)
     rt.encode_batch([grad] * n, res, r, k, list(range(n)), 3, idx, val, ws)
     torch.cuda.synchronize()
     for w in (0, n - 1):
         st = rt.encode_stats(ws[w * stride:(w + 1) * stride])
-        assert st["path"] == 0 and st["error_flags"] == 0, (w, st)
+        assert (st["path"] & 2 if abort else st["path"] == 0) and st["error_flags"] == 0, (w, st)
         got = (idx[w].cpu().numpy().view(np.uint32), val[w].cpu().numpy(), res[w].cpu().numpy())
         u.assert_encode_equal(got, oracle.encode(g, np.zeros(d, np.float32), r, k, w, 3), f"member {w} of {n}")
 
