@@ -1821,7 +1821,8 @@ __device__ __forceinline__ void wait_own_memory()
 // the one of 256 parts that decides. So they do with an octave whose bins some workgroup of count did not keep. Calls, us, with sample and bracket / counted, the bin as it is / narrowed, r = 1%:
 // uniform values, 2 M elements 42.9 / 60.6 / 39.5, 3 M 45.4 / 76.7 / 47.1; 1 + 1% normal, 200,003 42.6 / 257 / 32.8, 2^20
 // 46.9 / 83.3 / 38.6; clipped with noise of 1e-3, 200,003 42.8 / 3167 / 32.4, 2^20 70.9 / 124 / 39.2; one layer of 8192
-// in 1..1.05, 200,003 45.0 / 390 / 38.5; eight of 2^20, 1 + 5% normal 69.8 / 82.3 / 69.1. Where nothing
+// in 1..1.05, 200,003 45.0 / 390 / 38.5 (k = r / 40; with a tenth of r the layer's keys overflow M, by every path: 376 / 389 /
+// 336); eight of 2^20, 1 + 5% normal 69.8 / 82.3 / 69.1. Where nothing
 // narrows the call costs what it did (normal values, 2 M 34.3 / 34.4).
 //
 // For that they have to wait for each other (through device-scope atomics only, see grid_barrier). What bounds it is
